@@ -80,7 +80,8 @@ int vr_set_timing(vr_ctx* ctx, int enabled);
 
 /* Launch-shape knobs of the context (integer results never depend on them;
  * FP64 potentials only through the order of their partial sums):
- * "knn_leaf"      members per leaf of the neighbour-search tree (16..256, 64)
+ * "knn_leaf"      the neighbour-search tree's leaves of 32 members are built
+ *                 in workgroups of at most 8 * knn_leaf members (16..256, 256)
  * "unbind_tile"   j-tile of the potential kernel staged in LDS (64..4096, 256;
  *                 the persistent kernel uses at most 1024 per wavefront)
  * "unbind_jchunk" j-range of one potential work item (256..65536, 4096)
@@ -186,8 +187,7 @@ int vr_cell_moments(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts,
  * the 3D Epanechnikov kernel W(u) = 15/(8 pi) (1 - u^2); f_bg = Gaussian at
  * vbar(x_k), sigma(x_k) (vbar [n][3], sigma [n][6], particle-major as
  * vr_cell_moments writes them).  2 <= n_v <= n_se <= 256 and n_v <= 32 when
- * n_se > 64 (the paper's defaults, 256 and 32, are the largest case; beyond
- * n_se = 32 a workgroup's LDS heaps cut the occupancy), every host has
+ * n_se > 64 (the paper's defaults, 256 and 32, are the largest case), every host has
  * >= n_se members.  subset (may be NULL = all host members) lists the particles to
  * process; R is written only for them (NaN if sigma is not positive
  * definite, +inf if h = 0).  VR_ERR_INVALID_ARG, with nothing written to R,

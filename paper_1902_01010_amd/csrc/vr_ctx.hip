@@ -265,8 +265,9 @@ int vr_set_timing(vr_ctx* ctx, int enabled) {
     ctx->timers.clear();
     ctx->timing = enabled ? 1 : 0;
     if (enabled) {
-        if (!ctx->knn_cand) VR_HIP(ctx, hipMalloc((void**)&ctx->knn_cand, sizeof(unsigned long long)));
-        VR_HIP(ctx, hipMemset(ctx->knn_cand, 0, sizeof(unsigned long long)));
+        const size_t bytes = KNN_CAND_SLOTS * sizeof(unsigned long long);
+        if (!ctx->knn_cand) VR_HIP(ctx, hipMalloc((void**)&ctx->knn_cand, bytes));
+        VR_HIP(ctx, hipMemset(ctx->knn_cand, 0, bytes));
     }
     return VR_OK;
 }
@@ -332,9 +333,9 @@ int vr_kernel_time(vr_ctx* ctx, const char* kernel, int64_t* launches, double* t
     if (cand) {
         *work = 0.0;
         if (ctx->knn_cand) {
-            unsigned long long c = 0;
-            VR_HIP(ctx, hipMemcpy(&c, ctx->knn_cand, sizeof c, hipMemcpyDeviceToHost));
-            *work = (double)c;
+            unsigned long long c[KNN_CAND_SLOTS];
+            VR_HIP(ctx, hipMemcpy(c, ctx->knn_cand, sizeof c, hipMemcpyDeviceToHost));
+            for (unsigned long long x : c) *work += (double)x;
         }
     }
     return VR_OK;

@@ -14,6 +14,8 @@
 
 #define VR_WAVE 64
 
+constexpr int KNN_CAND_SLOTS = 1024;
+
 struct vr_buf {
     void* ptr = nullptr;
     size_t bytes = 0;
@@ -50,12 +52,13 @@ struct vr_ctx {
     hipEvent_t up_event = nullptr;
     bool up_pending = false;
     int tuned_tile = 0;     // potential j-tile picked by the autotuner (0 = default)
-    int knn_leaf = 64;      // members per leaf of the neighbour-search tree
+    int knn_leaf = 256;     // the neighbour tree's buckets hold at most 8 * knn_leaf members
     int unbind_jchunk = 4096;
     int unbind_bpc = 0;     // workgroups per CU of the persistent potential kernel (0 = occupancy limit)
     int unbind_wide = 4096; // members from which a leading group takes the 1024-thread group kernel
     int xcd_chunk = 64;     // consecutive workgroups per XCD in the neighbour sweeps (0 = hardware order)
-    // while timing: candidate distances of the neighbour search (device counter)
+    // while timing: candidate distances of the neighbour search
+    // (KNN_CAND_SLOTS partial sums on the device)
     unsigned long long* knn_cand = nullptr;
     // the presorted member lists of the last KD build (workspace slot
     // WS_KD_PRE), kept for the next build over the same members: their

@@ -302,8 +302,7 @@ __global__ __launch_bounds__(256) void k_split(const int* nact, const int* __res
         nd = nodes[id];
         if (mode == KD_WIDEST) {
             for (int d = 0; d < 3; ++d)
-                if (nd.bmax[d] > nd.bmin[d] && (best < 0 || nd.bmax[d] - nd.bmin[d] > nd.bmax[best] - nd.bmin[best]))
-                    best = d;
+                if (best < 0 || nd.bmax[d] - nd.bmin[d] > nd.bmax[best] - nd.bmin[best]) best = d;
         } else {
             const double S[3] = {Sdim[3 * (int64_t)i], Sdim[3 * (int64_t)i + 1], Sdim[3 * (int64_t)i + 2]};
             for (int d = 0; d < 3; ++d) {
@@ -454,9 +453,8 @@ __global__ void k_leaf_bbox(int nl, const int* __restrict__ leaves, KdNode* node
 }
 
 // Members by position in list-0 order, and the smallest index of each leaf.
-// c0..c2: the coordinates already in list-0 order, or null (then gathered).
+// c0..c2: the coordinates in list-0 order.
 __global__ void k_final(int64_t M, const int* __restrict__ l0, const int* __restrict__ seg_node,
-                        const int* __restrict__ u0, const int* __restrict__ u1, const int* __restrict__ u2,
                         const int* __restrict__ c0, const int* __restrict__ c1, const int* __restrict__ c2,
                         const int* __restrict__ g, const float* __restrict__ m, Elems F, int* __restrict__ leaf_min) {
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -464,9 +462,9 @@ __global__ void k_final(int64_t M, const int* __restrict__ l0, const int* __rest
     const int e = valid ? l0[p] : 0;
     const int gi = valid ? g[e] : 0x7FFFFFFF;
     if (valid) {
-        F.u[0][p] = c0 ? c0[p] : u0[e];
-        F.u[1][p] = c0 ? c1[p] : u1[e];
-        F.u[2][p] = c0 ? c2[p] : u2[e];
+        F.u[0][p] = c0[p];
+        F.u[1][p] = c1[p];
+        F.u[2][p] = c2[p];
         F.gidx[p] = gi;
         F.eid[p] = e;
         if (m) F.mass[p] = m[e];
@@ -523,7 +521,7 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
     Carve cv;
     int *U[3], *G, *H, *L[3], *Lalt[3], *seg, *leaf_min, *act0, *act1, *leaves, *ncell_d, *counters;
     int *C0[3], *C0alt[3];
-    const int64_t MC = mode != KD_WIDEST ? M : 1;
+    const int64_t MC = mode != KD_WIDEST ? M : 1;  // coordinates in list-0 order, and F
     float* Ms;
     uint8_t* lf8;
     uint32_t* lf;
@@ -549,10 +547,10 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
         act1 = cv.add<int>(node_cap);
         leaves = cv.add<int>(node_cap);
         leaf_min = cv.add<int>(node_cap);
-        for (int d = 0; d < 3; ++d) F.u[d] = cv.add<int>(M);
-        F.gidx = cv.add<int>(M);
-        F.eid = cv.add<int>(M);
-        F.mass = cv.add<float>(use_mass ? M : 1);
+        for (int d = 0; d < 3; ++d) F.u[d] = cv.add<int>(MC);
+        F.gidx = cv.add<int>(MC);
+        F.eid = cv.add<int>(MC);
+        F.mass = cv.add<float>(use_mass ? MC : 1);
         ncell_d = cv.add<int>(n_hosts);
         counters = cv.add<int>(8);
         hsh = cv.add<unsigned long long>(HASH_SLOTS);
@@ -739,6 +737,15 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
         }
         std::swap(cur, nxt);
     }
+    for (int d = 0; d < 3; ++d) tree.elem_u[d] = U[d];
+    tree.elem_host = H;
+    tree.use_mass = use_mass;
+    if (mode == KD_WIDEST) {
+        for (int d = 0; d < 3; ++d) tree.list[d] = L[d];
+        tree.elem_g = G;
+        tree.scratch = Lalt[0];
+        return VR_OK;
+    }
     if (!plan_na.empty()) {
         hipLaunchKernelGGL(k_level_counters, dim3(1), dim3(64), 0, st, counters, 1, 0);
         VR_LAUNCH_CHECK(ctx);
@@ -750,9 +757,8 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
     hipLaunchKernelGGL(k_leaf_bbox, dim3(grid_for(nleaf, 256)), dim3(256), 0, st, nleaf, leaves, nodes, L[0], L[1],
                        L[2], U[0], U[1], U[2], leaf_min, n_hosts);
     VR_LAUNCH_CHECK(ctx);
-    const bool have_c0 = mode != KD_WIDEST;
-    hipLaunchKernelGGL(k_final, dim3(gM), dim3(256), 0, st, M, L[0], seg, U[0], U[1], U[2], have_c0 ? C0[0] : nullptr,
-                       have_c0 ? C0[1] : nullptr, have_c0 ? C0[2] : nullptr, G, use_mass ? Ms : nullptr, F, leaf_min);
+    hipLaunchKernelGGL(k_final, dim3(gM), dim3(256), 0, st, M, L[0], seg, C0[0], C0[1], C0[2], G,
+                       use_mass ? Ms : nullptr, F, leaf_min);
     VR_LAUNCH_CHECK(ctx);
     tree.nodes = nodes;
     tree.leaves = leaves;
@@ -760,9 +766,6 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
     tree.seg_node = seg;
     tree.leaf_min = leaf_min;
     tree.F = F;
-    for (int d = 0; d < 3; ++d) tree.elem_u[d] = U[d];
-    tree.elem_host = H;
-    tree.use_mass = use_mass;
     return VR_OK;
 }
 

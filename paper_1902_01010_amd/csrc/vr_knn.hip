@@ -1,49 +1,64 @@
 // vr_knn.hip -- local velocity density ratio R = ln(f_l / f_bg) (Sec. 2.2).
 //
-// Each host gets a median-split KD tree (widest dimension, leaves of at most
-// 64 members, built by the presorted level-synchronous builder); members sit
-// in leaf order, so 64 consecutive queries share leaves.  One wavefront
-// serves 64 queries, one per lane: the wave first scans the leaves that hold
-// its own queries (which fills every heap with near neighbours), then walks
-// the tree of the host with a shared depth-first stack (near child first,
-// for the centre of the wave's queries), visiting a node when any lane's
-// ball -- radius = its current n_se-th neighbour -- reaches the node's
-// bounding box.  A visited leaf is
-// staged in LDS 64 members at a time.  A first pass over the chunk (the same
-// LDS address for every lane, no divergence) marks in a per-lane bit mask
-// the members whose FP32 squared distance may beat the lane's current worst;
-// a second pass inserts the marked ones with their exact keys, each lane
-// walking its own mask.  Every lane keeps its n_se best keys, unordered, in
-// LDS slots grouped by eight; the largest key of each group and its slot
-// sit in registers, so replacing the lane's worst key rewrites one slot and
-// rereads that group's eight keys at once, with no chain of dependent LDS
-// reads.  A key packs the exact integer squared distance above the member's
-// rank in its host's ascending index order, so ties break by particle index
-// exactly as the definition says.  The n_v velocity neighbours are then
-// chosen among the n_se by (FP64 dv2, index) and the Epanechnikov estimate
-// and the Gaussian background follow in FP64.
+// Members are ordered by a KD tree: the device-wide builder splits the hosts
+// at medians of the widest dimension down to buckets of a few hundred to
+// 2048 members, and one workgroup per bucket (k_buckets) finishes the tree
+// in LDS down to leaves of 32, all full but the bucket's last.  A leaf is 32
+// consecutive slots; buckets have at most 64 leaves, so one load a lane
+// tests a whole bucket's boxes against a wavefront's queries.
+//
+// LPQ lanes serve one query and a wavefront 64 / LPQ neighbouring ones
+// (k_knn).  Every lane takes its own 32 / LPQ members of a leaf and keeps the
+// L smallest FP32 squared distances it has met, sorted in registers: an
+// insertion is L median-of-three instructions without a branch.  LPQ lanes
+// holding KL = n_se / LPQ distances each below B have met n_se members below
+// B, so the largest of the lanes' KL-th distances bounds the search.  After
+// the walk a bisection over the kept distances finds a threshold X that
+// n_se or a few more members meet; a second pass over the visited leaves
+// lists them.  Where the list holds more than n_se (ties within FP32
+// rounding, or a lane whose list was too short) the largest exact keys leave
+// it: a key packs the exact integer squared distance above the member's rank
+// in its host's ascending index order, so ties break by particle index
+// exactly as the definition says.  Only the set matters from there on: the
+// bandwidth is the n_v-th smallest velocity distance of the set, a member at
+// that distance has weight zero, and the sums of the Epanechnikov estimate
+// and the Gaussian background follow in FP64.  Queries whose lists overflow
+// (many coincident members) go to k_knn_wave, a wavefront per query with
+// exact keys throughout.
 #include "vr_kd.h"
 
 #include <cmath>
+#include <cstring>
+#include <type_traits>
 
 namespace vr {
 namespace {
 
 constexpr int POS_BITS = 22;
 constexpr uint64_t POS_MASK = (uint64_t(1) << POS_BITS) - 1;
-constexpr int STACK = 128;
+constexpr int LEAF = 32;           // slots of a leaf
+constexpr int BUCKET_MAX = 2048;   // members of a bucket (64 leaves)
+constexpr float PAD = 1e30f;       // coordinate of an empty slot
+constexpr float SLACK = 1.000002f; // above the rounding of an FP32 squared distance (3 * 2^-24)
 
-__global__ void k_pos_of(int64_t M, const int* __restrict__ gidx, int* __restrict__ pos_of) {
-    int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < M) pos_of[gidx[k]] = (int)k;
-}
+// The neighbour tree over the hosts' members.
+struct Slots {
+    float *x, *y, *z;   // [n_slots] coordinates (exact integers)
+    int *gid, *eid;     // [n_slots] particle (-1: empty), element id (rank = eid - host offset)
+    float4* lbox;       // [n_leaves][2] lower and upper corner of a leaf's members
+    float4* bbox;       // [n_buckets][2]
+    int4* buckets;      // [n_buckets] first list position, members, first leaf, host
+    int* leaf_bucket;   // [n_leaves]
+    int* host_bucket;   // [n_hosts + 1]
+    int* hbox;          // [n_hosts][6] minima of u and of -u
+};
 
-__global__ void k_subset_pos(int64_t ns, int64_t n, const int32_t* __restrict__ subset, const int* __restrict__ pos_of,
-                             uint32_t* __restrict__ qpos, uint32_t* __restrict__ qval, int* __restrict__ bad) {
+__global__ void k_subset_slot(int64_t ns, int64_t n, const int32_t* __restrict__ subset, const int* __restrict__ slot_of,
+                              uint32_t* __restrict__ qpos, uint32_t* __restrict__ qval, int* __restrict__ bad) {
     int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (s >= ns) return;
     const int i = subset[s];
-    int p = (i >= 0 && i < n) ? pos_of[i] : -1;
+    int p = (i >= 0 && i < n) ? slot_of[i] : -1;
     if (p < 0) { atomicOr(bad, 1); p = 0; }
     qpos[s] = (uint32_t)p;
     qval[s] = (uint32_t)s;
@@ -71,515 +86,688 @@ __device__ __forceinline__ double log_fbg(const float* __restrict__ sigma, const
     return -0.5 * ((diag + 2.0 * offd) / A.det + log(A.det)) - HALF3_LN_2PI;
 }
 
-// rank_of[g] = the position of particle g in host_members (-1 beforehand);
-// a member outside [0, n) or listed twice raises *bad
-__global__ void k_rank_of(int64_t M, int64_t n, const int* __restrict__ mem, int* __restrict__ rank_of,
+// slot_of[g] = the position of particle g in host_members (-1 beforehand; the
+// bucket build replaces it by the slot); a member outside [0, n) or listed
+// twice raises *bad
+__global__ void k_rank_of(int64_t M, int64_t n, const int* __restrict__ mem, int* __restrict__ slot_of,
                           int* __restrict__ bad) {
     int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= M) return;
     const int g = mem[k];
-    if (g < 0 || g >= n || atomicExch(&rank_of[g], (int)k) != -1) atomicOr(bad, 1);
+    if (g < 0 || g >= n || atomicExch(&slot_of[g], (int)k) != -1) atomicOr(bad, 1);
 }
 
-// Per host member, at its host rank: (vx, vy, vz, mass) as one 16-byte
-// record, so a neighbour's velocity and mass are one cache line, and the
-// member's ln f_bg, so a query reads 8 bytes instead of nine floats spread
-// over nine arrays.  The pass runs in particle order, where its 12 input
-// arrays are read in full lines; a host's members are scattered over the
-// whole particle range, so a pass in rank order would fetch a line per value.
-__global__ void k_member_records(int64_t n, const int* __restrict__ rank_of, const float* __restrict__ vx,
+// Per host member, at its slot: (vx, vy, vz, mass) as one 16-byte record, so
+// a neighbour's velocity and mass are one cache line (and a query's
+// neighbours lie in a few leaves), and the member's ln f_bg, so a query
+// reads 8 bytes instead of nine floats spread over nine arrays.  The pass
+// runs in particle order, where its 12 input arrays are read in full lines;
+// a host's members are scattered over the whole particle range, so a pass in
+// slot order would fetch a line per value.
+__global__ void k_member_records(int64_t n, const int* __restrict__ slot_of, const float* __restrict__ vx,
                                  const float* __restrict__ vy, const float* __restrict__ vz,
                                  const float* __restrict__ mass, const float* __restrict__ vbar,
                                  const float* __restrict__ sigma, float4* __restrict__ V, double* __restrict__ FB) {
     int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (g >= n) return;
-    const int k = rank_of[g];
+    const int k = slot_of[g];
     if (k < 0) return;
     const float ux = vx[g], uy = vy[g], uz = vz[g];
     V[k] = make_float4(ux, uy, uz, mass ? mass[g] : 0.f);
     FB[k] = log_fbg(sigma, vbar, (int)g, (double)ux, (double)uy, (double)uz);
 }
 
-__device__ __forceinline__ bool vless(double a, int pa, double b, int pb) { return a < b || (a == b && pa < pb); }
+// Slot within a leaf of its i-th member in KD order: lane s of a query's LPQ
+// takes members s, s + LPQ, ..., at consecutive slots.  KD neighbours fall to
+// different lanes, which keeps the lanes' shares of a ball even.
+__device__ __forceinline__ int leaf_slot(int i, int lpq_log2) {
+    const int lpq = 1 << lpq_log2;
+    return (i & (lpq - 1)) * (LEAF >> lpq_log2) + (i >> lpq_log2);
+}
 
-// NSE: heap capacity (n_se <= NSE).  NVR > 0: exactly NVR velocity
-// neighbours kept in registers (sorted by an unrolled insertion network);
-// NVR == 0: any n_v <= NVLMAX, kept in LDS.
-template <int NSE, int NVR, int NVLMAX>
-__global__ __launch_bounds__(64) void k_knn(const uint32_t* __restrict__ qpos, int64_t nq,
-                                            const KdNode* __restrict__ nodes, Elems F, const int* __restrict__ leaf_of,
+// One workgroup finishes one bucket's tree in LDS.  The members' three
+// sorted lists (local ids, local id = position in list 0) are split by
+// stable partitions, segment by segment: at a multiple of 32 members nearest
+// the middle while a segment holds more than a leaf, then in halves down to
+// four.  Members, boxes and slots are written in the resulting order.
+// Bound by LDS round trips and barriers (three workgroups of 53 KB a CU); on
+// the 6.2 M members of a 256^3 box it takes 0.68 ms in place of three to four
+// device-wide levels of about 0.25 ms, and leaves of 32 instead of 192 (2,354
+// candidate distances a query before, about 600 now).
+__global__ __launch_bounds__(256) void k_buckets(const int* __restrict__ l0, const int* __restrict__ l1,
+                                                 const int* __restrict__ l2, const int* __restrict__ u0,
+                                                 const int* __restrict__ u1, const int* __restrict__ u2,
+                                                 const int* __restrict__ g, int* loc, int lpq_log2, Slots T,
+                                                 int* __restrict__ slot_of) {
+    constexpr int NT = 256, PT = BUCKET_MAX / NT;  // 8 consecutive positions a thread
+    __shared__ int cu[3][BUCKET_MAX];
+    __shared__ __align__(16) uint16_t ls[3][BUCKET_MAX];
+    __shared__ uint16_t pre[3][BUCKET_MAX];
+    __shared__ uint8_t side[BUCKET_MAX], sdim[BUCKET_MAX];
+    __shared__ unsigned long long wsum[NT / 64];
+    __shared__ int wbox[NT / 64][6];
+    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+    const int4 bk = T.buckets[blockIdx.x];
+    const int start = bk.x, n = bk.y, leaf0 = bk.z;
+    const int nleaf = (n + LEAF - 1) / LEAF;
+    for (int p = t; p < n; p += NT) {
+        const int e = l0[start + p];
+        cu[0][p] = u0[e];
+        cu[1][p] = u1[e];
+        cu[2][p] = u2[e];
+        ls[0][p] = (uint16_t)p;
+        loc[e] = p;
+    }
+    __syncthreads();
+    for (int p = t; p < n; p += NT) {
+        ls[1][p] = (uint16_t)loc[l1[start + p]];
+        ls[2][p] = (uint16_t)loc[l2[start + p]];
+    }
+    const int p0 = t * PT;
+    uint32_t se[PT];  // segment of the position: start << 16 | end
+#pragma unroll
+    for (int j = 0; j < PT; ++j) se[j] = (uint32_t)n;
+    auto middle = [](int s, int e) __attribute__((always_inline)) {
+        const int m = e - s;
+        return m > LEAF ? s + LEAF * (((m + LEAF - 1) / LEAF) >> 1) : s + (m >> 1);
+    };
+    const int levels = (nleaf > 1 ? 32 - __clz(nleaf - 1) : 0) + 3;
+    __syncthreads();
+    for (int lev = 0; lev < levels; ++lev) {
+        // the widest dimension of every segment, from the ends of its lists
+#pragma unroll
+        for (int j = 0; j < PT; ++j) {
+            const int p = p0 + j, s = (int)(se[j] >> 16), e = (int)(se[j] & 0xFFFFu);
+            if (p == s && p < n && e - s > 4) {
+                int best = 0, ext = -1;
+#pragma unroll
+                for (int d = 0; d < 3; ++d) {
+                    const int x = cu[d][ls[d][e - 1]] - cu[d][ls[d][s]];
+                    if (x > ext) { ext = x; best = d; }
+                }
+                sdim[s] = (uint8_t)best;
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < PT; ++j) {
+            const int p = p0 + j, s = (int)(se[j] >> 16), e = (int)(se[j] & 0xFFFFu);
+            if (p < n && e - s > 4) side[ls[sdim[s]][p]] = p < middle(s, e) ? 1 : 0;
+        }
+        __syncthreads();
+        // left flags of the three lists and their block-wide prefix sums
+        uint16_t el[3][PT];
+        uint32_t fl[3] = {0u, 0u, 0u};
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            const uint4 w = *reinterpret_cast<const uint4*>(&ls[d][p0]);
+            const uint32_t ww[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+            for (int j = 0; j < PT; ++j) {
+                el[d][j] = (uint16_t)(ww[j >> 1] >> (16 * (j & 1)));
+                const int s = (int)(se[j] >> 16), e = (int)(se[j] & 0xFFFFu);
+                if (p0 + j < n && e - s > 4 && side[el[d][j]]) fl[d] |= 1u << j;
+            }
+        }
+        unsigned long long c = (unsigned long long)__popc(fl[0]) | ((unsigned long long)__popc(fl[1]) << 16) |
+                               ((unsigned long long)__popc(fl[2]) << 32);
+        unsigned long long inc = c;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const unsigned long long y = __shfl_up(inc, o, 64);
+            if (lane >= o) inc += y;
+        }
+        if (lane == 63) wsum[wv] = inc;
+        __syncthreads();
+        unsigned long long ex = inc - c;
+        for (int w = 0; w < wv; ++w) ex += wsum[w];
+#pragma unroll
+        for (int j = 0; j < PT; ++j) {
+            const int s = (int)(se[j] >> 16);
+            if (p0 + j == s && p0 + j < n) {
+#pragma unroll
+                for (int d = 0; d < 3; ++d)
+                    pre[d][s] = (uint16_t)((uint32_t)(ex >> (16 * d)) + __popc(fl[d] & ((1u << j) - 1u)));
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < PT; ++j) {
+            const int p = p0 + j, s = (int)(se[j] >> 16), e = (int)(se[j] & 0xFFFFu);
+            if (p >= n || e - s <= 4) continue;
+            const int mid = middle(s, e);
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                const int before = (int)(uint16_t)((uint32_t)(ex >> (16 * d)) + __popc(fl[d] & ((1u << j) - 1u)));
+                const int r = before - (int)pre[d][s];  // left members of the segment before p
+                const int np = (fl[d] >> j) & 1u ? s + r : mid + (p - s - r);
+                ls[d][np] = el[d][j];
+            }
+            se[j] = p < mid ? ((uint32_t)s << 16) | (uint32_t)mid : ((uint32_t)mid << 16) | (uint32_t)e;
+        }
+        __syncthreads();
+    }
+    // members into slots, and the boxes of leaves, bucket and host
+    int mn[3] = {INT32_MAX, INT32_MAX, INT32_MAX}, mx[3] = {INT32_MIN, INT32_MIN, INT32_MIN};
+#pragma unroll
+    for (int j = 0; j < PT; ++j) {
+        const int p = p0 + j;
+        if (p >= nleaf * LEAF) break;
+        const int slot = (leaf0 + (p / LEAF)) * LEAF + leaf_slot(p & (LEAF - 1), lpq_log2);
+        if (p < n) {
+            const int a = ls[0][p];
+            const int e = l0[start + a], gi = g[e];
+            const int q[3] = {cu[0][a], cu[1][a], cu[2][a]};
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                mn[d] = min(mn[d], q[d]);
+                mx[d] = max(mx[d], q[d]);
+            }
+            T.x[slot] = (float)q[0];
+            T.y[slot] = (float)q[1];
+            T.z[slot] = (float)q[2];
+            T.gid[slot] = gi;
+            T.eid[slot] = e;
+            slot_of[gi] = slot;
+        } else {
+            T.x[slot] = T.y[slot] = T.z[slot] = PAD;
+            T.gid[slot] = -1;
+            T.eid[slot] = 0;
+        }
+    }
+    // a leaf is the 32 positions of four threads
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+#pragma unroll
+        for (int o = 1; o < 4; o <<= 1) {
+            mn[d] = min(mn[d], __shfl_xor(mn[d], o, 64));
+            mx[d] = max(mx[d], __shfl_xor(mx[d], o, 64));
+        }
+    }
+    if ((t & 3) == 0 && p0 < n) {
+        const int leaf = leaf0 + p0 / LEAF;
+        T.lbox[2 * leaf] = make_float4((float)mn[0], (float)mn[1], (float)mn[2], 0.f);
+        T.lbox[2 * leaf + 1] = make_float4((float)mx[0], (float)mx[1], (float)mx[2], 0.f);
+        T.leaf_bucket[leaf] = blockIdx.x;
+    }
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+#pragma unroll
+        for (int o = 4; o < 64; o <<= 1) {
+            mn[d] = min(mn[d], __shfl_xor(mn[d], o, 64));
+            mx[d] = max(mx[d], __shfl_xor(mx[d], o, 64));
+        }
+        if (lane == 0) {
+            wbox[wv][d] = mn[d];
+            wbox[wv][3 + d] = mx[d];
+        }
+    }
+    __syncthreads();
+    if (t == 0) {
+        for (int w = 1; w < NT / 64; ++w)
+            for (int d = 0; d < 3; ++d) {
+                wbox[0][d] = min(wbox[0][d], wbox[w][d]);
+                wbox[0][3 + d] = max(wbox[0][3 + d], wbox[w][3 + d]);
+            }
+        T.bbox[2 * blockIdx.x] = make_float4((float)wbox[0][0], (float)wbox[0][1], (float)wbox[0][2], 0.f);
+        T.bbox[2 * blockIdx.x + 1] = make_float4((float)wbox[0][3], (float)wbox[0][4], (float)wbox[0][5], 0.f);
+        int* hb = T.hbox + 6 * (int64_t)bk.w;
+        for (int d = 0; d < 3; ++d) {
+            atomicMin(&hb[d], wbox[0][d]);
+            atomicMin(&hb[3 + d], -wbox[0][3 + d]);
+        }
+    }
+}
+
+// ---- reductions over a query's lanes and the wavefront ---------------------
+// The DPP moves read lanes of the same row of 16, so every lane must be
+// active; a query's lanes are aligned to their number.
+template <int CTRL>
+__device__ __forceinline__ int dpp(int v) {
+    return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, true);
+}
+constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_HALF_MIRROR = 0x141, DPP_MIRROR = 0x140;
+
+// Folds v over groups of N lanes (N = 4, 8 or 16); every lane gets the result.
+template <int N, class T, class OP>
+__device__ __forceinline__ T fold(T v, OP op) {
+    auto mv = [&](auto c, T x) __attribute__((always_inline)) {
+        constexpr int C = decltype(c)::value;
+        if constexpr (sizeof(T) == 4) {
+            return __builtin_bit_cast(T, dpp<C>(__builtin_bit_cast(int, x)));
+        } else {
+            struct P { int lo, hi; };
+            P p = __builtin_bit_cast(P, x);
+            p.lo = dpp<C>(p.lo);
+            p.hi = dpp<C>(p.hi);
+            return __builtin_bit_cast(T, p);
+        }
+    };
+    v = op(v, mv(std::integral_constant<int, DPP_XOR1>{}, v));
+    v = op(v, mv(std::integral_constant<int, DPP_XOR2>{}, v));
+    if constexpr (N >= 8) v = op(v, mv(std::integral_constant<int, DPP_HALF_MIRROR>{}, v));
+    if constexpr (N >= 16) v = op(v, mv(std::integral_constant<int, DPP_MIRROR>{}, v));
+    return v;
+}
+struct OpMax { template <class T> __device__ __forceinline__ T operator()(T a, T b) const { return a > b ? a : b; } };
+struct OpMin { template <class T> __device__ __forceinline__ T operator()(T a, T b) const { return a < b ? a : b; } };
+struct OpAdd { template <class T> __device__ __forceinline__ T operator()(T a, T b) const { return a + b; } };
+
+// Wavefront-wide fold of a 32-bit value, uniform.
+template <class T, class OP>
+__device__ __forceinline__ T wave_fold(T v, OP op) {
+    v = fold<16>(v, op);
+    const int b = __builtin_bit_cast(int, v);
+    const T r0 = __builtin_bit_cast(T, __builtin_amdgcn_readlane(b, 0));
+    const T r1 = __builtin_bit_cast(T, __builtin_amdgcn_readlane(b, 16));
+    const T r2 = __builtin_bit_cast(T, __builtin_amdgcn_readlane(b, 32));
+    const T r3 = __builtin_bit_cast(T, __builtin_amdgcn_readlane(b, 48));
+    const T r = op(op(r0, r1), op(r2, r3));
+    return __builtin_bit_cast(T, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, r)));
+}
+
+// Lower bound on the squared distance between two boxes of unwrapped
+// coordinates.  A host narrower than half the box needs no minimum image:
+// its coordinate differences are the periodic ones (wrap false, uniform);
+// else an axis's gap is also bounded through the box of side S.
+__device__ __forceinline__ float box_gap2(float4 a0, float4 a1, float4 b0, float4 b1, bool wrap, float S) {
+    float g[3] = {fmaxf(fmaxf(a0.x - b1.x, b0.x - a1.x), 0.f), fmaxf(fmaxf(a0.y - b1.y, b0.y - a1.y), 0.f),
+                  fmaxf(fmaxf(a0.z - b1.z, b0.z - a1.z), 0.f)};
+    if (wrap) {
+        g[0] = fminf(g[0], fmaxf(S - (fmaxf(a1.x, b1.x) - fminf(a0.x, b0.x)), 0.f));
+        g[1] = fminf(g[1], fmaxf(S - (fmaxf(a1.y, b1.y) - fminf(a0.y, b0.y)), 0.f));
+        g[2] = fminf(g[2], fmaxf(S - (fmaxf(a1.z, b1.z) - fminf(a0.z, b0.z)), 0.f));
+    }
+    return fmaf(g[0], g[0], fmaf(g[1], g[1], g[2] * g[2]));
+}
+
+__device__ __forceinline__ bool host_wraps(const int* __restrict__ hbox, int h, int gb) {
+    const int* b = hbox + 6 * (int64_t)h;
+    const int half = 1 << (gb - 1);
+    // b[3 + d] holds the negated upper end
+    return !(-b[3] - b[0] < half && -b[4] - b[1] < half && -b[5] - b[2] < half);
+}
+
+__device__ __forceinline__ uint64_t exact_key(int dx, int dy, int dz, int rank, bool wrap, int gb) {
+    if (wrap) {
+        dx = min_image(dx, gb);
+        dy = min_image(dy, gb);
+        dz = min_image(dz, gb);
+    }
+    const uint64_t d2 = (uint64_t)((int64_t)dx * dx + (int64_t)dy * dy + (int64_t)dz * dz);
+    return (d2 << POS_BITS) | (uint64_t)(uint32_t)rank;
+}
+
+constexpr int VMAX = 256;  // leaves one wavefront may visit for one host
+
+// LPQ lanes a query; KL * LPQ >= n_se; L > KL distances kept a lane, so that
+// a lane's share of the n_se nearest seldom exceeds its list.
+//
+// Bound by VALU issue: 9.0 k instructions a wavefront of 16 queries at 32/8,
+// half of them the walk (19 leaves of 32, 18 instructions a lane and member),
+// a sixth the second pass, against 62 k for 64 queries of the one-lane-a-query
+// form with 64-bit keys in LDS that it replaces.  256^3 box, 6.2 M queries,
+// 32/8: 11.5 -> 5.6 ms; 48/16, 159 k queries: 4.2 -> 0.24 ms; 256/32, 335 k
+// queries (one wavefront a query before): 5.5 -> 1.6 ms.  L = 12 for KL = 8
+// (10: 12% slower by the exact removals, 14: 1%).  Four wavefronts a SIMD
+// (116 of 128 VGPRs): three were 12% slower, five 8% (spills).  Eight lanes a
+// query were 3% slower on the box: a leaf visit's fixed cost falls on half
+// the queries.
+template <int LPQ, int KL, int L>
+__global__ __launch_bounds__(64, 4) void k_knn(const uint32_t* __restrict__ qpos, int64_t nq, Slots T,
                                             const float4* __restrict__ V, const double* __restrict__ FB,
-                                            const int* __restrict__ elem_host, const int32_t* __restrict__ host_off,
-                                            int n_se, int n_v, int use_mass, double mass_value, int gb,
-                                            float* __restrict__ R, unsigned xchunk,
+                                            const int32_t* __restrict__ host_off, int n_se, int n_v, int use_mass,
+                                            double mass_value, double mass_sum, int gb, float* __restrict__ R,
+                                            unsigned xchunk, int* __restrict__ flagged, int* __restrict__ n_flagged,
                                             unsigned long long* __restrict__ ncand) {
-    constexpr int NVL = NVR > 0 ? 1 : NVLMAX;
-    __shared__ uint64_t heap[NSE][64];
-    __shared__ double vd[NVL][64];
-    __shared__ int vp[NVL][64];
-    __shared__ int stack[STACK];
-    // the leaf chunk being scanned, SoA: x, y, z (exact integers as float)
-    // and rank; four consecutive candidates are one 16-byte broadcast read
-    __shared__ __align__(16) float cxs[64];
-    __shared__ __align__(16) float cys[64];
-    __shared__ __align__(16) float czs[64];
-    __shared__ int crk[64];
-    const int lane = threadIdx.x;
-    const int64_t qi = (int64_t)xcd_swizzle(blockIdx.x, gridDim.x, xchunk) * 64 + lane;
-    const bool active = qi < nq;
-    const int e = active ? (qpos ? (int)qpos[qi] : (int)qi) : 0;
-    const int h = active ? elem_host[e] : -1;
-    const int base = active ? host_off[h] : 0;
-    const int own = active ? leaf_of[e] : -1;
-    const int px = F.u[0][e], py = F.u[1][e], pz = F.u[2][e];
-    const float pxf = (float)px, pyf = (float)py, pzf = (float)pz;
-    int count = 0;
-    uint64_t worst = ~0ull;
-    unsigned long long wcand = 0;  // wave-uniform
-    // the kept keys: slot s of group s / 8; per group its largest key and
-    // that key's slot; wg = the group holding the lane's largest key
-    constexpr int LGS = 3;  // groups of 2^LGS slots
-    constexpr int GS = 1 << LGS;
-    constexpr int NG = NSE >> LGS;
-    static_assert(NG * 6 <= 64, "slot indices of the group maxima are packed 6 bits each");
-    uint64_t gmx[NG];
-    uint64_t gix = 0;  // slot of group g's largest key in bits [6g, 6g + 6)
+    constexpr int W = 64 / LPQ;        // queries of the wavefront
+    constexpr int E = LEAF / LPQ;      // members of a leaf a lane takes
+    constexpr int CAPL = L + 12;       // listed members a lane
+    constexpr int LOG2 = LPQ == 4 ? 2 : LPQ == 8 ? 3 : 4;
+    __shared__ int vis[VMAX];
+    __shared__ uint16_t lst[CAPL][64];
+    __shared__ int nbr[W][KL * LPQ];
+    const int lane = threadIdx.x, sub = lane & (LPQ - 1), q = lane / LPQ;
+    const int64_t qi = (int64_t)xcd_swizzle(blockIdx.x, gridDim.x, xchunk) * W + q;
+    int slot = 0;
+    bool active = qi < nq;
+    if (active) slot = qpos ? (int)qpos[qi] : (int)(qi & ~(int64_t)(LEAF - 1)) + leaf_slot((int)qi & (LEAF - 1), LOG2);
+    const int gid = T.gid[slot];
+    active = active && gid >= 0;
+    const int own = slot / LEAF;
+    const int obk = T.leaf_bucket[own];
+    const int h = active ? T.buckets[obk].w : -1;
+    const float qx = T.x[slot], qy = T.y[slot], qz = T.z[slot];
+    float d[L];
 #pragma unroll
-    for (int g = 0; g < NG; ++g) gmx[g] = 0;
-    int wg = 0;
-    // Slots from n_se up hold key 0, which never exceeds a kept key, so the
-    // group maxima need no bound checks (a group whose largest key is 0
-    // takes no replacement: no key is below 0).
-    for (int sl = n_se; sl < NG * GS; ++sl) heap[sl][lane] = 0;
-    // every selection below is a value select, not a branch on the lane's
-    // group index
-    auto top_update = [&]() __attribute__((always_inline)) {
-        uint64_t m = gmx[0];
-        int mg = 0;
-#pragma unroll
-        for (int g = 1; g < NG; ++g) {
-            const bool gt = gmx[g] > m;
-            m = gt ? gmx[g] : m;
-            mg = gt ? g : mg;
-        }
-        worst = m;
-        wg = mg;
-    };
-    // keeps key: appended while fewer than n_se are kept, else it takes the
-    // slot of the largest (the caller has checked key < worst)
-    auto insert = [&](uint64_t key) __attribute__((always_inline)) {
-        if (count < n_se) {
-            const int sl = count++;
-            heap[sl][lane] = key;
-            const int g = sl >> LGS;
-            const bool first = (sl & (GS - 1)) == 0;
-            bool up = false;
-#pragma unroll
-            for (int k = 0; k < NG; ++k) {
-                const bool u = k == g && (first || key > gmx[k]);
-                gmx[k] = u ? key : gmx[k];
-                up = up || u;
-            }
-            const uint64_t fld = uint64_t(63) << (6 * g);
-            gix = up ? ((gix & ~fld) | ((uint64_t)sl << (6 * g))) : gix;
-            if (count == n_se) top_update();
-            return;
-        }
-        const int sl = (int)((gix >> (6 * wg)) & 63);
-        heap[sl][lane] = key;
-        const int s0 = wg << LGS;
-        uint64_t v[GS];
-#pragma unroll
-        for (int u = 0; u < GS; ++u) v[u] = heap[s0 + u][lane];
-        uint64_t m = v[0];
-        int ms = s0;
-#pragma unroll
-        for (int u = 1; u < GS; ++u) {
-            const bool gt = v[u] > m;
-            m = gt ? v[u] : m;
-            ms = gt ? s0 + u : ms;
-        }
-#pragma unroll
-        for (int k = 0; k < NG; ++k) gmx[k] = k == wg ? m : gmx[k];
-        const uint64_t fld = uint64_t(63) << (6 * wg);
-        gix = (gix & ~fld) | ((uint64_t)ms << (6 * wg));
-        top_update();
-    };
-    // While a heap is not full it accepts only squared distances <= tau, a
-    // bound that at least n_se members of the host are known to meet (so the
-    // n_se nearest all meet it); NO_BOUND until such a bound is found.
-    constexpr uint64_t NO_BOUND = ~0ull >> POS_BITS;
-    uint64_t tau = NO_BOUND;
-    // the same bound on keys: d2 <= tau exactly when key < (tau + 1) << POS_BITS
-    uint64_t tau_key = ~0ull;
-
-    // Stages the members [c0, min(c0 + 64, t_end)) of a leaf in LDS for the
-    // unwrapped (no minimum image) scan; padding slots sit far away.
-    auto stage_chunk = [&](int c0, int t_end, int hbase) __attribute__((always_inline)) {
-        const int j = c0 + lane;
-        const bool vj = j < t_end;
-        cxs[lane] = vj ? (float)F.u[0][j] : 1e30f;
-        cys[lane] = vj ? (float)F.u[1][j] : 1e30f;
-        czs[lane] = vj ? (float)F.u[2][j] : 1e30f;
-        crk[lane] = vj ? F.eid[j] - hbase : 0;
-        __builtin_amdgcn_wave_barrier();
-    };
-
-    // Inserts the members of leaf `node` for the lanes in `mine`.
-    auto scan_leaf = [&](int node, bool mine, bool nowrap, int hbase) __attribute__((always_inline)) {
-        const KdNode& nd = nodes[node];
-        const int s = nd.start, t_end = nd.end;
-        for (int c0 = s; c0 < t_end; c0 += 64) {
-            const int m = min(64, t_end - c0);
-            // candidate distances this chunk gives the wave's queries
-            wcand += (unsigned long long)m * (unsigned long long)__popcll(__ballot(mine));
-            if (nowrap) {
-                // FP32 prefilter: coordinates are integers below 2^24, so the
-                // differences are exact and the rounded sum of squares is within
-                // 2e-7 of the exact one; only candidates that may beat the
-                // current worst key (or meet tau) get the exact integer key.
-                stage_chunk(c0, t_end, hbase);
-                // pass 1 (no divergence): which candidates may beat this lane's
-                // current worst key; pass 2: insert them, each lane walking its
-                // own mask, so the wave spends max-over-lanes insertions per
-                // chunk instead of one per candidate that any lane takes.
-                // Pass 1 is unrolled in blocks of 16 candidates.  The bound
-                // wf enters the FMA chain, dx^2 + dy^2 + (dz^2 - wf), whose
-                // rounding (three roundings of values below max(d2, wf)) stays
-                // inside wf's relative slack, so a negative result marks every
-                // candidate that may be taken; its sign bit is shifted into the
-                // mask from the bottom, candidates from the highest index down,
-                // so candidate t ends at bit t % 32 of word t / 32.  Bits past
-                // the chunk's end are cleared.
-                const float wf = count < n_se ? (tau == NO_BOUND ? INFINITY : (float)tau * 1.000001f + 1.0f)
-                                              : (float)(worst >> POS_BITS) * 1.000001f + 1.0f;
-                const float nwf = -wf;
-                uint32_t tk[2] = {0u, 0u};
-#pragma unroll
-                for (int b = 3; b >= 0; --b) {
-                    if (16 * b < m) {
-#pragma unroll
-                        for (int t4 = 12; t4 >= 0; t4 -= 4) {
-                            const int t = 16 * b + t4;
-                            const float4 X = *reinterpret_cast<const float4*>(&cxs[t]);
-                            const float4 Y = *reinterpret_cast<const float4*>(&cys[t]);
-                            const float4 Z = *reinterpret_cast<const float4*>(&czs[t]);
-                            const float xs[4] = {X.x, X.y, X.z, X.w}, ys[4] = {Y.x, Y.y, Y.z, Y.w},
-                                        zs[4] = {Z.x, Z.y, Z.z, Z.w};
-#pragma unroll
-                            for (int u = 3; u >= 0; --u) {
-                                const float dxf = xs[u] - pxf, dyf = ys[u] - pyf, dzf = zs[u] - pzf;
-                                const float sd = fmaf(dxf, dxf, fmaf(dyf, dyf, fmaf(dzf, dzf, nwf)));
-                                tk[b >> 1] = __builtin_amdgcn_alignbit(tk[b >> 1], __float_as_uint(sd), 31);
-                            }
-                        }
-                    }
-                }
-                uint64_t take = ((uint64_t)tk[1] << 32) | tk[0];
-                if (m < 64) take &= (uint64_t(1) << m) - 1;
-                if (!mine) take = 0;
-                while (take) {
-                    const int t = __builtin_ctzll(take);
-                    take &= take - 1;
-                    // |d| < 2^21: signed 64-bit squares, exact sum
-                    const int dx = (int)(cxs[t] - pxf), dy = (int)(cys[t] - pyf), dz = (int)(czs[t] - pzf);
-                    const uint64_t d2 = (uint64_t)((int64_t)dx * dx + (int64_t)dy * dy + (int64_t)dz * dz);
-                    const uint64_t key = (d2 << POS_BITS) | (uint64_t)(uint32_t)crk[t];
-                    if (key < (count < n_se ? tau_key : worst)) insert(key);
-                }
-                __builtin_amdgcn_wave_barrier();
-                continue;
-            }
-            // one member per lane, shared by lane reads
-            const int j = c0 + lane;
-            const bool vj = j < t_end;
-            const int lx = vj ? F.u[0][j] : 0, ly = vj ? F.u[1][j] : 0, lz = vj ? F.u[2][j] : 0;
-            const int le = vj ? F.eid[j] - hbase : 0;
-            for (int t = 0; t < m; ++t) {
-                const int cx = __builtin_amdgcn_readlane(lx, t);
-                const int cy = __builtin_amdgcn_readlane(ly, t);
-                const int cz = __builtin_amdgcn_readlane(lz, t);
-                const int ce = __builtin_amdgcn_readlane(le, t);
-                const int ddx = min_image(cx - px, gb);
-                const int ddy = min_image(cy - py, gb);
-                const int ddz = min_image(cz - pz, gb);
-                uint64_t d2;
-                if (max(max(abs(ddx), abs(ddy)), abs(ddz)) < 32768)
-                    d2 = (uint64_t)((uint32_t)(ddx * ddx) + (uint32_t)(ddy * ddy) + (uint32_t)(ddz * ddz));
-                else
-                    d2 = (uint64_t)((int64_t)ddx * ddx + (int64_t)ddy * ddy + (int64_t)ddz * ddz);
-                const uint64_t key = (d2 << POS_BITS) | (uint64_t)(uint32_t)ce;
-                if (mine && (count < n_se || key < worst)) insert(key);
-            }
-        }
-    };
-    // Box distances in FP32: the per-axis gaps are exact integers below
-    // 2^23 and the rounded sum is within 2^-22 of the exact one, so a bound
-    // raised by 2^-20 visits every node the exact test would.
-    auto needed = [&](const KdNode& nd, bool mine) __attribute__((always_inline)) {
-        const float dx = (float)max(max(nd.bmin[0] - px, px - nd.bmax[0]), 0);
-        const float dy = (float)max(max(nd.bmin[1] - py, py - nd.bmax[1]), 0);
-        const float dz = (float)max(max(nd.bmin[2] - pz, pz - nd.bmax[2]), 0);
-        const float md2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
-        const float bnd = count < n_se ? (tau == NO_BOUND ? INFINITY : (float)tau * (1.0f + 0x1p-20f) + 1.0f)
-                                       : (float)(worst >> POS_BITS) * (1.0f + 0x1p-20f) + 1.0f;
-        return __ballot(mine && md2 <= bnd) != 0;
-    };
+    for (int i = 0; i < L; ++i) d[i] = INFINITY;
+    bool over = false;  // the query goes to the exact kernel
+    unsigned long long wcand = 0;
 
     bool pending = active;
-    while (__ballot(pending)) {
-        const uint64_t pm = __ballot(pending);
-        const int fl = __ffsll((unsigned long long)pm) - 1;
-        const int hh = __shfl(h, fl, 64);
-        const int hbase = host_off[hh];
+    for (uint64_t pm = __ballot(pending); pm; pm = __ballot(pending)) {
+        const int hh = __builtin_amdgcn_readlane(h, __builtin_ctzll(pm));
         const bool mine = pending && h == hh;
-        // a host narrower than half the box needs no minimum image: its
-        // unwrapped coordinate differences are the periodic ones
-        const KdNode& root = nodes[hh];
-        const int half = 1 << (gb - 1);
-        const bool nowrap = root.bmax[0] - root.bmin[0] < half && root.bmax[1] - root.bmin[1] < half &&
-                            root.bmax[2] - root.bmin[2] < half;
-        // the centre of this host's queries: near children and visiting order follow it
-        int64_t sx = mine ? px : 0, sy = mine ? py : 0, sz = mine ? pz : 0;
-        int cnt = mine ? 1 : 0;
-        for (int o = 32; o > 0; o >>= 1) {
-            sx += __shfl_xor(sx, o, 64);
-            sy += __shfl_xor(sy, o, 64);
-            sz += __shfl_xor(sz, o, 64);
-            cnt += __shfl_xor(cnt, o, 64);
-        }
-        // wave-uniform; the near child is picked arithmetically on the split
-        // dimension (a select over the three would go through memory)
-        const int ccx = __builtin_amdgcn_readfirstlane((int)(sx / cnt));
-        const int ccy = __builtin_amdgcn_readfirstlane((int)(sy / cnt));
-        const int ccz = __builtin_amdgcn_readfirstlane((int)(sz / cnt));
-        // Depth-first walk of the host's tree, near child first; skip_own:
-        // the leaves holding a query of this pass were scanned already.
-        auto walk = [&](bool skip_own) __attribute__((always_inline)) {
-            if (lane == 0) stack[0] = hh;
-            int sp = 1;
-            __builtin_amdgcn_wave_barrier();
-            while (sp > 0) {
-                const int node = stack[--sp];
-                __builtin_amdgcn_wave_barrier();
-                const KdNode& nd = nodes[node];
-                if (!needed(nd, mine)) continue;
-                if (nd.dim < 0) {
-                    if (!(skip_own && __ballot(mine && own == node))) scan_leaf(node, mine, nowrap, hbase);
-                    continue;
+        const bool wrap = host_wraps(T.hbox, hh, gb);
+        const float S = (float)(1 << gb);
+        // queries of other hosts stand far away and keep nothing
+        const float px = mine ? qx : 3.f * PAD, py = mine ? qy : 3.f * PAD, pz = mine ? qz : 3.f * PAD;
+        const float4 q4 = make_float4(qx, qy, qz, 0.f);
+        const float4 w0 = make_float4(wave_fold(mine ? qx : INFINITY, OpMin{}), wave_fold(mine ? qy : INFINITY, OpMin{}),
+                                      wave_fold(mine ? qz : INFINITY, OpMin{}), 0.f);
+        const float4 w1 = make_float4(wave_fold(mine ? qx : -INFINITY, OpMax{}),
+                                      wave_fold(mine ? qy : -INFINITY, OpMax{}),
+                                      wave_fold(mine ? qz : -INFINITY, OpMax{}), 0.f);
+        float B = mine ? INFINITY : -1.f;  // squared radius no member of the query's set exceeds
+        float Bmax = INFINITY;             // the wavefront's largest (with slack)
+        int nvis = 0;
+        const int nmine = __popcll(__ballot(mine)) / LPQ;
+
+        // squared distances of the lane's members of a leaf, plus c
+        auto distances = [&](int leaf, float c, float (&sd)[E]) __attribute__((always_inline)) {
+            const size_t b = (size_t)(uint32_t)leaf * LEAF;  // uniform
+            const uint32_t o = (uint32_t)(sub * E);
+            float xs[E], ys[E], zs[E];
+            __builtin_memcpy(xs, T.x + b + o, sizeof xs);
+            __builtin_memcpy(ys, T.y + b + o, sizeof ys);
+            __builtin_memcpy(zs, T.z + b + o, sizeof zs);
+            if (wrap) {
+                // (an empty slot stays far away)
+                auto img = [&](float a, float p) __attribute__((always_inline)) {
+                    const float d = fabsf(a - p);
+                    return p + (d < S ? fminf(d, S - d) : d);
+                };
+#pragma unroll
+                for (int k = 0; k < E; ++k) {
+                    xs[k] = img(xs[k], px);
+                    ys[k] = img(ys[k], py);
+                    zs[k] = img(zs[k], pz);
                 }
-                if (sp + 2 > STACK) break;  // cannot happen for trees of depth < 64
-                const int dm = nd.dim;
-                const int cf = ccx + (dm >= 1) * (ccy - ccx) + (dm == 2) * (ccz - ccy);
-                const int nearc = cf < nd.t ? nd.left : nd.right;
-                const int farc = cf < nd.t ? nd.right : nd.left;
-                if (lane == 0) {
-                    stack[sp] = farc;
-                    stack[sp + 1] = nearc;
-                }
-                sp += 2;
-                __builtin_amdgcn_wave_barrier();
+            }
+#pragma unroll
+            for (int k = 0; k < E; ++k) {
+                const float dx = xs[k] - px, dy = ys[k] - py, dz = zs[k] - pz;
+                sd[k] = fmaf(dx, dx, fmaf(dy, dy, fmaf(dz, dz, c)));
             }
         };
-        if (!nowrap) {
-            walk(false);
-        } else {
-            // The bound tau: a lane's own leaf suggests a squared radius T0
-            // holding about n_se members (its density, n_se / (4/3 pi r^3)).
-            // Members of the wave's own leaves (all in this host) are counted
-            // under eight thresholds T0 * 2^((k-2)/2); the smallest threshold
-            // met by n_se of them, rounded up past the FP32 error of the
-            // counted distances, is a bound that n_se members meet.
-            float thr[8];
-            uint32_t cnt[8];
-            {
-                float T0 = 0.f;
-                if (mine) {
-                    const KdNode& on = nodes[own];
-                    const float vol = (float)(on.bmax[0] - on.bmin[0] + 1) * (float)(on.bmax[1] - on.bmin[1] + 1) *
-                                      (float)(on.bmax[2] - on.bmin[2] + 1);
-                    const float r = cbrtf(3.0f * (float)n_se * vol / (4.0f * (float)M_PI * (float)(on.end - on.start)));
-                    T0 = r * r;
-                }
+        auto scan = [&](int leaf) __attribute__((always_inline)) {
+            float sd[E];
+            distances(leaf, 0.f, sd);
+            wcand += (unsigned long long)(LEAF * nmine);
+            // a leaf whose box a ball reaches may still hold no member of it
+            float near = sd[0];
 #pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    thr[k] = T0 * exp2f(0.5f * (float)(k - 2));
-                    cnt[k] = 0;
-                }
+            for (int k = 1; k < E; ++k) near = fminf(near, sd[k]);
+            if (__ballot(near <= B * SLACK) == 0) return;
+#pragma unroll
+            for (int k = 0; k < E; ++k) {
+#pragma unroll
+                for (int i = L - 1; i > 0; --i) d[i] = __builtin_amdgcn_fmed3f(sd[k], d[i - 1], d[i]);
+                d[0] = fminf(d[0], sd[k]);
             }
-            for (uint64_t todo = __ballot(mine); todo;) {
-                const int L = __builtin_amdgcn_readlane(own, __ffsll((unsigned long long)todo) - 1);
-                const KdNode& nl = nodes[L];
-                for (int c0 = nl.start; c0 < nl.end; c0 += 64) {
-                    stage_chunk(c0, nl.end, hbase);
-                    const int m = min(64, nl.end - c0);
-#pragma unroll
-                    for (int b = 0; b < 4; ++b) {
-                        if (16 * b < m) {
-#pragma unroll
-                            for (int t4 = 0; t4 < 16; t4 += 4) {
-                                const int t = 16 * b + t4;
-                                const float4 X = *reinterpret_cast<const float4*>(&cxs[t]);
-                                const float4 Y = *reinterpret_cast<const float4*>(&cys[t]);
-                                const float4 Z = *reinterpret_cast<const float4*>(&czs[t]);
-                                const float xs[4] = {X.x, X.y, X.z, X.w}, ys[4] = {Y.x, Y.y, Y.z, Y.w},
-                                            zs[4] = {Z.x, Z.y, Z.z, Z.w};
-#pragma unroll
-                                for (int u = 0; u < 4; ++u) {
-                                    const float dxf = xs[u] - pxf, dyf = ys[u] - pyf, dzf = zs[u] - pzf;
-                                    const float d2f = fmaf(dxf, dxf, fmaf(dyf, dyf, dzf * dzf));
-#pragma unroll
-                                    for (int k = 0; k < 8; ++k) cnt[k] += d2f <= thr[k] ? 1u : 0u;
-                                }
-                            }
-                        }
-                    }
-                    __builtin_amdgcn_wave_barrier();
-                }
-                todo &= ~__ballot(mine && own == L);
+            if (nvis < VMAX) vis[nvis] = leaf;  // every lane the same word
+            else over = over || mine;
+            nvis = min(nvis + 1, VMAX);
+            const float b = fold<LPQ>(d[KL - 1], OpMax{});
+            B = mine ? b : -1.f;
+            // (as integers the radii order as they do as floats, -1 lowest)
+            Bmax = __int_as_float(wave_fold(__float_as_int(B), OpMax{})) * SLACK;
+        };
+        // whether a ball of the wavefront's queries reaches a box
+        auto reaches = [&](float4 lo, float4 hi) __attribute__((always_inline)) {
+            return __ballot(mine && box_gap2(lo, hi, q4, q4, wrap, S) <= B * SLACK) != 0;
+        };
+        // visits the lanes' boxes that a ball reaches, those near the queries
+        // first (within 0.2 of the largest squared radius: a strict order by
+        // distance, a wavefront-wide minimum a box, was 1% slower on the
+        // 256^3 box, touching boxes first 6%)
+        auto near_first = [&](float4 lo, float4 hi, bool valid, auto visit) __attribute__((always_inline)) {
+            const float g2 = box_gap2(lo, hi, w0, w1, wrap, S);
+            uint64_t far = __ballot(valid && g2 <= Bmax), near = __ballot(valid && g2 <= 0.2f * Bmax);
+            while (far) {
+                const int l = __builtin_ctzll(near ? near : far);
+                near &= ~(uint64_t(1) << l);
+                far &= ~(uint64_t(1) << l);
+                auto rl = [&](float f) __attribute__((always_inline)) {
+                    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(f), l));
+                };
+                if (reaches(make_float4(rl(lo.x), rl(lo.y), rl(lo.z), 0.f), make_float4(rl(hi.x), rl(hi.y), rl(hi.z), 0.f)))
+                    visit(l);
             }
-            if (mine) {
-#pragma unroll
-                for (int k = 7; k >= 0; --k)
-                    if (cnt[k] >= (uint32_t)n_se) tau = (uint64_t)((double)thr[k] * (1.0 + 1e-6)) + 1;
-                tau_key = tau >= NO_BOUND ? ~0ull : (tau + 1) << POS_BITS;
-            }
-            // the leaves of the queries themselves first: they fill every
-            // heap with near neighbours, so the walk prunes from its start
-            uint64_t todo = __ballot(mine);
-            while (todo) {
-                const int L = __builtin_amdgcn_readlane(own, __ffsll((unsigned long long)todo) - 1);
-                scan_leaf(L, mine, true, hbase);
-                todo &= ~__ballot(mine && own == L);
-            }
-            walk(true);
+        };
+        auto bucket = [&](int b) __attribute__((always_inline)) {
+            const int4 bk = T.buckets[b];
+            const int nl = (bk.y + LEAF - 1) / LEAF;
+            const int leaf = bk.z + min(lane, nl - 1);
+            near_first(T.lbox[2 * leaf], T.lbox[2 * leaf + 1], lane < nl, [&](int l) __attribute__((always_inline)) {
+                // the leaves of the queries themselves were scanned first
+                if (__ballot(mine && own == bk.z + l) == 0) scan(bk.z + l);
+            });
+        };
+        // the queries' own leaves first, then the rest of their buckets, then
+        // the host's other buckets
+        for (uint64_t todo = __ballot(mine); todo;) {
+            const int leaf = __builtin_amdgcn_readlane(own, __builtin_ctzll(todo));
+            scan(leaf);
+            todo &= ~__ballot(own == leaf);
         }
+        const int hb0 = T.host_bucket[hh], hb1 = T.host_bucket[hh + 1];
+        for (int pass = 0; pass < 2; ++pass) {
+            if (pass == 0) {
+                for (uint64_t todo = __ballot(mine); todo;) {
+                    const int b = __builtin_amdgcn_readlane(obk, __builtin_ctzll(todo));
+                    todo &= ~__ballot(obk == b);
+                    bucket(b);
+                }
+                continue;
+            }
+            for (int g0 = hb0; g0 < hb1; g0 += 64) {
+                const int b = min(g0 + lane, hb1 - 1);
+                // queries' own buckets are done
+                bool done = false;
+                for (uint64_t todo = __ballot(mine); todo;) {
+                    const int ob = __builtin_amdgcn_readlane(obk, __builtin_ctzll(todo));
+                    todo &= ~__ballot(obk == ob);
+                    done = done || ob == b;
+                }
+                near_first(T.bbox[2 * b], T.bbox[2 * b + 1], g0 + lane < hb1 && !done,
+                              [&](int l) __attribute__((always_inline)) { bucket(g0 + l); });
+            }
+        }
+        // a threshold X that at least n_se members meet, and hardly more
+        auto count_le = [&](float x) __attribute__((always_inline)) {
+            int c = 0;
+#pragma unroll
+            for (int i = 0; i < L; ++i) c += d[i] <= x ? 1 : 0;
+            return fold<LPQ>(c, OpAdd{});
+        };
+        float hi = B;
+        if (__ballot(mine && !(B < INFINITY))) {
+            // a lane met fewer than KL members (small hosts)
+            float m = 0.f;
+#pragma unroll
+            for (int i = 0; i < L; ++i) m = d[i] < INFINITY ? fmaxf(m, d[i]) : m;
+            m = fold<LPQ>(m, OpMax{});
+            if (mine && !(B < INFINITY)) hi = m;
+        }
+        float lo = 0.f;
+        int chi = count_le(hi), clo = 0;
+        if (mine && chi < n_se) over = true;
+        bool found = !mine || chi <= n_se;
+        // by the counts' linear interpolation, every third step halving
+        for (int it = 0; it < 24 && __ballot(!found); ++it) {
+            const float w = it % 3 == 2 ? 0.5f : ((float)(n_se - clo) + 0.5f) * __builtin_amdgcn_rcpf((float)(chi - clo) + 0.5f);
+            const float mid = fminf(fmaf(w, hi - lo, lo), hi);
+            const int cm = count_le(mid);
+            if (!found) {
+                if (cm >= n_se) {
+                    hi = mid;
+                    chi = cm;
+                    found = cm == n_se;
+                } else {
+                    lo = mid;
+                    clo = cm;
+                }
+            }
+        }
+        const float X = mine ? hi * SLACK : -1.f;
+        // the members within X: the sign of d2 - X marks them (SLACK covers its
+        // rounding), 32 marks a word, then each lane lists its marks
+        int nl = 0;
+        __builtin_amdgcn_wave_barrier();
+        constexpr int LPW = 32 / E;  // leaves a word
+        for (int v0 = 0; v0 < nvis; v0 += LPW) {
+            uint32_t mark = 0;
+            const int nv = min(LPW, nvis - v0);
+            for (int v = 0; v < nv; ++v) {
+                float sd[E];
+                distances(__builtin_amdgcn_readfirstlane(vis[v0 + v]), -X, sd);
+#pragma unroll
+                for (int k = 0; k < E; ++k)
+                    mark = __builtin_amdgcn_alignbit(mark, __float_as_uint(sd[k]), 31);
+            }
+            // the first member's mark is the highest of nv * E bits
+            mark <<= 32 - nv * E;
+            while (mark) {
+                const int t = __clz(mark);
+                mark &= ~(0x80000000u >> t);
+                if (nl < CAPL) lst[nl][lane] = (uint16_t)(v0 * E + t);
+                ++nl;
+            }
+        }
+        int total = fold<LPQ>(nl, OpAdd{});
+        if (fold<LPQ>(nl, OpMax{}) > CAPL || total < n_se) over = over || mine;
+        nl = min(nl, CAPL);
+        auto listed = [&](int i) __attribute__((always_inline)) {
+            const int code = lst[i][lane];
+            return vis[code / E] * LEAF + sub * E + code % E;
+        };
+        __builtin_amdgcn_wave_barrier();
+        // more than n_se: the largest exact keys leave
+        bool extra = mine && !over && total > n_se;
+        while (__ballot(extra)) {
+            uint64_t big = 0;
+            int at = 0;
+            if (extra)
+                for (int i = 0; i < nl; ++i) {
+                    const int s = listed(i);
+                    const uint64_t key = exact_key((int)(T.x[s] - qx), (int)(T.y[s] - qy), (int)(T.z[s] - qz),
+                                                   T.eid[s] - host_off[hh], wrap, gb) + 1;
+                    if (key > big) {
+                        big = key;
+                        at = i;
+                    }
+                }
+            const uint64_t top = fold<LPQ>(big, OpMax{});
+            if (extra && big == top) {
+                --nl;
+                lst[at][lane] = lst[nl][lane];
+            }
+            __builtin_amdgcn_wave_barrier();
+            --total;
+            extra = extra && total > n_se;
+        }
+        int first = nl;  // members listed by the query's lanes before this one
+#pragma unroll
+        for (int o = 1; o < LPQ; o <<= 1) {
+            const int y = __shfl_up(first, o, LPQ);
+            if (sub >= o) first += y;
+        }
+        first -= nl;
+        if (mine && !over)
+            for (int i = 0; i < nl; ++i) nbr[q][first + i] = listed(i);
+        __builtin_amdgcn_wave_barrier();
         pending = pending && !mine;
     }
-    if (ncand && lane == 0) atomicAdd(ncand, wcand);
-    if (!active) return;
-    // velocity neighbours among the spatial ones, by (dv2, index); velocities
-    // and masses are indexed by element id = host base + rank
-    const int qe = F.eid[e];
-    const float4 vq = V[qe];
+    if (ncand && lane == 0) atomicAdd(ncand + blockIdx.x % KNN_CAND_SLOTS, wcand);
+    // velocity distances of the set, LPQ lanes sharing it
+    const bool ok = active && !over;
+    const float4 vq = V[ok ? slot : 0];
     const double vqx = (double)vq.x, vqy = (double)vq.y, vqz = (double)vq.z;
+    double dv[KL];
+    float ms[KL];
     double msum = 0.0;
-    double h2, sw = 0.0;
-    const double kW = 15.0 / (8.0 * M_PI);
-    // the neighbours' velocities and masses, eight at a time: the loads of a
-    // batch are issued together and waited for once
-    constexpr int VB = 8;
-    int bpos[VB];
-    float bvx[VB], bvy[VB], bvz[VB], bms[VB];
-    auto fetch = [&](int a0) __attribute__((always_inline)) {
 #pragma unroll
-        for (int u = 0; u < VB; ++u) {
-            const int a = a0 + u;
-            bpos[u] = a < n_se ? (int)(heap[a][lane] & POS_MASK) : 0;
-        }
-#pragma unroll
-        for (int u = 0; u < VB; ++u) {
-            const float4 w = V[base + bpos[u]];
-            bvx[u] = w.x;
-            bvy[u] = w.y;
-            bvz[u] = w.z;
-            bms[u] = w.w;
-        }
-    };
-    if constexpr (NVR > 0) {
-        double vdr[NVR];
-        int vpr[NVR];
-#pragma unroll
-        for (int i = 0; i < NVR; ++i) { vdr[i] = INFINITY; vpr[i] = 0x7FFFFFFF; }
-        for (int a0 = 0; a0 < n_se; a0 += VB) {
-            fetch(a0);
-#pragma unroll
-            for (int u = 0; u < VB; ++u) {
-                if (a0 + u >= n_se) break;
-                const int pos = bpos[u];
-                msum += use_mass ? (double)bms[u] : mass_value;
-                const double ax = vqx - (double)bvx[u], ay = vqy - (double)bvy[u], az = vqz - (double)bvz[u];
-                const double dv2 = ax * ax + ay * ay + az * az;
-#pragma unroll
-                for (int i = NVR - 1; i > 0; --i) {
-                    const bool lp = vless(dv2, pos, vdr[i - 1], vpr[i - 1]);
-                    const bool lc = vless(dv2, pos, vdr[i], vpr[i]);
-                    vdr[i] = lp ? vdr[i - 1] : (lc ? dv2 : vdr[i]);
-                    vpr[i] = lp ? vpr[i - 1] : (lc ? pos : vpr[i]);
-                }
-                if (vless(dv2, pos, vdr[0], vpr[0])) { vdr[0] = dv2; vpr[0] = pos; }
-            }
-        }
-        h2 = vdr[NVR - 1];
-        if (h2 != 0.0) {
-#pragma unroll
-            for (int a = 0; a < NVR; ++a) {
-                const double m = use_mass ? (double)V[base + vpr[a]].w : mass_value;
-                sw += m * kW * (1.0 - vdr[a] / h2);
-            }
-        }
-    } else {
-        int nv = 0;
-        for (int a0 = 0; a0 < n_se; a0 += VB) {
-            fetch(a0);
-            for (int u = 0; u < VB && a0 + u < n_se; ++u) {
-                const int pos = bpos[u];
-                msum += use_mass ? (double)bms[u] : mass_value;
-                const double ax = vqx - (double)bvx[u], ay = vqy - (double)bvy[u], az = vqz - (double)bvz[u];
-                const double dv2 = ax * ax + ay * ay + az * az;
-                if (nv == n_v) {
-                    if (!vless(dv2, pos, vd[n_v - 1][lane], vp[n_v - 1][lane])) continue;
-                    --nv;
-                }
-                int i = nv++;
-                while (i > 0 && vless(dv2, pos, vd[i - 1][lane], vp[i - 1][lane])) {
-                    vd[i][lane] = vd[i - 1][lane];
-                    vp[i][lane] = vp[i - 1][lane];
-                    --i;
-                }
-                vd[i][lane] = dv2;
-                vp[i][lane] = pos;
-            }
-        }
-        h2 = vd[n_v - 1][lane];
-        if (h2 != 0.0)
-            for (int a = 0; a < n_v; ++a) {
-                const double m = use_mass ? (double)V[base + vp[a][lane]].w : mass_value;
-                sw += m * kW * (1.0 - vd[a][lane] / h2);
-            }
+    for (int k = 0; k < KL; ++k) {
+        const int a = sub + LPQ * k;
+        const bool in = ok && a < n_se;
+        const float4 w = V[in ? nbr[q][a] : 0];
+        const double ax = vqx - (double)w.x, ay = vqy - (double)w.y, az = vqz - (double)w.z;
+        dv[k] = in ? ax * ax + ay * ay + az * az : (double)INFINITY;
+        ms[k] = w.w;
+        if (in && use_mass) msum += (double)w.w;
     }
-    const double lfl = h2 == 0.0 ? INFINITY : log(sw) - 1.5 * log(h2) - log(msum);
-    R[F.gidx[e]] = (float)(lfl - FB[qe]);
+    msum = use_mass ? fold<LPQ>(msum, OpAdd{}) : mass_sum;
+    // h2, the n_v-th smallest: bisection to a value that n_v of them meet,
+    // then the largest of those; equal values are taken off one by one
+    auto count_v = [&](double x) __attribute__((always_inline)) {
+        int c = 0;
+#pragma unroll
+        for (int k = 0; k < KL; ++k) c += dv[k] <= x ? 1 : 0;
+        return fold<LPQ>(c, OpAdd{});
+    };
+    auto largest = [&](double x, bool below) __attribute__((always_inline)) {
+        double m = -1.0;
+#pragma unroll
+        for (int k = 0; k < KL; ++k) m = (below ? dv[k] < x : dv[k] <= x) && dv[k] > m ? dv[k] : m;
+        return fold<LPQ>(m, OpMax{});
+    };
+    double vlo = 0.0, vhi = largest(INFINITY, true);
+    int clo = 0, chi = n_se;
+    bool found = !ok || n_v >= n_se;
+    for (int it = 0; it < 48 && __ballot(!found); ++it) {
+        const float w = it % 3 == 2 ? 0.5f : ((float)(n_v - clo) + 0.5f) * __builtin_amdgcn_rcpf((float)(chi - clo) + 0.5f);
+        const double mid = fmin(vlo + (double)w * (vhi - vlo), vhi);
+        const int c = count_v(mid);
+        if (!found) {
+            if (c >= n_v) {
+                vhi = mid;
+                chi = c;
+                found = c == n_v;
+            } else {
+                vlo = mid;
+                clo = c;
+            }
+        }
+    }
+    double h2 = largest(vhi, false);
+    for (;;) {
+        const double nx = largest(h2, true);
+        const bool less = ok && nx >= 0.0 && count_v(nx) >= n_v;
+        if (!__ballot(less)) break;
+        if (less) h2 = nx;
+    }
+    double sw = 0.0;
+    const double kW = 15.0 / (8.0 * M_PI);
+#pragma unroll
+    for (int k = 0; k < KL; ++k)
+        if (dv[k] < h2) sw += (use_mass ? (double)ms[k] : mass_value) * kW * (1.0 - dv[k] / h2);
+    sw = fold<LPQ>(sw, OpAdd{});
+    // one logarithm a lane: ln f_l = ln sw - 1.5 ln h2 - ln msum
+    const double term = log(sub == 0 ? sw : sub == 1 ? h2 : msum);
+    const double t1 = __shfl(term, (lane & ~(LPQ - 1)) + 1, 64), t2 = __shfl(term, (lane & ~(LPQ - 1)) + 2, 64);
+    if (sub != 0) return;
+    if (ok) {
+        const double lfl = h2 == 0.0 ? INFINITY : term - 1.5 * t1 - t2;
+        R[gid] = (float)(lfl - FB[slot]);
+    } else if (active) {
+        flagged[atomicAdd(n_flagged, 1)] = slot;
+    }
 }
 
-template <int NSE, int NVR, int NVLMAX>
-int launch_knn(vr_ctx* ctx, const uint32_t* qpos, int64_t nq, const KdTree& tree, const float4* V,
-               const double* FB, const int32_t* host_off, const vr_particles* p, int n_se, int n_v, float* R,
-               hipStream_t st) {
-    VR_TIMED(ctx, "knn", st, nq,
-             hipLaunchKernelGGL((k_knn<NSE, NVR, NVLMAX>), dim3(grid_for(nq, 64)), dim3(64), 0, st, qpos, nq, tree.nodes,
-                                tree.F, tree.seg_node, V, FB, tree.elem_host, host_off, n_se, n_v, tree.use_mass, p->mass_value, p->grid_bits, R, (unsigned)ctx->xcd_chunk,
-                                ctx->timing ? ctx->knn_cand : nullptr));
-    VR_LAUNCH_CHECK(ctx);
-    return VR_OK;
-}
-
-
-// ---- large neighbour sets (n_se > 64, up to the paper's 256) --------------
-// One wavefront per query.  Candidates of a visited leaf are keyed by the
-// lanes (exact d2 << 22 | rank, minimum image), and those below the current
-// bound W are appended to an LDS buffer.  When the buffer holds n_se + 64
-// keys or more, a bitwise radix select over the wave finds the n_se-th
-// smallest key T; the keys up to T are kept and W = T.  The tree walk (one
-// shared stack, near child first) prunes nodes whose box is no nearer than
-// W allows.  The n_v velocity neighbours are then taken from the n_se by
-// repeated wave-wide minima of (FP64 dv2, rank).
+// ---- one wavefront per query, exact keys throughout -------------------------
+// For the queries the kernel above could not finish.  Candidates of a visited
+// leaf are keyed by the lanes, and those below the current bound are appended
+// to an LDS buffer.  When the buffer holds n_se + 192 keys or more, a radix
+// select over the wave finds the n_se-th smallest key; the keys up to it are
+// kept and it becomes the bound.
 constexpr int BIG_CAP = 256;              // largest n_se
 constexpr int BIG_EXTRA = 192;            // keys appended past n_se before the buffer is cut back
-constexpr int BIG_BUF = BIG_CAP + BIG_EXTRA + 64;  // room for one more leaf chunk
+constexpr int BIG_BUF = BIG_CAP + BIG_EXTRA + 64;  // room for one more leaf
 constexpr int BIG_J = BIG_BUF / 64;       // buffer slots per lane
 
-// The r-th smallest (0-based) of the valid keys k[j] of all lanes.
+__device__ __forceinline__ bool vless(double a, int pa, double b, int pb) { return a < b || (a == b && pa < pb); }
+
 // The key of rank r (0-based) among the valid keys of the wavefront, by a
 // radix select over byte digits: per digit, a histogram of the keys that
 // share the digits chosen so far, and a wave-wide prefix over its 256
@@ -646,172 +834,182 @@ __device__ __forceinline__ uint64_t wave_select(const uint64_t (&k)[BIG_J], cons
     return prefix;
 }
 
-__global__ __launch_bounds__(64) void k_knn_big(const uint32_t* __restrict__ qpos, int64_t nq,
-                                                const KdNode* __restrict__ nodes, Elems F,
-                                                const float4* __restrict__ V, const double* __restrict__ FB,
-                                                const int* __restrict__ elem_host, const int32_t* __restrict__ host_off,
-                                                int n_se, int n_v, int use_mass, double mass_value, int gb,
-                                                float* __restrict__ R, unsigned xchunk) {
+__global__ __launch_bounds__(64) void k_knn_wave(const int* __restrict__ flagged, const int* __restrict__ n_flagged,
+                                                 Slots T, const float4* __restrict__ V, const double* __restrict__ FB,
+                                                 const int32_t* __restrict__ host_off, int n_se, int n_v, int use_mass,
+                                                 double mass_value, int gb, float* __restrict__ R) {
     __shared__ uint64_t buf[BIG_BUF];
+    __shared__ int bslot[BIG_BUF];
     __shared__ uint32_t sel_hist[256];
-    __shared__ int stack[STACK];
-    __shared__ double sel_d[32];
-    __shared__ int sel_p[32];
+    __shared__ double sel_d[64];
+    __shared__ float sel_m[64];
     const int lane = threadIdx.x;
-    const int64_t qi = (int64_t)xcd_swizzle(blockIdx.x, gridDim.x, xchunk);
-    if (qi >= nq) return;  // uniform
-    const int e = qpos ? (int)qpos[qi] : (int)qi;
-    const int h = elem_host[e];
-    const int base = host_off[h];
-    const int px = F.u[0][e], py = F.u[1][e], pz = F.u[2][e];
-    int nb = 0;            // keys in buf (uniform)
-    uint64_t W = ~0ull;    // keys below W are taken (uniform)
-
-    auto compact = [&]() __attribute__((always_inline)) {
-        uint64_t k[BIG_J];
-        bool v[BIG_J];
+    const int nf = *n_flagged;
+    for (int f = blockIdx.x; f < nf; f += gridDim.x) {
+        const int slot = flagged[f];
+        const int h = T.buckets[T.leaf_bucket[slot / LEAF]].w;
+        const int base = host_off[h];
+        const bool wrap = host_wraps(T.hbox, h, gb);
+        const float qx = T.x[slot], qy = T.y[slot], qz = T.z[slot];
+        const float4 q4 = make_float4(qx, qy, qz, 0.f);
+        int nb = 0;            // keys in buf (uniform)
+        uint64_t W = ~0ull;    // keys below W are taken (uniform)
+        auto compact = [&]() __attribute__((always_inline)) {
+            uint64_t k[BIG_J];
+            int sl[BIG_J];
+            bool v[BIG_J];
 #pragma unroll
-        for (int j = 0; j < BIG_J; ++j) {
-            v[j] = lane + 64 * j < nb;
-            k[j] = v[j] ? buf[lane + 64 * j] : 0;
-        }
-        const uint64_t T = wave_select(k, v, n_se - 1, sel_hist);
-        __builtin_amdgcn_wave_barrier();
-        int at = 0;
+            for (int j = 0; j < BIG_J; ++j) {
+                v[j] = lane + 64 * j < nb;
+                k[j] = v[j] ? buf[lane + 64 * j] : 0;
+                sl[j] = v[j] ? bslot[lane + 64 * j] : 0;
+            }
+            const uint64_t top = wave_select(k, v, n_se - 1, sel_hist);
+            __builtin_amdgcn_wave_barrier();
+            int at = 0;
 #pragma unroll
-        for (int j = 0; j < BIG_J; ++j) {
-            const bool keep = v[j] && k[j] <= T;
-            const uint64_t m = __ballot(keep);
-            if (keep) buf[at + __popcll(m & lanemask_lt())] = k[j];
-            at += __popcll(m);
-        }
-        __builtin_amdgcn_wave_barrier();
-        nb = n_se;
-        W = T;
-    };
-    auto scan = [&](int node) __attribute__((always_inline)) {
-        const KdNode& nd = nodes[node];
-        for (int c0 = nd.start; c0 < nd.end; c0 += 64) {
-            const int j = c0 + lane;
+            for (int j = 0; j < BIG_J; ++j) {
+                const bool keep = v[j] && k[j] <= top;
+                const uint64_t m = __ballot(keep);
+                if (keep) {
+                    const int to = at + __popcll(m & lanemask_lt());
+                    buf[to] = k[j];
+                    bslot[to] = sl[j];
+                }
+                at += __popcll(m);
+            }
+            __builtin_amdgcn_wave_barrier();
+            nb = n_se;
+            W = top;
+        };
+        // whether the lane's box may hold a member of the set
+        auto near = [&](const float4* box) __attribute__((always_inline)) {
+            const float g2 = box_gap2(box[0], box[1], q4, q4, wrap, (float)(1 << gb));
+            return nb < n_se || g2 <= (float)(W >> POS_BITS) * SLACK + 1.f;
+        };
+        auto scan = [&](int leaf) __attribute__((always_inline)) {
+            const int s = leaf * LEAF + (lane & (LEAF - 1));
             bool take = false;
             uint64_t key = 0;
-            if (j < nd.end) {
-                const int64_t dx = min_image(F.u[0][j] - px, gb), dy = min_image(F.u[1][j] - py, gb),
-                              dz = min_image(F.u[2][j] - pz, gb);
-                const uint64_t d2 = (uint64_t)(dx * dx + dy * dy + dz * dz);
-                key = (d2 << POS_BITS) | (uint64_t)(uint32_t)(F.eid[j] - base);
+            if (lane < LEAF && T.gid[s] >= 0) {
+                key = exact_key((int)(T.x[s] - qx), (int)(T.y[s] - qy), (int)(T.z[s] - qz), T.eid[s] - base, wrap, gb);
                 take = key < W;
             }
             const uint64_t m = __ballot(take);
-            if (take) buf[nb + __popcll(m & lanemask_lt())] = key;
+            if (take) {
+                const int to = nb + __popcll(m & lanemask_lt());
+                buf[to] = key;
+                bslot[to] = s;
+            }
             nb += __popcll(m);
             __builtin_amdgcn_wave_barrier();
             if (nb >= n_se + BIG_EXTRA) compact();
+        };
+        auto bucket = [&](int b) __attribute__((always_inline)) {
+            const int4 bk = T.buckets[b];
+            const int nl = (bk.y + LEAF - 1) / LEAF;
+            for (uint64_t todo = __ballot(lane < nl && near(T.lbox + 2 * (bk.z + min(lane, nl - 1)))); todo;
+                 todo &= todo - 1)
+                scan(bk.z + __builtin_ctzll(todo));
+        };
+        // the query's own bucket first, then the host's others, 64 at a time
+        const int ob = T.leaf_bucket[slot / LEAF], b1 = T.host_bucket[h + 1];
+        bucket(ob);
+        for (int b0 = T.host_bucket[h]; b0 < b1; b0 += 64) {
+            const int b = min(b0 + lane, b1 - 1);
+            for (uint64_t todo = __ballot(b0 + lane < b1 && b != ob && near(T.bbox + 2 * b)); todo; todo &= todo - 1)
+                bucket(b0 + __builtin_ctzll(todo));
         }
-    };
-    if (lane == 0) stack[0] = h;
-    int sp = 1;
-    __builtin_amdgcn_wave_barrier();
-    while (sp > 0) {
-        const int node = stack[--sp];
+        if (nb > n_se) compact();
+        // the n_se spatial neighbours: velocity distances and the mass of the set
+        const float4 vq = V[slot];
+        const double vqx = (double)vq.x, vqy = (double)vq.y, vqz = (double)vq.z;
+        double dv[BIG_CAP / 64];
+        int ps[BIG_CAP / 64];
+        float mm[BIG_CAP / 64];
+        double msum = 0.0;
+#pragma unroll
+        for (int j = 0; j < BIG_CAP / 64; ++j) {
+            const int a = lane + 64 * j;
+            dv[j] = INFINITY;
+            ps[j] = 0x7FFFFFFF;
+            mm[j] = 0.f;
+            if (a < n_se) {
+                const float4 w = V[bslot[a]];
+                msum += use_mass ? (double)w.w : mass_value;
+                const double ax = vqx - (double)w.x, ay = vqy - (double)w.y, az = vqz - (double)w.z;
+                dv[j] = ax * ax + ay * ay + az * az;
+                ps[j] = (int)(buf[a] & POS_MASK);
+                mm[j] = w.w;
+            }
+        }
+        for (int o = 32; o > 0; o >>= 1) msum += __shfl_xor(msum, o, 64);
+        // the n_v nearest in velocity, smallest first, by (dv2, rank)
+        for (int i = 0; i < n_v; ++i) {
+            double bd = INFINITY;
+            int bp = 0x7FFFFFFF;
+            float bm = 0.f;
+#pragma unroll
+            for (int j = 0; j < BIG_CAP / 64; ++j)
+                if (vless(dv[j], ps[j], bd, bp)) {
+                    bd = dv[j];
+                    bp = ps[j];
+                    bm = mm[j];
+                }
+            for (int o = 32; o > 0; o >>= 1) {
+                const double od = __shfl_xor(bd, o, 64);
+                const int op = __shfl_xor(bp, o, 64);
+                const float om = __shfl_xor(bm, o, 64);
+                if (vless(od, op, bd, bp)) {
+                    bd = od;
+                    bp = op;
+                    bm = om;
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < BIG_CAP / 64; ++j)
+                if (ps[j] == bp) {
+                    dv[j] = INFINITY;
+                    ps[j] = 0x7FFFFFFF;
+                }
+            if (lane == 0) {
+                sel_d[i] = bd;
+                sel_m[i] = bm;
+            }
+        }
         __builtin_amdgcn_wave_barrier();
-        const KdNode& nd = nodes[node];
-        const int64_t bx = max(max(nd.bmin[0] - px, px - nd.bmax[0]), 0);
-        const int64_t by = max(max(nd.bmin[1] - py, py - nd.bmax[1]), 0);
-        const int64_t bz = max(max(nd.bmin[2] - pz, pz - nd.bmax[2]), 0);
-        int64_t md2 = bx * bx + by * by + bz * bz;
-        if (md2 > (int64_t(1) << 41)) md2 = int64_t(1) << 41;
-        if (nb >= n_se && ((uint64_t)md2 << POS_BITS) >= W) continue;
-        if (nd.dim < 0) {
-            scan(node);
-            continue;
-        }
-        if (sp + 2 > STACK) break;  // cannot happen for trees of depth < 64
-        const int dm = nd.dim;
-        const int cf = px + (dm >= 1) * (py - px) + (dm == 2) * (pz - py);
-        const int nearc = cf < nd.t ? nd.left : nd.right;
-        const int farc = cf < nd.t ? nd.right : nd.left;
         if (lane == 0) {
-            stack[sp] = farc;
-            stack[sp + 1] = nearc;
+            const double kW = 15.0 / (8.0 * M_PI);
+            const double h2 = sel_d[n_v - 1];
+            double sw = 0.0;
+            if (h2 != 0.0)
+                for (int a = 0; a < n_v; ++a) {
+                    const double m = use_mass ? (double)sel_m[a] : mass_value;
+                    sw += m * kW * (1.0 - sel_d[a] / h2);
+                }
+            const double lfl = h2 == 0.0 ? INFINITY : log(sw) - 1.5 * log(h2) - log(msum);
+            R[T.gid[slot]] = (float)(lfl - FB[slot]);
         }
-        sp += 2;
         __builtin_amdgcn_wave_barrier();
     }
-    if (nb > n_se) compact();
-    // the n_se spatial neighbours: velocity distances and the mass of the set
-    const int qe = F.eid[e];
-    const float4 vq = V[qe];
-    const double vqx = (double)vq.x, vqy = (double)vq.y, vqz = (double)vq.z;
-    double dv[BIG_CAP / 64];
-    int ps[BIG_CAP / 64];
-    double msum = 0.0;
-#pragma unroll
-    for (int j = 0; j < BIG_CAP / 64; ++j) {
-        const int a = lane + 64 * j;
-        dv[j] = INFINITY;
-        ps[j] = 0x7FFFFFFF;
-        if (a < n_se) {
-            const int pos = (int)(buf[a] & POS_MASK);
-            const float4 w = V[base + pos];
-            msum += use_mass ? (double)w.w : mass_value;
-            const double ax = vqx - (double)w.x, ay = vqy - (double)w.y, az = vqz - (double)w.z;
-            dv[j] = ax * ax + ay * ay + az * az;
-            ps[j] = pos;
-        }
-    }
-    for (int o = 32; o > 0; o >>= 1) msum += __shfl_xor(msum, o, 64);
-    // the n_v nearest in velocity, smallest first, by (dv2, rank)
-    for (int i = 0; i < n_v; ++i) {
-        double bd = INFINITY;
-        int bp = 0x7FFFFFFF;
-#pragma unroll
-        for (int j = 0; j < BIG_CAP / 64; ++j)
-            if (vless(dv[j], ps[j], bd, bp)) {
-                bd = dv[j];
-                bp = ps[j];
-            }
-        for (int o = 32; o > 0; o >>= 1) {
-            const double od = __shfl_xor(bd, o, 64);
-            const int op = __shfl_xor(bp, o, 64);
-            if (vless(od, op, bd, bp)) {
-                bd = od;
-                bp = op;
-            }
-        }
-#pragma unroll
-        for (int j = 0; j < BIG_CAP / 64; ++j)
-            if (ps[j] == bp) {
-                dv[j] = INFINITY;
-                ps[j] = 0x7FFFFFFF;
-            }
-        if (lane == 0) {
-            sel_d[i] = bd;
-            sel_p[i] = bp;
-        }
-    }
-    __builtin_amdgcn_wave_barrier();
-    if (lane != 0) return;
-    const double kW = 15.0 / (8.0 * M_PI);
-    const double h2 = sel_d[n_v - 1];
-    double sw = 0.0;
-    if (h2 != 0.0)
-        for (int a = 0; a < n_v; ++a) {
-            const double m = use_mass ? (double)V[base + sel_p[a]].w : mass_value;
-            sw += m * kW * (1.0 - sel_d[a] / h2);
-        }
-    const double lfl = h2 == 0.0 ? INFINITY : log(sw) - 1.5 * log(h2) - log(msum);
-    R[F.gidx[e]] = (float)(lfl - FB[qe]);
 }
 
-int launch_knn_big(vr_ctx* ctx, const uint32_t* qpos, int64_t nq, const KdTree& tree, const float4* V,
-                   const double* FB, const int32_t* host_off, const vr_particles* p, int n_se, int n_v, float* R,
-                   hipStream_t st) {
-    if (nq > INT32_MAX) return set_err(ctx, VR_ERR_UNSUPPORTED, "too many queries for one launch");
-    VR_TIMED(ctx, "knn", st, nq,
-             hipLaunchKernelGGL(k_knn_big, dim3((unsigned)std::max<int64_t>(nq, 1)), dim3(64), 0, st, qpos, nq,
-                                tree.nodes, tree.F, V, FB, tree.elem_host, host_off, n_se,
-                                n_v, tree.use_mass, p->mass_value, p->grid_bits, R, (unsigned)ctx->xcd_chunk));
+template <int LPQ, int KL, int L>
+int launch_knn(vr_ctx* ctx, const uint32_t* qpos, int64_t nq, int64_t n_queries, const Slots& T, const float4* V,
+               const double* FB, const int32_t* host_off, const vr_particles* p, int n_se, int n_v, float* R,
+               int* flagged, int* n_flagged, hipStream_t st) {
+    const int use_mass = p->mass ? 1 : 0;
+    double mass_sum = 0.0;  // of n_se equal masses, added one by one
+    for (int k = 0; k < n_se; ++k) mass_sum += p->mass_value;
+    VR_TIMED(ctx, "knn", st, n_queries,
+             hipLaunchKernelGGL((k_knn<LPQ, KL, L>), dim3(grid_for(nq, 64 / LPQ)), dim3(64), 0, st, qpos, nq, T, V, FB,
+                                host_off, n_se, n_v, use_mass, p->mass_value, mass_sum, p->grid_bits, R,
+                                (unsigned)ctx->xcd_chunk, flagged, n_flagged, ctx->timing ? ctx->knn_cand : nullptr));
+    VR_LAUNCH_CHECK(ctx);
+    // almost always without work: a few wavefronts that stride over the flagged queries
+    const unsigned nw = (unsigned)std::min<int64_t>(n_queries, 4 * ctx->num_cus);
+    hipLaunchKernelGGL(k_knn_wave, dim3(std::max(nw, 1u)), dim3(64), 0, st, flagged, n_flagged, T, V, FB, host_off, n_se,
+                       n_v, use_mass, p->mass_value, p->grid_bits, R);
     VR_LAUNCH_CHECK(ctx);
     return VR_OK;
 }
@@ -843,60 +1041,116 @@ extern "C" int vr_local_vdensity(vr_ctx* ctx, const vr_particles* p, int32_t n_h
         if ((int64_t)off[h + 1] - off[h] > (int64_t(1) << POS_BITS))
             return set_err(ctx, VR_ERR_UNSUPPORTED, "host %d has more than 2^%d members", h, POS_BITS);
     const int64_t M = off[n_hosts];
-    VR_WS(rank_of, ctx, int32_t, WS_C2, p->n);
+    VR_WS(slot_of, ctx, int32_t, WS_C2, p->n);
     VR_WS(dup, ctx, int, WS_FLAG, 4);
-    rc = fill_i32(ctx, rank_of, -1, p->n, st);
+    rc = fill_i32(ctx, slot_of, -1, p->n, st);
     if (rc) return rc;
-    rc = fill_i32(ctx, dup, 0, 1, st);
+    rc = fill_i32(ctx, dup, 0, 2, st);
     if (rc) return rc;
-    hipLaunchKernelGGL(k_rank_of, dim3(grid_for(M, 256)), dim3(256), 0, st, M, p->n, host_members, rank_of, dup);
+    hipLaunchKernelGGL(k_rank_of, dim3(grid_for(M, 256)), dim3(256), 0, st, M, p->n, host_members, slot_of, dup);
     VR_LAUNCH_CHECK(ctx);
     int duph = 0;
     rc = read_back(ctx, dup, &duph, sizeof duph, st);
     if (rc) return rc;
     if (duph) return set_err(ctx, VR_ERR_INVALID_ARG, "host_members lists a particle twice or outside [0, n)");
-    std::vector<int> nc(n_hosts, ctx->knn_leaf);
+    // Device-wide levels down to buckets of at most `cap` members.
+    const int cap = std::min(BUCKET_MAX, 8 * ctx->knn_leaf);
+    std::vector<int> nc(n_hosts, cap);
     KdTree tree;
     rc = kd_build(ctx, p, n_hosts, host_offsets, host_members, off, nc, KD_WIDEST, 2, tree, st);
     if (rc) return rc;
-    VR_WS(V, ctx, float4, WS_C0, M);
-    VR_WS(FB, ctx, double, WS_C1, M);
-    hipLaunchKernelGGL(k_member_records, dim3(grid_for(p->n, 256)), dim3(256), 0, st, p->n, rank_of, p->vx, p->vy,
+    // The buckets follow from the sizes: every node above `cap` is halved.
+    std::vector<int4> buckets;
+    std::vector<int> hb(n_hosts + 1, 0);
+    int64_t n_leaves = 0;
+    for (int h = 0; h < n_hosts; ++h) {
+        std::vector<std::pair<int, int>> todo{{off[h], off[h + 1] - off[h]}};
+        while (!todo.empty()) {
+            const auto [s, n] = todo.back();
+            todo.pop_back();
+            if (n > cap) {
+                todo.push_back({s + n / 2, n - n / 2});
+                todo.push_back({s, n / 2});
+                continue;
+            }
+            buckets.push_back(make_int4(s, n, (int)n_leaves, h));
+            n_leaves += (n + LEAF - 1) / LEAF;
+        }
+        hb[h + 1] = (int)buckets.size();
+    }
+    const int64_t nb = (int64_t)buckets.size(), n_slots = n_leaves * LEAF;
+    if (n_slots > INT32_MAX) return set_err(ctx, VR_ERR_UNSUPPORTED, "too many host members for one call");
+    Slots T{};
+    Carve cv;
+    auto layout = [&]() {
+        T.x = cv.add<float>(n_slots);
+        T.y = cv.add<float>(n_slots);
+        T.z = cv.add<float>(n_slots);
+        T.gid = cv.add<int>(n_slots);
+        T.eid = cv.add<int>(n_slots);
+        T.lbox = cv.add<float4>(2 * n_leaves);
+        T.bbox = cv.add<float4>(2 * nb);
+        T.leaf_bucket = cv.add<int>(n_leaves);
+        T.hbox = cv.add<int>(6 * (size_t)n_hosts);
+        T.buckets = cv.add<int4>(nb);
+        T.host_bucket = cv.add<int>(n_hosts + 1);
+    };
+    layout();
+    const size_t total = cv.bytes;
+    cv.bytes = 0;
+    cv.base = static_cast<char*>(ws(ctx, WS_C3, total));
+    if (!cv.base) return VR_ERR_OUT_OF_MEMORY;
+    layout();
+    {
+        const size_t b0 = nb * sizeof(int4), b1 = hb.size() * sizeof(int);
+        char* up = static_cast<char*>(upload_begin(ctx, b0 + b1));
+        if (!up) return VR_ERR_HIP;
+        std::memcpy(up, buckets.data(), b0);
+        std::memcpy(up + b0, hb.data(), b1);
+        VR_HIP(ctx, hipMemcpyAsync(T.buckets, up, b0, hipMemcpyHostToDevice, st));
+        VR_HIP(ctx, hipMemcpyAsync(T.host_bucket, up + b0, b1, hipMemcpyHostToDevice, st));
+        if ((rc = upload_end(ctx, st))) return rc;
+    }
+    VR_WS(V, ctx, float4, WS_C0, n_slots);
+    VR_WS(FB, ctx, double, WS_C1, n_slots);
+    VR_WS(flagged, ctx, int, WS_C4, subset ? n_subset : M);
+    if ((rc = fill_i32(ctx, T.hbox, INT32_MAX, 6 * (int64_t)n_hosts, st))) return rc;
+    const int lpq_log2 = n_se > 64 ? 4 : 2;
+    hipLaunchKernelGGL(k_buckets, dim3((unsigned)nb), dim3(256), 0, st, tree.list[0], tree.list[1], tree.list[2],
+                       tree.elem_u[0], tree.elem_u[1], tree.elem_u[2], tree.elem_g, tree.scratch, lpq_log2, T, slot_of);
+    VR_LAUNCH_CHECK(ctx);
+    hipLaunchKernelGGL(k_member_records, dim3(grid_for(p->n, 256)), dim3(256), 0, st, p->n, slot_of, p->vx, p->vy,
                        p->vz, p->mass, vbar, sigma, V, FB);
     VR_LAUNCH_CHECK(ctx);
     const uint32_t* qpos = nullptr;
-    int64_t nq = M;
+    int64_t nq = n_slots, n_queries = M;
     if (subset) {
-        VR_WS(pos_of, ctx, int, WS_C4, p->n);
         VR_WS(qp, ctx, uint32_t, WS_C5, n_subset);
         VR_WS(qv, ctx, uint32_t, WS_C6, n_subset);
         VR_WS(bad, ctx, int, WS_FLAG2, 4);
-        rc = fill_i32(ctx, pos_of, -1, p->n, st);
-        if (rc) return rc;
         rc = fill_i32(ctx, bad, 0, 1, st);
         if (rc) return rc;
-        hipLaunchKernelGGL(k_pos_of, dim3(grid_for(M, 256)), dim3(256), 0, st, M, tree.F.gidx, pos_of);
-        VR_LAUNCH_CHECK(ctx);
-        hipLaunchKernelGGL(k_subset_pos, dim3(grid_for(n_subset, 256)), dim3(256), 0, st, n_subset, p->n, subset, pos_of,
-                           qp, qv, bad);
+        hipLaunchKernelGGL(k_subset_slot, dim3(grid_for(n_subset, 256)), dim3(256), 0, st, n_subset, p->n, subset,
+                           slot_of, qp, qv, bad);
         VR_LAUNCH_CHECK(ctx);
         int badh = 0;
         rc = read_back(ctx, bad, &badh, sizeof badh, st);
         if (rc) return rc;
         if (badh) return set_err(ctx, VR_ERR_INVALID_ARG, "subset lists a particle that is in no host");
         int bits = 1;
-        while ((int64_t(1) << bits) < M) ++bits;
+        while ((int64_t(1) << bits) < n_slots) ++bits;
         rc = sort_pairs_u32(ctx, qp, qv, n_subset, bits, st);
         if (rc) return rc;
         qpos = qp;
-        nq = n_subset;
+        nq = n_queries = n_subset;
     }
-    if (n_se <= 32 && n_v == 8)
-        return launch_knn<32, 8, 1>(ctx, qpos, nq, tree, V, FB, host_offsets, p, n_se, n_v, R, st);
+    int* nfl = dup + 1;  // zero since the fill above
     if (n_se <= 32)
-        return launch_knn<32, 0, 32>(ctx, qpos, nq, tree, V, FB, host_offsets, p, n_se, n_v, R, st);
+        return launch_knn<4, 8, 12>(ctx, qpos, nq, n_queries, T, V, FB, host_offsets, p, n_se, n_v, R, flagged, nfl, st);
     if (n_se <= 64)
-        return launch_knn<64, 0, 64>(ctx, qpos, nq, tree, V, FB, host_offsets, p, n_se, n_v, R, st);
-    // larger sets, up to the paper's defaults (n_se 256, n_v 32): a wavefront per query
-    return launch_knn_big(ctx, qpos, nq, tree, V, FB, host_offsets, p, n_se, n_v, R, st);
+        return launch_knn<4, 16, 22>(ctx, qpos, nq, n_queries, T, V, FB, host_offsets, p, n_se, n_v, R, flagged, nfl, st);
+    // up to the paper's defaults (n_se 256, n_v 32)
+    if (n_se <= 128)
+        return launch_knn<16, 8, 14>(ctx, qpos, nq, n_queries, T, V, FB, host_offsets, p, n_se, n_v, R, flagged, nfl, st);
+    return launch_knn<16, 16, 24>(ctx, qpos, nq, n_queries, T, V, FB, host_offsets, p, n_se, n_v, R, flagged, nfl, st);
 }

@@ -1,0 +1,106 @@
+"""The neighbour tree and search at the sizes where they can go wrong: hosts
+around multiples of a leaf and of a bucket, neighbour counts at the limits of
+each kernel form, hosts wider than half the box, more coincident members than
+a query's lists hold, and subsets whose wavefronts span hosts."""
+import numpy as np
+import pytest
+
+from paper_1902_01010_amd import synth
+from tests.gpu_common import R_agrees, both, dev_tensor
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def vr():
+    from paper_1902_01010_amd import vr as m
+    return m
+
+
+@pytest.fixture(scope="module")
+def ctx(vr):
+    return vr.Context(0)
+
+
+def _hosts(rng, sizes, box=1.0, extent=0.02, masses=False, wide=()):
+    """Gaussian blobs of the given sizes as one workload and its host table;
+    hosts listed in `wide` fill 0.8 of the box instead."""
+    n = int(sum(sizes))
+    pos = np.empty((3, n))
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    for h, s in enumerate(sizes):
+        c = rng.random((3, 1)) * box
+        pos[:, off[h]:off[h + 1]] = (c + (rng.random((3, s)) - 0.5) * 0.8 * box if h in wide
+                                     else c + rng.normal(0, extent, (3, s)))
+    vel = rng.normal(0, 100.0, (3, n))
+    x = np.mod(pos, box).astype(np.float32)
+    x[x >= np.float32(box)] = 0
+    m = (0.5 + rng.random(n)).astype(np.float32) if masses else None
+    w = synth.Workload("blobs", x, vel.astype(np.float32), m, 1.0, box, 21, {}, {})
+    vbar = rng.normal(0, 10.0, (3, n)).astype(np.float32)
+    s2 = rng.uniform(0.5e4, 2e4, (3, n))
+    sigma = np.concatenate([s2, 0.1 * s2]).astype(np.float32)
+    return w, off, np.arange(n, dtype=np.int32), vbar, sigma
+
+
+def _check(ctx, vr, ref, case, n_se, n_v, subset=None):
+    w, off, mem, vbar, sigma = case
+    P, Pr = both(ctx, vr, ref, w)
+    exp = ref.local_vdensity(Pr, off, mem, vbar, sigma, n_se, n_v, subset=subset)["R"]
+    got = ctx.local_vdensity(P, dev_tensor(off), dev_tensor(mem), dev_tensor(vbar), dev_tensor(sigma), n_se, n_v,
+                             subset=None if subset is None else dev_tensor(subset)).cpu().numpy()
+    assert np.isfinite(exp).any()
+    R_agrees(got, exp)
+
+
+@pytest.mark.parametrize("n_se,n_v,masses", [(2, 2, False), (31, 8, True), (32, 32, False), (33, 8, False), (64, 64, True),
+                                             (65, 3, False), (128, 32, True), (129, 32, False), (256, 32, True)])
+def test_leaf_and_bucket_edges(ctx, vr, ref, n_se, n_v, masses):
+    """Hosts of exactly n_se members, one leaf more or less, and around 2048
+    (a full bucket) and 4096 (two)."""
+    rng = np.random.default_rng(n_se)
+    sizes = [n_se, n_se + 1] + [s for s in (63, 64, 65, 257, 2047, 2048, 2049, 4097) if s >= n_se]
+    saved = ctx.get_tune("knn_leaf")
+    try:
+        for leaf in (16, 256):  # buckets of 128 and 2048 members
+            ctx.tune("knn_leaf", leaf)
+            _check(ctx, vr, ref, _hosts(rng, sizes, masses=masses), n_se, n_v)
+    finally:
+        ctx.tune("knn_leaf", saved)
+
+
+@pytest.mark.parametrize("n_se,n_v", [(32, 8), (256, 32)])
+def test_host_wider_than_half_the_box(ctx, vr, ref, n_se, n_v):
+    """Neighbours across the edge of the unwrapped host count at their
+    periodic distance, whichever leaves hold them."""
+    rng = np.random.default_rng(5)
+    _check(ctx, vr, ref, _hosts(rng, [600, 5000, 400], wide=(1,)), n_se, n_v)
+
+
+@pytest.mark.parametrize("n_se,n_v", [(32, 8), (48, 16), (256, 32)])
+def test_coincident_members_overflow_the_lists(ctx, vr, ref, n_se, n_v):
+    """700 members at one point: every query there has more members at its
+    radius than its lists hold; ties break by particle index."""
+    rng = np.random.default_rng(6)
+    case = _hosts(rng, [1500, 900], masses=True)
+    case[0].x[:, 200:900] = case[0].x[:, 200:201]
+    case[0].x[:, 1500:1540] = case[0].x[:, 1500:1501]
+    _check(ctx, vr, ref, case, n_se, n_v)
+
+
+def test_equal_velocities(ctx, vr, ref):
+    """Velocity ties at the n_v-th neighbour, and n_v members at distance zero."""
+    rng = np.random.default_rng(7)
+    case = _hosts(rng, [2000])
+    case[0].v[:, ::3] = np.round(case[0].v[:, ::3] / 80) * 80
+    case[0].v[:, :60] = case[0].v[:, :1]
+    case[0].x[:, :60] = case[0].x[:, :1]
+    _check(ctx, vr, ref, case, 32, 8)
+
+
+def test_subset_across_hosts(ctx, vr, ref):
+    """A sparse subset: a wavefront's queries lie in many hosts and leaves."""
+    rng = np.random.default_rng(8)
+    case = _hosts(rng, [300] * 40 + [3000], wide=(7,))
+    sub = np.sort(rng.permutation(case[0].n)[:700]).astype(np.int32)
+    _check(ctx, vr, ref, case, 32, 8, subset=rng.permutation(sub).astype(np.int32))
