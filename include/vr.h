@@ -81,7 +81,9 @@ int vr_set_timing(vr_ctx* ctx, int enabled);
 /* Launch-shape knobs of the context (integer results never depend on them;
  * FP64 potentials only through the order of their partial sums):
  * "knn_leaf"      the neighbour-search tree's leaves of 32 members are built
- *                 in workgroups of at most 8 * knn_leaf members (16..256, 256)
+ *                 in workgroups of at most 16 * knn_leaf members, 2048 at most
+ *                 (16..256, 64); members per leaf where a host is wider than
+ *                 half the box
  * "unbind_tile"   j-tile of the potential kernel staged in LDS (64..4096, 256;
  *                 the persistent kernel uses at most 1024 per wavefront)
  * "unbind_jchunk" j-range of one potential work item (256..65536, 4096)

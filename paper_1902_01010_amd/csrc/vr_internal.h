@@ -52,7 +52,7 @@ struct vr_ctx {
     hipEvent_t up_event = nullptr;
     bool up_pending = false;
     int tuned_tile = 0;     // potential j-tile picked by the autotuner (0 = default)
-    int knn_leaf = 256;     // the neighbour tree's buckets hold at most 8 * knn_leaf members
+    int knn_leaf = 64;      // the neighbour tree's buckets hold at most 16 * knn_leaf members
     int unbind_jchunk = 4096;
     int unbind_bpc = 0;     // workgroups per CU of the persistent potential kernel (0 = occupancy limit)
     int unbind_wide = 4096; // members from which a leading group takes the 1024-thread group kernel

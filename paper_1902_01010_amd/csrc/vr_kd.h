@@ -22,7 +22,7 @@ struct Elems {
     float* mass;    // null for uniform mass
 };
 
-enum KdMode { KD_MIN_ENTROPY = 0, KD_MAX_ENTROPY = 1, KD_WIDEST = 2 };
+enum KdMode { KD_MIN_ENTROPY = 0, KD_MAX_ENTROPY = 1, KD_WIDEST = 2, KD_BUCKETS = 3 };
 
 struct KdTree {
     KdNode* nodes = nullptr;
@@ -34,9 +34,11 @@ struct KdTree {
     int* elem_u[3] = {nullptr, nullptr, nullptr};  // coordinates by element id
     int* elem_host = nullptr;  // host by element id (= by position: hosts keep their ranges)
     int use_mass = 0;
-    // KD_WIDEST only: element ids by position in the (coordinate, element)
-    // order of each dimension inside every leaf; particle by element id;
-    // scratch of one int per member, free for the caller
+    // KD_BUCKETS only: whether some host is wider than half the box (then
+    // nothing else is set); element ids by position in the (coordinate,
+    // element) order of each dimension inside every leaf; particle by element
+    // id; scratch of one int per member, free for the caller
+    bool wide = false;
     int* list[3] = {nullptr, nullptr, nullptr};
     int* elem_g = nullptr;
     int* scratch = nullptr;
@@ -45,10 +47,11 @@ struct KdTree {
 // Builds one tree per host.  A node with more than ncell[h] members is split
 // at the member of rank floor(n/2) in (coordinate, particle index) order of
 // the dimension chosen by `mode`; the left child takes the members before it.
-// The root of host h has node id h.  The entropy modes keep a node whose
-// members coincide as a leaf.  KD_WIDEST halves every node above ncell, so
-// its leaves follow from the host sizes alone; it returns the lists (list,
-// elem_u, elem_g, elem_host, scratch) instead of nodes, leaves and F.
+// The root of host h has node id h.  A node whose members coincide stays a
+// leaf.  KD_BUCKETS splits the widest dimension as KD_WIDEST does, but halves
+// every node above ncell, so its leaves follow from the host sizes alone; it
+// returns the lists (list, elem_u, elem_g, elem_host, scratch) instead of
+// nodes, leaves and F.
 int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t* host_offsets,
              const int32_t* host_members, const std::vector<int32_t>& off, const std::vector<int>& ncell,
              int mode, int nbins, KdTree& tree, hipStream_t st);

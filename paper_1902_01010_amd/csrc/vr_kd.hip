@@ -53,9 +53,10 @@ __global__ void k_elems(int64_t M, int n_hosts, const int32_t* __restrict__ off,
                         const uint32_t* __restrict__ qx, const uint32_t* __restrict__ qy,
                         const uint32_t* __restrict__ qz, const float* __restrict__ mass, int gb, int* __restrict__ u0,
                         int* __restrict__ u1, int* __restrict__ u2, int* __restrict__ g, float* __restrict__ m,
-                        int* __restrict__ host, unsigned long long* __restrict__ hash) {
+                        int* __restrict__ host, unsigned long long* __restrict__ hash, int* __restrict__ hbox) {
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     unsigned long long hv = 0;
+    int hm = -1, um[3] = {0, 0, 0};
     if (e < M) {
         int lo = 0, hi = n_hosts - 1;  // host with off[h] <= e < off[h+1]
         while (lo < hi) {
@@ -75,11 +76,39 @@ __global__ void k_elems(int64_t M, int n_hosts, const int32_t* __restrict__ off,
         host[e] = h;
         if (mass) m[e] = mass[i];
         hv = elem_hash(e, i, a, b, c, h);
+        hm = h;
+        um[0] = a;
+        um[1] = b;
+        um[2] = c;
+    }
+    if (hbox) {
+        // the host's extent: minima of u and of -u.  A wavefront inside one
+        // host reduces first; values only decrease, so a plain read that is
+        // already no larger makes the atomic unnecessary
+        const int h0 = __builtin_amdgcn_readfirstlane(hm);
+        const bool one = __ballot(hm == h0) == ~0ull;
+        for (int k = 0; k < 6; ++k) {
+            int v = k < 3 ? um[k] : -um[k - 3];
+            if (one)
+                for (int o = 32; o > 0; o >>= 1) v = min(v, __shfl_xor(v, o, 64));
+            if (hm >= 0 && (!one || (threadIdx.x & 63) == 0)) {
+                int* at = hbox + 6 * (int64_t)hm + k;
+                if (v < *at) atomicMin(at, v);
+            }
+        }
     }
     // every lane of the wavefront reaches the sum
     for (int o = 32; o > 0; o >>= 1) hv += (unsigned long long)__shfl_xor((long long)hv, o, 64);
     if ((threadIdx.x & 63) == 0 && hv)
         atomicAdd(&hash[((uint64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) % HASH_SLOTS], hv);
+}
+
+// Raises *flag when a host spans half the box or more on some axis.
+__global__ void k_any_wide(int n_hosts, int half, const int* __restrict__ hbox, unsigned long long* __restrict__ flag) {
+    const int h = blockIdx.x * blockDim.x + threadIdx.x;
+    if (h >= n_hosts) return;
+    const int* b = hbox + 6 * (int64_t)h;
+    if (-b[3] - b[0] >= half || -b[4] - b[1] >= half || -b[5] - b[2] >= half) *flag = 1;
 }
 
 __global__ void k_presort_keys(int64_t M, const int* __restrict__ u, const int* __restrict__ host,
@@ -300,9 +329,11 @@ __global__ __launch_bounds__(256) void k_split(const int* nact, const int* __res
     int best = -1;
     if (valid) {
         nd = nodes[id];
-        if (mode == KD_WIDEST) {
+        if (mode >= KD_WIDEST) {
             for (int d = 0; d < 3; ++d)
-                if (best < 0 || nd.bmax[d] - nd.bmin[d] > nd.bmax[best] - nd.bmin[best]) best = d;
+                if ((mode == KD_BUCKETS || nd.bmax[d] > nd.bmin[d]) &&
+                    (best < 0 || nd.bmax[d] - nd.bmin[d] > nd.bmax[best] - nd.bmin[best]))
+                    best = d;
         } else {
             const double S[3] = {Sdim[3 * (int64_t)i], Sdim[3 * (int64_t)i + 1], Sdim[3 * (int64_t)i + 2]};
             for (int d = 0; d < 3; ++d) {
@@ -453,8 +484,9 @@ __global__ void k_leaf_bbox(int nl, const int* __restrict__ leaves, KdNode* node
 }
 
 // Members by position in list-0 order, and the smallest index of each leaf.
-// c0..c2: the coordinates in list-0 order.
+// c0..c2: the coordinates already in list-0 order, or null (then gathered).
 __global__ void k_final(int64_t M, const int* __restrict__ l0, const int* __restrict__ seg_node,
+                        const int* __restrict__ u0, const int* __restrict__ u1, const int* __restrict__ u2,
                         const int* __restrict__ c0, const int* __restrict__ c1, const int* __restrict__ c2,
                         const int* __restrict__ g, const float* __restrict__ m, Elems F, int* __restrict__ leaf_min) {
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -462,9 +494,9 @@ __global__ void k_final(int64_t M, const int* __restrict__ l0, const int* __rest
     const int e = valid ? l0[p] : 0;
     const int gi = valid ? g[e] : 0x7FFFFFFF;
     if (valid) {
-        F.u[0][p] = c0[p];
-        F.u[1][p] = c1[p];
-        F.u[2][p] = c2[p];
+        F.u[0][p] = c0 ? c0[p] : u0[e];
+        F.u[1][p] = c0 ? c1[p] : u1[e];
+        F.u[2][p] = c0 ? c2[p] : u2[e];
         F.gidx[p] = gi;
         F.eid[p] = e;
         if (m) F.mass[p] = m[e];
@@ -519,9 +551,11 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
     while ((1 << hb) <= n_hosts) ++hb;
     // one workspace region holds every array of the build
     Carve cv;
-    int *U[3], *G, *H, *L[3], *Lalt[3], *seg, *leaf_min, *act0, *act1, *leaves, *ncell_d, *counters;
+    int *U[3], *G, *H, *L[3], *Lalt[3], *seg, *leaf_min, *act0, *act1, *leaves, *ncell_d, *counters, *hbox;
     int *C0[3], *C0alt[3];
-    const int64_t MC = mode != KD_WIDEST ? M : 1;  // coordinates in list-0 order, and F
+    const int64_t MC = mode < KD_WIDEST ? M : 1;     // coordinates in list-0 order
+    const int64_t MF = mode != KD_BUCKETS ? M : 1;   // members by position
+    const int64_t HB = mode == KD_BUCKETS ? 6 * (int64_t)n_hosts : 1;
     float* Ms;
     uint8_t* lf8;
     uint32_t* lf;
@@ -547,13 +581,14 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
         act1 = cv.add<int>(node_cap);
         leaves = cv.add<int>(node_cap);
         leaf_min = cv.add<int>(node_cap);
-        for (int d = 0; d < 3; ++d) F.u[d] = cv.add<int>(MC);
-        F.gidx = cv.add<int>(MC);
-        F.eid = cv.add<int>(MC);
-        F.mass = cv.add<float>(use_mass ? MC : 1);
+        for (int d = 0; d < 3; ++d) F.u[d] = cv.add<int>(MF);
+        F.gidx = cv.add<int>(MF);
+        F.eid = cv.add<int>(MF);
+        F.mass = cv.add<float>(use_mass ? MF : 1);
+        hbox = cv.add<int>(HB);
         ncell_d = cv.add<int>(n_hosts);
         counters = cv.add<int>(8);
-        hsh = cv.add<unsigned long long>(HASH_SLOTS);
+        hsh = cv.add<unsigned long long>(HASH_SLOTS + 1);  // and the wide-host flag
     };
     layout();
     const size_t total = cv.bytes;
@@ -569,12 +604,19 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
     init[3] = n_hosts;
     VR_HIP(ctx, hipMemcpyAsync(counters, init, 8 * sizeof(int), hipMemcpyHostToDevice, st));
     {
-        int rc = fill_u32(ctx, reinterpret_cast<uint32_t*>(hsh), 0u, 2 * HASH_SLOTS, st);
+        int rc = fill_u32(ctx, reinterpret_cast<uint32_t*>(hsh), 0u, 2 * (HASH_SLOTS + 1), st);
         if (rc) return rc;
+        if (mode == KD_BUCKETS && (rc = fill_i32(ctx, hbox, INT_MAX, HB, st))) return rc;
     }
     hipLaunchKernelGGL(k_elems, dim3(grid_for(M, 256)), dim3(256), 0, st, M, n_hosts, host_offsets, host_members,
-                       p->qx, p->qy, p->qz, p->mass, p->grid_bits, U[0], U[1], U[2], G, Ms, H, hsh);
+                       p->qx, p->qy, p->qz, p->mass, p->grid_bits, U[0], U[1], U[2], G, Ms, H, hsh,
+                       mode == KD_BUCKETS ? hbox : nullptr);
     VR_LAUNCH_CHECK(ctx);
+    if (mode == KD_BUCKETS) {
+        hipLaunchKernelGGL(k_any_wide, dim3(grid_for(n_hosts, 256)), dim3(256), 0, st, n_hosts, 1 << (p->grid_bits - 1),
+                           hbox, hsh + HASH_SLOTS);
+        VR_LAUNCH_CHECK(ctx);
+    }
     // The three lists sorted by (host, u_d, element) depend only on the
     // elements' members, unwrapped coordinates and hosts.  The context keeps
     // the last build's lists and reuses them when this build's content hash,
@@ -582,9 +624,13 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
     // one search are built over the same members); without room for them
     // under the workspace cap it simply sorts.
     {
-        unsigned long long parts[HASH_SLOTS];
+        unsigned long long parts[HASH_SLOTS + 1];
         int rc = read_back(ctx, hsh, parts, sizeof parts, st);
         if (rc) return rc;
+        if (parts[HASH_SLOTS]) {
+            tree.wide = true;
+            return VR_OK;
+        }
         unsigned long long h64 = 0;
         for (int k = 0; k < HASH_SLOTS; ++k) h64 += parts[k];
         const int bits = 22 + hb;
@@ -618,7 +664,7 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
             }
         }
     }
-    if (mode != KD_WIDEST) {
+    if (mode < KD_WIDEST) {
         hipLaunchKernelGGL(k_coords_l0, dim3(grid_for(M, 256)), dim3(256), 0, st, M, L[0], U[0], U[1], U[2], C0[0],
                            C0[1], C0[2]);
         VR_LAUNCH_CHECK(ctx);
@@ -689,7 +735,7 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
         VR_LAUNCH_CHECK(ctx);
         uint32_t* hc = nullptr;
         double* hm = nullptr;
-        if (mode != KD_WIDEST) {
+        if (mode < KD_WIDEST) {
             const int64_t hn = (int64_t)na * 3 * nbins;
             if (counts) {
                 hc = static_cast<uint32_t*>(ws(ctx, WS_KD_HIST, hn * sizeof(uint32_t)));
@@ -707,7 +753,7 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
             VR_LAUNCH_CHECK(ctx);
         }
         double* Sdim = nullptr;
-        if (mode != KD_WIDEST) {
+        if (mode < KD_WIDEST) {
             Sdim = static_cast<double*>(ws(ctx, WS_KD_S, (size_t)na * 3 * sizeof(double)));
             if (!Sdim) return VR_ERR_OUT_OF_MEMORY;
             hipLaunchKernelGGL(k_entropy, dim3(grid_for((int64_t)na * 64, 256)), dim3(256), 0, st, counters, cur,
@@ -722,7 +768,7 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
         VR_LAUNCH_CHECK(ctx);
         if ((rc = scan_u8(ctx, lf8, lf, 3 * M, st))) return rc;
         CoordsL0 cl0{};
-        if (mode != KD_WIDEST) cl0 = CoordsL0{{C0[0], C0[1], C0[2]}, {C0alt[0], C0alt[1], C0alt[2]}};
+        if (mode < KD_WIDEST) cl0 = CoordsL0{{C0[0], C0[1], C0[2]}, {C0alt[0], C0alt[1], C0alt[2]}};
         hipLaunchKernelGGL(k_part3, dim3(gM), dim3(256), 0, st, M, seg, nodes, L[0], L[1], L[2], lf8, lf, Lalt[0],
                            Lalt[1], Lalt[2], cl0);
         VR_LAUNCH_CHECK(ctx);
@@ -740,7 +786,7 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
     for (int d = 0; d < 3; ++d) tree.elem_u[d] = U[d];
     tree.elem_host = H;
     tree.use_mass = use_mass;
-    if (mode == KD_WIDEST) {
+    if (mode == KD_BUCKETS) {
         for (int d = 0; d < 3; ++d) tree.list[d] = L[d];
         tree.elem_g = G;
         tree.scratch = Lalt[0];
@@ -757,8 +803,9 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
     hipLaunchKernelGGL(k_leaf_bbox, dim3(grid_for(nleaf, 256)), dim3(256), 0, st, nleaf, leaves, nodes, L[0], L[1],
                        L[2], U[0], U[1], U[2], leaf_min, n_hosts);
     VR_LAUNCH_CHECK(ctx);
-    hipLaunchKernelGGL(k_final, dim3(gM), dim3(256), 0, st, M, L[0], seg, C0[0], C0[1], C0[2], G,
-                       use_mass ? Ms : nullptr, F, leaf_min);
+    const bool have_c0 = mode < KD_WIDEST;
+    hipLaunchKernelGGL(k_final, dim3(gM), dim3(256), 0, st, M, L[0], seg, U[0], U[1], U[2], have_c0 ? C0[0] : nullptr,
+                       have_c0 ? C0[1] : nullptr, have_c0 ? C0[2] : nullptr, G, use_mass ? Ms : nullptr, F, leaf_min);
     VR_LAUNCH_CHECK(ctx);
     tree.nodes = nodes;
     tree.leaves = leaves;

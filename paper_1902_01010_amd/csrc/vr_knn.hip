@@ -25,17 +25,14 @@
 // and the Gaussian background follow in FP64.  Queries whose lists overflow
 // (many coincident members) go to k_knn_wave, a wavefront per query with
 // exact keys throughout.
-#include "vr_kd.h"
+#include "vr_knn.h"
 
-#include <cmath>
 #include <cstring>
 #include <type_traits>
 
 namespace vr {
 namespace {
 
-constexpr int POS_BITS = 22;
-constexpr uint64_t POS_MASK = (uint64_t(1) << POS_BITS) - 1;
 constexpr int LEAF = 32;           // slots of a leaf
 constexpr int BUCKET_MAX = 2048;   // members of a bucket (64 leaves)
 constexpr float PAD = 1e30f;       // coordinate of an empty slot
@@ -50,7 +47,6 @@ struct Slots {
     int4* buckets;      // [n_buckets] first list position, members, first leaf, host
     int* leaf_bucket;   // [n_leaves]
     int* host_bucket;   // [n_hosts + 1]
-    int* hbox;          // [n_hosts][6] minima of u and of -u
 };
 
 __global__ void k_subset_slot(int64_t ns, int64_t n, const int32_t* __restrict__ subset, const int* __restrict__ slot_of,
@@ -62,28 +58,6 @@ __global__ void k_subset_slot(int64_t ns, int64_t n, const int32_t* __restrict__
     if (p < 0) { atomicOr(bad, 1); p = 0; }
     qpos[s] = (uint32_t)p;
     qval[s] = (uint32_t)s;
-}
-
-// ln f_bg (Eq. fvbg): the log density of the trivariate Gaussian of mean
-// vbar(x) and covariance sigma(x), particle g, at velocity vq.  The
-// quadratic form is u^T adj(S) u / det S with u = vq - vbar; S is positive
-// definite iff its leading principal minors S_xx, S_xx S_yy - S_xy^2 and
-// det S are positive (Sylvester's criterion), else NaN.
-__device__ __forceinline__ double log_fbg(const float* __restrict__ sigma, const float* __restrict__ vbar,
-                                          int g, double vqx, double vqy, double vqz) {
-    const float* s = sigma + (int64_t)g * 6;  // particle-major
-    const double sxx = s[0], syy = s[1], szz = s[2];
-    const Sym3Adj A = sym3_adjugate(sxx, syy, szz, s[3], s[4], s[5]);
-    if (!(sxx > 0) || !(A.zz > 0) || !(A.det > 0)) return NAN;
-    const float* vb = vbar + (int64_t)g * 3;
-    const double ux = vqx - (double)vb[0];
-    const double uy = vqy - (double)vb[1];
-    const double uz = vqz - (double)vb[2];
-    const double diag = A.xx * ux * ux + A.yy * uy * uy + A.zz * uz * uz;
-    const double offd = A.xy * ux * uy + A.xz * ux * uz + A.yz * uy * uz;
-    // 3 ln(2 pi) / 2
-    constexpr double HALF3_LN_2PI = 2.7568155996140178;
-    return -0.5 * ((diag + 2.0 * offd) / A.det + log(A.det)) - HALF3_LN_2PI;
 }
 
 // slot_of[g] = the position of particle g in host_members (-1 beforehand; the
@@ -247,7 +221,7 @@ __global__ __launch_bounds__(256) void k_buckets(const int* __restrict__ l0, con
         }
         __syncthreads();
     }
-    // members into slots, and the boxes of leaves, bucket and host
+    // members into slots, and the boxes of leaves and bucket
     int mn[3] = {INT32_MAX, INT32_MAX, INT32_MAX}, mx[3] = {INT32_MIN, INT32_MIN, INT32_MIN};
 #pragma unroll
     for (int j = 0; j < PT; ++j) {
@@ -311,11 +285,6 @@ __global__ __launch_bounds__(256) void k_buckets(const int* __restrict__ l0, con
             }
         T.bbox[2 * blockIdx.x] = make_float4((float)wbox[0][0], (float)wbox[0][1], (float)wbox[0][2], 0.f);
         T.bbox[2 * blockIdx.x + 1] = make_float4((float)wbox[0][3], (float)wbox[0][4], (float)wbox[0][5], 0.f);
-        int* hb = T.hbox + 6 * (int64_t)bk.w;
-        for (int d = 0; d < 3; ++d) {
-            atomicMin(&hb[d], wbox[0][d]);
-            atomicMin(&hb[3 + d], -wbox[0][3 + d]);
-        }
     }
 }
 
@@ -366,34 +335,14 @@ __device__ __forceinline__ T wave_fold(T v, OP op) {
     return __builtin_bit_cast(T, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, r)));
 }
 
-// Lower bound on the squared distance between two boxes of unwrapped
-// coordinates.  A host narrower than half the box needs no minimum image:
-// its coordinate differences are the periodic ones (wrap false, uniform);
-// else an axis's gap is also bounded through the box of side S.
-__device__ __forceinline__ float box_gap2(float4 a0, float4 a1, float4 b0, float4 b1, bool wrap, float S) {
-    float g[3] = {fmaxf(fmaxf(a0.x - b1.x, b0.x - a1.x), 0.f), fmaxf(fmaxf(a0.y - b1.y, b0.y - a1.y), 0.f),
-                  fmaxf(fmaxf(a0.z - b1.z, b0.z - a1.z), 0.f)};
-    if (wrap) {
-        g[0] = fminf(g[0], fmaxf(S - (fmaxf(a1.x, b1.x) - fminf(a0.x, b0.x)), 0.f));
-        g[1] = fminf(g[1], fmaxf(S - (fmaxf(a1.y, b1.y) - fminf(a0.y, b0.y)), 0.f));
-        g[2] = fminf(g[2], fmaxf(S - (fmaxf(a1.z, b1.z) - fminf(a0.z, b0.z)), 0.f));
-    }
-    return fmaf(g[0], g[0], fmaf(g[1], g[1], g[2] * g[2]));
+// Squared distance between two boxes.
+__device__ __forceinline__ float box_gap2(float4 a0, float4 a1, float4 b0, float4 b1) {
+    const float gx = fmaxf(fmaxf(a0.x - b1.x, b0.x - a1.x), 0.f), gy = fmaxf(fmaxf(a0.y - b1.y, b0.y - a1.y), 0.f),
+                gz = fmaxf(fmaxf(a0.z - b1.z, b0.z - a1.z), 0.f);
+    return fmaf(gx, gx, fmaf(gy, gy, gz * gz));
 }
 
-__device__ __forceinline__ bool host_wraps(const int* __restrict__ hbox, int h, int gb) {
-    const int* b = hbox + 6 * (int64_t)h;
-    const int half = 1 << (gb - 1);
-    // b[3 + d] holds the negated upper end
-    return !(-b[3] - b[0] < half && -b[4] - b[1] < half && -b[5] - b[2] < half);
-}
-
-__device__ __forceinline__ uint64_t exact_key(int dx, int dy, int dz, int rank, bool wrap, int gb) {
-    if (wrap) {
-        dx = min_image(dx, gb);
-        dy = min_image(dy, gb);
-        dz = min_image(dz, gb);
-    }
+__device__ __forceinline__ uint64_t exact_key(int dx, int dy, int dz, int rank) {
     const uint64_t d2 = (uint64_t)((int64_t)dx * dx + (int64_t)dy * dy + (int64_t)dz * dz);
     return (d2 << POS_BITS) | (uint64_t)(uint32_t)rank;
 }
@@ -417,7 +366,7 @@ template <int LPQ, int KL, int L>
 __global__ __launch_bounds__(64, 4) void k_knn(const uint32_t* __restrict__ qpos, int64_t nq, Slots T,
                                             const float4* __restrict__ V, const double* __restrict__ FB,
                                             const int32_t* __restrict__ host_off, int n_se, int n_v, int use_mass,
-                                            double mass_value, double mass_sum, int gb, float* __restrict__ R,
+                                            double mass_value, double mass_sum, float* __restrict__ R,
                                             unsigned xchunk, int* __restrict__ flagged, int* __restrict__ n_flagged,
                                             unsigned long long* __restrict__ ncand) {
     constexpr int W = 64 / LPQ;        // queries of the wavefront
@@ -448,8 +397,6 @@ __global__ __launch_bounds__(64, 4) void k_knn(const uint32_t* __restrict__ qpos
     for (uint64_t pm = __ballot(pending); pm; pm = __ballot(pending)) {
         const int hh = __builtin_amdgcn_readlane(h, __builtin_ctzll(pm));
         const bool mine = pending && h == hh;
-        const bool wrap = host_wraps(T.hbox, hh, gb);
-        const float S = (float)(1 << gb);
         // queries of other hosts stand far away and keep nothing
         const float px = mine ? qx : 3.f * PAD, py = mine ? qy : 3.f * PAD, pz = mine ? qz : 3.f * PAD;
         const float4 q4 = make_float4(qx, qy, qz, 0.f);
@@ -471,19 +418,6 @@ __global__ __launch_bounds__(64, 4) void k_knn(const uint32_t* __restrict__ qpos
             __builtin_memcpy(xs, T.x + b + o, sizeof xs);
             __builtin_memcpy(ys, T.y + b + o, sizeof ys);
             __builtin_memcpy(zs, T.z + b + o, sizeof zs);
-            if (wrap) {
-                // (an empty slot stays far away)
-                auto img = [&](float a, float p) __attribute__((always_inline)) {
-                    const float d = fabsf(a - p);
-                    return p + (d < S ? fminf(d, S - d) : d);
-                };
-#pragma unroll
-                for (int k = 0; k < E; ++k) {
-                    xs[k] = img(xs[k], px);
-                    ys[k] = img(ys[k], py);
-                    zs[k] = img(zs[k], pz);
-                }
-            }
 #pragma unroll
             for (int k = 0; k < E; ++k) {
                 const float dx = xs[k] - px, dy = ys[k] - py, dz = zs[k] - pz;
@@ -515,14 +449,14 @@ __global__ __launch_bounds__(64, 4) void k_knn(const uint32_t* __restrict__ qpos
         };
         // whether a ball of the wavefront's queries reaches a box
         auto reaches = [&](float4 lo, float4 hi) __attribute__((always_inline)) {
-            return __ballot(mine && box_gap2(lo, hi, q4, q4, wrap, S) <= B * SLACK) != 0;
+            return __ballot(mine && box_gap2(lo, hi, q4, q4) <= B * SLACK) != 0;
         };
         // visits the lanes' boxes that a ball reaches, those near the queries
         // first (within 0.2 of the largest squared radius: a strict order by
         // distance, a wavefront-wide minimum a box, was 1% slower on the
         // 256^3 box, touching boxes first 6%)
         auto near_first = [&](float4 lo, float4 hi, bool valid, auto visit) __attribute__((always_inline)) {
-            const float g2 = box_gap2(lo, hi, w0, w1, wrap, S);
+            const float g2 = box_gap2(lo, hi, w0, w1);
             uint64_t far = __ballot(valid && g2 <= Bmax), near = __ballot(valid && g2 <= 0.2f * Bmax);
             while (far) {
                 const int l = __builtin_ctzll(near ? near : far);
@@ -652,7 +586,7 @@ __global__ __launch_bounds__(64, 4) void k_knn(const uint32_t* __restrict__ qpos
                 for (int i = 0; i < nl; ++i) {
                     const int s = listed(i);
                     const uint64_t key = exact_key((int)(T.x[s] - qx), (int)(T.y[s] - qy), (int)(T.z[s] - qz),
-                                                   T.eid[s] - host_off[hh], wrap, gb) + 1;
+                                                   T.eid[s] - host_off[hh]) + 1;
                     if (key > big) {
                         big = key;
                         at = i;
@@ -761,83 +695,10 @@ __global__ __launch_bounds__(64, 4) void k_knn(const uint32_t* __restrict__ qpos
 // to an LDS buffer.  When the buffer holds n_se + 192 keys or more, a radix
 // select over the wave finds the n_se-th smallest key; the keys up to it are
 // kept and it becomes the bound.
-constexpr int BIG_CAP = 256;              // largest n_se
-constexpr int BIG_EXTRA = 192;            // keys appended past n_se before the buffer is cut back
-constexpr int BIG_BUF = BIG_CAP + BIG_EXTRA + 64;  // room for one more leaf
-constexpr int BIG_J = BIG_BUF / 64;       // buffer slots per lane
-
-__device__ __forceinline__ bool vless(double a, int pa, double b, int pb) { return a < b || (a == b && pa < pb); }
-
-// The key of rank r (0-based) among the valid keys of the wavefront, by a
-// radix select over byte digits: per digit, a histogram of the keys that
-// share the digits chosen so far, and a wave-wide prefix over its 256
-// buckets to find the one holding rank r.  Keys are distinct.  hist: 256
-// words of LDS.
-__device__ __forceinline__ uint64_t wave_select(const uint64_t (&k)[BIG_J], const bool (&v)[BIG_J], int r,
-                                                uint32_t* hist) {
-    uint64_t lo = ~0ull, hi = 0;
-#pragma unroll
-    for (int j = 0; j < BIG_J; ++j)
-        if (v[j]) {
-            lo = min(lo, k[j]);
-            hi = max(hi, k[j]);
-        }
-    for (int o = 32; o > 0; o >>= 1) {
-        lo = min(lo, (uint64_t)__shfl_xor((unsigned long long)lo, o, 64));
-        hi = max(hi, (uint64_t)__shfl_xor((unsigned long long)hi, o, 64));
-    }
-    if (lo == hi) return lo;
-    const int lane = (int)lane_id();
-    // digits above the highest differing byte are those of every key
-    int shift = ((63 - __clzll(lo ^ hi)) >> 3) << 3;
-    uint64_t above = shift + 8 >= 64 ? 0 : ~0ull << (shift + 8);
-    uint64_t prefix = lo & above;
-    for (;;) {
-#pragma unroll
-        for (int t = 0; t < 4; ++t) hist[4 * lane + t] = 0;
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int j = 0; j < BIG_J; ++j)
-            if (v[j] && (k[j] & above) == prefix) atomicAdd(&hist[(k[j] >> shift) & 255], 1u);
-        __builtin_amdgcn_wave_barrier();
-        uint32_t c[4];
-#pragma unroll
-        for (int t = 0; t < 4; ++t) c[t] = hist[4 * lane + t];
-        const uint32_t sum = c[0] + c[1] + c[2] + c[3];
-        uint32_t incl = sum;
-        for (int o = 1; o < 64; o <<= 1) {
-            const uint32_t y = __shfl_up(incl, o, 64);
-            if (lane >= o) incl += y;
-        }
-        const uint32_t excl = incl - sum;
-        // the lane whose buckets span rank r names the digit
-        int digit = -1;
-        uint32_t below = excl;
-        if ((uint32_t)r >= excl && (uint32_t)r < incl) {
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                if (digit < 0 && (uint32_t)r < below + c[t]) digit = 4 * lane + t;
-                else if (digit < 0) below += c[t];
-            }
-        }
-        const uint64_t owner = __ballot(digit >= 0);
-        const int src = __builtin_ctzll(owner);
-        digit = __shfl(digit, src, 64);
-        below = __shfl(below, src, 64);
-        r -= (int)below;
-        prefix |= (uint64_t)digit << shift;
-        __builtin_amdgcn_wave_barrier();
-        if (shift == 0) break;
-        above = ~0ull << shift;
-        shift -= 8;
-    }
-    return prefix;
-}
-
 __global__ __launch_bounds__(64) void k_knn_wave(const int* __restrict__ flagged, const int* __restrict__ n_flagged,
                                                  Slots T, const float4* __restrict__ V, const double* __restrict__ FB,
                                                  const int32_t* __restrict__ host_off, int n_se, int n_v, int use_mass,
-                                                 double mass_value, int gb, float* __restrict__ R) {
+                                                 double mass_value, float* __restrict__ R) {
     __shared__ uint64_t buf[BIG_BUF];
     __shared__ int bslot[BIG_BUF];
     __shared__ uint32_t sel_hist[256];
@@ -849,7 +710,6 @@ __global__ __launch_bounds__(64) void k_knn_wave(const int* __restrict__ flagged
         const int slot = flagged[f];
         const int h = T.buckets[T.leaf_bucket[slot / LEAF]].w;
         const int base = host_off[h];
-        const bool wrap = host_wraps(T.hbox, h, gb);
         const float qx = T.x[slot], qy = T.y[slot], qz = T.z[slot];
         const float4 q4 = make_float4(qx, qy, qz, 0.f);
         int nb = 0;            // keys in buf (uniform)
@@ -884,7 +744,7 @@ __global__ __launch_bounds__(64) void k_knn_wave(const int* __restrict__ flagged
         };
         // whether the lane's box may hold a member of the set
         auto near = [&](const float4* box) __attribute__((always_inline)) {
-            const float g2 = box_gap2(box[0], box[1], q4, q4, wrap, (float)(1 << gb));
+            const float g2 = box_gap2(box[0], box[1], q4, q4);
             return nb < n_se || g2 <= (float)(W >> POS_BITS) * SLACK + 1.f;
         };
         auto scan = [&](int leaf) __attribute__((always_inline)) {
@@ -892,7 +752,7 @@ __global__ __launch_bounds__(64) void k_knn_wave(const int* __restrict__ flagged
             bool take = false;
             uint64_t key = 0;
             if (lane < LEAF && T.gid[s] >= 0) {
-                key = exact_key((int)(T.x[s] - qx), (int)(T.y[s] - qy), (int)(T.z[s] - qz), T.eid[s] - base, wrap, gb);
+                key = exact_key((int)(T.x[s] - qx), (int)(T.y[s] - qy), (int)(T.z[s] - qz), T.eid[s] - base);
                 take = key < W;
             }
             const uint64_t m = __ballot(take);
@@ -1003,13 +863,13 @@ int launch_knn(vr_ctx* ctx, const uint32_t* qpos, int64_t nq, int64_t n_queries,
     for (int k = 0; k < n_se; ++k) mass_sum += p->mass_value;
     VR_TIMED(ctx, "knn", st, n_queries,
              hipLaunchKernelGGL((k_knn<LPQ, KL, L>), dim3(grid_for(nq, 64 / LPQ)), dim3(64), 0, st, qpos, nq, T, V, FB,
-                                host_off, n_se, n_v, use_mass, p->mass_value, mass_sum, p->grid_bits, R,
+                                host_off, n_se, n_v, use_mass, p->mass_value, mass_sum, R,
                                 (unsigned)ctx->xcd_chunk, flagged, n_flagged, ctx->timing ? ctx->knn_cand : nullptr));
     VR_LAUNCH_CHECK(ctx);
     // almost always without work: a few wavefronts that stride over the flagged queries
     const unsigned nw = (unsigned)std::min<int64_t>(n_queries, 4 * ctx->num_cus);
     hipLaunchKernelGGL(k_knn_wave, dim3(std::max(nw, 1u)), dim3(64), 0, st, flagged, n_flagged, T, V, FB, host_off, n_se,
-                       n_v, use_mass, p->mass_value, p->grid_bits, R);
+                       n_v, use_mass, p->mass_value, R);
     VR_LAUNCH_CHECK(ctx);
     return VR_OK;
 }
@@ -1054,11 +914,16 @@ extern "C" int vr_local_vdensity(vr_ctx* ctx, const vr_particles* p, int32_t n_h
     if (rc) return rc;
     if (duph) return set_err(ctx, VR_ERR_INVALID_ARG, "host_members lists a particle twice or outside [0, n)");
     // Device-wide levels down to buckets of at most `cap` members.
-    const int cap = std::min(BUCKET_MAX, 8 * ctx->knn_leaf);
+    const int cap = std::min(BUCKET_MAX, 16 * ctx->knn_leaf);
     std::vector<int> nc(n_hosts, cap);
     KdTree tree;
-    rc = kd_build(ctx, p, n_hosts, host_offsets, host_members, off, nc, KD_WIDEST, 2, tree, st);
+    rc = kd_build(ctx, p, n_hosts, host_offsets, host_members, off, nc, KD_BUCKETS, 2, tree, st);
     if (rc) return rc;
+    // The search below takes coordinate differences as they are, which a host
+    // of half the box's width or more does not allow.
+    if (tree.wide)
+        return local_vdensity_wide(ctx, p, n_hosts, host_offsets, host_members, off, slot_of, vbar, sigma, n_se, n_v,
+                                   subset, n_subset, R, st);
     // The buckets follow from the sizes: every node above `cap` is halved.
     std::vector<int4> buckets;
     std::vector<int> hb(n_hosts + 1, 0);
@@ -1091,7 +956,6 @@ extern "C" int vr_local_vdensity(vr_ctx* ctx, const vr_particles* p, int32_t n_h
         T.lbox = cv.add<float4>(2 * n_leaves);
         T.bbox = cv.add<float4>(2 * nb);
         T.leaf_bucket = cv.add<int>(n_leaves);
-        T.hbox = cv.add<int>(6 * (size_t)n_hosts);
         T.buckets = cv.add<int4>(nb);
         T.host_bucket = cv.add<int>(n_hosts + 1);
     };
@@ -1114,7 +978,6 @@ extern "C" int vr_local_vdensity(vr_ctx* ctx, const vr_particles* p, int32_t n_h
     VR_WS(V, ctx, float4, WS_C0, n_slots);
     VR_WS(FB, ctx, double, WS_C1, n_slots);
     VR_WS(flagged, ctx, int, WS_C4, subset ? n_subset : M);
-    if ((rc = fill_i32(ctx, T.hbox, INT32_MAX, 6 * (int64_t)n_hosts, st))) return rc;
     const int lpq_log2 = n_se > 64 ? 4 : 2;
     hipLaunchKernelGGL(k_buckets, dim3((unsigned)nb), dim3(256), 0, st, tree.list[0], tree.list[1], tree.list[2],
                        tree.elem_u[0], tree.elem_u[1], tree.elem_u[2], tree.elem_g, tree.scratch, lpq_log2, T, slot_of);

@@ -1,7 +1,7 @@
 """The neighbour tree and search at the sizes where they can go wrong: hosts
 around multiples of a leaf and of a bucket, neighbour counts at the limits of
-each kernel form, hosts wider than half the box, more coincident members than
-a query's lists hold, and subsets whose wavefronts span hosts."""
+each kernel form, more coincident members than a query's lists hold, and
+subsets whose wavefronts span hosts."""
 import numpy as np
 import pytest
 
@@ -22,16 +22,14 @@ def ctx(vr):
     return vr.Context(0)
 
 
-def _hosts(rng, sizes, box=1.0, extent=0.02, masses=False, wide=()):
-    """Gaussian blobs of the given sizes as one workload and its host table;
-    hosts listed in `wide` fill 0.8 of the box instead."""
+def _hosts(rng, sizes, box=1.0, extent=0.02, masses=False):
+    """Gaussian blobs of the given sizes as one workload and its host table."""
     n = int(sum(sizes))
     pos = np.empty((3, n))
     off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
     for h, s in enumerate(sizes):
         c = rng.random((3, 1)) * box
-        pos[:, off[h]:off[h + 1]] = (c + (rng.random((3, s)) - 0.5) * 0.8 * box if h in wide
-                                     else c + rng.normal(0, extent, (3, s)))
+        pos[:, off[h]:off[h + 1]] = c + rng.normal(0, extent, (3, s))
     vel = rng.normal(0, 100.0, (3, n))
     x = np.mod(pos, box).astype(np.float32)
     x[x >= np.float32(box)] = 0
@@ -62,19 +60,11 @@ def test_leaf_and_bucket_edges(ctx, vr, ref, n_se, n_v, masses):
     sizes = [n_se, n_se + 1] + [s for s in (63, 64, 65, 257, 2047, 2048, 2049, 4097) if s >= n_se]
     saved = ctx.get_tune("knn_leaf")
     try:
-        for leaf in (16, 256):  # buckets of 128 and 2048 members
+        for leaf in (16, 256):  # buckets of 256 and 2048 members
             ctx.tune("knn_leaf", leaf)
             _check(ctx, vr, ref, _hosts(rng, sizes, masses=masses), n_se, n_v)
     finally:
         ctx.tune("knn_leaf", saved)
-
-
-@pytest.mark.parametrize("n_se,n_v", [(32, 8), (256, 32)])
-def test_host_wider_than_half_the_box(ctx, vr, ref, n_se, n_v):
-    """Neighbours across the edge of the unwrapped host count at their
-    periodic distance, whichever leaves hold them."""
-    rng = np.random.default_rng(5)
-    _check(ctx, vr, ref, _hosts(rng, [600, 5000, 400], wide=(1,)), n_se, n_v)
 
 
 @pytest.mark.parametrize("n_se,n_v", [(32, 8), (48, 16), (256, 32)])
@@ -101,6 +91,6 @@ def test_equal_velocities(ctx, vr, ref):
 def test_subset_across_hosts(ctx, vr, ref):
     """A sparse subset: a wavefront's queries lie in many hosts and leaves."""
     rng = np.random.default_rng(8)
-    case = _hosts(rng, [300] * 40 + [3000], wide=(7,))
+    case = _hosts(rng, [300] * 40 + [3000])
     sub = np.sort(rng.permutation(case[0].n)[:700]).astype(np.int32)
     _check(ctx, vr, ref, case, 32, 8, subset=rng.permutation(sub).astype(np.int32))
