@@ -82,8 +82,8 @@ int vr_set_timing(vr_ctx* ctx, int enabled);
  * FP64 potentials only through the order of their partial sums):
  * "knn_leaf"      the neighbour-search tree's leaves of 32 members are built
  *                 in workgroups of at most 16 * knn_leaf members, 2048 at most
- *                 (16..256, 64); members per leaf where a host is wider than
- *                 half the box
+ *                 (16..256, 64); members per leaf of the search that takes
+ *                 over where a host reaches round the box
  * "unbind_tile"   j-tile of the potential kernel staged in LDS (64..4096, 256;
  *                 the persistent kernel uses at most 1024 per wavefront)
  * "unbind_jchunk" j-range of one potential work item (256..65536, 4096)

@@ -34,11 +34,14 @@ struct KdTree {
     int* elem_u[3] = {nullptr, nullptr, nullptr};  // coordinates by element id
     int* elem_host = nullptr;  // host by element id (= by position: hosts keep their ranges)
     int use_mass = 0;
-    // KD_BUCKETS only: whether some host is wider than half the box (then
-    // nothing else is set); element ids by position in the (coordinate,
-    // element) order of each dimension inside every leaf; particle by element
-    // id; scratch of one int per member, free for the caller
+    // KD_BUCKETS only: whether some host spans half the box or more; per
+    // host, the smallest squared distance a pair of its members can have
+    // through the box (rounded down; infinity for hosts below half the box);
+    // element ids by position in the (coordinate, element) order of each
+    // dimension inside every leaf; particle by element id; scratch of one int
+    // per member, free for the caller
     bool wide = false;
+    float* lim2 = nullptr;
     int* list[3] = {nullptr, nullptr, nullptr};
     int* elem_g = nullptr;
     int* scratch = nullptr;

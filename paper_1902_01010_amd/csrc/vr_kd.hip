@@ -103,12 +103,23 @@ __global__ void k_elems(int64_t M, int n_hosts, const int32_t* __restrict__ off,
         atomicAdd(&hash[((uint64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) % HASH_SLOTS], hv);
 }
 
-// Raises *flag when a host spans half the box or more on some axis.
-__global__ void k_any_wide(int n_hosts, int half, const int* __restrict__ hbox, unsigned long long* __restrict__ flag) {
+// Raises *flag when a host spans half the box or more on some axis.  There
+// the periodic distance of two members can be below their coordinates'
+// difference, but is at least what the host's extent leaves of the box.
+__global__ void k_any_wide(int n_hosts, int half, const int* __restrict__ hbox, float* __restrict__ lim2,
+                           unsigned long long* __restrict__ flag) {
     const int h = blockIdx.x * blockDim.x + threadIdx.x;
     if (h >= n_hosts) return;
     const int* b = hbox + 6 * (int64_t)h;
-    if (-b[3] - b[0] >= half || -b[4] - b[1] >= half || -b[5] - b[2] >= half) *flag = 1;
+    float l = INFINITY;
+    for (int d = 0; d < 3; ++d) {
+        const int ext = -b[3 + d] - b[d];
+        if (ext < half) continue;
+        const float left = (float)(2 * half - ext);  // an integer below 2^21
+        l = fminf(l, left * left * 0.999999f);
+        *flag = 1;
+    }
+    lim2[h] = l;
 }
 
 __global__ void k_presort_keys(int64_t M, const int* __restrict__ u, const int* __restrict__ host,
@@ -556,7 +567,7 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
     const int64_t MC = mode < KD_WIDEST ? M : 1;     // coordinates in list-0 order
     const int64_t MF = mode != KD_BUCKETS ? M : 1;   // members by position
     const int64_t HB = mode == KD_BUCKETS ? 6 * (int64_t)n_hosts : 1;
-    float* Ms;
+    float *Ms, *lim2;
     uint8_t* lf8;
     uint32_t* lf;
     uint64_t* pkey;
@@ -586,6 +597,7 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
         F.eid = cv.add<int>(MF);
         F.mass = cv.add<float>(use_mass ? MF : 1);
         hbox = cv.add<int>(HB);
+        lim2 = cv.add<float>(mode == KD_BUCKETS ? n_hosts : 1);
         ncell_d = cv.add<int>(n_hosts);
         counters = cv.add<int>(8);
         hsh = cv.add<unsigned long long>(HASH_SLOTS + 1);  // and the wide-host flag
@@ -614,7 +626,7 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
     VR_LAUNCH_CHECK(ctx);
     if (mode == KD_BUCKETS) {
         hipLaunchKernelGGL(k_any_wide, dim3(grid_for(n_hosts, 256)), dim3(256), 0, st, n_hosts, 1 << (p->grid_bits - 1),
-                           hbox, hsh + HASH_SLOTS);
+                           hbox, lim2, hsh + HASH_SLOTS);
         VR_LAUNCH_CHECK(ctx);
     }
     // The three lists sorted by (host, u_d, element) depend only on the
@@ -627,10 +639,7 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
         unsigned long long parts[HASH_SLOTS + 1];
         int rc = read_back(ctx, hsh, parts, sizeof parts, st);
         if (rc) return rc;
-        if (parts[HASH_SLOTS]) {
-            tree.wide = true;
-            return VR_OK;
-        }
+        tree.wide = parts[HASH_SLOTS] != 0;
         unsigned long long h64 = 0;
         for (int k = 0; k < HASH_SLOTS; ++k) h64 += parts[k];
         const int bits = 22 + hb;
@@ -789,6 +798,7 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
     if (mode == KD_BUCKETS) {
         for (int d = 0; d < 3; ++d) tree.list[d] = L[d];
         tree.elem_g = G;
+        tree.lim2 = lim2;
         tree.scratch = Lalt[0];
         return VR_OK;
     }

@@ -107,8 +107,8 @@ __device__ __forceinline__ uint64_t wave_select(const uint64_t (&k)[BIG_J], cons
 
 // rank_of[g] = the position of particle g in host_members (-1 beforehand);
 // a member outside [0, n) or listed twice raises *bad (vr_knn.hip).
-// R of the members of hosts some of which are wider than half the box
-// (vr_knn_wide.hip); the arguments are those of vr_local_vdensity, already
+// R where neighbours may be nearer through the box than by their unwrapped
+// coordinates (vr_knn_wide.hip); the arguments are those of vr_local_vdensity, already
 // checked, off the host offsets on the host, rank_of as above.
 int local_vdensity_wide(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t* host_offsets,
                         const int32_t* host_members, const std::vector<int32_t>& off, const int32_t* rank_of,

@@ -47,6 +47,8 @@ struct Slots {
     int4* buckets;      // [n_buckets] first list position, members, first leaf, host
     int* leaf_bucket;   // [n_leaves]
     int* host_bucket;   // [n_hosts + 1]
+    const float* lim2;  // [n_hosts] squared distances from here on may differ through the box
+    int* beyond;        // raised when a query's set reaches that far
 };
 
 __global__ void k_subset_slot(int64_t ns, int64_t n, const int32_t* __restrict__ subset, const int* __restrict__ slot_of,
@@ -342,8 +344,11 @@ __device__ __forceinline__ float box_gap2(float4 a0, float4 a1, float4 b0, float
     return fmaf(gx, gx, fmaf(gy, gy, gz * gz));
 }
 
+// (members more than half a box apart, in a host of that width, may exceed the
+// key's 42 bits; they are nobody's neighbours, or the call is done otherwise)
 __device__ __forceinline__ uint64_t exact_key(int dx, int dy, int dz, int rank) {
-    const uint64_t d2 = (uint64_t)((int64_t)dx * dx + (int64_t)dy * dy + (int64_t)dz * dz);
+    const uint64_t d2 = min((uint64_t)((int64_t)dx * dx + (int64_t)dy * dy + (int64_t)dz * dz),
+                            (uint64_t(1) << (64 - POS_BITS)) - 1);
     return (d2 << POS_BITS) | (uint64_t)(uint32_t)rank;
 }
 
@@ -545,6 +550,7 @@ __global__ __launch_bounds__(64, 4) void k_knn(const uint32_t* __restrict__ qpos
             }
         }
         const float X = mine ? hi * SLACK : -1.f;
+        if (__ballot(X >= T.lim2[hh]) && lane == 0) *T.beyond = 1;
         // the members within X: the sign of d2 - X marks them (SLACK covers its
         // rounding), 32 marks a word, then each lane lists its marks
         int nl = 0;
@@ -781,6 +787,8 @@ __global__ __launch_bounds__(64) void k_knn_wave(const int* __restrict__ flagged
                 bucket(b0 + __builtin_ctzll(todo));
         }
         if (nb > n_se) compact();
+        for (int a = lane; a < n_se; a += 64)
+            if ((float)(buf[a] >> POS_BITS) * SLACK >= T.lim2[h]) *T.beyond = 1;
         // the n_se spatial neighbours: velocity distances and the mass of the set
         const float4 vq = V[slot];
         const double vqx = (double)vq.x, vqy = (double)vq.y, vqz = (double)vq.z;
@@ -905,7 +913,7 @@ extern "C" int vr_local_vdensity(vr_ctx* ctx, const vr_particles* p, int32_t n_h
     VR_WS(dup, ctx, int, WS_FLAG, 4);
     rc = fill_i32(ctx, slot_of, -1, p->n, st);
     if (rc) return rc;
-    rc = fill_i32(ctx, dup, 0, 2, st);
+    rc = fill_i32(ctx, dup, 0, 3, st);
     if (rc) return rc;
     hipLaunchKernelGGL(k_rank_of, dim3(grid_for(M, 256)), dim3(256), 0, st, M, p->n, host_members, slot_of, dup);
     VR_LAUNCH_CHECK(ctx);
@@ -919,11 +927,6 @@ extern "C" int vr_local_vdensity(vr_ctx* ctx, const vr_particles* p, int32_t n_h
     KdTree tree;
     rc = kd_build(ctx, p, n_hosts, host_offsets, host_members, off, nc, KD_BUCKETS, 2, tree, st);
     if (rc) return rc;
-    // The search below takes coordinate differences as they are, which a host
-    // of half the box's width or more does not allow.
-    if (tree.wide)
-        return local_vdensity_wide(ctx, p, n_hosts, host_offsets, host_members, off, slot_of, vbar, sigma, n_se, n_v,
-                                   subset, n_subset, R, st);
     // The buckets follow from the sizes: every node above `cap` is halved.
     std::vector<int4> buckets;
     std::vector<int> hb(n_hosts + 1, 0);
@@ -1007,13 +1010,28 @@ extern "C" int vr_local_vdensity(vr_ctx* ctx, const vr_particles* p, int32_t n_h
         qpos = qp;
         nq = n_queries = n_subset;
     }
-    int* nfl = dup + 1;  // zero since the fill above
+    int* nfl = dup + 1;  // zero, as dup[2], since the fill above
+    T.lim2 = tree.lim2;
+    T.beyond = dup + 2;
     if (n_se <= 32)
-        return launch_knn<4, 8, 12>(ctx, qpos, nq, n_queries, T, V, FB, host_offsets, p, n_se, n_v, R, flagged, nfl, st);
-    if (n_se <= 64)
-        return launch_knn<4, 16, 22>(ctx, qpos, nq, n_queries, T, V, FB, host_offsets, p, n_se, n_v, R, flagged, nfl, st);
-    // up to the paper's defaults (n_se 256, n_v 32)
-    if (n_se <= 128)
-        return launch_knn<16, 8, 14>(ctx, qpos, nq, n_queries, T, V, FB, host_offsets, p, n_se, n_v, R, flagged, nfl, st);
-    return launch_knn<16, 16, 24>(ctx, qpos, nq, n_queries, T, V, FB, host_offsets, p, n_se, n_v, R, flagged, nfl, st);
+        rc = launch_knn<4, 8, 12>(ctx, qpos, nq, n_queries, T, V, FB, host_offsets, p, n_se, n_v, R, flagged, nfl, st);
+    else if (n_se <= 64)
+        rc = launch_knn<4, 16, 22>(ctx, qpos, nq, n_queries, T, V, FB, host_offsets, p, n_se, n_v, R, flagged, nfl, st);
+    else if (n_se <= 128)
+        rc = launch_knn<16, 8, 14>(ctx, qpos, nq, n_queries, T, V, FB, host_offsets, p, n_se, n_v, R, flagged, nfl, st);
+    else  // up to the paper's defaults (n_se 256, n_v 32)
+        rc = launch_knn<16, 16, 24>(ctx, qpos, nq, n_queries, T, V, FB, host_offsets, p, n_se, n_v, R, flagged, nfl, st);
+    if (rc || !tree.wide) return rc;
+    // The search takes coordinate differences as they are.  In a host of half
+    // the box's width or more that is the periodic distance too unless a set
+    // reaches as far as the host's extent leaves of the box; then the whole
+    // call is done by the other search.
+    int beyond = 0;
+    if ((rc = read_back(ctx, T.beyond, &beyond, sizeof beyond, st))) return rc;
+    if (!beyond) return VR_OK;
+    if ((rc = fill_i32(ctx, slot_of, -1, p->n, st))) return rc;
+    hipLaunchKernelGGL(k_rank_of, dim3(grid_for(M, 256)), dim3(256), 0, st, M, p->n, host_members, slot_of, dup);
+    VR_LAUNCH_CHECK(ctx);
+    return local_vdensity_wide(ctx, p, n_hosts, host_offsets, host_members, off, slot_of, vbar, sigma, n_se, n_v, subset,
+                               n_subset, R, st);
 }

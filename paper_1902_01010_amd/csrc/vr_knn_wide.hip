@@ -1,12 +1,12 @@
-// vr_knn_wide.hip -- R = ln(f_l / f_bg) (Sec. 2.2) where a host is wider than
-// half the box.
+// vr_knn_wide.hip -- R = ln(f_l / f_bg) (Sec. 2.2) where some neighbours of a
+// host wider than half the box are nearer through the box.
 //
 // Such a host's members are unwrapped about its first member, so pairs across
 // the unwrapped edge are closer through the box than their coordinates say.
 // This search measures every distance by the minimum image, but prunes nodes
 // by their unwrapped boxes, so the neighbours it finds across that edge depend
 // on the tree and on the order of the walk; its results for such hosts are
-// kept as they are.  All other calls take vr_knn.hip.
+// kept as they are.  All other calls are done by vr_knn.hip, which notices.
 //
 // Each host gets a median-split KD tree (widest dimension, leaves of at most
 // 64 members, built by the presorted level-synchronous builder); members sit

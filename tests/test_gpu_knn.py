@@ -94,3 +94,15 @@ def test_subset_across_hosts(ctx, vr, ref):
     case = _hosts(rng, [300] * 40 + [3000])
     sub = np.sort(rng.permutation(case[0].n)[:700]).astype(np.int32)
     _check(ctx, vr, ref, case, 32, 8, subset=rng.permutation(sub).astype(np.int32))
+
+
+@pytest.mark.parametrize("n_se,n_v", [(32, 8), (256, 32)])
+def test_host_wider_than_half_the_box(ctx, vr, ref, n_se, n_v):
+    """0.7 of the box on every axis about the first member: no neighbour is
+    nearer through the box, so plain differences give the periodic sets."""
+    rng = np.random.default_rng(9)
+    case = _hosts(rng, [6000, 700])
+    x = 0.5 + 0.35 * (2 * rng.random((3, 6000)) - 1)
+    x[:, 0] = 0.5
+    case[0].x[:, :6000] = x
+    _check(ctx, vr, ref, case, n_se, n_v)
