@@ -84,8 +84,8 @@ int vr_set_timing(vr_ctx* ctx, int enabled);
  *                 in workgroups of at most 16 * knn_leaf members, 2048 at most
  *                 (16..256, 64); members per leaf of the search that takes
  *                 over where a host reaches round the box
- * "unbind_tile"   j-tile of the potential kernel staged in LDS (64..4096, 256;
- *                 the persistent kernel uses at most 1024 per wavefront)
+ * "unbind_tile"   j-tile of the host-planned potential kernel staged in LDS
+ *                 (64..4096, 256; the persistent kernel's tiles are fixed)
  * "unbind_jchunk" j-range of one potential work item (256..65536, 4096)
  * "unbind_bpc"    workgroups per CU of the persistent potential kernel
  *                 (0..8, 0 = as many as fit)

@@ -2,9 +2,8 @@
 // (Sec. 2.2, Eq. binding), all groups batched per pass.
 //
 // Every pass has two launches.  The potential launch runs over work items
-// (group, i-tile, j-range): the j members are staged through LDS as float
-// grid-unit coordinates (exact small integers) and mass; each lane owns one i
-// and sums 1/sqrt(r^2 + eps^2) terms in FP32 over runs of at most 64 j
+// (group, i-tile, j-range) with the members as float grid-unit coordinates
+// (exact small integers) and mass; each lane owns one i and sums 1/sqrt(r^2 + eps^2) terms in FP32 over runs of at most 64 j
 // before adding the run into an FP64 accumulator, which is then added
 // atomically to the member's FP64 potential.  The per-group launch (one
 // workgroup per active group) then finds the potential minimum (candidates
@@ -37,10 +36,9 @@ constexpr int MAX_CAND = 64;
 constexpr double REFINE_TOL = 4e-5;     // > twice the FP32 error bound of the tiled sums
 
 struct Members {
-    int32_t* gidx;
-    float *x, *y, *z;    // grid units relative to the group's first member (exact integers)
-    float *vx, *vy, *vz;
-    float* m;            // null for uniform mass
+    float4* p;      // x, y, z in grid units relative to the group's first member (exact integers); mass (1 if uniform)
+    float4* v;      // velocity; particle index (bits)
+    int uniform;    // every particle has the same mass
 };
 
 // Members removed by a group's last pass, at the group's base (stable
@@ -49,7 +47,7 @@ struct Members {
 // full recompute; mode = 1 when the next pass may subtract them instead of
 // recomputing.
 struct Removed {
-    float *x, *y, *z, *m;
+    float4* p;
     int *nrm, *since, *mode;
 };
 
@@ -71,14 +69,9 @@ __global__ void k_ub_init(int ng, int64_t M, const int32_t* __restrict__ off, co
     const int r = mem[off[lo]];
     const int i = mem[k];
     const int rx = (int)qx[r], ry = (int)qy[r], rz = (int)qz[r];
-    W.gidx[k] = i;
-    W.x[k] = (float)min_image((int)qx[i] - rx, gb);
-    W.y[k] = (float)min_image((int)qy[i] - ry, gb);
-    W.z[k] = (float)min_image((int)qz[i] - rz, gb);
-    W.vx[k] = vx[i];
-    W.vy[k] = vy[i];
-    W.vz[k] = vz[i];
-    if (mass) W.m[k] = mass[i];
+    W.p[k] = make_float4((float)min_image((int)qx[i] - rx, gb), (float)min_image((int)qy[i] - ry, gb),
+                         (float)min_image((int)qz[i] - rz, gb), mass ? mass[i] : 1.f);
+    W.v[k] = make_float4(vx[i], vy[i], vz[i], __int_as_float(i));
     bound[i] = 0;
     phi[i] = NAN;
 }
@@ -143,15 +136,13 @@ __global__ __launch_bounds__(UB) void k_ub_potential(const int4* __restrict__ it
     const int g = it.x, base = off[g], n = cnt[g];
     const int i = it.y + (int)threadIdx.x;
     const bool valid = i < n;
-    const float xi = valid ? W.x[base + i] : 0.f, yi = valid ? W.y[base + i] : 0.f, zi = valid ? W.z[base + i] : 0.f;
+    const float4 pi = valid ? W.p[base + i] : make_float4(0.f, 0.f, 0.f, 0.f);
+    const float xi = pi.x, yi = pi.y, zi = pi.z;
     double accd = 0.0;
     for (int j0 = it.z; j0 < it.w; j0 += tile) {
         const int jn = min(tile, it.w - j0);
         __syncthreads();
-        for (int t = threadIdx.x; t < jn; t += blockDim.x) {
-            const int k = base + j0 + t;
-            sj[t] = make_float4(W.x[k], W.y[k], W.z[k], UNIFORM ? 1.f : W.m[k]);
-        }
+        for (int t = threadIdx.x; t < jn; t += blockDim.x) sj[t] = W.p[base + j0 + t];
         __syncthreads();
         // rows of this wavefront: [iw, iw + 64)
         const int iw = it.y + ((int)threadIdx.x & ~63);
@@ -213,13 +204,57 @@ __device__ __forceinline__ uint32_t bscan(uint32_t v, uint32_t* sm, uint32_t* to
 }
 
 __device__ __forceinline__ uint64_t ref_key(const Members& W, int base, int pos, int px, int py, int pz, int gb) {
-    const int64_t dx = min_image((int)W.x[base + pos] - px, gb);
-    const int64_t dy = min_image((int)W.y[base + pos] - py, gb);
-    const int64_t dz = min_image((int)W.z[base + pos] - pz, gb);
+    const float4 v = W.p[base + pos];
+    const int64_t dx = min_image((int)v.x - px, gb);
+    const int64_t dy = min_image((int)v.y - py, gb);
+    const int64_t dz = min_image((int)v.z - pz, gb);
     return ((uint64_t)(dx * dx + dy * dy + dz * dz) << 22) | (uint64_t)pos;
 }
 
-// One group per workgroup of BS threads.  With split != 0 (no active list)
+// Bin of a squared distance for the first step of the frame's select: the
+// upper bits of its FP32 value (64 bins an octave over [2^6, 2^38), the rest
+// in the end bins), which order as the distances do.
+constexpr int SEL_BINS = 2048;
+__device__ __forceinline__ int sel_bin(uint64_t d2) {
+    const int b = (int)(__float_as_uint((float)d2) >> 17) - ((127 + 6) << 6);
+    return min(max(b, 0), SEL_BINS - 1);
+}
+constexpr int SEL_LIST = 1024;  // keys of the rank's bin that are ranked in LDS
+
+// f(k, v) for every member k of [0, n) with v = load(k), U loads in flight a
+// thread, k ascending for each thread.
+template <int U, class L, class F>
+__device__ __forceinline__ void for_members(int n, L load, F f) {
+    const int bs = (int)blockDim.x;
+    for (int c0 = (int)threadIdx.x; c0 < n; c0 += U * bs) {
+        decltype(load(0)) v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = load(min(c0 + u * bs, n - 1));
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (c0 + u * bs < n) f(c0 + u * bs, v[u]);
+    }
+}
+
+// 1 / sqrt(x) of a positive normal x to FP64 rounding: the hardware estimate
+// (29 bits) and two Newton steps, a third of the instructions of a square
+// root and a division.
+__device__ __forceinline__ double rsqrt64(double x) {
+    double y = __builtin_amdgcn_rsq(x);
+#pragma unroll
+    for (int k = 0; k < 2; ++k) y = fma(0.5 * y, fma(-x * y, y, 1.0), y);
+    return y;
+}
+
+// One group per workgroup of BS threads.  Bound by the latency of the member
+// reads on one CU, so every pass over the members keeps several loads a
+// thread in flight, and there are few of them: extreme, candidates, select
+// (two: a histogram of distance bins, then the rank's bin), frame, energies
+// and compaction.  A single candidate needs no exact sum.  A 120 k-member
+// group's first pass 0.60 -> 0.34 ms, all 36 passes of 600 groups 4.65 ->
+// 2.0 ms (before: one load in flight, six select passes, a square root and a
+// division per exact term, compaction 1,024 members and two scans at a time,
+// members in seven arrays).  With split != 0 (no active list)
 // BS = UB_WIDE takes the groups before *nbig and BS = UB the others, so the
 // largest groups get four times the threads.
 constexpr int UB_WIDE = 1024;
@@ -239,8 +274,11 @@ __global__ __launch_bounds__(BS) void k_ub_group(const int* __restrict__ active,
     __shared__ uint32_t smu[NW];
     __shared__ uint32_t hist[2048];
     __shared__ int cand[MAX_CAND];
-    __shared__ int s_p, s_bucket;
+    __shared__ uint64_t list[SEL_LIST];
+    __shared__ int s_p, s_bucket, s_n;
     __shared__ uint32_t s_below;
+    __shared__ uint64_t s_key;
+    __shared__ uint32_t ckept[64];
     __shared__ double s_min;
     __shared__ int s_minpos;
     // with no active list every group has a block and finished ones leave
@@ -250,15 +288,14 @@ __global__ __launch_bounds__(BS) void k_ub_group(const int* __restrict__ active,
     const int base = off[g];
     const int n = cnt[g];
     const int tid = threadIdx.x, lane = __lane_id(), w = tid >> 6, nw = blockDim.x >> 6;
-    const bool uniform = W.m == nullptr;
+    const bool uniform = W.uniform != 0;
 
     // 1. largest accumulated 1/r sum = deepest potential (ties: lowest position)
     double best = -1.0;
     int bpos = 0x7FFFFFFF;
-    for (int k = tid; k < n; k += blockDim.x) {
-        const double a = acc[base + k];
+    for_members<8>(n, [&](int k) { return acc[base + k]; }, [&](int k, double a) {
         if (a > best || (a == best && k < bpos)) { best = a; bpos = k; }
-    }
+    });
     for (int o = 32; o > 0; o >>= 1) {
         const double ob = __shfl_xor(best, o, 64);
         const int op = __shfl_xor(bpos, o, 64);
@@ -273,6 +310,7 @@ __global__ __launch_bounds__(BS) void k_ub_group(const int* __restrict__ active,
             if (smd[ww] > b || (smd[ww] == b && (int)smu[ww] < bp)) { b = smd[ww]; bp = (int)smu[ww]; }
         s_min = b;
         s_minpos = bp;
+        s_n = 0;
     }
     __syncthreads();
     // 2-3. every member within the FP32 error band of the extreme gets an
@@ -281,35 +319,59 @@ __global__ __launch_bounds__(BS) void k_ub_group(const int* __restrict__ active,
     const double thr = s_min * (1.0 - REFINE_TOL);
     double cbest = -1.0;
     int cpos = s_minpos;
-    for (uint32_t first = 0;; first += MAX_CAND) {
-        uint32_t seen = 0;
-        for (int c0 = 0; c0 < n; c0 += blockDim.x) {
-            const int k = c0 + tid;
-            const bool in = k < n && acc[base + k] >= thr;
-            uint32_t tot;
-            const uint32_t r = seen + bscan(in ? 1u : 0u, smu, &tot);
-            if (in && r >= first && r < first + MAX_CAND) cand[r - first] = k;
-            seen += tot;
+    for_members<8>(n, [&](int k) { return acc[base + k]; }, [&](int k, double a) {
+        if (a >= thr) {
+            const int at = atomicAdd(&s_n, 1);
+            if (at < MAX_CAND) cand[at] = k;
         }
-        __syncthreads();
-        const int ncand = (int)min(seen - first, (uint32_t)MAX_CAND);
-        for (int c = 0; c < ncand; ++c) {
-            const int pc = cand[c];
-            const double cx = (double)W.x[base + pc], cy = (double)W.y[base + pc], cz = (double)W.z[base + pc];
-            double s1[1] = {0.0};
-            for (int k = tid; k < n; k += blockDim.x) {
-                if (k == pc) continue;
-                const double dx = cx - (double)W.x[base + k], dy = cy - (double)W.y[base + k],
-                             dz = cz - (double)W.z[base + k];
-                const double r2 = dx * dx + dy * dy + dz * dz;
-                if (eps2g == 0.0 && r2 == 0.0) continue;
-                const double m = uniform ? 1.0 : (double)W.m[base + k];
-                s1[0] += m / sqrt(r2 + eps2g);
+    });
+    __syncthreads();
+    const uint32_t total_cand = (uint32_t)s_n;
+    for (uint32_t first = 0; total_cand > 1; first += MAX_CAND) {
+        if (total_cand > MAX_CAND) {
+            uint32_t seen = 0;
+            for (int c0 = 0; c0 < n; c0 += blockDim.x) {
+                const int k = c0 + tid;
+                const bool in = k < n && acc[base + k] >= thr;
+                uint32_t tot;
+                const uint32_t r = seen + bscan(in ? 1u : 0u, smu, &tot);
+                if (in && r >= first && r < first + MAX_CAND) cand[r - first] = k;
+                seen += tot;
             }
-            bsum<1>(s1, smd);
-            if (s1[0] > cbest || (s1[0] == cbest && pc < cpos)) { cbest = s1[0]; cpos = pc; }
+            __syncthreads();
         }
-        if (first + MAX_CAND >= seen) break;
+        const int ncand = (int)min(total_cand - first, (uint32_t)MAX_CAND);
+        // NC candidates a pass over the members
+        constexpr int NC = 4;
+        for (int c = 0; c < ncand; c += NC) {
+            int pc[NC];
+            double cx[NC], cy[NC], cz[NC], s1[NC];
+#pragma unroll
+            for (int q = 0; q < NC; ++q) {
+                pc[q] = c + q < ncand ? cand[c + q] : -1;
+                const float4 v = W.p[base + max(pc[q], 0)];
+                cx[q] = (double)v.x;
+                cy[q] = (double)v.y;
+                cz[q] = (double)v.z;
+                s1[q] = 0.0;
+            }
+            for_members<2>(n, [&](int k) { return W.p[base + k]; }, [&](int k, float4 v) {
+                const double x = (double)v.x, y = (double)v.y, z = (double)v.z, m = (double)v.w;
+#pragma unroll
+                for (int q = 0; q < NC; ++q) {
+                    if (pc[q] < 0) continue;  // uniform
+                    const double dx = cx[q] - x, dy = cy[q] - y, dz = cz[q] - z;
+                    const double r2 = dx * dx + dy * dy + dz * dz;
+                    const double t = m * rsqrt64(r2 + eps2g);
+                    s1[q] += k == pc[q] || (eps2g == 0.0 && r2 == 0.0) ? 0.0 : t;
+                }
+            });
+            bsum<NC>(s1, smd);
+#pragma unroll
+            for (int q = 0; q < NC; ++q)
+                if (pc[q] >= 0 && (s1[q] > cbest || (s1[q] == cbest && pc[q] < cpos))) { cbest = s1[q]; cpos = pc[q]; }
+        }
+        if (first + MAX_CAND >= total_cand) break;
     }
     if (tid == 0) s_p = cpos;
     __syncthreads();
@@ -320,19 +382,19 @@ __global__ __launch_bounds__(BS) void k_ub_group(const int* __restrict__ active,
         int64_t nref = (int64_t)ceil(frac_ref * (double)n);
         if (nref < n_ref_min) nref = n_ref_min;
         if (nref > n) nref = n;
-        const int px = (int)W.x[base + p], py = (int)W.y[base + p], pz = (int)W.z[base + p];
-        // radix select of the key of rank nref-1, 11 bits at a time from the top
+        const float4 vp = W.p[base + p];
+        const int px = (int)vp.x, py = (int)vp.y, pz = (int)vp.z;
+        auto member = [&](int k) { return W.p[base + k]; };
+        auto dist2 = [&](float4 v) -> uint64_t {
+            const int64_t dx = min_image((int)v.x - px, gb), dy = min_image((int)v.y - py, gb),
+                          dz = min_image((int)v.z - pz, gb);
+            return (uint64_t)(dx * dx + dy * dy + dz * dz);
+        };
+        // the key of rank nref - 1: the bin that holds it, then its keys in
+        // LDS, each ranked against the others
         uint64_t prefix = 0;
         uint32_t rank = (uint32_t)(nref - 1);
-        for (int shift = 55; shift >= 0; shift -= 11) {
-            for (int k = tid; k < 2048; k += blockDim.x) hist[k] = 0;
-            __syncthreads();
-            const uint64_t hmask = (shift + 11 >= 64) ? 0ull : ~((1ull << (shift + 11)) - 1);
-            for (int k = tid; k < n; k += blockDim.x) {
-                const uint64_t key = ref_key(W, base, k, px, py, pz, gb);
-                if (((key ^ prefix) & hmask) == 0) atomicAdd(&hist[(key >> shift) & 2047u], 1u);
-            }
-            __syncthreads();
+        auto find_bucket = [&]() {
             uint32_t loc = 0;
             for (int k = 0; k < BPT; ++k) loc += hist[tid * BPT + k];
             uint32_t tot;
@@ -346,75 +408,131 @@ __global__ __launch_bounds__(BS) void k_ub_group(const int* __restrict__ active,
                 }
             }
             __syncthreads();
-            prefix |= (uint64_t)s_bucket << shift;
-            rank -= s_below;
+        };
+        for (int k = tid; k < SEL_BINS; k += blockDim.x) hist[k] = 0;
+        if (tid == 0) s_n = 0;
+        __syncthreads();
+        for_members<4>(n, member, [&](int k, float4 v) { atomicAdd(&hist[sel_bin(dist2(v))], 1u); });
+        __syncthreads();
+        find_bucket();
+        const int bucket = s_bucket;
+        const uint32_t in_bucket = hist[bucket];
+        __syncthreads();
+        if (in_bucket <= (uint32_t)SEL_LIST) {
+            const uint32_t want = rank - s_below;
+            for_members<4>(n, member, [&](int k, float4 v) {
+                const uint64_t d2 = dist2(v);
+                if (sel_bin(d2) == bucket) list[atomicAdd(&s_n, 1)] = (d2 << 22) | (uint64_t)k;
+            });
             __syncthreads();
+            for (int e = tid; e < (int)in_bucket; e += blockDim.x) {
+                const uint64_t key = list[e];
+                uint32_t r = 0;
+                for (uint32_t j = 0; j < in_bucket; ++j) r += list[j] < key ? 1u : 0u;
+                if (r == want) s_key = key;
+            }
+            __syncthreads();
+            prefix = s_key;
+        } else {
+            // a crowded bin (coincident members): radix select of the whole
+            // keys, 11 bits at a time from the top
+            for (int shift = 55; shift >= 0; shift -= 11) {
+                for (int k = tid; k < 2048; k += blockDim.x) hist[k] = 0;
+                __syncthreads();
+                const uint64_t hmask = (shift + 11 >= 64) ? 0ull : ~((1ull << (shift + 11)) - 1);
+                for (int k = tid; k < n; k += blockDim.x) {
+                    const uint64_t key = ref_key(W, base, k, px, py, pz, gb);
+                    if (((key ^ prefix) & hmask) == 0) atomicAdd(&hist[(key >> shift) & 2047u], 1u);
+                }
+                __syncthreads();
+                find_bucket();
+                prefix |= (uint64_t)s_bucket << shift;
+                rank -= s_below;
+                __syncthreads();
+            }
         }
-        for (int k = tid; k < n; k += blockDim.x) {
-            if (ref_key(W, base, k, px, py, pz, gb) > prefix) continue;
-            const double m = uniform ? mass_value : (double)W.m[base + k];
+        for_members<4>(n, member, [&](int k, float4 v) {
+            if (((dist2(v) << 22) | (uint64_t)k) > prefix) return;
+            const double m = uniform ? mass_value : (double)v.w;
+            const float4 u = W.v[base + k];
             fr[0] += m;
-            fr[1] += m * (double)W.vx[base + k];
-            fr[2] += m * (double)W.vy[base + k];
-            fr[3] += m * (double)W.vz[base + k];
-        }
+            fr[1] += m * (double)u.x;
+            fr[2] += m * (double)u.y;
+            fr[3] += m * (double)u.z;
+        });
     } else {
         for (int k = tid; k < n; k += blockDim.x) {
-            const double m = uniform ? mass_value : (double)W.m[base + k];
+            const double m = uniform ? mass_value : (double)W.p[base + k].w;
+            const float4 u = W.v[base + k];
             fr[0] += m;
-            fr[1] += m * (double)W.vx[base + k];
-            fr[2] += m * (double)W.vy[base + k];
-            fr[3] += m * (double)W.vz[base + k];
+            fr[1] += m * (double)u.x;
+            fr[2] += m * (double)u.y;
+            fr[3] += m * (double)u.z;
         }
     }
     bsum<4>(fr, smd);
     const double vr0 = fr[1] / fr[0], vr1 = fr[2] / fr[0], vr2 = fr[3] / fr[0];
-    // 5. energies, removal and stable in-place compaction; survivors keep
-    // their sums, removed members go to the side list
+    // 5. energies, removal and stable in-place compaction; survivors
+    // keep their sums, removed members go to the side list.  A chunk is CI
+    // members a thread, read before any is rewritten; the members before the
+    // first removed one stay where they are.
+    constexpr int CI = 4;
+    static_assert(CI * NW <= 64, "one wavefront scans the chunk's kept counts");
     uint32_t kept = 0, gone = 0;
-    for (int c0 = 0; c0 < n; c0 += blockDim.x) {
-        const int k = c0 + tid;
-        const bool valid = k < n;
-        int32_t gi = 0;
-        float x = 0, y = 0, z = 0, ux = 0, uy = 0, uz = 0, mm = 0;
-        double a = 0.0;
-        bool keep = false;
-        if (valid) {
-            gi = W.gidx[base + k];
-            x = W.x[base + k]; y = W.y[base + k]; z = W.z[base + k];
-            ux = W.vx[base + k]; uy = W.vy[base + k]; uz = W.vz[base + k];
-            mm = uniform ? 0.f : W.m[base + k];
-            a = acc[base + k];
-            const double m = uniform ? mass_value : (double)mm;
-            const double ph = scale * (uniform ? mass_value : 1.0) * a;
-            const double dx = (double)ux - vr0, dy = (double)uy - vr1, dz = (double)uz - vr2;
-            const double T = 0.5 * m * (dx * dx + dy * dy + dz * dz);
-            const double Wp = m * ph;
-            const double E = beta_E * T + Wp;
-            keep = !(E >= 0.0);
-            phi[gi] = ph;
+    for (int c0 = 0; c0 < n; c0 += CI * BS) {
+        float4 P[CI], V[CI];
+        double a[CI];
+#pragma unroll
+        for (int u = 0; u < CI; ++u) {
+            const int k = base + min(c0 + u * BS + tid, n - 1);
+            P[u] = W.p[k];
+            V[u] = W.v[k];
+            a[u] = acc[k];
         }
-        uint32_t tot, totr;
-        const uint32_t r = bscan(keep ? 1u : 0u, smu, &tot);
-        const uint32_t rr = bscan((valid && !keep) ? 1u : 0u, smu, &totr);
-        if (keep) {
-            const int dst = base + (int)(kept + r);
-            W.gidx[dst] = gi;
-            W.x[dst] = x; W.y[dst] = y; W.z[dst] = z;
-            W.vx[dst] = ux; W.vy[dst] = uy; W.vz[dst] = uz;
-            if (!uniform) W.m[dst] = mm;
-            acc[dst] = a;
-        } else if (valid) {
-            const int dst = base + (int)(gone + rr);
-            Rm.x[dst] = x; Rm.y[dst] = y; Rm.z[dst] = z;
-            Rm.m[dst] = uniform ? 1.f : mm;
+        uint64_t kb[CI];  // kept members of the wavefront
+#pragma unroll
+        for (int u = 0; u < CI; ++u) {
+            bool keep = false;
+            if (c0 + u * BS + tid < n) {
+                const double m = uniform ? mass_value : (double)P[u].w;
+                const double ph = scale * (uniform ? mass_value : 1.0) * a[u];
+                const double dx = (double)V[u].x - vr0, dy = (double)V[u].y - vr1, dz = (double)V[u].z - vr2;
+                const double T = 0.5 * m * (dx * dx + dy * dy + dz * dz);
+                const double Wp = m * ph;
+                const double E = beta_E * T + Wp;
+                keep = !(E >= 0.0);
+                phi[__float_as_int(V[u].w)] = ph;
+            }
+            kb[u] = __ballot(keep);
+            if (lane == 0) ckept[u * NW + w] = (uint32_t)__popcll(kb[u]);
+        }
+        __syncthreads();
+        // kept members before (u, w) in the chunk
+        const uint32_t mine = lane < CI * NW ? ckept[lane] : 0u;
+        const uint32_t inc = wscan(mine);
+        const uint32_t tot = __shfl(inc, CI * NW - 1, 64);
+#pragma unroll
+        for (int u = 0; u < CI; ++u) {
+            const int ci = u * BS + tid;
+            const uint32_t kbefore = __shfl(inc - mine, u * NW + w, 64) + (uint32_t)__popcll(kb[u] & lanemask_lt());
+            if (c0 + ci >= n) continue;
+            if ((kb[u] >> lane) & 1ull) {
+                const int dst = base + (int)(kept + kbefore);
+                if (dst != base + c0 + ci) {
+                    W.p[dst] = P[u];
+                    W.v[dst] = V[u];
+                    acc[dst] = a[u];
+                }
+            } else {
+                Rm.p[base + (int)(gone + (uint32_t)ci - kbefore)] = P[u];
+            }
         }
         kept += tot;
-        gone += totr;
+        gone += (uint32_t)min(CI * BS, n - c0) - tot;
         __syncthreads();
     }
     if (kept == (uint32_t)n) {
-        for (int k = tid; k < n; k += blockDim.x) bound[W.gidx[base + k]] = 1;
+        for (int k = tid; k < n; k += blockDim.x) bound[__float_as_int(W.v[base + k].w)] = 1;
         if (tid == 0) state[g] = ST_BOUND;
     } else if ((int)kept < n_min) {
         if (tid == 0) state[g] = ST_DISSOLVED;
@@ -450,6 +568,21 @@ __global__ void k_ub_plan_reset(UbPlan* plan) {
     if (threadIdx.x == 0) plan->pairs = 0.0;
 }
 
+// Work items of a full recompute of T tiles of 64 members: every pair of
+// tiles once.  Item = (row tile a, chunk c of C column tiles from c C on),
+// columns from the diagonal on, so chunk c has rows 0 .. min(T, (c + 1) C) - 1.
+__device__ __forceinline__ uint32_t full_items(int T, int C) {
+    const int last = (T + C - 1) / C - 1;  // chunks before the last have all their rows
+    return (uint32_t)((int64_t)C * last * (last + 1) / 2) + (uint32_t)T;
+}
+// chunk and row of item l
+__device__ __forceinline__ void full_item(int l, int C, int& c, int& a) {
+    c = (int)((sqrtf(8.f * (float)l / (float)C + 1.f) - 1.f) * 0.5f);
+    while ((int64_t)C * c * (c + 1) / 2 > l) --c;
+    while ((int64_t)C * (c + 1) * (c + 2) / 2 <= l) ++c;
+    a = l - (int)((int64_t)C * c * (c + 1) / 2);
+}
+
 constexpr int PLAN_T = 1024;
 
 __global__ __launch_bounds__(PLAN_T) void k_ub_plan(int ng, const int* __restrict__ cnt, const int* __restrict__ state,
@@ -467,7 +600,8 @@ __global__ __launch_bounds__(PLAN_T) void k_ub_plan(int ng, const int* __restric
         // j over all members (full) or over the members removed last pass
         const int nj = (on && mode[g]) ? nrm[g] : n;
         pairs += (double)n * (double)(on && mode[g] ? nj : (n > 0 ? n - 1 : 0));
-        const uint32_t items = on ? (uint32_t)(((n + 63) / 64) * ((nj + jchunk - 1) / jchunk)) : 0u;
+        const uint32_t items = !on ? 0u : mode[g] ? (uint32_t)(((n + 63) / 64) * ((nj + jchunk - 1) / jchunk))
+                                                  : full_items((n + 63) / 64, jchunk / 64);
         uint32_t tg, ti;
         const uint32_t pg = bscan(on ? 1u : 0u, sm, &tg);
         const uint32_t pi = bscan(items, sm, &ti);
@@ -505,20 +639,113 @@ __global__ void k_ub_zero_p(const UbPlan* __restrict__ plan, const int* __restri
 // Persistent potential kernel: wavefront w takes item w first, then pops
 // items nwaves, nwaves + 1, ... from the queue until it is empty (so a light
 // pass costs no burst of atomics on the queue head, and wavefronts beyond the
-// item count leave at once); lane = one i of a 64-row tile, j staged through
-// the wave's LDS slice.
+// item count leave at once); lane = one i of a 64-row tile.
+//
+// A full recompute takes every pair of tiles once: the lane's own sum runs
+// over the columns, the reciprocal distances also go to LDS, and lane j then
+// sums its column over the rows -- the same FP32 terms in the same order as
+// if its own row had been summed (a pair's squared distance is the same
+// either way round).  Bound by VALU issue and, a tenth, by the columns' FP64
+// atomics: 10 instruction slots for two ordered pairs against 9 for one (17 KB
+// of LDS a wavefront, eight wavefronts a CU; columns in two halves of 32, 16
+// wavefronts a CU, were 9% slower).  2.1e10 ordered pairs, largest group
+// 120 k: 5.28 -> 3.86 ms; incremental passes lose occupancy (0.83 -> 1.01 ms
+// for the first, the only long one).
+constexpr int COLS = 68;  // floats a column of 64, padded: eight lanes' 16-byte reads cover all banks
+constexpr int STAGE = 512;  // removed members staged at a time
+constexpr int UBP = 128;  // threads per workgroup (two slices of LDS below 64 KB)
+constexpr int UB_LDS = 64 * COLS * 4 + 64 * 16 + 64 * 4;  // columns, staged j, masses of the rows
+
+// One lane's row of a 64 x 64 tile: the FP32 sum over the members q in
+// order, and every reciprocal distance to its column's LDS (stride COLS).
+// ZERO: eps = 0, coincident pairs are left out.  q is uniform: for a full
+// tile it points to global memory, and the members come through the scalar
+// cache (as LDS broadcasts, 8 clocks each on a CU's LDS, they bound the
+// kernel: 4.4 ms against 3.9 ms); the last tile of a group is staged in LDS
+// and padded.
+template <bool UNIFORM, bool ZERO>
+__device__ __forceinline__ float tile_rows(const float4* __restrict__ q, float4 pi, float eps2, float* out) {
+    // the next block's members are asked for before this block is worked on
+    constexpr int U = 8, BLOCKS = UNIFORM ? 4 : 1;
+    float4 a[U], b[U];
+    float accf = 0.f;
+    auto block = [&](const float4 (&v)[U], int t) __attribute__((always_inline)) {
+        float r[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const float dx = pi.x - v[u].x, dy = pi.y - v[u].y, dz = pi.z - v[u].z;
+            const float s2 = fmaf(dx, dx, fmaf(dy, dy, fmaf(dz, dz, eps2)));
+            r[u] = __builtin_amdgcn_rsqf(s2);
+            if (ZERO) r[u] = s2 > 0.f ? r[u] : 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            accf = UNIFORM ? accf + r[u] : fmaf(v[u].w, r[u], accf);
+            out[(t + u) * COLS] = r[u];
+        }
+    };
+#pragma unroll
+    for (int u = 0; u < U; ++u) a[u] = q[u];
+    // (with masses the unrolled loop took 270 registers, one wavefront a SIMD)
+#pragma unroll BLOCKS
+    for (int t = 0; t < 64; t += 2 * U) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) b[u] = q[t + U + u];
+        __builtin_amdgcn_sched_barrier(0);
+        block(a, t);
+        __builtin_amdgcn_sched_barrier(0);
+        if (t + 2 * U < 64) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) a[u] = q[t + 2 * U + u];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        block(b, t + U);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    return accf;
+}
+
+// The sum of one column over the 64 rows in order.
 template <bool UNIFORM>
-__global__ __launch_bounds__(UB) void k_ub_potential_p(UbPlan* plan, const int* __restrict__ act,
+__device__ __forceinline__ float tile_column(const float* cj, const float* smi) {
+    float cs = 0.f;
+#pragma unroll
+    for (int t0 = 0; t0 < 64; t0 += 32) {
+        float4 r[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) r[u] = *reinterpret_cast<const float4*>(cj + t0 + 4 * u);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            if (UNIFORM) {
+                cs = (((cs + r[u].x) + r[u].y) + r[u].z) + r[u].w;
+            } else {
+                const float4 m = *reinterpret_cast<const float4*>(smi + t0 + 4 * u);
+                cs = fmaf(m.w, r[u].w, fmaf(m.z, r[u].z, fmaf(m.y, r[u].y, fmaf(m.x, r[u].x, cs))));
+            }
+        }
+    }
+    return cs;
+}
+
+template <bool UNIFORM>
+__global__ __launch_bounds__(UBP, 2) void k_ub_potential_p(UbPlan* plan, const int* __restrict__ act,
                                                        const int* __restrict__ item_off, const int32_t* __restrict__ off,
-                                                       const int* __restrict__ cnt, Members W, Removed Rm, float eps2,
-                                                       double* __restrict__ acc, int jchunk, int tile) {
-    extern __shared__ float4 sjall[];
+                                                       const int* __restrict__ cnt, const float4* __restrict__ wp,
+                                                       const float4* __restrict__ rp, const int* __restrict__ nrm,
+                                                       const int* __restrict__ mode, float eps2,
+                                                       double* __restrict__ acc, int jchunk) {
+    extern __shared__ __align__(16) char ldsall[];
     const int lane = __lane_id(), wv = threadIdx.x >> 6;
-    float4* sj = sjall + wv * tile;
+    // the wavefront's slice: columns, one tile of members and the rows' masses
+    char* slice = ldsall + wv * UB_LDS;
+    float* col = reinterpret_cast<float*>(slice);
+    float4* sjt = reinterpret_cast<float4*>(slice + 64 * COLS * 4);
+    float* smi = reinterpret_cast<float*>(slice + 64 * COLS * 4 + 64 * 16);
     const int na = plan->n_active, total = plan->total_items;
     const int nwaves = (int)(gridDim.x * (blockDim.x >> 6));
     int it = (int)(blockIdx.x * (blockDim.x >> 6)) + wv;
     for (;; ) {
+        it = __builtin_amdgcn_readfirstlane(it);
         if (it >= total) break;
         // the group holding item `it`
         int lo = 0, hi = na - 1;
@@ -528,39 +755,64 @@ __global__ __launch_bounds__(UB) void k_ub_potential_p(UbPlan* plan, const int* 
         }
         const int g = act[lo];
         const int base = off[g], n = cnt[g];
-        // full: j over the members; incremental: j over last pass's removed
-        const bool incr = Rm.mode[g] != 0;
-        const int nj = incr ? Rm.nrm[g] : n;
-        const float* __restrict__ jx = incr ? Rm.x : W.x;
-        const float* __restrict__ jy = incr ? Rm.y : W.y;
-        const float* __restrict__ jz = incr ? Rm.z : W.z;
-        const float* __restrict__ jm = incr ? Rm.m : W.m;
-        const int njc = (nj + jchunk - 1) / jchunk;
         const int local = it - item_off[lo];
-        const int i0 = (local / njc) * 64, j0 = (local % njc) * jchunk;
-        const int j1 = min(nj, j0 + jchunk);
-        const int i = i0 + lane;
-        const bool valid = i < n;
-        const float xi = valid ? W.x[base + i] : 0.f, yi = valid ? W.y[base + i] : 0.f, zi = valid ? W.z[base + i] : 0.f;
-        // a removed member is never i itself; only coincident pairs need care
-        const int iself = incr ? -1 : i;
         double accd = 0.0;
-        for (int jb = j0; jb < j1; jb += tile) {
-            const int jn = min(tile, j1 - jb);
-            __builtin_amdgcn_wave_barrier();
-            for (int t = lane; t < jn; t += 64) {
-                const int k = base + jb + t;
-                sj[t] = make_float4(jx[k], jy[k], jz[k], UNIFORM ? 1.f : jm[k]);
+        int i;
+        if (mode[g] != 0) {
+            // incremental: j over last pass's removed members, staged in LDS
+            const int nj = nrm[g];
+            const int njc = (nj + jchunk - 1) / jchunk;
+            const int i0 = (local / njc) * 64, j0 = (local % njc) * jchunk;
+            const int j1 = min(nj, j0 + jchunk);
+            i = i0 + lane;
+            const float4 pi = i < n ? wp[base + i] : make_float4(0.f, 0.f, 0.f, 0.f);
+            float4* sj = reinterpret_cast<float4*>(slice);
+            for (int jb = j0; jb < j1; jb += STAGE) {
+                const int jn = min(STAGE, j1 - jb);
+                __builtin_amdgcn_wave_barrier();
+                for (int t = lane; t < jn; t += 64) sj[t] = rp[base + jb + t];
+                __builtin_amdgcn_wave_barrier();
+                // a removed member is never i itself; only coincident pairs need care
+                for (int t0 = 0; t0 < jn; t0 += 64) {
+                    const int t1 = min(t0 + 64, jn);
+                    accd -= (double)(eps2 == 0.f ? tile_sum<UNIFORM, true>(sj, t0, t1, pi.x, pi.y, pi.z, eps2, jb, -1)
+                                                 : tile_sum<UNIFORM, false>(sj, t0, t1, pi.x, pi.y, pi.z, eps2, jb, -1));
+                }
             }
-            __builtin_amdgcn_wave_barrier();
-            for (int t0 = 0; t0 < jn; t0 += 64) {
-                const int t1 = min(t0 + 64, jn);
-                const bool check = eps2 == 0.f || (!incr && jb + t0 < i0 + 64 && jb + t1 > i0);
-                accd += (double)(check ? tile_sum<UNIFORM, true>(sj, t0, t1, xi, yi, zi, eps2, jb, iself)
-                                       : tile_sum<UNIFORM, false>(sj, t0, t1, xi, yi, zi, eps2, jb, iself));
+        } else {
+            const int T = (n + 63) / 64, C = jchunk / 64;
+            int c, a;
+            full_item(local, C, c, a);
+            i = a * 64 + lane;
+            const float4 pi = i < n ? wp[base + i] : make_float4(0.f, 0.f, 0.f, 0.f);
+            if (!UNIFORM) smi[lane] = pi.w;
+            for (int b = max(a, c * C); b < min(T, (c + 1) * C); ++b) {
+                const int jb = b * 64, jn = min(64, n - jb);
+                __builtin_amdgcn_wave_barrier();
+                if (b == a || jn < 64 || eps2 == 0.f) {
+                    // (beyond the last member: infinitely far, 1 / r = 0)
+                    sjt[lane] = lane < jn ? wp[base + jb + lane] : make_float4(INFINITY, 0.f, 0.f, 0.f);
+                    __builtin_amdgcn_wave_barrier();
+                }
+                if (b == a) {  // the diagonal tile, row by row
+                    accd += (double)tile_sum<UNIFORM, true>(sjt, 0, jn, pi.x, pi.y, pi.z, eps2, jb, i);
+                    continue;
+                }
+                // rows before the last tile are all there
+                if (jn < 64 || eps2 == 0.f)
+                    accd += (double)(eps2 == 0.f ? tile_rows<UNIFORM, true>(sjt, pi, eps2, col + lane)
+                                                 : tile_rows<UNIFORM, false>(sjt, pi, eps2, col + lane));
+                else
+                    accd += (double)tile_rows<UNIFORM, false>(wp + base + jb, pi, eps2, col + lane);
+                __builtin_amdgcn_wave_barrier();
+                const float cs = tile_column<UNIFORM>(col + lane * COLS, smi);
+                if (lane < jn) atomicAdd(&acc[base + jb + lane], (double)cs);
             }
         }
-        if (valid) atomicAdd(&acc[base + i], incr ? -accd : accd);
+        if (i < n) atomicAdd(&acc[base + i], accd);
+        // (a light pass has no more items than wavefronts: thousands of pops
+        // of an empty queue, one address, cost 25 us)
+        if (total <= nwaves) break;
         int nx = 0;
         if (lane == 0) nx = atomicAdd(&plan->head, 1);
         it = nwaves + __shfl(nx, 0, 64);
@@ -591,13 +843,12 @@ using namespace vr;
 
 namespace {
 
-constexpr int PERSIST_MAX_TILE = 1024;  // 4 waves x tile x 16 B of LDS per workgroup
 constexpr int PASSES_PER_GRAPH = 4;
 
 // Everything a captured pass depends on; a cached graph is reused only when
 // all of it is unchanged.
 struct UbGraphKey {
-    const void* ptrs[24];
+    const void* ptrs[16];
     int ints[12];
     double dbls[6];
 };
@@ -618,27 +869,27 @@ void ub_graph_release(vr_ctx* ctx) {
 int unbind_persistent(vr_ctx* ctx, const vr_particles* p, int32_t ng, const int32_t* offsets,
                       const vr_unbind_params* up, const Members& W, const Removed& Rm, double* acc, int* cnt, int* state,
                       int32_t* iters, uint8_t* bound, double* phi, int* act, const int* nbig, float eps2f,
-                      double eps2g, double scale, int tile, hipStream_t st) {
+                      double eps2g, double scale, hipStream_t st) {
     VR_WS(plan, ctx, UbPlan, WS_D4, 1);
     VR_WS(item_off, ctx, int, WS_D5, (int64_t)ng + 1);
-    const bool uniform = W.m == nullptr;
+    const bool uniform = W.uniform != 0;
     const int jchunk = ctx->unbind_jchunk;
-    const size_t lds = (size_t)(UB / 64) * tile * sizeof(float4);
+    const size_t lds = (size_t)(UBP / 64) * UB_LDS;
     int bpc = 0;
     if (uniform)
-        VR_HIP(ctx, hipOccupancyMaxActiveBlocksPerMultiprocessor(&bpc, k_ub_potential_p<true>, UB, lds));
+        VR_HIP(ctx, hipOccupancyMaxActiveBlocksPerMultiprocessor(&bpc, k_ub_potential_p<true>, UBP, lds));
     else
-        VR_HIP(ctx, hipOccupancyMaxActiveBlocksPerMultiprocessor(&bpc, k_ub_potential_p<false>, UB, lds));
+        VR_HIP(ctx, hipOccupancyMaxActiveBlocksPerMultiprocessor(&bpc, k_ub_potential_p<false>, UBP, lds));
     if (ctx->unbind_bpc > 0 && ctx->unbind_bpc < bpc) bpc = ctx->unbind_bpc;
     if (bpc < 1) bpc = 1;
     const unsigned pgrid = (unsigned)(ctx->num_cus * bpc);
 
     UbGraphKey key;
     std::memset(&key, 0, sizeof key);
-    const void* kp[24] = {offsets, W.gidx, W.x, W.y, W.z, W.vx, W.vy, W.vz, W.m, acc, cnt, state, iters, bound, phi,
-                          act, Rm.x, Rm.y, Rm.z, Rm.m, Rm.nrm, Rm.since, Rm.mode, nbig};
+    const void* kp[16] = {offsets, W.p, W.v, acc, cnt, state, iters, bound, phi, act, Rm.p, Rm.nrm, Rm.since, Rm.mode,
+                          nbig, nullptr};
     std::memcpy(key.ptrs, kp, sizeof kp);
-    const int ki[12] = {ng, up->max_iter, jchunk, tile, (int)pgrid, up->n_min, up->n_ref_min, up->frame_type,
+    const int ki[12] = {ng, up->max_iter, jchunk, 0, (int)pgrid, up->n_min, up->n_ref_min, up->frame_type,
                         p->grid_bits, uniform ? 1 : 0, 0, 0};
     std::memcpy(key.ints, ki, sizeof ki);
     const double kd[6] = {(double)eps2f, eps2g, scale, p->mass_value, up->beta_E, up->frac_ref};
@@ -658,11 +909,11 @@ int unbind_persistent(vr_ctx* ctx, const vr_particles* p, int32_t ng, const int3
                                Rm.nrm, Rm.mode, act, item_off, plan);
             hipLaunchKernelGGL(k_ub_zero_p, dim3(ng), dim3(256), 0, cs, plan, act, offsets, cnt, Rm.mode, acc);
             if (uniform)
-                hipLaunchKernelGGL(k_ub_potential_p<true>, dim3(pgrid), dim3(UB), lds, cs, plan, act, item_off,
-                                   offsets, cnt, W, Rm, eps2f, acc, jchunk, tile);
+                hipLaunchKernelGGL(k_ub_potential_p<true>, dim3(pgrid), dim3(UBP), lds, cs, plan, act, item_off,
+                                   offsets, cnt, W.p, Rm.p, Rm.nrm, Rm.mode, eps2f, acc, jchunk);
             else
-                hipLaunchKernelGGL(k_ub_potential_p<false>, dim3(pgrid), dim3(UB), lds, cs, plan, act, item_off,
-                                   offsets, cnt, W, Rm, eps2f, acc, jchunk, tile);
+                hipLaunchKernelGGL(k_ub_potential_p<false>, dim3(pgrid), dim3(UBP), lds, cs, plan, act, item_off,
+                                   offsets, cnt, W.p, Rm.p, Rm.nrm, Rm.mode, eps2f, acc, jchunk);
             hipLaunchKernelGGL(k_ub_group<UB_WIDE>, dim3(ng), dim3(UB_WIDE), 0, cs, (const int*)nullptr, offsets, cnt,
                                state, iters, W, Rm, acc, eps2g, scale, p->mass_value, up->beta_E, up->frac_ref,
                                up->n_min, up->n_ref_min, up->frame_type, p->grid_bits, bound, phi, up->max_iter, nbig);
@@ -758,20 +1009,19 @@ extern "C" int vr_unbind(vr_ctx* ctx, const vr_particles* p, int32_t n_groups, c
     if (M > p->n) return set_err(ctx, VR_ERR_INVALID_ARG, "more members than particles");
     const bool uniform = p->mass == nullptr;
     Members W;
-    VR_WS(wg, ctx, int32_t, WS_C0, M);
-    VR_WS(wx, ctx, float, WS_C1, M); VR_WS(wy, ctx, float, WS_C2, M); VR_WS(wz, ctx, float, WS_C3, M);
-    VR_WS(wvx, ctx, float, WS_C4, M); VR_WS(wvy, ctx, float, WS_C5, M); VR_WS(wvz, ctx, float, WS_C6, M);
-    VR_WS(wm, ctx, float, WS_C7, uniform ? 1 : M);
-    W.gidx = wg; W.x = wx; W.y = wy; W.z = wz; W.vx = wvx; W.vy = wvy; W.vz = wvz; W.m = uniform ? nullptr : wm;
+    VR_WS(wp, ctx, float4, WS_C1, M);
+    VR_WS(wvel, ctx, float4, WS_C4, M);
+    W.p = wp;
+    W.v = wvel;
+    W.uniform = uniform ? 1 : 0;
     VR_WS(acc, ctx, double, WS_C8, M);
     VR_WS(cnt, ctx, int, WS_D0, n_groups);
     VR_WS(state, ctx, int, WS_D1, n_groups);
     VR_WS(act, ctx, int, WS_D2, n_groups);
     Removed Rm;
-    VR_WS(rx, ctx, float, WS_B0, M); VR_WS(ry, ctx, float, WS_B1, M); VR_WS(rz, ctx, float, WS_B2, M);
-    VR_WS(rmass, ctx, float, WS_B3, M);
+    VR_WS(rp, ctx, float4, WS_B0, M);
     VR_WS(nrm, ctx, int, WS_B4, n_groups); VR_WS(since, ctx, int, WS_B5, n_groups); VR_WS(mode, ctx, int, WS_B6, n_groups);
-    Rm.x = rx; Rm.y = ry; Rm.z = rz; Rm.m = rmass; Rm.nrm = nrm; Rm.since = since; Rm.mode = mode;
+    Rm.p = rp; Rm.nrm = nrm; Rm.since = since; Rm.mode = mode;
     VR_WS(nbig, ctx, int, WS_D6, 1);
     {
         int rc = fill_i32(ctx, nbig, n_groups, 1, st);
@@ -794,7 +1044,7 @@ extern "C" int vr_unbind(vr_ctx* ctx, const vr_particles* p, int32_t n_groups, c
     int tile = up->tile ? up->tile : (ctx->tuned_tile ? ctx->tuned_tile : 256);
     if (up->persistent)
         return unbind_persistent(ctx, p, n_groups, offsets, up, W, Rm, acc, cnt, state, iters, bound, phi, act, nbig,
-                                 eps2f, eps2g, scale, std::min(tile, PERSIST_MAX_TILE), st);
+                                 eps2f, eps2g, scale, st);
     std::vector<int> hcnt(n_groups), hstate(n_groups), hact;
     std::vector<int4> items;
     for (int pass = 0;; ++pass) {
