@@ -202,6 +202,12 @@ int sort_input_u32(vr_ctx* ctx, uint32_t* keys, uint32_t* vals, int64_t n, int b
                    uint32_t** vin);
 int sort_pairs_u32_from(vr_ctx* ctx, uint32_t* kin, uint32_t* vin, uint32_t* keys, uint32_t* vals, int64_t n,
                         int bits, hipStream_t s);
+// `batch` sorts of n <= SORT_BATCH_MAX pairs each whose arrays follow each
+// other, in the launches of one (larger ones fill the device alone).  Input
+// as placed by sort_input_u64 for batch * n pairs.
+constexpr int64_t SORT_BATCH_MAX = 524288;
+int sort_batch_u64(vr_ctx* ctx, uint64_t* kin, uint32_t* vin, uint64_t* keys, uint32_t* vals, int64_t n, int batch,
+                   int bits, hipStream_t s);
 // Fill helpers (kernels, never memset nodes, so they are safe to capture).
 int fill_i32(vr_ctx* ctx, int32_t* p, int32_t v, int64_t n, hipStream_t s);
 int fill_u32(vr_ctx* ctx, uint32_t* p, uint32_t v, int64_t n, hipStream_t s);

@@ -122,10 +122,15 @@ __global__ void k_any_wide(int n_hosts, int half, const int* __restrict__ hbox, 
     lim2[h] = l;
 }
 
-__global__ void k_presort_keys(int64_t M, const int* __restrict__ u, const int* __restrict__ host,
-                               uint64_t* __restrict__ key, uint32_t* __restrict__ val) {
+// blockIdx.y: the dimension of u0..u2 (a batch of sorts, one after the other).
+__global__ void k_presort_keys(int64_t M, const int* __restrict__ u0, const int* __restrict__ u1,
+                               const int* __restrict__ u2, const int* __restrict__ host, uint64_t* __restrict__ key,
+                               uint32_t* __restrict__ val) {
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= M) return;
+    const int* u = blockIdx.y == 0 ? u0 : (blockIdx.y == 1 ? u1 : u2);
+    key += blockIdx.y * M;
+    val += blockIdx.y * M;
     // unwrapped coordinates lie in [-2^20, 3 * 2^20): 22 bits after the shift
     key[e] = ((uint64_t)host[e] << 22) | (uint64_t)(uint32_t)(u[e] + (1 << 20));
     val[e] = (uint32_t)e;
@@ -560,6 +565,10 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
     const int counts = use_mass ? 0 : 1;
     int hb = 1;
     while ((1 << hb) <= n_hosts) ++hb;
+    // Sorts that do not fill the device run the three dimensions together
+    // (a third of the launches); with a workspace cap one after the other,
+    // in a third of the room.
+    const bool batch = M <= SORT_BATCH_MAX && ctx->max_ws == 0;
     // one workspace region holds every array of the build
     Carve cv;
     int *U[3], *G, *H, *L[3], *Lalt[3], *seg, *leaf_min, *act0, *act1, *leaves, *ncell_d, *counters, *hbox;
@@ -586,7 +595,7 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
         seg = cv.add<int>(M);
         lf8 = cv.add<uint8_t>(3 * M);
         lf = cv.add<uint32_t>(3 * M + 1);
-        pkey = cv.add<uint64_t>(M);
+        pkey = cv.add<uint64_t>(batch ? 3 * M : M);
         nodes = cv.add<KdNode>(node_cap);
         act0 = cv.add<int>(node_cap);
         act1 = cv.add<int>(node_cap);
@@ -629,6 +638,11 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
                            hbox, lim2, hsh + HASH_SLOTS);
         VR_LAUNCH_CHECK(ctx);
     }
+    // The lists a level reads: first the sorted ones, where they are kept (read
+    // only), then Lalt and L in turn.
+    int* Lin[3] = {L[0], L[1], L[2]};
+    int* Lout[3] = {Lalt[0], Lalt[1], Lalt[2]};
+    int* Lnext[3] = {L[0], L[1], L[2]};
     // The three lists sorted by (host, u_d, element) depend only on the
     // elements' members, unwrapped coordinates and hosts.  The context keeps
     // the last build's lists and reuses them when this build's content hash,
@@ -649,23 +663,25 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
         const bool hit = pre && ctx->kd_pre_ptr == pre && ctx->kd_pre_m == M && ctx->kd_pre_bits == bits &&
                          ctx->kd_pre_hash == h64;
         if (hit) {
-            for (int d = 0; d < 3; ++d)
-                VR_HIP(ctx, hipMemcpyAsync(L[d], pre + d * M, (size_t)M * sizeof(int), hipMemcpyDeviceToDevice, st));
+            for (int d = 0; d < 3; ++d) Lin[d] = pre + d * M;
         } else {
-            for (int d = 0; d < 3; ++d) {
-                uint32_t* ld = reinterpret_cast<uint32_t*>(L[d]);
+            ctx->kd_pre_m = -1;
+            if (pre)
+                for (int d = 0; d < 3; ++d) Lin[d] = pre + d * M;
+            const int step = batch && pre ? 3 : 1;  // dimensions a sort
+            for (int d = 0; d < 3; d += step) {
+                uint32_t* ld = reinterpret_cast<uint32_t*>(Lin[d]);
                 uint64_t* kin;
                 uint32_t* vin;
-                if ((rc = sort_input_u64(ctx, pkey, ld, M, bits, &kin, &vin))) return rc;
-                hipLaunchKernelGGL(k_presort_keys, dim3(grid_for(M, 256)), dim3(256), 0, st, M, U[d], H, kin, vin);
+                if ((rc = sort_input_u64(ctx, pkey, ld, step * M, bits, &kin, &vin))) return rc;
+                hipLaunchKernelGGL(k_presort_keys, dim3(grid_for(M, 256), step), dim3(256), 0, st, M, U[d],
+                                   step == 3 ? U[1] : nullptr, step == 3 ? U[2] : nullptr, H, kin, vin);
                 VR_LAUNCH_CHECK(ctx);
-                if ((rc = sort_pairs_u64_from(ctx, kin, vin, pkey, ld, M, bits, st))) return rc;
+                if ((rc = step == 3 ? sort_batch_u64(ctx, kin, vin, pkey, ld, M, 3, bits, st)
+                                    : sort_pairs_u64_from(ctx, kin, vin, pkey, ld, M, bits, st)))
+                    return rc;
             }
-            ctx->kd_pre_m = -1;
             if (pre) {
-                for (int d = 0; d < 3; ++d)
-                    VR_HIP(ctx, hipMemcpyAsync(pre + d * M, L[d], (size_t)M * sizeof(int), hipMemcpyDeviceToDevice,
-                                               st));
                 ctx->kd_pre_ptr = pre;
                 ctx->kd_pre_m = M;
                 ctx->kd_pre_bits = bits;
@@ -674,7 +690,7 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
         }
     }
     if (mode < KD_WIDEST) {
-        hipLaunchKernelGGL(k_coords_l0, dim3(grid_for(M, 256)), dim3(256), 0, st, M, L[0], U[0], U[1], U[2], C0[0],
+        hipLaunchKernelGGL(k_coords_l0, dim3(grid_for(M, 256)), dim3(256), 0, st, M, Lin[0], U[0], U[1], U[2], C0[0],
                            C0[1], C0[2]);
         VR_LAUNCH_CHECK(ctx);
     }
@@ -739,7 +755,7 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
         }
         hipLaunchKernelGGL(k_level_counters, dim3(1), dim3(64), 0, st, counters, level > 0 ? 1 : 0, 1);
         VR_LAUNCH_CHECK(ctx);
-        hipLaunchKernelGGL(k_bbox, dim3(grid_for(na, 256)), dim3(256), 0, st, counters, cur, nodes, L[0], L[1], L[2],
+        hipLaunchKernelGGL(k_bbox, dim3(grid_for(na, 256)), dim3(256), 0, st, counters, cur, nodes, Lin[0], Lin[1], Lin[2],
                            U[0], U[1], U[2], n_hosts);
         VR_LAUNCH_CHECK(ctx);
         uint32_t* hc = nullptr;
@@ -750,13 +766,13 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
                 hc = static_cast<uint32_t*>(ws(ctx, WS_KD_HIST, hn * sizeof(uint32_t)));
                 if (!hc) return VR_ERR_OUT_OF_MEMORY;
                 if ((rc = fill_u32(ctx, hc, 0u, hn, st))) return rc;
-                hipLaunchKernelGGL(k_hist<true>, dim3(grid_for(M, HCH)), dim3(KB), 0, st, M, seg, nodes, L[0], C0[0],
+                hipLaunchKernelGGL(k_hist<true>, dim3(grid_for(M, HCH)), dim3(KB), 0, st, M, seg, nodes, Lin[0], C0[0],
                                    C0[1], C0[2], Ms, nbins, hc, hm);
             } else {
                 hm = static_cast<double*>(ws(ctx, WS_KD_HIST, hn * sizeof(double)));
                 if (!hm) return VR_ERR_OUT_OF_MEMORY;
                 if ((rc = fill_u32(ctx, reinterpret_cast<uint32_t*>(hm), 0u, 2 * hn, st))) return rc;
-                hipLaunchKernelGGL(k_hist<false>, dim3(grid_for(M, HCH)), dim3(KB), 0, st, M, seg, nodes, L[0], C0[0],
+                hipLaunchKernelGGL(k_hist<false>, dim3(grid_for(M, HCH)), dim3(KB), 0, st, M, seg, nodes, Lin[0], C0[0],
                                    C0[1], C0[2], Ms, nbins, hc, hm);
             }
             VR_LAUNCH_CHECK(ctx);
@@ -769,20 +785,21 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
                                nodes, nbins, counts, hc, hm, Sdim);
             VR_LAUNCH_CHECK(ctx);
         }
-        hipLaunchKernelGGL(k_split, dim3(grid_for(na, 256)), dim3(256), 0, st, counters, cur, nodes, L[0], L[1], L[2],
+        hipLaunchKernelGGL(k_split, dim3(grid_for(na, 256)), dim3(256), 0, st, counters, cur, nodes, Lin[0], Lin[1], Lin[2],
                            U[0], U[1], U[2], mode, Sdim, ncell_d, nxt, leaves, counters);
         VR_LAUNCH_CHECK(ctx);
-        hipLaunchKernelGGL(k_lflag3, dim3(gM), dim3(256), 0, st, M, seg, nodes, L[0], L[1], L[2], U[0], U[1], U[2],
+        hipLaunchKernelGGL(k_lflag3, dim3(gM), dim3(256), 0, st, M, seg, nodes, Lin[0], Lin[1], Lin[2], U[0], U[1], U[2],
                            lf8);
         VR_LAUNCH_CHECK(ctx);
         if ((rc = scan_u8(ctx, lf8, lf, 3 * M, st))) return rc;
         CoordsL0 cl0{};
         if (mode < KD_WIDEST) cl0 = CoordsL0{{C0[0], C0[1], C0[2]}, {C0alt[0], C0alt[1], C0alt[2]}};
-        hipLaunchKernelGGL(k_part3, dim3(gM), dim3(256), 0, st, M, seg, nodes, L[0], L[1], L[2], lf8, lf, Lalt[0],
-                           Lalt[1], Lalt[2], cl0);
+        hipLaunchKernelGGL(k_part3, dim3(gM), dim3(256), 0, st, M, seg, nodes, Lin[0], Lin[1], Lin[2], lf8, lf, Lout[0],
+                           Lout[1], Lout[2], cl0);
         VR_LAUNCH_CHECK(ctx);
         for (int j = 0; j < 3; ++j) {
-            std::swap(L[j], Lalt[j]);
+            Lin[j] = Lout[j];
+            std::swap(Lout[j], Lnext[j]);
             std::swap(C0[j], C0alt[j]);
         }
         if (ctx->timing) {
@@ -796,10 +813,10 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
     tree.elem_host = H;
     tree.use_mass = use_mass;
     if (mode == KD_BUCKETS) {
-        for (int d = 0; d < 3; ++d) tree.list[d] = L[d];
+        for (int d = 0; d < 3; ++d) tree.list[d] = Lin[d];
         tree.elem_g = G;
         tree.lim2 = lim2;
-        tree.scratch = Lalt[0];
+        tree.scratch = Lout[0];
         return VR_OK;
     }
     if (!plan_na.empty()) {
@@ -810,11 +827,11 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
     int rc = read_back(ctx, counters, c, sizeof c, st);
     if (rc) return rc;
     const int nleaf = c[2];
-    hipLaunchKernelGGL(k_leaf_bbox, dim3(grid_for(nleaf, 256)), dim3(256), 0, st, nleaf, leaves, nodes, L[0], L[1],
-                       L[2], U[0], U[1], U[2], leaf_min, n_hosts);
+    hipLaunchKernelGGL(k_leaf_bbox, dim3(grid_for(nleaf, 256)), dim3(256), 0, st, nleaf, leaves, nodes, Lin[0], Lin[1],
+                       Lin[2], U[0], U[1], U[2], leaf_min, n_hosts);
     VR_LAUNCH_CHECK(ctx);
     const bool have_c0 = mode < KD_WIDEST;
-    hipLaunchKernelGGL(k_final, dim3(gM), dim3(256), 0, st, M, L[0], seg, U[0], U[1], U[2], have_c0 ? C0[0] : nullptr,
+    hipLaunchKernelGGL(k_final, dim3(gM), dim3(256), 0, st, M, Lin[0], seg, U[0], U[1], U[2], have_c0 ? C0[0] : nullptr,
                        have_c0 ? C0[1] : nullptr, have_c0 ? C0[2] : nullptr, G, use_mass ? Ms : nullptr, F, leaf_min);
     VR_LAUNCH_CHECK(ctx);
     tree.nodes = nodes;
