@@ -8,8 +8,9 @@
 // and the bounding box are read off directly.  One level costs a handful of
 // element-parallel passes for all nodes of all hosts at once: entropy
 // histograms (cells tree), the split decision per node, a left/right flag
-// per member, and a stable partition of each list by a global prefix sum
-// (subtracting the prefix at the segment start makes it segmented).  No
+// per member with counts per tile of positions, and a stable partition of
+// each list from the tiles' prefixes: four launches, two without histograms
+// (eleven and eight before: 12 k members in ten levels 1.0 -> 0.5 ms).  No
 // node is ever handled by a single workgroup, so the few huge top-level
 // nodes cost no more per member than the many small ones.  The levels and
 // the active-node counts that size their launches follow from the host
@@ -18,14 +19,27 @@
 // (kept as leaves) make smaller.
 #include "vr_kd.h"
 
+#include <algorithm>
 #include <climits>
 #include <cmath>
+#include <cstring>
+#include <type_traits>
 
 namespace vr {
 namespace {
 
 constexpr int KB = 256;
 constexpr int HCH = 2048;  // positions per histogram block
+// Up to this many members a block takes 256 positions (a 12 k host's level
+// would keep 6 of 256 CUs busy with 2,048: histograms 16 -> 4 us), beyond it
+// BIG_TILE in the flags and the partition, whose blocks add up to M / tile
+// counts each, and HCH in the histograms.
+constexpr int64_t SMALL_M = 1 << 20;
+constexpr int BIG_TILE = 1024;
+// Counters of a build: leaves, nodes, and from CN_ACTIVE on the active nodes
+// of every level.
+constexpr int MAX_LEVELS = 64;
+enum { CN_LEAVES = 0, CN_NODES = 1, CN_ACTIVE = 2, CN_COUNT = CN_ACTIVE + MAX_LEVELS + 1 };
 constexpr int HASH_SLOTS = 256;  // partial sums of the content hash
 
 // One element's share of the content hash of a build's inputs: a 64-bit
@@ -57,12 +71,21 @@ __global__ void k_elems(int64_t M, int n_hosts, const int32_t* __restrict__ off,
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     unsigned long long hv = 0;
     int hm = -1, um[3] = {0, 0, 0};
-    if (e < M) {
-        int lo = 0, hi = n_hosts - 1;  // host with off[h] <= e < off[h+1]
+    // host with off[h] <= e < off[h+1]: the block's first and last elements
+    // search among all hosts, the others between those two
+    __shared__ int hrange[2];
+    auto host_at = [&](int64_t at, int lo, int hi) {
         while (lo < hi) {
             const int mid = (lo + hi + 1) >> 1;
-            if (off[mid] <= e) lo = mid; else hi = mid - 1;
+            if (off[mid] <= at) lo = mid; else hi = mid - 1;
         }
+        return lo;
+    };
+    if (threadIdx.x < 2)
+        hrange[threadIdx.x] = host_at(min(((int64_t)blockIdx.x + threadIdx.x) * blockDim.x, M) - threadIdx.x, 0, n_hosts - 1);
+    __syncthreads();
+    if (e < M) {
+        const int lo = host_at(e, hrange[0], hrange[1]);
         const int h = lo;
         const int r = mem[off[h]];
         const int i = mem[e];
@@ -82,19 +105,31 @@ __global__ void k_elems(int64_t M, int n_hosts, const int32_t* __restrict__ off,
         um[2] = c;
     }
     if (hbox) {
-        // the host's extent: minima of u and of -u.  A wavefront inside one
-        // host reduces first; values only decrease, so a plain read that is
-        // already no larger makes the atomic unnecessary
-        const int h0 = __builtin_amdgcn_readfirstlane(hm);
-        const bool one = __ballot(hm == h0) == ~0ull;
+        // the host's extent: minima of u and of -u.  A block inside one host
+        // (its members are consecutive) reduces first; values only decrease,
+        // so a plain read that is already no larger makes the atomic
+        // unnecessary
+        __shared__ int ends[2], wmin[4][6];
+        if (threadIdx.x == 0) ends[0] = hm;
+        if (threadIdx.x == blockDim.x - 1) ends[1] = hm;
+        __syncthreads();
+        const bool one = ends[0] == ends[1];
         for (int k = 0; k < 6; ++k) {
             int v = k < 3 ? um[k] : -um[k - 3];
-            if (one)
+            if (one) {
                 for (int o = 32; o > 0; o >>= 1) v = min(v, __shfl_xor(v, o, 64));
-            if (hm >= 0 && (!one || (threadIdx.x & 63) == 0)) {
+                if ((threadIdx.x & 63) == 0) wmin[threadIdx.x >> 6][k] = v;
+            } else if (hm >= 0) {
                 int* at = hbox + 6 * (int64_t)hm + k;
                 if (v < *at) atomicMin(at, v);
             }
+        }
+        __syncthreads();
+        if (one && threadIdx.x < 6) {
+            const int k = threadIdx.x;
+            const int v = min(min(wmin[0][k], wmin[1][k]), min(wmin[2][k], wmin[3][k]));
+            int* at = hbox + 6 * (int64_t)hm + k;
+            if (v < *at) atomicMin(at, v);
         }
     }
     // every lane of the wavefront reaches the sum
@@ -136,10 +171,29 @@ __global__ void k_presort_keys(int64_t M, const int* __restrict__ u0, const int*
     val[e] = (uint32_t)e;
 }
 
-__global__ void k_roots(int n_hosts, const int32_t* __restrict__ off, const int* __restrict__ ncell, KdNode* nodes,
-                        int* active, int* counters, int* leaves, int* __restrict__ seg_node_unused) {
-    const int h = blockIdx.x * blockDim.x + threadIdx.x;
-    if (h >= n_hosts) return;
+// Positions and roots of the first level: every position's node is its host's
+// root (hosts keep their ranges in every list), the coordinates in list-0
+// order (c0 null: none) and zeros for the first histograms; a root's bounding
+// box, which is its region, is read off its sorted lists.
+__global__ void k_start(int64_t M, int n_hosts, const int32_t* __restrict__ off, const int* __restrict__ ncell,
+                        const int* __restrict__ host, const int* __restrict__ l0, const int* __restrict__ l1,
+                        const int* __restrict__ l2, const int* __restrict__ u0, const int* __restrict__ u1,
+                        const int* __restrict__ u2, KdNode* __restrict__ nodes, int* __restrict__ active,
+                        int* __restrict__ counters, int* __restrict__ leaves, int* __restrict__ leaf_min,
+                        int* __restrict__ seg_node, int* __restrict__ c0, int* __restrict__ c1, int* __restrict__ c2,
+                        uint32_t* __restrict__ hist, int64_t hist_words) {
+    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    for (int64_t k = p; k < hist_words; k += (int64_t)gridDim.x * blockDim.x) hist[k] = 0;
+    if (p >= M) return;
+    seg_node[p] = host[p];
+    if (c0) {
+        const int e = l0[p];
+        c0[p] = u0[e];
+        c1[p] = u1[e];
+        c2[p] = u2[e];
+    }
+    if (p >= n_hosts) return;
+    const int h = (int)p;
     KdNode nd;
     nd.host = h;
     nd.start = off[h];
@@ -148,59 +202,24 @@ __global__ void k_roots(int n_hosts, const int32_t* __restrict__ off, const int*
     nd.dim = -1;
     nd.t = 0;
     nd.left = nd.right = -1;
-    for (int d = 0; d < 3; ++d) nd.lo[d] = nd.hi[d] = nd.bmin[d] = nd.bmax[d] = 0;
-    nodes[h] = nd;
-    if (nd.end - nd.start > ncell[h]) {
-        active[atomicAdd(&counters[0], 1)] = h;
-        atomicAdd(&counters[4], nd.end - nd.start);
-    } else {
-        leaves[atomicAdd(&counters[2], 1)] = h;
-    }
-    (void)seg_node_unused;
-}
-
-// Between two levels: the next level's active-node and member counts become
-// the current ones, and the next ones restart from zero (counters[0] and
-// [4] are this level's, [1] and [5] the next level's).  One thread.
-__global__ void k_level_counters(int* counters, int roll, int clear) {
-    if (threadIdx.x != 0) return;
-    if (roll) {
-        counters[0] = counters[1];
-        counters[4] = counters[5];
-    }
-    if (clear) {
-        counters[1] = 0;
-        counters[5] = 0;
-    }
-}
-
-__global__ void k_seg_init(int64_t M, const int* __restrict__ host, int* __restrict__ seg_node) {
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p < M) seg_node[p] = host[p];  // hosts keep their ranges in every list
-}
-
-// Bounding box of every active node from the sorted lists; the root region is
-// its bounding box.
-__global__ void k_bbox(const int* __restrict__ nact, const int* __restrict__ active, KdNode* nodes,
-                       const int* __restrict__ l0, const int* __restrict__ l1, const int* __restrict__ l2,
-                       const int* __restrict__ u0, const int* __restrict__ u1, const int* __restrict__ u2,
-                       int n_hosts) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= *nact) return;
-    const int id = active[i];
-    KdNode& nd = nodes[id];
     const int s = nd.start, e = nd.end - 1;
-    nd.bmin[0] = u0[l0[s]]; nd.bmax[0] = u0[l0[e]];
-    nd.bmin[1] = u1[l1[s]]; nd.bmax[1] = u1[l1[e]];
-    nd.bmin[2] = u2[l2[s]]; nd.bmax[2] = u2[l2[e]];
-    nd.slot = i;
-    if (id < n_hosts)
-        for (int d = 0; d < 3; ++d) { nd.lo[d] = nd.bmin[d]; nd.hi[d] = nd.bmax[d]; }
+    nd.lo[0] = nd.bmin[0] = u0[l0[s]]; nd.hi[0] = nd.bmax[0] = u0[l0[e]];
+    nd.lo[1] = nd.bmin[1] = u1[l1[s]]; nd.hi[1] = nd.bmax[1] = u1[l1[e]];
+    nd.lo[2] = nd.bmin[2] = u2[l2[s]]; nd.hi[2] = nd.bmax[2] = u2[l2[e]];
+    if (nd.end - nd.start > ncell[h]) {
+        nd.slot = atomicAdd(&counters[CN_ACTIVE], 1);
+        active[nd.slot] = h;
+    } else {
+        leaves[atomicAdd(&counters[CN_LEAVES], 1)] = h;
+    }
+    nodes[h] = nd;
+    leaf_min[h] = 0x7FFFFFFF;
 }
 
 // Mass histograms (counts for uniform mass) of the active nodes, nb bins per
 // dimension spanning the members' extent.  A block whose positions all
-// belong to one node accumulates in LDS first.
+// belong to one node accumulates in LDS first.  The bin of a coordinate is
+// taken in 32 bits: a node spans less than 2^22 of them and nb <= 64.
 // The three coordinates carried in list-0 order (null when no histogram
 // needs them), permuted with list 0 at every level.
 struct CoordsL0 {
@@ -217,12 +236,12 @@ template <bool COUNTS>
 __global__ __launch_bounds__(KB) void k_hist(int64_t M, const int* __restrict__ seg_node, const KdNode* __restrict__ nodes,
                                              const int* __restrict__ l0, const int* __restrict__ c0,
                                              const int* __restrict__ c1, const int* __restrict__ c2,
-                                             const float* __restrict__ mass, int nb, uint32_t* __restrict__ hc,
-                                             double* __restrict__ hm) {
+                                             const float* __restrict__ mass, int nb, int hch,
+                                             uint32_t* __restrict__ hc, double* __restrict__ hm) {
     __shared__ uint32_t lc[COUNTS ? HK * 3 * 64 : 1];
     __shared__ double lm[COUNTS ? 1 : HK * 3 * 64];
-    const int64_t p0 = (int64_t)blockIdx.x * HCH;
-    const int64_t p1 = min(p0 + HCH, M);
+    const int64_t p0 = (int64_t)blockIdx.x * hch;
+    const int64_t p1 = min(p0 + hch, M);
     const KdNode& nf = nodes[seg_node[p0]];
     const KdNode& nl = nodes[seg_node[p1 - 1]];
     const bool af = nf.slot >= 0 && nf.dim < 0, al = nl.slot >= 0 && nl.dim < 0;
@@ -243,7 +262,7 @@ __global__ __launch_bounds__(KB) void k_hist(int64_t M, const int* __restrict__ 
         const double w = COUNTS ? 1.0 : (double)mass[l0[p]];
         for (int d = 0; d < 3; ++d) {
             if (nd.bmax[d] == nd.bmin[d]) continue;
-            const int bin = (int)(((int64_t)(u[d] - nd.bmin[d]) * nb) / ((int64_t)nd.bmax[d] - nd.bmin[d] + 1));
+            const int bin = (int)((uint32_t)(u[d] - nd.bmin[d]) * (uint32_t)nb / (uint32_t)(nd.bmax[d] - nd.bmin[d] + 1));
             if (local) {
                 if (COUNTS) atomicAdd(&lc[li * nb3 + d * nb + bin], 1u);
                 else atomicAdd(&lm[li * nb3 + d * nb + bin], w);
@@ -279,37 +298,35 @@ __global__ __launch_bounds__(256) void k_entropy(const int* __restrict__ nact, c
     const int lane = __lane_id();
     if (i >= *nact) return;
     const KdNode& nd = nodes[active[i]];
-    __shared__ double sh[4][64];
-    __shared__ double stot[4];
+    __shared__ double sh[4][3][65];
     const int w = threadIdx.x >> 6;
+    // totals and entropy sums run over the bins in order, as a serial loop
+    // would, one lane a dimension; the logarithms are spread over the lanes
+    double h[3];
     for (int d = 0; d < 3; ++d) {
-        const int64_t b0 = ((int64_t)i * 3 + d) * nb;
-        const double h = lane < nb ? (counts ? (double)hc[b0 + lane] : hm[b0 + lane]) : 0.0;
-        // totals and entropy sums run over the bins in order, as a serial
-        // loop would; only the logarithms are spread over the lanes
-        sh[w][lane] = h;
-        __builtin_amdgcn_wave_barrier();
-        if (lane == 0) {
-            double tot = 0.0;
-            for (int k = 0; k < nb; ++k) tot += sh[w][k];
-            stot[w] = tot;
-        }
-        __builtin_amdgcn_wave_barrier();
-        const double tot = stot[w];
+        const int64_t at = ((int64_t)i * 3 + d) * nb + lane;
+        h[d] = lane < nb ? (counts ? (double)hc[at] : hm[at]) : 0.0;
+        sh[w][d][lane] = h[d];
+    }
+    __builtin_amdgcn_wave_barrier();
+    double tot = 0.0;
+    if (lane < 3)
+        for (int k = 0; k < nb; ++k) tot += sh[w][lane][k];
+    __builtin_amdgcn_wave_barrier();
+    for (int d = 0; d < 3; ++d) {
+        const double td = __shfl(tot, d, 64);
         double term = 0.0;
-        if (h > 0) {
-            const double pk = h / tot;
+        if (h[d] > 0) {
+            const double pk = h[d] / td;
             term = -pk * log(pk);
         }
-        __builtin_amdgcn_wave_barrier();
-        sh[w][lane] = term;
-        __builtin_amdgcn_wave_barrier();
-        if (lane == 0) {
-            double sacc = 0.0;
-            for (int k = 0; k < nb; ++k) sacc += sh[w][k];
-            S[3 * (int64_t)i + d] = nd.bmax[d] == nd.bmin[d] ? 0.0 : sacc / log((double)nb);
-        }
-        __builtin_amdgcn_wave_barrier();
+        sh[w][d][lane] = term;
+    }
+    __builtin_amdgcn_wave_barrier();
+    if (lane < 3) {
+        double sacc = 0.0;
+        for (int k = 0; k < nb; ++k) sacc += sh[w][lane][k];
+        S[3 * (int64_t)i + lane] = nd.bmax[lane] == nd.bmin[lane] ? 0.0 : sacc / log((double)nb);
     }
 }
 
@@ -330,14 +347,16 @@ __device__ __forceinline__ int wave_reserve(int* counter, int n) {
     return base + x - n;
 }
 
-// Split decision of every active node and creation of its children.  All
-// lanes run to the end (the counters are reserved per wavefront).
+// Split decision of every active node and creation of its children (their
+// bounding boxes follow from the partition).  All lanes reserve (the counters
+// are reserved per wavefront).
 __global__ __launch_bounds__(256) void k_split(const int* nact, const int* __restrict__ active, KdNode* nodes,
                                                const int* __restrict__ l0, const int* __restrict__ l1,
                                                const int* __restrict__ l2, const int* __restrict__ u0,
                                                const int* __restrict__ u1, const int* __restrict__ u2, int mode,
                                                const double* __restrict__ Sdim, const int* __restrict__ ncell,
-                                               int* next_active, int* leaves, int* counters) {
+                                               int* next_active, int* leaves, int* __restrict__ leaf_min,
+                                               int* counters, int* nnext) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     const bool valid = i < *nact;
     const int id = valid ? active[i] : 0;
@@ -366,13 +385,9 @@ __global__ __launch_bounds__(256) void k_split(const int* nact, const int* __res
     const int n = split ? nd.end - nd.start : 0, nl = n / 2;
     const int nc = split ? ncell[nd.host] : 0;
     const bool lact = split && nl > nc, ract = split && n - nl > nc;
-    const int c0 = wave_reserve(&counters[3], split ? 2 : 0);
-    const int na0 = wave_reserve(&counters[1], (int)lact + (int)ract);
-    const int nl0 = wave_reserve(&counters[2], (int)stays + (split ? (int)!lact + (int)!ract : 0));
-    int grow = (lact ? nl : 0) + (ract ? n - nl : 0);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) grow += __shfl_xor(grow, o, 64);
-    if (__lane_id() == 0 && grow) atomicAdd(&counters[5], grow);
+    const int c0 = wave_reserve(&counters[CN_NODES], split ? 2 : 0);
+    const int na0 = wave_reserve(nnext, (int)lact + (int)ract);
+    const int nl0 = wave_reserve(&counters[CN_LEAVES], (int)stays + (split ? (int)!lact + (int)!ract : 0));
     if (stays) {
         nodes[id].slot = -1;
         leaves[nl0] = id;
@@ -386,7 +401,9 @@ __global__ __launch_bounds__(256) void k_split(const int* nact, const int* __res
     R.start = nd.start + nl;
     L.hi[best] = t - 1;
     R.lo[best] = t;
-    L.slot = R.slot = -1;
+    int ka = na0, kl = nl0;
+    L.slot = lact ? ka++ : -1;
+    R.slot = ract ? ka : -1;
     L.dim = R.dim = -1;
     L.left = L.right = R.left = R.right = -1;
     nodes[c0] = L;
@@ -395,9 +412,9 @@ __global__ __launch_bounds__(256) void k_split(const int* nact, const int* __res
     nodes[id].t = t;
     nodes[id].left = c0;
     nodes[id].right = c0 + 1;
-    int ka = na0, kl = nl0;
-    if (lact) next_active[ka++] = c0; else leaves[kl++] = c0;
-    if (ract) next_active[ka] = c0 + 1; else leaves[kl] = c0 + 1;
+    leaf_min[c0] = leaf_min[c0 + 1] = 0x7FFFFFFF;
+    if (lact) next_active[L.slot] = c0; else leaves[kl++] = c0;
+    if (ract) next_active[R.slot] = c0 + 1; else leaves[kl] = c0 + 1;
 }
 
 // The left flags of the three lists at once (list j at lf[j * M + p]).  A
@@ -405,98 +422,163 @@ __global__ __launch_bounds__(256) void k_split(const int* nact, const int* __res
 // which is ordered by (u_d, element): the list along d takes its flag from
 // the position, and an element of the other two lists goes left when its
 // (u_d, element) is below the median's (t, em), em = that list's entry at
-// rank nl.
-__global__ void k_lflag3(int64_t M, const int* __restrict__ seg_node, const KdNode* __restrict__ nodes,
-                         const int* __restrict__ l0, const int* __restrict__ l1, const int* __restrict__ l2,
-                         const int* __restrict__ u0, const int* __restrict__ u1, const int* __restrict__ u2,
-                         uint8_t* __restrict__ lf) {
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= M) return;
-    const KdNode& nd = nodes[seg_node[p]];
-    const int dim = nd.dim;
-    if (dim < 0) {
-        lf[p] = 0;
-        lf[M + p] = 0;
-        lf[2 * M + p] = 0;
-        return;
-    }
-    const int nl = (nd.end - nd.start) / 2;
-    const uint8_t own = (p - nd.start) < nl ? 1 : 0;
-    const int* ld = dim == 0 ? l0 : (dim == 1 ? l1 : l2);
-    const int* ud = dim == 0 ? u0 : (dim == 1 ? u1 : u2);
-    const int em = ld[nd.start + nl], t = nd.t;
-    auto left = [&](int e) -> uint8_t {
-        const int ue = ud[e];
-        return (ue < t || (ue == t && e < em)) ? 1 : 0;
-    };
-    lf[p] = dim == 0 ? own : left(l0[p]);
-    lf[M + p] = dim == 1 ? own : left(l1[p]);
-    lf[2 * M + p] = dim == 2 ? own : left(l2[p]);
-}
-
-// Stable partition of the three lists inside every split node (the scan
-// runs over the three flag arrays back to back; differences are taken
-// inside one list), then the position's node moves to its child.  The left
-// flags are read by list position (lf, list j at lf[j * M + p]), coalesced.
-__global__ void k_part3(int64_t M, int* __restrict__ seg_node, const KdNode* __restrict__ nodes,
-                        const int* __restrict__ l0, const int* __restrict__ l1, const int* __restrict__ l2,
-                        const uint8_t* __restrict__ lf, const uint32_t* __restrict__ scan, int* __restrict__ o0,
-                        int* __restrict__ o1, int* __restrict__ o2, CoordsL0 c) {
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= M) return;
-    const KdNode& nd = nodes[seg_node[p]];
-    const int e0 = l0[p], e1 = l1[p], e2 = l2[p];
-    if (nd.dim < 0) {
-        o0[p] = e0;
-        o1[p] = e1;
-        o2[p] = e2;
-        if (c.in[0]) {
-            for (int d = 0; d < 3; ++d) c.out[d][p] = c.in[d][p];
+// rank nl.  tail[j * tiles + tile]: the tile's left members of the node that
+// its last position is in.
+template <int NT>
+__global__ __launch_bounds__(NT) void k_lflag3(int64_t M, const int* __restrict__ seg_node,
+                                               const KdNode* __restrict__ nodes, const int* __restrict__ l0,
+                                               const int* __restrict__ l1, const int* __restrict__ l2,
+                                               const int* __restrict__ u0, const int* __restrict__ u1,
+                                               const int* __restrict__ u2, uint8_t* __restrict__ lf,
+                                               uint32_t* __restrict__ tail) {
+    __shared__ uint32_t cnt[NT / 64][3];
+    const int64_t p0 = (int64_t)blockIdx.x * NT, p = p0 + threadIdx.x;
+    const int last = seg_node[min(p0 + NT, M) - 1];
+    uint32_t f = 0;
+    int id = -1;
+    if (p < M) {
+        id = seg_node[p];
+        const KdNode& nd = nodes[id];
+        const int dim = nd.dim;
+        if (dim >= 0) {
+            const int nl = (nd.end - nd.start) / 2;
+            const uint32_t own = (p - nd.start) < nl ? 1 : 0;
+            const int* ld = dim == 0 ? l0 : (dim == 1 ? l1 : l2);
+            const int* ud = dim == 0 ? u0 : (dim == 1 ? u1 : u2);
+            // the two other lists, in order
+            const int ea = (dim == 0 ? l1 : l0)[p], eb = (dim == 2 ? l1 : l2)[p];
+            const int em = ld[nd.start + nl], t = nd.t;
+            const int ua = ud[ea], ub = ud[eb];
+            const uint32_t a = ua < t || (ua == t && ea < em) ? 1 : 0;
+            const uint32_t b = ub < t || (ub == t && eb < em) ? 1 : 0;
+            f = dim == 0 ? own | a << 1 | b << 2 : dim == 1 ? a | own << 1 | b << 2 : a | b << 1 | own << 2;
         }
-        return;
     }
-    const int s = nd.start, nl = (nd.end - nd.start) / 2;
-    const int e[3] = {e0, e1, e2};
-    int* out[3] = {o0, o1, o2};
 #pragma unroll
     for (int j = 0; j < 3; ++j) {
-        const int rl = (int)(scan[j * M + p] - scan[j * M + s]);  // left members before p in the node
-        const int np = lf[j * M + p] ? s + rl : s + nl + ((int)p - s - rl);
-        out[j][np] = e[j];
-        if (j == 0 && c.in[0]) {
-            for (int d = 0; d < 3; ++d) c.out[d][np] = c.in[d][p];
+        const uint32_t bit = (f >> j) & 1u;
+        if (p < M) lf[j * M + p] = (uint8_t)bit;
+        const uint64_t m = __ballot(bit && id == last);
+        if (__lane_id() == 0) cnt[threadIdx.x >> 6][j] = (uint32_t)__popcll(m);
+    }
+    __syncthreads();
+    if (threadIdx.x < 3) {
+        uint32_t s = 0;
+        for (int w = 0; w < NT / 64; ++w) s += cnt[w][threadIdx.x];
+        tail[(int64_t)threadIdx.x * gridDim.x + blockIdx.x] = s;
+    }
+}
+
+// Stable partition of the three lists inside every split node; the
+// position's node moves to its child, the entries that come to lie at a
+// child's ends give its bounding box, and the next level's histograms are
+// cleared.  A member's rank among its node's left members is the tile's own
+// prefix of flags, from the node's start where the node begins in the tile;
+// a node that began in an earlier tile is the last of every tile from there
+// on, so the tails of those tiles add up to what is missing.  (Scanned flags
+// took three more launches and 24 bytes a member and level: 1.42 ms against
+// 1.18 ms for the 15 levels of a 256^3 box.)
+template <int IT>
+__global__ __launch_bounds__(KB) void k_part3(int64_t M, int* __restrict__ seg_node, KdNode* __restrict__ nodes,
+                                              const int* __restrict__ l0, const int* __restrict__ l1,
+                                              const int* __restrict__ l2, const int* __restrict__ u0,
+                                              const int* __restrict__ u1, const int* __restrict__ u2,
+                                              const uint8_t* __restrict__ lf, const uint32_t* __restrict__ tail,
+                                              int* __restrict__ o0, int* __restrict__ o1, int* __restrict__ o2,
+                                              CoordsL0 c, uint32_t* __restrict__ hist, int64_t hist_words) {
+    constexpr int NW = KB / 64, CH = NW * IT;  // chunks of 64 positions
+    __shared__ uint16_t pre[3][KB * IT];
+    __shared__ uint32_t cc[3][CH];
+    __shared__ uint32_t before[NW][3];
+    const int tid = threadIdx.x, lane = __lane_id(), w = tid >> 6;
+    const int64_t tile = blockIdx.x, tiles = gridDim.x, p0 = tile * (KB * IT);
+    for (int64_t k = tile * KB + tid; k < hist_words; k += tiles * KB) hist[k] = 0;
+    const int* lists[3] = {l0, l1, l2};
+    const int* us[3] = {u0, u1, u2};
+    int* outs[3] = {o0, o1, o2};
+    // left members before the tile of the node that reaches into it
+    uint32_t b[3] = {0, 0, 0};
+    {
+        const KdNode& nd = nodes[seg_node[p0]];
+        if (nd.dim >= 0 && nd.start < p0)
+            for (int64_t k = nd.start / (KB * IT) + tid; k < tile; k += KB)
+                for (int j = 0; j < 3; ++j) b[j] += tail[j * tiles + k];
+    }
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+        for (int o = 32; o > 0; o >>= 1) b[j] += __shfl_xor(b[j], o, 64);
+        if (lane == 0) before[w][j] = b[j];
+    }
+    int node[IT], e[3][IT];
+    uint32_t f[IT];
+#pragma unroll
+    for (int k = 0; k < IT; ++k) {
+        const int64_t p = p0 + k * KB + tid;
+        const bool valid = p < M;
+        node[k] = valid ? seg_node[p] : -1;
+        f[k] = 0;
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            e[j][k] = valid ? lists[j][p] : 0;
+            f[k] |= valid && lf[j * M + p] ? 1u << j : 0u;
         }
     }
-    seg_node[p] = p < s + nl ? nd.left : nd.right;
-}
-
-// coordinates in list-0 order, for the histograms
-__global__ void k_coords_l0(int64_t M, const int* __restrict__ l0, const int* __restrict__ u0,
-                            const int* __restrict__ u1, const int* __restrict__ u2, int* __restrict__ c0,
-                            int* __restrict__ c1, int* __restrict__ c2) {
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= M) return;
-    const int e = l0[p];
-    c0[p] = u0[e];
-    c1[p] = u1[e];
-    c2[p] = u2[e];
-}
-
-__global__ void k_leaf_bbox(int nl, const int* __restrict__ leaves, KdNode* nodes, const int* __restrict__ l0,
-                            const int* __restrict__ l1, const int* __restrict__ l2, const int* __restrict__ u0,
-                            const int* __restrict__ u1, const int* __restrict__ u2, int* __restrict__ leaf_min,
-                            int n_hosts) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= nl) return;
-    const int id = leaves[i];
-    KdNode& nd = nodes[id];
-    const int s = nd.start, e = nd.end - 1;
-    nd.bmin[0] = u0[l0[s]]; nd.bmax[0] = u0[l0[e]];
-    nd.bmin[1] = u1[l1[s]]; nd.bmax[1] = u1[l1[e]];
-    nd.bmin[2] = u2[l2[s]]; nd.bmax[2] = u2[l2[e]];
-    if (id < n_hosts)  // a root that was never split: its region is its bounding box
-        for (int d = 0; d < 3; ++d) { nd.lo[d] = nd.bmin[d]; nd.hi[d] = nd.bmax[d]; }
-    leaf_min[id] = 0x7FFFFFFF;
+#pragma unroll
+    for (int k = 0; k < IT; ++k)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            const uint64_t m = __ballot((f[k] >> j) & 1u);
+            pre[j][k * KB + tid] = (uint16_t)__popcll(m & lanemask_lt());
+            if (lane == 0) cc[j][k * NW + w] = (uint32_t)__popcll(m);
+        }
+    __syncthreads();
+    if (w < 3) {
+        const uint32_t v = lane < CH ? cc[w][lane] : 0u;
+        uint32_t x = v;
+#pragma unroll
+        for (int o = 1; o < CH; o <<= 1) {
+            const uint32_t t = __shfl_up(x, o, 64);
+            if (lane >= o) x += t;
+        }
+        if (lane < CH) cc[w][lane] = x - v;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+        b[j] = 0;
+#pragma unroll
+        for (int k = 0; k < NW; ++k) b[j] += before[k][j];
+    }
+    // flags before position q of the tile
+    auto prefix = [&](int j, int q) { return cc[j][q >> 6] + (uint32_t)pre[j][q]; };
+#pragma unroll
+    for (int k = 0; k < IT; ++k) {
+        const int64_t p = p0 + k * KB + tid;
+        if (p >= M) continue;
+        const KdNode& nd = nodes[node[k]];
+        if (nd.dim < 0) {
+#pragma unroll
+            for (int j = 0; j < 3; ++j) outs[j][p] = e[j][k];
+            if (c.in[0])
+                for (int d = 0; d < 3; ++d) c.out[d][p] = c.in[d][p];
+            continue;
+        }
+        const int s = nd.start, end = nd.end, nl = (end - s) / 2, left = nd.left, right = nd.right;
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            const uint32_t at = prefix(j, k * KB + tid);
+            const int rl = (int)(s >= p0 ? at - prefix(j, (int)(s - p0)) : at + b[j]);
+            const int np = (f[k] >> j) & 1u ? s + rl : s + nl + ((int)p - s - rl);
+            outs[j][np] = e[j][k];
+            if (j == 0 && c.in[0])
+                for (int d = 0; d < 3; ++d) c.out[d][np] = c.in[d][p];
+            if (np == s) nodes[left].bmin[j] = us[j][e[j][k]];
+            if (np == s + nl - 1) nodes[left].bmax[j] = us[j][e[j][k]];
+            if (np == s + nl) nodes[right].bmin[j] = us[j][e[j][k]];
+            if (np == end - 1) nodes[right].bmax[j] = us[j][e[j][k]];
+        }
+        seg_node[p] = p < s + nl ? left : right;
+    }
 }
 
 // Members by position in list-0 order, and the smallest index of each leaf.
@@ -517,19 +599,17 @@ __global__ void k_final(int64_t M, const int* __restrict__ l0, const int* __rest
         F.eid[p] = e;
         if (m) F.mass[p] = m[e];
     }
-    // smallest particle index per leaf (wave-reduced when the wave is in one leaf)
-    const int key = valid ? seg_node[p] : 0;
-    const uint64_t act = __ballot(valid);
-    if (act == 0) return;
-    const int first = __ffsll((unsigned long long)act) - 1;
-    const int k0 = __shfl(key, first, 64);
-    if (__ballot(valid && key == k0) == act) {
-        int v = gi;
-        for (int o = 32; o > 0; o >>= 1) v = min(v, __shfl_xor(v, o, 64));
-        if ((int)__lane_id() == first) atomicMin(&leaf_min[k0], v);
-    } else if (valid) {
-        atomicMin(&leaf_min[key], gi);
+    // smallest particle index per leaf: leaves are runs of positions, so a
+    // minimum over each run of the wavefront, then one atomic a run
+    const int lane = __lane_id(), key = valid ? seg_node[p] : -1;
+    int v = gi;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int t = __shfl_up(v, o, 64), k = __shfl_up(key, o, 64);
+        if (lane >= o && k == key) v = min(v, t);
     }
+    const int next = __shfl_down(key, 1, 64);
+    if (valid && (lane == 63 || next != key)) atomicMin(&leaf_min[key], v);
 }
 
 }  // namespace
@@ -569,6 +649,8 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
     // (a third of the launches); with a workspace cap one after the other,
     // in a third of the room.
     const bool batch = M <= SORT_BATCH_MAX && ctx->max_ws == 0;
+    const bool small = M <= SMALL_M;
+    const int64_t tile = small ? KB : BIG_TILE, tiles = (M + tile - 1) / tile;
     // one workspace region holds every array of the build
     Carve cv;
     int *U[3], *G, *H, *L[3], *Lalt[3], *seg, *leaf_min, *act0, *act1, *leaves, *ncell_d, *counters, *hbox;
@@ -578,7 +660,7 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
     const int64_t HB = mode == KD_BUCKETS ? 6 * (int64_t)n_hosts : 1;
     float *Ms, *lim2;
     uint8_t* lf8;
-    uint32_t* lf;
+    uint32_t* tail;
     uint64_t* pkey;
     unsigned long long* hsh;
     KdNode* nodes;
@@ -594,7 +676,7 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
         for (int d = 0; d < 3; ++d) C0alt[d] = cv.add<int>(MC);
         seg = cv.add<int>(M);
         lf8 = cv.add<uint8_t>(3 * M);
-        lf = cv.add<uint32_t>(3 * M + 1);
+        tail = cv.add<uint32_t>(3 * tiles);
         pkey = cv.add<uint64_t>(batch ? 3 * M : M);
         nodes = cv.add<KdNode>(node_cap);
         act0 = cv.add<int>(node_cap);
@@ -607,9 +689,8 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
         F.mass = cv.add<float>(use_mass ? MF : 1);
         hbox = cv.add<int>(HB);
         lim2 = cv.add<float>(mode == KD_BUCKETS ? n_hosts : 1);
-        ncell_d = cv.add<int>(n_hosts);
-        counters = cv.add<int>(8);
-        hsh = cv.add<unsigned long long>(HASH_SLOTS + 1);  // and the wide-host flag
+        // one upload: content hash and wide-host flag, counters, cell sizes
+        hsh = cv.add<unsigned long long>(HASH_SLOTS + 1 + (CN_COUNT + n_hosts + 1) / 2);
     };
     layout();
     const size_t total = cv.bytes;
@@ -618,14 +699,18 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
     if (!cv.base) return VR_ERR_OUT_OF_MEMORY;
     layout();
     if (!use_mass) F.mass = nullptr;
-    // counters: 0 active nodes, 1 active next level, 2 leaves, 3 nodes, 4 members now, 5 members next
-    VR_HIP(ctx, hipMemcpyAsync(ncell_d, ncell.data(), n_hosts * sizeof(int), hipMemcpyHostToDevice, st));
-    int* init = reinterpret_cast<int*>(ctx->pinned);
-    for (int k = 0; k < 8; ++k) init[k] = 0;
-    init[3] = n_hosts;
-    VR_HIP(ctx, hipMemcpyAsync(counters, init, 8 * sizeof(int), hipMemcpyHostToDevice, st));
+    counters = reinterpret_cast<int*>(hsh + HASH_SLOTS + 1);
+    ncell_d = counters + CN_COUNT;
     {
-        int rc = fill_u32(ctx, reinterpret_cast<uint32_t*>(hsh), 0u, 2 * (HASH_SLOTS + 1), st);
+        const size_t nb = (HASH_SLOTS + 1) * sizeof(*hsh) + (CN_COUNT + (size_t)n_hosts) * sizeof(int);
+        char* up = static_cast<char*>(upload_begin(ctx, nb));
+        if (!up) return VR_ERR_HIP;
+        std::memset(up, 0, (HASH_SLOTS + 1) * sizeof(*hsh) + CN_COUNT * sizeof(int));
+        int* cn = reinterpret_cast<int*>(up + (HASH_SLOTS + 1) * sizeof(*hsh));
+        cn[CN_NODES] = n_hosts;
+        std::memcpy(cn + CN_COUNT, ncell.data(), (size_t)n_hosts * sizeof(int));
+        VR_HIP(ctx, hipMemcpyAsync(hsh, up, nb, hipMemcpyHostToDevice, st));
+        int rc = upload_end(ctx, st);
         if (rc) return rc;
         if (mode == KD_BUCKETS && (rc = fill_i32(ctx, hbox, INT_MAX, HB, st))) return rc;
     }
@@ -689,16 +774,6 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
             }
         }
     }
-    if (mode < KD_WIDEST) {
-        hipLaunchKernelGGL(k_coords_l0, dim3(grid_for(M, 256)), dim3(256), 0, st, M, Lin[0], U[0], U[1], U[2], C0[0],
-                           C0[1], C0[2]);
-        VR_LAUNCH_CHECK(ctx);
-    }
-    hipLaunchKernelGGL(k_roots, dim3(grid_for(n_hosts, 256)), dim3(256), 0, st, n_hosts, host_offsets, ncell_d, nodes,
-                       act0, counters, leaves, seg);
-    VR_LAUNCH_CHECK(ctx);
-    hipLaunchKernelGGL(k_seg_init, dim3(grid_for(M, 256)), dim3(256), 0, st, M, H, seg);
-    VR_LAUNCH_CHECK(ctx);
     int* cur = act0;
     int* nxt = act1;
     const unsigned gM = grid_for(M, 256);
@@ -742,61 +817,69 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
             if (na == 0) break;
             plan_na.push_back(na);
             plan_members.push_back(mem);
-            if (plan_na.size() > 64) return set_err(ctx, VR_ERR_NOT_CONVERGED, "KD build exceeded 64 levels");
+            if (plan_na.size() > MAX_LEVELS) return set_err(ctx, VR_ERR_NOT_CONVERGED, "KD build exceeded 64 levels");
         }
     }
+    // histograms and entropies of the widest level
+    uint32_t* hc = nullptr;
+    double *hm = nullptr, *Sdim = nullptr;
+    int64_t hwords = 0;  // 32-bit words a node
+    if (mode < KD_WIDEST && !plan_na.empty()) {
+        const int64_t na = *std::max_element(plan_na.begin(), plan_na.end());
+        hwords = 3 * nbins * (counts ? 1 : 2);
+        hc = static_cast<uint32_t*>(ws(ctx, WS_KD_HIST, na * hwords * sizeof(uint32_t)));
+        Sdim = static_cast<double*>(ws(ctx, WS_KD_S, (size_t)na * 3 * sizeof(double)));
+        if (!hc || !Sdim) return VR_ERR_OUT_OF_MEMORY;
+        hm = reinterpret_cast<double*>(hc);
+    }
+    const bool have_c0 = mode < KD_WIDEST;
+    hipLaunchKernelGGL(k_start, dim3(gM), dim3(256), 0, st, M, n_hosts, host_offsets, ncell_d, H, Lin[0], Lin[1], Lin[2],
+                       U[0], U[1], U[2], nodes, act0, counters, leaves, leaf_min, seg, have_c0 ? C0[0] : nullptr, C0[1],
+                       C0[2], hc, plan_na.empty() ? 0 : plan_na[0] * hwords);
+    VR_LAUNCH_CHECK(ctx);
+    const int hch = small ? KB : HCH;
     for (int level = 0; level < (int)plan_na.size(); ++level) {
-        int rc = VR_OK;
         const int na = (int)plan_na[level];
+        const int* nact = counters + CN_ACTIVE + level;
         hipEvent_t e0 = nullptr;
         if (ctx->timing) {
             e0 = timer_event(ctx);
             (void)hipEventRecord(e0, st);
         }
-        hipLaunchKernelGGL(k_level_counters, dim3(1), dim3(64), 0, st, counters, level > 0 ? 1 : 0, 1);
-        VR_LAUNCH_CHECK(ctx);
-        hipLaunchKernelGGL(k_bbox, dim3(grid_for(na, 256)), dim3(256), 0, st, counters, cur, nodes, Lin[0], Lin[1], Lin[2],
-                           U[0], U[1], U[2], n_hosts);
-        VR_LAUNCH_CHECK(ctx);
-        uint32_t* hc = nullptr;
-        double* hm = nullptr;
         if (mode < KD_WIDEST) {
-            const int64_t hn = (int64_t)na * 3 * nbins;
-            if (counts) {
-                hc = static_cast<uint32_t*>(ws(ctx, WS_KD_HIST, hn * sizeof(uint32_t)));
-                if (!hc) return VR_ERR_OUT_OF_MEMORY;
-                if ((rc = fill_u32(ctx, hc, 0u, hn, st))) return rc;
-                hipLaunchKernelGGL(k_hist<true>, dim3(grid_for(M, HCH)), dim3(KB), 0, st, M, seg, nodes, Lin[0], C0[0],
-                                   C0[1], C0[2], Ms, nbins, hc, hm);
-            } else {
-                hm = static_cast<double*>(ws(ctx, WS_KD_HIST, hn * sizeof(double)));
-                if (!hm) return VR_ERR_OUT_OF_MEMORY;
-                if ((rc = fill_u32(ctx, reinterpret_cast<uint32_t*>(hm), 0u, 2 * hn, st))) return rc;
-                hipLaunchKernelGGL(k_hist<false>, dim3(grid_for(M, HCH)), dim3(KB), 0, st, M, seg, nodes, Lin[0], C0[0],
-                                   C0[1], C0[2], Ms, nbins, hc, hm);
-            }
+            if (counts)
+                hipLaunchKernelGGL(k_hist<true>, dim3(grid_for(M, hch)), dim3(KB), 0, st, M, seg, nodes, Lin[0], C0[0],
+                                   C0[1], C0[2], Ms, nbins, hch, hc, hm);
+            else
+                hipLaunchKernelGGL(k_hist<false>, dim3(grid_for(M, hch)), dim3(KB), 0, st, M, seg, nodes, Lin[0], C0[0],
+                                   C0[1], C0[2], Ms, nbins, hch, hc, hm);
+            VR_LAUNCH_CHECK(ctx);
+            hipLaunchKernelGGL(k_entropy, dim3(grid_for((int64_t)na * 64, 256)), dim3(256), 0, st, nact, cur, nodes,
+                               nbins, counts, hc, hm, Sdim);
             VR_LAUNCH_CHECK(ctx);
         }
-        double* Sdim = nullptr;
-        if (mode < KD_WIDEST) {
-            Sdim = static_cast<double*>(ws(ctx, WS_KD_S, (size_t)na * 3 * sizeof(double)));
-            if (!Sdim) return VR_ERR_OUT_OF_MEMORY;
-            hipLaunchKernelGGL(k_entropy, dim3(grid_for((int64_t)na * 64, 256)), dim3(256), 0, st, counters, cur,
-                               nodes, nbins, counts, hc, hm, Sdim);
-            VR_LAUNCH_CHECK(ctx);
-        }
-        hipLaunchKernelGGL(k_split, dim3(grid_for(na, 256)), dim3(256), 0, st, counters, cur, nodes, Lin[0], Lin[1], Lin[2],
-                           U[0], U[1], U[2], mode, Sdim, ncell_d, nxt, leaves, counters);
+        hipLaunchKernelGGL(k_split, dim3(grid_for(na, 256)), dim3(256), 0, st, nact, cur, nodes, Lin[0], Lin[1], Lin[2],
+                           U[0], U[1], U[2], mode, Sdim, ncell_d, nxt, leaves, leaf_min, counters,
+                           counters + CN_ACTIVE + level + 1);
         VR_LAUNCH_CHECK(ctx);
-        hipLaunchKernelGGL(k_lflag3, dim3(gM), dim3(256), 0, st, M, seg, nodes, Lin[0], Lin[1], Lin[2], U[0], U[1], U[2],
-                           lf8);
-        VR_LAUNCH_CHECK(ctx);
-        if ((rc = scan_u8(ctx, lf8, lf, 3 * M, st))) return rc;
         CoordsL0 cl0{};
-        if (mode < KD_WIDEST) cl0 = CoordsL0{{C0[0], C0[1], C0[2]}, {C0alt[0], C0alt[1], C0alt[2]}};
-        hipLaunchKernelGGL(k_part3, dim3(gM), dim3(256), 0, st, M, seg, nodes, Lin[0], Lin[1], Lin[2], lf8, lf, Lout[0],
-                           Lout[1], Lout[2], cl0);
-        VR_LAUNCH_CHECK(ctx);
+        if (have_c0) cl0 = CoordsL0{{C0[0], C0[1], C0[2]}, {C0alt[0], C0alt[1], C0alt[2]}};
+        const int64_t hz = level + 1 < (int)plan_na.size() ? plan_na[level + 1] * hwords : 0;
+        // (flags: one position a thread; the partition, which has the tile's
+        // prefix to pass round: four.  Box of 256^3, 15 levels: 0.87 + 1.18 ms,
+        // the other way round 1.28 + 1.99 ms)
+        auto partition = [&](auto tile_t) {
+            constexpr int TILE = decltype(tile_t)::value;
+            hipLaunchKernelGGL(k_lflag3<TILE>, dim3((unsigned)tiles), dim3(TILE), 0, st, M, seg, nodes, Lin[0], Lin[1],
+                               Lin[2], U[0], U[1], U[2], lf8, tail);
+            VR_LAUNCH_CHECK(ctx);
+            hipLaunchKernelGGL(k_part3<TILE / KB>, dim3((unsigned)tiles), dim3(KB), 0, st, M, seg, nodes, Lin[0],
+                               Lin[1], Lin[2], U[0], U[1], U[2], lf8, tail, Lout[0], Lout[1], Lout[2], cl0, hc, hz);
+            VR_LAUNCH_CHECK(ctx);
+            return (int)VR_OK;
+        };
+        int rc = small ? partition(std::integral_constant<int, KB>{}) : partition(std::integral_constant<int, BIG_TILE>{});
+        if (rc) return rc;
         for (int j = 0; j < 3; ++j) {
             Lin[j] = Lout[j];
             std::swap(Lout[j], Lnext[j]);
@@ -819,18 +902,9 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
         tree.scratch = Lout[0];
         return VR_OK;
     }
-    if (!plan_na.empty()) {
-        hipLaunchKernelGGL(k_level_counters, dim3(1), dim3(64), 0, st, counters, 1, 0);
-        VR_LAUNCH_CHECK(ctx);
-    }
-    int c[8];
-    int rc = read_back(ctx, counters, c, sizeof c, st);
+    int nleaf = 0;
+    int rc = read_back(ctx, counters + CN_LEAVES, &nleaf, sizeof nleaf, st);
     if (rc) return rc;
-    const int nleaf = c[2];
-    hipLaunchKernelGGL(k_leaf_bbox, dim3(grid_for(nleaf, 256)), dim3(256), 0, st, nleaf, leaves, nodes, Lin[0], Lin[1],
-                       Lin[2], U[0], U[1], U[2], leaf_min, n_hosts);
-    VR_LAUNCH_CHECK(ctx);
-    const bool have_c0 = mode < KD_WIDEST;
     hipLaunchKernelGGL(k_final, dim3(gM), dim3(256), 0, st, M, Lin[0], seg, U[0], U[1], U[2], have_c0 ? C0[0] : nullptr,
                        have_c0 ? C0[1] : nullptr, have_c0 ? C0[2] : nullptr, G, use_mass ? Ms : nullptr, F, leaf_min);
     VR_LAUNCH_CHECK(ctx);

@@ -2,7 +2,7 @@
 one or four pairs a thread, small and large tiles whose counts the scatter adds
 up itself, and scanned counts; batched sorts of the three dimensions, with and
 without a workspace cap; scans in one workgroup, with and without their tile
-sums scanned.  Labels, group lists and cell numbers are exact."""
+sums scanned; partitions with tiles of 256 and of 1,024 positions.  Labels, group lists and cell numbers are exact."""
 import numpy as np
 import pytest
 
@@ -47,9 +47,9 @@ def test_labels_and_groups(ctx, vr, ref, n):
 
 
 @pytest.mark.parametrize("cap", [0, 1 << 32])
-@pytest.mark.parametrize("n", [1000, 1024, 1025, 4097, 131073, 524288, 524289])
+@pytest.mark.parametrize("n", [1000, 1024, 1025, 4097, 131073, 524288, 524289, 1048576, 1048577, 1050625])
 def test_member_lists(vr, ref, n, cap):
-    """One host of n members: three sorts of n keys each."""
+    """One host of n members: three sorts of n keys each, and its tree's levels."""
     c = vr.Context(0, cap)
     q, v = _clumps(n, n + 1)
     P = vr.Particles(dev_tensor(q.view(np.int32)), dev_tensor(v), None, 1.0, 1.0, BITS)
