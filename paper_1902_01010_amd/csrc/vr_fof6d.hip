@@ -121,20 +121,25 @@ __global__ void k_compact_part(int64_t n, const uint32_t* __restrict__ flag, con
     orig[k] = (int32_t)i;
 }
 
-// per sorted position: original particle index, velocity and host
+// per sorted position: original particle index and host, or (rec not null)
+// the index and the records (coordinates, host) and (velocity, 0)
 __global__ void k_sorted_attrs(int64_t np, const uint32_t* __restrict__ cidx, const int32_t* __restrict__ orig,
-                               const float* __restrict__ vx, const float* __restrict__ vy, const float* __restrict__ vz,
+                               const uint32_t* __restrict__ sx, const uint32_t* __restrict__ sy,
+                               const uint32_t* __restrict__ sz, const float* __restrict__ vx,
+                               const float* __restrict__ vy, const float* __restrict__ vz,
                                const int32_t* __restrict__ host_of, int32_t* __restrict__ sorig,
-                               float* __restrict__ svx, float* __restrict__ svy, float* __restrict__ svz,
-                               int32_t* __restrict__ shost) {
+                               int32_t* __restrict__ shost, int4* __restrict__ rec, float4* __restrict__ vel) {
     int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= np) return;
     const int32_t i = orig[cidx[p]];
     sorig[p] = i;
-    svx[p] = vx[i];
-    svy[p] = vy[i];
-    svz[p] = vz[i];
-    shost[p] = host_of[i];
+    const int h = host_of[i];
+    if (rec) {
+        rec[p] = make_int4((int)sx[p], (int)sy[p], (int)sz[p], h);
+        vel[p] = make_float4(vx[i], vy[i], vz[i], 0.f);
+    } else {
+        shost[p] = h;
+    }
 }
 
 // Velocity relative to the local mean velocity and its norm, per sorted
@@ -163,10 +168,8 @@ struct SubLink {
 // PAPER = false: Eq. fof6d; true: Eq. linkingcriteria (sub.* used, ellv not).
 template <bool HALF, bool PAPER>
 __global__ __launch_bounds__(256) void k_link6d(int64_t np, const ckey_t* __restrict__ key,
-                                                const uint32_t* __restrict__ sx, const uint32_t* __restrict__ sy,
-                                                const uint32_t* __restrict__ sz, const float* __restrict__ svx,
-                                                const float* __restrict__ svy, const float* __restrict__ svz,
-                                                const int32_t* __restrict__ shost, const double* __restrict__ ellv,
+                                                const int4* __restrict__ rec, const float4* __restrict__ vel,
+                                                const double* __restrict__ ellv,
                                                 const uint32_t* __restrict__ cell_start,
                                                 const ckey_t* __restrict__ hkeys, const uint32_t* __restrict__ hvals,
                                                 uint32_t hmask, int b, int gb, double ell2, int* parent,
@@ -176,9 +179,9 @@ __global__ __launch_bounds__(256) void k_link6d(int64_t np, const ckey_t* __rest
     const ckey_t k = key[p];
     const int nc = 1 << b;
     const int cx = (int)(k & (nc - 1)), cy = (int)((k >> b) & (nc - 1)), cz = (int)(k >> (2 * b));
-    const int px = (int)sx[p], py = (int)sy[p], pz = (int)sz[p];
-    const double vpx = (double)svx[p], vpy = (double)svy[p], vpz = (double)svz[p];
-    const int hp = shost[p];
+    const int4 P = rec[p];
+    const float4 VP = vel[p];
+    const int hp = P.w;
     const double ev = PAPER ? 1.0 : ellv[hp];
     const double ev2 = ev * ev;
     double up0 = 0, up1 = 0, up2 = 0, sp = 0;
@@ -223,12 +226,13 @@ __global__ __launch_bounds__(256) void k_link6d(int64_t np, const ckey_t* __rest
         uint32_t s = cell_start[c], e = cell_start[c + 1];
         if (((nk == k) || !HALF) && s <= (uint32_t)p) s = (uint32_t)p + 1;
         for (uint32_t q = s; q < e; ++q) {
-            const int ddx = min_image((int)sx[q] - px, gb);
-            const int ddy = min_image((int)sy[q] - py, gb);
-            const int ddz = min_image((int)sz[q] - pz, gb);
+            const int4 Q = rec[q];
+            const int ddx = min_image(Q.x - P.x, gb);
+            const int ddy = min_image(Q.y - P.y, gb);
+            const int ddz = min_image(Q.z - P.z, gb);
             const double d2 = (double)ddx * ddx + (double)ddy * ddy + (double)ddz * ddz;
             // d2 >= ell2 makes the rounded d2/ell2 >= 1 and so t >= 1: no link
-            if (d2 >= ell2 || shost[q] != hp) continue;
+            if (d2 >= ell2 || Q.w != hp) continue;
             if constexpr (PAPER) {
                 const double sq = sub.s[q];
                 if (!(sq > 0) || !(sp <= sub.Vr * sq && sq <= sub.Vr * sp)) continue;
@@ -236,7 +240,9 @@ __global__ __launch_bounds__(256) void k_link6d(int64_t np, const ckey_t* __rest
                 if (dot >= sub.cos_op * (sp * sq)) join((int)q);
                 continue;
             }
-            const double ax = vpx - (double)svx[q], ay = vpy - (double)svy[q], az = vpz - (double)svz[q];
+            const float4 VQ = vel[q];
+            const double ax = (double)VP.x - (double)VQ.x, ay = (double)VP.y - (double)VQ.y,
+                         az = (double)VP.z - (double)VQ.z;
             const double dv2 = ax * ax + ay * ay + az * az;
             const double ta = d2 * rl2 + dv2 * rv2;
             bool link = ta < 1.0 - 1e-9;
@@ -248,18 +254,31 @@ __global__ __launch_bounds__(256) void k_link6d(int64_t np, const ckey_t* __rest
 
 
 // ---- the linking sweep by tiles ---------------------------------------------
-// One wavefront per tile of (at most) 64 participants of one cell, lane =
-// participant p.  The own cell (candidates after p) and its 13 forward
-// neighbour cells are staged through LDS 64 candidates at a time --
-// coordinates, velocity, host, the paper linker's relative velocity, and the
-// candidate's union-find root as read at staging -- so each candidate is
-// fetched once per wavefront and read by all lanes from LDS.  An FP32
-// distance prefilter (coordinate differences are exact integers below 2^21,
-// the rounded square sum lies within 2e-7 of the exact one) passes every
-// candidate that may lie inside the linking length; those get the exact
-// integer d2 and the FP64 predicate of k_link6d.  A candidate's parent, read
-// at staging, is one of its ancestors: equal to p's root, the pair is already
-// joined and no further global access is needed.
+// Tiles of (at most) 64 participants of one cell, lane = participant p.  The
+// candidates -- the own cell after p, then its 13 forward neighbour cells --
+// come 64 at a time, a lane each, with coordinates relative to the cell's
+// corner (exact in FP32, so pairs need no periodic wrap), velocity, host and
+// the union-find root as read then; the next 64 are fetched while these are
+// tested.  A chunk goes row by row: a candidate, the same for all lanes, from
+// LDS; or the other way round, a participant against the lanes' candidates.
+// Most pairs of a dense cell are in one component R0 already, where a link
+// changes nothing: with R0 the root of most lanes, candidates with another
+// root are taken against all participants, and participants with another
+// root against all candidates.  Where that is no less than all of either
+// kind, the fewer are taken: cells of a few participants cost as many rows.  A pair passes an
+// FP32 test first (squared distance; for Eq. fof6d also the sum of both
+// terms): its terms are positive and rounded to a few 2^-24 each, so nothing
+// beyond the margins links.  The rest get the exact integer d2 and the FP64
+// predicate of k_link6d.
+//
+// Bound by the chains of root lookups and unions, with VALU issue a third of
+// it.  A tile of a heavy cell is split over the two wavefronts of a workgroup,
+// chunk by chunk: one wavefront left the densest cells' chains alone on the
+// device (100 k halo 349 us), four and eight found less merged when they
+// looked (500 k field 1.44 and 1.74 ms).  Six wavefronts a SIMD, 1.00 ms
+// against 1.10 ms without the bound.  All pairs of a tile, 64 rows a chunk,
+// before: 500 k particles linked in 6D 2.77 -> 1.00 ms, the outliers of a
+// 256^3 box 1.05 -> 0.50 ms, of a 100 k halo 964 -> 101 us, 12 k 195 -> 54 us.
 
 // tiles of 64 participants per cell
 // Tiles of cells with at least HEAVY_CELL participants (subhalo cores, whose
@@ -287,27 +306,30 @@ __global__ void k_tile_write(int64_t ncell, const uint32_t* __restrict__ cell_st
     for (uint32_t q = s; q < e; q += 64) tiles[t++] = make_int2((int)c, (int)q);
 }
 
+constexpr int L6_WAVES = 2;  // wavefronts a workgroup: for one heavy tile, or a light tile each
+
 template <bool PAPER>
-__global__ __launch_bounds__(64) void k_link6d_tile(const int2* __restrict__ tiles, const uint32_t* __restrict__ ntiles,
-                                                    const ckey_t* __restrict__ key, const uint32_t* __restrict__ sx,
-                                                    const uint32_t* __restrict__ sy, const uint32_t* __restrict__ sz,
-                                                    const float* __restrict__ svx, const float* __restrict__ svy,
-                                                    const float* __restrict__ svz, const int32_t* __restrict__ shost,
-                                                    const double* __restrict__ ellv,
-                                                    const uint32_t* __restrict__ cell_start,
-                                                    const ckey_t* __restrict__ hkeys, const uint32_t* __restrict__ hvals,
-                                                    uint32_t hmask, int b, int gb, double ell2, int* parent,
-                                                    unsigned xchunk, SubLink sub) {
-    __shared__ __align__(16) int cxs[64];
-    __shared__ __align__(16) int cys[64];
-    __shared__ __align__(16) int czs[64];
-    __shared__ __align__(16) int crt[64];
-    __shared__ int chs[64], cq[64];
-    __shared__ float cvx[64], cvy[64], cvz[64];
-    __shared__ double cu0[PAPER ? 64 : 1], cu1[PAPER ? 64 : 1], cu2[PAPER ? 64 : 1], cs_[PAPER ? 64 : 1];
-    const uint32_t t = xcd_swizzle(blockIdx.x, gridDim.x, xchunk);
+__global__ __launch_bounds__(64 * L6_WAVES, 6) void k_link6d_tile(
+    const int2* __restrict__ tiles, const uint32_t* __restrict__ ntiles, const uint32_t* __restrict__ nheavy,
+    const ckey_t* __restrict__ key, const int4* __restrict__ rec, const float4* __restrict__ vel,
+    const double* __restrict__ ellv, const uint32_t* __restrict__ cell_start, const ckey_t* __restrict__ hkeys,
+    const uint32_t* __restrict__ hvals, uint32_t hmask, int b, int gb, double ell2, int* parent, unsigned xchunk,
+    SubLink sub) {
+    __shared__ float4 spos[L6_WAVES][64];  // x, y, z; root (bits)
+    __shared__ float4 svel[L6_WAVES][64];  // velocity; host (bits)
+    __shared__ double4 su[L6_WAVES][PAPER ? 64 : 1];
+    const int lane = __lane_id(), w = threadIdx.x >> 6;
+    const uint32_t blk = xcd_swizzle(blockIdx.x, gridDim.x, xchunk), nh = nheavy[0];
+    uint32_t t = blk, slice = 0, nslice = 1;
+    if (blk < nh) {
+        slice = w;
+        nslice = L6_WAVES;
+    } else {
+        t = nh + (blk - nh) * L6_WAVES + w;
+    }
     if (t >= ntiles[0]) return;
-    const int lane = (int)threadIdx.x;
+    float4 *cpos = spos[w], *cvel = svel[w];
+    double4* cu = su[w];
     const int2 tl = tiles[t];
     const uint32_t q0 = (uint32_t)tl.y, cend = cell_start[tl.x + 1];
     const uint32_t p = q0 + (uint32_t)lane;
@@ -315,16 +337,16 @@ __global__ __launch_bounds__(64) void k_link6d_tile(const int2* __restrict__ til
     const ckey_t k = key[q0];
     const int nc = 1 << b;
     const int cx = (int)(k & (nc - 1)), cy = (int)((k >> b) & (nc - 1)), cz = (int)(k >> (2 * b));
-    // lane o < 14: the candidate range of segment o -- the 13 forward
-    // neighbour cells, then the own cell from the tile's first participant --
-    // all looked up at once
+    // lane o < 14: the candidate range of segment o -- the own cell from the
+    // tile's first participant, then the 13 forward neighbour cells -- all
+    // looked up at once
     uint32_t seg_s = 0, seg_n = 0;
     if (lane < 14) {
-        if (lane == 13) {
+        if (lane == 0) {
             seg_s = q0;
             seg_n = cend - q0;
         } else {
-            const int o = 14 + lane;  // forward offsets 14..26
+            const int o = 13 + lane;  // forward offsets 14..26
             const int dz = o / 9 - 1, dy = (o / 3) % 3 - 1, dx = o % 3 - 1;
             const uint32_t nx = (uint32_t)((cx + dx + nc) & (nc - 1));
             const uint32_t ny = (uint32_t)((cy + dy + nc) & (nc - 1));
@@ -343,135 +365,175 @@ __global__ __launch_bounds__(64) void k_link6d_tile(const int2* __restrict__ til
         const uint32_t v = __shfl_up(incl, o, 64);
         if (lane >= o) incl += v;
     }
-    const uint32_t total = __shfl(incl, 13, 64);
+    const uint32_t total = __shfl(incl, 13, 64), own = __shfl(incl, 0, 64);
     const uint32_t seg_b = incl - seg_n;  // first candidate number of this lane's segment
-    const uint32_t own_b = __shfl(seg_b, 13, 64);
+    if (64 * slice >= total) return;
 
-    const int px = valid ? (int)sx[p] : 0, py = valid ? (int)sy[p] : 0, pz = valid ? (int)sz[p] : 0;
-    const double vpx = valid ? (double)svx[p] : 0.0, vpy = valid ? (double)svy[p] : 0.0,
-                 vpz = valid ? (double)svz[p] : 0.0;
-    const int hp = valid ? shost[p] : -1;
+    // coordinates relative to the cell's corner: a neighbour's lie in
+    // [-1, 2) cells, and there are at least four of them in the box
+    const int sh = gb - b, ox = cx << sh, oy = cy << sh, oz = cz << sh;
+    const int4 P = valid ? rec[p] : make_int4(ox, oy, oz, -1);
+    const float4 VP = valid ? vel[p] : make_float4(0.f, 0.f, 0.f, 0.f);
+    const float px = (float)(P.x - ox), py = (float)(P.y - oy), pz = (float)(P.z - oz);
+    const int hp = P.w;
     const double ev = (PAPER || !valid) ? 1.0 : ellv[hp];
     const double ev2 = ev * ev;
-    double up0 = 0, up1 = 0, up2 = 0, sp = 0;
+    double4 up = make_double4(0, 0, 0, 0);
     if constexpr (PAPER) {
-        if (valid) {
-            up0 = sub.u0[p];
-            up1 = sub.u1[p];
-            up2 = sub.u2[p];
-            sp = sub.s[p];
-        }
-        if (!(sp > 0)) valid = false;  // no direction: links nothing
+        if (valid) up = make_double4(sub.u0[p], sub.u1[p], sub.u2[p], sub.s[p]);
+        if (!(up.w > 0)) valid = false;  // no direction: links nothing
     }
     const double rl2 = 1.0 / ell2, rv2 = 1.0 / ev2;
     // no candidate with an FP32 square sum above this lies within ell
     const float ellf = (float)(ell2 * (1.0 + 1e-6)) + 1.0f;
+    // FP32 terms of t; a scale of dv2 that is no ordinary number tests nothing
+    const float rlf = (float)rl2, rvf = rv2 > 1e-30 && rv2 < 1e30 ? (float)rv2 : 0.f;
+    constexpr float TF = 1.00001f;
+    // Eq. fof6d in FP64: t = d2/ell2 + dv2/ev2 is formed with reciprocals
+    // first; only t within 1e-9 of 1 needs the divided form
+    auto linked = [&](float dx, float dy, float dz, float4 a, float4 c, double qv2, double qr2) {
+        const double d2 = (double)dx * dx + (double)dy * dy + (double)dz * dz;
+        if (d2 >= ell2) return false;
+        const double ax = (double)a.x - (double)c.x, ay = (double)a.y - (double)c.y, az = (double)a.z - (double)c.z;
+        const double dv2 = ax * ax + ay * ay + az * az;
+        const double ta = d2 * rl2 + dv2 * qr2;
+        return ta < 1.0 - 1e-9 || (ta <= 1.0 + 1e-9 && d2 / ell2 + dv2 / qv2 < 1.0);
+    };
+    // Eq. linkingcriteria, a having a direction
+    auto sub_linked = [&](float dx, float dy, float dz, double4 a, double4 c) {
+        const double d2 = (double)dx * dx + (double)dy * dy + (double)dz * dz;
+        return d2 < ell2 && c.w > 0 && a.w <= sub.Vr * c.w && c.w <= sub.Vr * a.w &&
+               a.x * c.x + a.y * c.y + a.z * c.z >= sub.cos_op * (a.w * c.w);
+    };
     int rp = valid ? uf_find(parent, (int)p) : -1;
-    // Near the box faces a forward neighbour can sit across the periodic
-    // boundary; elsewhere the plain coordinate differences are the minimum
-    // images (cells span far less than half the box).
-    const int ncm = nc - 1;
-    const bool wrap = cx == 0 || cx == ncm || cy == 0 || cy == ncm || cz == ncm;
-    for (uint32_t c0 = 0; c0 < total; c0 += 64) {
-        const uint32_t c = c0 + (uint32_t)lane;
-        // the segment holding candidate c: the last lane o < 14 whose first
-        // candidate number is <= c (empty segments share numbers); every lane
-        // takes part in the shuffles, lanes past the end load nothing
+    auto join = [&](int q) __attribute__((always_inline)) {
+        const int rq = uf_find(parent, q);
+        if (rq == rp) return;
+        rp = uf_find(parent, rp);
+        if (rp != rq) uf_union(parent, rp, rq);
+    };
+    // candidate c of the tile: the segment holding it is the last lane o < 14
+    // whose first candidate number is <= c (empty segments share numbers);
+    // every lane takes part in the shuffles
+    auto position = [&](uint32_t c) {
         int sg = 0;
 #pragma unroll
         for (int o = 1; o < 14; ++o) {
             const uint32_t bo = __shfl(seg_b, o, 64);
             if (bo <= c) sg = o;
         }
-        const uint32_t q = __shfl(seg_s, sg, 64) + (c - __shfl(seg_b, sg, 64));
+        return __shfl(seg_s, sg, 64) + (c - __shfl(seg_b, sg, 64));
+    };
+    uint32_t q = position(64 * slice + lane);
+    int4 Q = make_int4(0, 0, 0, -1);
+    float4 V = make_float4(0.f, 0.f, 0.f, 0.f);
+    double4 uq = make_double4(0, 0, 0, 0);
+    int qpar = -1;
+    auto fetch = [&](uint32_t c) {
+        if (c >= total) return;
+        Q = rec[q];
+        V = vel[q];
+        qpar = parent[q];
+        if constexpr (PAPER) uq = make_double4(sub.u0[q], sub.u1[q], sub.u2[q], sub.s[q]);
+    };
+    fetch(64 * slice + lane);
+    for (uint32_t c0 = 64 * slice; c0 < total; c0 += 64 * nslice) {
+        const bool cand = c0 + (uint32_t)lane < total;
+        const int qi = (int)q;
+        const float fx = (float)min_image(Q.x - ox, gb), fy = (float)min_image(Q.y - oy, gb),
+                    fz = (float)min_image(Q.z - oz, gb);
+        const float4 CV = make_float4(V.x, V.y, V.z, __int_as_float(Q.w));
+        int root = cand ? uf_find(parent, qpar) : -1;
+        rp = valid ? uf_find(parent, rp) : -1;  // as fresh as the candidates' roots
         __builtin_amdgcn_wave_barrier();
-        if (c < total) {
-            cq[lane] = (int)q;
-            cxs[lane] = (int)sx[q];
-            cys[lane] = (int)sy[q];
-            czs[lane] = (int)sz[q];
-            chs[lane] = shost[q];
-            cvx[lane] = svx[q];
-            cvy[lane] = svy[q];
-            cvz[lane] = svz[q];
-            // q's root as of staging (one find per candidate and chunk, all
-            // lanes at once): once a core has merged, a linked pair then
-            // matches the participant's root without a find of its own
-            crt[lane] = uf_find(parent, (int)q);
-            if constexpr (PAPER) {
-                cu0[lane] = sub.u0[q];
-                cu1[lane] = sub.u1[q];
-                cu2[lane] = sub.u2[q];
-                cs_[lane] = sub.s[q];
+        cpos[lane] = make_float4(fx, fy, fz, __int_as_float(root));
+        cvel[lane] = CV;
+        if constexpr (PAPER) cu[lane] = uq;
+        __builtin_amdgcn_wave_barrier();
+        q = position(c0 + 64 * nslice + lane);
+        fetch(c0 + 64 * nslice + lane);
+        const uint64_t vmask = __ballot(valid);
+        if (vmask == 0) return;
+        // the root of most lanes, guessed from two of them
+        int R0 = __builtin_amdgcn_readlane(rp, __builtin_ctzll(vmask));
+        uint64_t in0 = __ballot(valid && rp == R0);
+        if (2 * __popcll(in0) < __popcll(vmask)) {
+            const int R1 = __builtin_amdgcn_readlane(rp, __builtin_ctzll(vmask & ~in0));
+            const uint64_t in1 = __ballot(valid && rp == R1);
+            if (__popcll(in1) > __popcll(in0)) {
+                R0 = R1;
+                in0 = in1;
             }
         }
-        __builtin_amdgcn_wave_barrier();
-        const int m = (int)min(64u, total - c0);
-        if (!valid) continue;
-        rp = uf_find(parent, rp);  // as fresh as the staged roots
-        // pass 1, no divergence: a bit per staged candidate whose FP32
-        // squared distance may lie within ell (differences are exact
-        // integers below 2^22; the rounded sum is within 2e-7 of the exact
-        // one, which ellf covers) and whose staged root is not the lane's
-        // (a link inside one component changes nothing); pass 2 takes the
-        // marked ones exactly
-        uint32_t tk[2] = {0u, 0u};
-#pragma unroll
-        for (int b4 = 0; b4 < 16; ++b4) {
-            if (4 * b4 < m) {
-                const int4 X = *reinterpret_cast<const int4*>(&cxs[4 * b4]);
-                const int4 Y = *reinterpret_cast<const int4*>(&cys[4 * b4]);
-                const int4 Z = *reinterpret_cast<const int4*>(&czs[4 * b4]);
-                const int4 RT = *reinterpret_cast<const int4*>(&crt[4 * b4]);
-                const int xs[4] = {X.x, X.y, X.z, X.w}, ys[4] = {Y.x, Y.y, Y.z, Y.w}, zs[4] = {Z.x, Z.y, Z.z, Z.w};
-                const int rts[4] = {RT.x, RT.y, RT.z, RT.w};
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    int dx = xs[u] - px, dy = ys[u] - py, dz = zs[u] - pz;
-                    if (wrap) {
-                        dx = min_image(dx, gb);
-                        dy = min_image(dy, gb);
-                        dz = min_image(dz, gb);
-                    }
-                    const float fx = (float)dx, fy = (float)dy, fz = (float)dz;
-                    const int bit = 4 * b4 + u;
-                    if (fmaf(fx, fx, fmaf(fy, fy, fz * fz)) <= ellf && rts[u] != rp) tk[bit >> 5] |= 1u << (bit & 31);
-                }
-            }
+        // rows: candidates taken against the lanes' participants; cols:
+        // participants taken against the lanes' candidates
+        uint64_t rows = __ballot(cand && root != R0), cols = vmask & ~in0;
+        const uint64_t all = __ballot(cand);
+        const int ncand = __popcll(all), nval = __popcll(vmask);
+        if (__popcll(rows) + __popcll(cols) >= min(ncand, nval)) {
+            rows = ncand <= nval ? all : 0;
+            cols = ncand <= nval ? 0 : vmask;
         }
-        uint64_t take = ((uint64_t)tk[1] << 32) | tk[0];
-        if (m < 64) take &= (uint64_t(1) << m) - 1;
-        while (take) {
-            const int j = __builtin_ctzll(take);
-            take &= take - 1;
-            const int qq = cq[j];
+        float4 next = rows ? cpos[__builtin_ctzll(rows)] : make_float4(0.f, 0.f, 0.f, 0.f);
+        while (rows) {
+            const int j = __builtin_ctzll(rows);
+            rows &= rows - 1;
+            const float4 C = next;
+            if (rows) next = cpos[__builtin_ctzll(rows)];
+            const float dx = C.x - px, dy = C.y - py, dz = C.z - pz;
+            const float d2f = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
             // own cell: only the candidates after p
-            if (c0 + (uint32_t)j >= own_b && (uint32_t)qq <= p) continue;
-            if (chs[j] != hp) continue;
-            const int ddx = min_image(cxs[j] - px, gb);
-            const int ddy = min_image(cys[j] - py, gb);
-            const int ddz = min_image(czs[j] - pz, gb);
-            const double d2 = (double)ddx * ddx + (double)ddy * ddy + (double)ddz * ddz;
-            if (d2 >= ell2) continue;
-            bool link;
+            const bool later = c0 + (uint32_t)j >= own || c0 + (uint32_t)j > (uint32_t)lane;
+            bool near = valid && later && d2f <= ellf && __float_as_int(C.w) != rp;
+            if (!__any(near)) continue;
+            const float4 W = cvel[j];
             if constexpr (PAPER) {
-                const double sq = cs_[j];
-                if (!(sq > 0) || !(sp <= sub.Vr * sq && sq <= sub.Vr * sp)) continue;
-                const double dot = up0 * cu0[j] + up1 * cu1[j] + up2 * cu2[j];
-                link = dot >= sub.cos_op * (sp * sq);
+                near = near && __float_as_int(W.w) == hp;
+                if (near) near = sub_linked(dx, dy, dz, up, cu[j]);
             } else {
-                const double ax = vpx - (double)cvx[j], ay = vpy - (double)cvy[j], az = vpz - (double)cvz[j];
-                const double dv2 = ax * ax + ay * ay + az * az;
-                const double ta = d2 * rl2 + dv2 * rv2;
-                link = ta < 1.0 - 1e-9;
-                if (!link && ta <= 1.0 + 1e-9) link = d2 / ell2 + dv2 / ev2 < 1.0;
+                const float ax = VP.x - W.x, ay = VP.y - W.y, az = VP.z - W.z;
+                const float tf = fmaf(fmaf(ax, ax, fmaf(ay, ay, az * az)), rvf, d2f * rlf);
+                near = near && __float_as_int(W.w) == hp && !(tf > TF);
+                if (near) near = linked(dx, dy, dz, VP, W, ev2, rv2);
             }
-            if (!link || crt[j] == rp) continue;
-            const int rq = uf_find(parent, qq);
-            if (rq == rp) continue;
-            rp = uf_find(parent, rp);
-            if (rp != rq) uf_union(parent, rp, rq);
-            rp = uf_find(parent, rp);
+            if (!__any(near)) continue;
+            const int qj = __builtin_amdgcn_readlane(qi, j);
+            if (near) join(qj);
+            // what the joins changed, for the rows to come
+            if (cand) root = uf_find(parent, root);
+            if (valid) rp = uf_find(parent, rp);
+            __builtin_amdgcn_wave_barrier();
+            cpos[lane].w = __int_as_float(root);
+            __builtin_amdgcn_wave_barrier();
+        }
+        while (cols) {
+            const int j = __builtin_ctzll(cols);
+            cols &= cols - 1;
+            auto of = [&](float v) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), j)); };
+            const int rj = __builtin_amdgcn_readlane(rp, j);
+            const float dx = fx - of(px), dy = fy - of(py), dz = fz - of(pz);
+            const float d2f = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+            const bool later = c0 + (uint32_t)lane >= own || c0 + (uint32_t)lane > (uint32_t)j;
+            bool near = cand && later && d2f <= ellf && root != rj &&
+                        __float_as_int(CV.w) == __builtin_amdgcn_readlane(hp, j);
+            if (!__any(near)) continue;
+            if constexpr (PAPER) {
+                const double4 u = make_double4(__shfl(up.x, j, 64), __shfl(up.y, j, 64), __shfl(up.z, j, 64),
+                                               __shfl(up.w, j, 64));
+                if (near) near = sub_linked(dx, dy, dz, u, cu[lane]);
+            } else {
+                const float4 W = make_float4(of(VP.x), of(VP.y), of(VP.z), 0.f);
+                const float ax = W.x - CV.x, ay = W.y - CV.y, az = W.z - CV.z;
+                const float tf = fmaf(fmaf(ax, ax, fmaf(ay, ay, az * az)), of(rvf), d2f * rlf);
+                near = near && !(tf > TF);
+                if (!__any(near)) continue;
+                const double ev2j = __shfl(ev2, j, 64), rv2j = __shfl(rv2, j, 64);
+                if (near) near = linked(dx, dy, dz, W, CV, ev2j, rv2j);
+            }
+            if (!__any(near)) continue;
+            if (near) uf_union(parent, rj, root);
+            if (cand) root = uf_find(parent, root);
+            if (valid) rp = uf_find(parent, rp);
         }
     }
 }
@@ -789,14 +851,12 @@ int link_outliers(vr_ctx* ctx, const vr_particles* p, const int32_t* host_of, co
     rc = build_cell_list(ctx, np, cx, cy, cz, gb, s, cl, st);
     if (rc) return rc;
     VR_WS(sorig, ctx, int32_t, WS_C6, np);
-    VR_WS(svx, ctx, float, WS_C7, np);
-    VR_WS(svy, ctx, float, WS_C8, np);
-    VR_WS(svz, ctx, float, WS_D0, np);
-    VR_WS(shost, ctx, int32_t, WS_D1, np);
+    VR_WS(rec, ctx, int4, WS_C7, np);
+    VR_WS(vel, ctx, float4, WS_C8, np);
     VR_WS(parent, ctx, int, WS_D2, np);
     VR_WS(mn, ctx, int, WS_D3, np);
-    hipLaunchKernelGGL(k_sorted_attrs, dim3(grid_for(np, 256)), dim3(256), 0, st, np, cl.idx, orig, p->vx, p->vy,
-                       p->vz, host_of, sorig, svx, svy, svz, shost);
+    hipLaunchKernelGGL(k_sorted_attrs, dim3(grid_for(np, 256)), dim3(256), 0, st, np, cl.idx, orig, cl.sx, cl.sy, cl.sz,
+                       p->vx, p->vy, p->vz, host_of, sorig, nullptr, rec, vel);
     VR_LAUNCH_CHECK(ctx);
     hipLaunchKernelGGL(k_iota_i, dim3(grid_for(np, 256)), dim3(256), 0, st, np, parent);
     VR_LAUNCH_CHECK(ctx);
@@ -816,13 +876,15 @@ int link_outliers(vr_ctx* ctx, const vr_particles* p, const int32_t* host_of, co
     const dim3 g(grid_for(np, 256));
 #define VR_LINK6D(HALF, PAPER)                                                                                    \
     VR_TIMED(ctx, sub ? "fof_link_sub" : "fof_link6d", st, np,                                                  \
-             hipLaunchKernelGGL((k_link6d<HALF, PAPER>), g, dim3(256), 0, st, np, cl.key, cl.sx, cl.sy, cl.sz, svx, \
-                                svy, svz, shost, ellv_host, cl.cell_start, cl.hkeys, cl.hvals, cl.hmask, b, gb, ell2, \
+             hipLaunchKernelGGL((k_link6d<HALF, PAPER>), g, dim3(256), 0, st, np, cl.key, rec, vel, ellv_host,      \
+                                cl.cell_start, cl.hkeys, cl.hvals, cl.hmask, b, gb, ell2, \
                                 parent, xc, sl))
     if ((1 << b) >= 4) {
         // tiles of 64 participants per cell: at most ncell + np / 64 of them
         const int64_t ncell = cl.n_cells;
         const int64_t tmax = ncell + (np + 63) / 64;
+        // a heavy cell of m participants has at most m / 32 tiles
+        const int64_t tgrid = np / (HEAVY_CELL / 2) + ncell / L6_WAVES + 1;
         VR_WS(tcnt, ctx, uint32_t, WS_D8, 2 * ncell + 1);
         VR_WS(ttot, ctx, uint32_t, WS_D9, 4);
         VR_WS(tiles, ctx, int2, WS_B7, tmax);
@@ -833,9 +895,9 @@ int link_outliers(vr_ctx* ctx, const vr_particles* p, const int32_t* host_of, co
         VR_LAUNCH_CHECK(ctx);
 #define VR_LINK6T(PAPER)                                                                                           \
         VR_TIMED(ctx, sub ? "fof_link_sub" : "fof_link6d", st, np,                                               \
-                 hipLaunchKernelGGL((k_link6d_tile<PAPER>), dim3((unsigned)tmax), dim3(64), 0, st, tiles, ttot, cl.key, \
-                                    cl.sx, cl.sy, cl.sz, svx, svy, svz, shost, ellv_host, cl.cell_start, cl.hkeys,   \
-                                    cl.hvals, cl.hmask, b, gb, ell2, parent, xc, sl))
+                 hipLaunchKernelGGL((k_link6d_tile<PAPER>), dim3((unsigned)tgrid), dim3(64 * L6_WAVES), 0, st, tiles, ttot,  \
+                                    tcnt + ncell, cl.key, rec, vel, ellv_host, cl.cell_start, cl.hkeys, cl.hvals, \
+                                    cl.hmask, b, gb, ell2, parent, xc, sl))
         if (sub) VR_LINK6T(true); else VR_LINK6T(false);
 #undef VR_LINK6T
     } else {
@@ -932,9 +994,6 @@ extern "C" int vr_sub_grow(vr_ctx* ctx, const vr_particles* p, const int32_t* ho
     CellList cl;
     if ((rc = build_cell_list(ctx, np, cx, cy, cz, gb, sb, cl, st))) return rc;
     VR_WS(sorig, ctx, int32_t, WS_C6, np);
-    VR_WS(svx, ctx, float, WS_C7, np);
-    VR_WS(svy, ctx, float, WS_C8, np);
-    VR_WS(svz, ctx, float, WS_D0, np);
     VR_WS(shost, ctx, int32_t, WS_D1, np);
     VR_WS(tagA, ctx, int32_t, WS_D2, np);
     VR_WS(tagB, ctx, int32_t, WS_D3, np);
@@ -942,8 +1001,8 @@ extern "C" int vr_sub_grow(vr_ctx* ctx, const vr_particles* p, const int32_t* ho
     VR_WS(su1, ctx, double, WS_D5, np);
     VR_WS(su2, ctx, double, WS_D6, np);
     VR_WS(ss, ctx, double, WS_D7, np);
-    hipLaunchKernelGGL(k_sorted_attrs, dim3(grid_for(np, 256)), dim3(256), 0, st, np, cl.idx, orig, p->vx, p->vy,
-                       p->vz, host_of, sorig, svx, svy, svz, shost);
+    hipLaunchKernelGGL(k_sorted_attrs, dim3(grid_for(np, 256)), dim3(256), 0, st, np, cl.idx, orig, cl.sx, cl.sy, cl.sz,
+                       p->vx, p->vy, p->vz, host_of, sorig, shost, nullptr, nullptr);
     hipLaunchKernelGGL(k_sorted_u, dim3(grid_for(np, 256)), dim3(256), 0, st, np, n, sorig, p->vx, p->vy, p->vz, vbar,
                        su0, su1, su2, ss);
     hipLaunchKernelGGL(k_first_tags, dim3(grid_for(np, 256)), dim3(256), 0, st, np, sorig, label1, size, n_min, tagA);
