@@ -368,7 +368,7 @@ constexpr int VMAX = 256;  // leaves one wavefront may visit for one host
 // query were 3% slower on the box: a leaf visit's fixed cost falls on half
 // the queries.
 template <int LPQ, int KL, int L>
-__global__ __launch_bounds__(64, 4) void k_knn(const uint32_t* __restrict__ qpos, int64_t nq, Slots T,
+__global__ __launch_bounds__(64, 4) void k_knn(const uint32_t* __restrict__ qpos, int64_t q0, int64_t nq, Slots T,
                                             const float4* __restrict__ V, const double* __restrict__ FB,
                                             const int32_t* __restrict__ host_off, int n_se, int n_v, int use_mass,
                                             double mass_value, double mass_sum, float* __restrict__ R,
@@ -382,7 +382,7 @@ __global__ __launch_bounds__(64, 4) void k_knn(const uint32_t* __restrict__ qpos
     __shared__ uint16_t lst[CAPL][64];
     __shared__ int nbr[W][KL * LPQ];
     const int lane = threadIdx.x, sub = lane & (LPQ - 1), q = lane / LPQ;
-    const int64_t qi = (int64_t)xcd_swizzle(blockIdx.x, gridDim.x, xchunk) * W + q;
+    const int64_t qi = q0 + (int64_t)xcd_swizzle(blockIdx.x, gridDim.x, xchunk) * W + q;
     int slot = 0;
     bool active = qi < nq;
     if (active) slot = qpos ? (int)qpos[qi] : (int)(qi & ~(int64_t)(LEAF - 1)) + leaf_slot((int)qi & (LEAF - 1), LOG2);
@@ -869,10 +869,14 @@ int launch_knn(vr_ctx* ctx, const uint32_t* qpos, int64_t nq, int64_t n_queries,
     const int use_mass = p->mass ? 1 : 0;
     double mass_sum = 0.0;  // of n_se equal masses, added one by one
     for (int k = 0; k < n_se; ++k) mass_sum += p->mass_value;
+    // a launch holds fewer than 2^32 threads, LPQ of them a query
+    constexpr int64_t QMAX = int64_t(1) << 26;
     VR_TIMED(ctx, "knn", st, n_queries,
-             hipLaunchKernelGGL((k_knn<LPQ, KL, L>), dim3(grid_for(nq, 64 / LPQ)), dim3(64), 0, st, qpos, nq, T, V, FB,
-                                host_off, n_se, n_v, use_mass, p->mass_value, mass_sum, R,
-                                (unsigned)ctx->xcd_chunk, flagged, n_flagged, ctx->timing ? ctx->knn_cand : nullptr));
+             for (int64_t q0 = 0; q0 < nq; q0 += QMAX)
+                 hipLaunchKernelGGL((k_knn<LPQ, KL, L>), dim3(grid_for(std::min(nq - q0, QMAX), 64 / LPQ)), dim3(64), 0,
+                                    st, qpos, q0, nq, T, V, FB, host_off, n_se, n_v, use_mass, p->mass_value, mass_sum,
+                                    R, (unsigned)ctx->xcd_chunk, flagged, n_flagged,
+                                    ctx->timing ? ctx->knn_cand : nullptr));
     VR_LAUNCH_CHECK(ctx);
     // almost always without work: a few wavefronts that stride over the flagged queries
     const unsigned nw = (unsigned)std::min<int64_t>(n_queries, 4 * ctx->num_cus);
