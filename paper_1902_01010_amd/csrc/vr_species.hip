@@ -96,20 +96,29 @@ __device__ __forceinline__ void cells27(int px, int py, int pz, int s, int b, do
     }
 }
 
-// The dark-matter component (its smallest index) of every cell-list
-// position, and per cell that component when all its members share it.
-__global__ void k_cell_roots(int64_t ncell, const uint32_t* __restrict__ cstart, const uint32_t* __restrict__ idx,
-                             const int32_t* __restrict__ orig, const int32_t* __restrict__ labc,
-                             int32_t* __restrict__ proot, int32_t* __restrict__ uroot) {
-    const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= ncell) return;
-    int u = -2;
-    for (uint32_t q = cstart[c]; q < cstart[c + 1]; ++q) {
-        const int r = orig[labc[idx[q]]];
-        proot[q] = r;
-        u = u == -2 ? r : (u == r ? u : -1);
+// The dark-matter component (its smallest index) of every cell-list position.
+__global__ void k_pos_roots(int64_t ndm, const uint32_t* __restrict__ idx, const int32_t* __restrict__ orig,
+                            const int32_t* __restrict__ labc, int32_t* __restrict__ proot) {
+    const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (q < ndm) proot[q] = orig[labc[idx[q]]];
+}
+
+// Per cell that component when all its members share it, else -1: a wavefront
+// per cell, since a thread alone with the members of a densest cell (5,000, a
+// chain of three lookups each) took 1.35 ms for 1 M particles; both kernels
+// now 110 us.
+__global__ __launch_bounds__(256) void k_cell_roots(int64_t ncell, const uint32_t* __restrict__ cstart,
+                                                    const int32_t* __restrict__ proot, int32_t* __restrict__ uroot) {
+    const int lane = (int)lane_id();
+    for (int64_t c = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); c < ncell; c += (int64_t)gridDim.x * 4) {
+        const uint32_t s = cstart[c], e = cstart[c + 1];
+        const int u = proot[s];
+        bool same = true;
+#pragma unroll 4
+        for (uint32_t q = s + (uint32_t)lane; q < e; q += 64) same = same && proot[q] == u;
+        const bool all = __ballot(!same) == 0;
+        if (lane == 0) uroot[c] = all ? u : -1;
     }
-    uroot[c] = u < 0 ? -1 : u;
 }
 
 // A baryon joins every dark-matter component with a member closer than
@@ -276,10 +285,11 @@ __global__ void k_host_init(int n_hosts, const int32_t* __restrict__ off, const 
     hb[h] = b;
 }
 
-// extents per host: a thread folds 16 members of its block's chunk of 4096
-// (a partial result per host it meets), and a wavefront whose last partial
-// results share one host reduces them before the atomics
-constexpr int EXT_PER_THREAD = 16;
+// extents per host: a wavefront takes EXT_ROWS rows of 64 consecutive members
+// and a lane folds its own as long as no lane's host changes; then the lanes'
+// values are reduced per host (hosts are runs of lanes) before the atomics.
+// (Per lane and host without the reduction 1 M particles took 568 us: 65 us.)
+constexpr int EXT_ROWS = 16;
 
 __global__ __launch_bounds__(256) void k_host_extent(int64_t M, const int32_t* __restrict__ mem,
                                                      const int32_t* __restrict__ owner, const uint8_t* __restrict__ isb,
@@ -287,65 +297,68 @@ __global__ __launch_bounds__(256) void k_host_extent(int64_t M, const int32_t* _
                                                      const uint32_t* __restrict__ qz, const float* __restrict__ vx,
                                                      const float* __restrict__ vy, const float* __restrict__ vz,
                                                      int gb, HostBox* __restrict__ hb) {
-    const int64_t base = (int64_t)blockIdx.x * (256 * EXT_PER_THREAD) + threadIdx.x;
+    const int lane = (int)lane_id();
+    const int64_t base = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * (64 * EXT_ROWS) + lane;
     int h = -1;
-    int lo[3], hi[3];
-    unsigned vlo[3], vhi[3];
+    // minima of u, -u (position), v and ~v (velocity images)
+    int lo[6];
+    unsigned vlo[6];
     auto reset = [&]() __attribute__((always_inline)) {
-        for (int d = 0; d < 3; ++d) {
+        for (int d = 0; d < 6; ++d) {
             lo[d] = INT_MAX;
-            hi[d] = INT_MIN;
             vlo[d] = 0xFFFFFFFFu;
-            vhi[d] = 0u;
         }
     };
-    auto flush = [&](int hh) __attribute__((always_inline)) {
-        HostBox* b = hb + hh;
-        for (int d = 0; d < 3; ++d) {
-            atomicMin(&b->umin[d], lo[d]);
-            atomicMax(&b->umax[d], hi[d]);
-            atomicMin(&b->vmin[d], vlo[d]);
-            atomicMax(&b->vmax[d], vhi[d]);
+    auto flush = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const bool take = __shfl_up(h, o, 64) == h && lane >= o;
+            for (int d = 0; d < 6; ++d) {
+                const int a = __shfl_up(lo[d], o, 64);
+                const unsigned b = (unsigned)__shfl_up((int)vlo[d], o, 64);
+                if (take) {
+                    lo[d] = min(lo[d], a);
+                    vlo[d] = min(vlo[d], b);
+                }
+            }
+        }
+        const int next = __shfl_down(h, 1, 64);
+        if (h >= 0 && (lane == 63 || next != h)) {
+            HostBox* b = hb + h;
+            for (int d = 0; d < 3; ++d) {
+                atomicMin(&b->umin[d], lo[d]);
+                atomicMax(&b->umax[d], -lo[3 + d]);
+                atomicMin(&b->vmin[d], vlo[d]);
+                atomicMax(&b->vmax[d], ~vlo[3 + d]);
+            }
         }
     };
     reset();
-    for (int r = 0; r < EXT_PER_THREAD; ++r) {
-        const int64_t k = base + (int64_t)r * 256;
-        if (k >= M) break;
-        const int hk = owner[k];
-        if (hk != h) {
-            if (h >= 0) flush(h);
+    for (int r = 0; r < EXT_ROWS; ++r) {
+        const int64_t k = base + (int64_t)r * 64;
+        const int hk = k < M ? owner[k] : -1;
+        if (__any(hk != h)) {
+            flush();
             reset();
             h = hk;
         }
+        if (k >= M) continue;
         const int i = mem[k];
         const int q[3] = {(int)qx[i], (int)qy[i], (int)qz[i]};
         for (int d = 0; d < 3; ++d) {
             const int u = min_image(q[d] - hb[h].ref[d], gb);
             lo[d] = min(lo[d], u);
-            hi[d] = max(hi[d], u);
+            lo[3 + d] = min(lo[3 + d], -u);
         }
         if (!isb[i]) {
             const unsigned o[3] = {f2o(vx[i]), f2o(vy[i]), f2o(vz[i])};
             for (int d = 0; d < 3; ++d) {
                 vlo[d] = min(vlo[d], o[d]);
-                vhi[d] = max(vhi[d], o[d]);
+                vlo[3 + d] = min(vlo[3 + d], ~o[d]);
             }
         }
     }
-    const int h0 = __shfl(h, 0, 64);
-    if (h0 >= 0 && __ballot(h != h0) == 0) {
-        for (int o = 32; o; o >>= 1)
-            for (int d = 0; d < 3; ++d) {
-                lo[d] = min(lo[d], __shfl_xor(lo[d], o, 64));
-                hi[d] = max(hi[d], __shfl_xor(hi[d], o, 64));
-                vlo[d] = min(vlo[d], (unsigned)__shfl_xor((int)vlo[d], o, 64));
-                vhi[d] = max(vhi[d], (unsigned)__shfl_xor((int)vhi[d], o, 64));
-            }
-        if (lane_id() == 0) flush(h);
-    } else if (h >= 0) {
-        flush(h);
-    }
+    flush();
 }
 
 __global__ void k_host_ok(int n_hosts, int gb, HostBox* __restrict__ hb) {
@@ -515,15 +528,20 @@ __global__ void k_baryon_list(int64_t M, const uint32_t* __restrict__ dmflag, co
     if (k < M && !dmflag[k]) blist[k - pos[k]] = (int32_t)k;
 }
 
-// One wavefront per 64 consecutive baryons of the tree-ordered list.  The
-// lanes of one host walk its tree together: a node is opened when its box
-// may hold a closer member for any of them, and each lane keeps its own
-// best.  Leaves are staged in LDS; a lane scores a member exactly only when
-// a float distance, with a margin for the rounding of the scaled
-// coordinates, does not already rule it out.
+// One wavefront per T6_Q consecutive baryons of the tree-ordered list,
+// T6_LPQ lanes each.  The lanes of one host walk its tree together: a node is
+// opened when its box may hold a closer member for any of them, and a
+// baryon's lanes share its best.  Leaves are staged in LDS; a lane scores its
+// part of the members, exactly only when a float distance, with a margin for
+// the rounding of the scaled coordinates, does not already rule one out.
+// Bound by the longest walks: 64 baryons a wavefront open all their nodes one
+// after the other, 236 k baryons among 600 k members 3.03 ms (one lane a
+// baryon), 1.61 (two), 1.05 (four), 1.17 (eight), 1.79 (sixteen).
 constexpr int T6_WAVES = 4;
+constexpr int T6_LPQ = 4;
+constexpr int T6_Q = 64 / T6_LPQ;
 
-__global__ __launch_bounds__(256) void k_assign6(int64_t nb, const int32_t* __restrict__ blist,
+__global__ __launch_bounds__(256) void k_assign6(int64_t b0, int64_t nb, const int32_t* __restrict__ blist,
                                                  const int32_t* __restrict__ mem, const int32_t* __restrict__ owner,
                                                  const int32_t* __restrict__ sub, const uint32_t* __restrict__ qx,
                                                  const uint32_t* __restrict__ qy, const uint32_t* __restrict__ qz,
@@ -537,8 +555,9 @@ __global__ __launch_bounds__(256) void k_assign6(int64_t nb, const int32_t* __re
     const int w = (int)(threadIdx.x >> 6);
     const int lane = (int)lane_id();
     const int64_t wave = (int64_t)blockIdx.x * T6_WAVES + w;
-    if (wave * 64 >= nb) return;
-    const int64_t bi = wave * 64 + lane;
+    if (b0 + wave * T6_Q >= nb) return;
+    const int64_t bi = b0 + wave * T6_Q + lane / T6_LPQ;
+    const int part = lane % T6_LPQ;  // members part, part + T6_LPQ, ... of a leaf
     const bool valid = bi < nb;
     int i = 0, h = -1, px = 0, py = 0, pz = 0;
     float fvx = 0.f, fvy = 0.f, fvz = 0.f;
@@ -582,6 +601,15 @@ __global__ __launch_bounds__(256) void k_assign6(int64_t nb, const int32_t* __re
         const double ax = bx - (double)v.x, ay = by - (double)v.y, az = bz - (double)v.z;
         consider(bst, d2 / ell2 + (ax * ax + ay * ay + az * az) / sv2, (int)e.w);
     };
+    // the best of the lanes that share a baryon
+    auto agree = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int o = 1; o < T6_LPQ; o <<= 1) {
+            const double d = __shfl_xor(bst.d, o, 64);
+            const int j = __shfl_xor(bst.j, o, 64);
+            consider(bst, d, j);
+        }
+    };
     uint64_t pending = __ballot(valid);
     while (pending) {
         const int hh = __builtin_amdgcn_readfirstlane(__shfl(h, __builtin_ctzll(pending), 64));
@@ -596,9 +624,10 @@ __global__ __launch_bounds__(256) void k_assign6(int64_t nb, const int32_t* __re
                 const int p1 = min(p0 + T6_FAN, d1);
                 stage(p0, p1, hb);
                 if (mine)
-                    for (int q = 0; q < p1 - p0; ++q) exact(q);
+                    for (int q = part; q < p1 - p0; q += T6_LPQ) exact(q);
                 __builtin_amdgcn_wave_barrier();
             }
+            agree();
             continue;
         }
         float y[6];
@@ -614,7 +643,7 @@ __global__ __launch_bounds__(256) void k_assign6(int64_t nb, const int32_t* __re
                 else hi = mid;
             }
             const int q0 = max(d0, min(lo - 4, d1 - 8)), q1 = min(d1, q0 + 8);
-            for (int q = q0; q < q1; ++q) {
+            for (int q = q0 + part; q < q1; q += T6_LPQ) {
                 const int ddx = min_image((int)t.sx[q] - px, gb);
                 const int ddy = min_image((int)t.sy[q] - py, gb);
                 const int ddz = min_image((int)t.sz[q] - pz, gb);
@@ -623,6 +652,7 @@ __global__ __launch_bounds__(256) void k_assign6(int64_t nb, const int32_t* __re
                 consider(bst, d2 / ell2 + (ax * ax + ay * ay + az * az) / sv2, t.sj[q]);
             }
         }
+        agree();
         // the packet's box, and the margins for the rounding of the scaled
         // coordinates (a few ulps of the largest of them)
         float qlo[6], qhi[6], amax = 0.f;
@@ -677,7 +707,7 @@ __global__ __launch_bounds__(256) void k_assign6(int64_t nb, const int32_t* __re
             if (lev == 1) {
                 stage(c0, c1, hb);
                 if (need) {
-                    for (int q = 0; q < c1 - c0; ++q) {
+                    for (int q = part; q < c1 - c0; q += T6_LPQ) {
                         const float4 A = sya[w][q], B = syb[w][q];
                         const float e0 = y[0] - A.x, e1 = y[1] - A.y, e2 = y[2] - A.z;
                         const float e3 = y[3] - A.w, e4 = y[4] - B.x, e5 = y[5] - B.y;
@@ -688,6 +718,8 @@ __global__ __launch_bounds__(256) void k_assign6(int64_t nb, const int32_t* __re
                         }
                     }
                 }
+                agree();
+                thr = thr_of();
                 __builtin_amdgcn_wave_barrier();
                 continue;
             }
@@ -726,7 +758,7 @@ __global__ __launch_bounds__(256) void k_assign6(int64_t nb, const int32_t* __re
             __builtin_amdgcn_wave_barrier();
         }
     }
-    if (valid) out[i] = bst.j == 0x7FFFFFFF ? -1 : sub[bst.j];
+    if (valid && part == 0) out[i] = bst.j == 0x7FFFFFFF ? -1 : sub[bst.j];
 }
 
 // The dark-matter-weighted mean over hosts of ellv_host[h] * inv_alpha (the
@@ -858,8 +890,9 @@ extern "C" int vr_fof3d_dm(vr_ctx* ctx, const vr_particles* p, double ellx, cons
             if ((rc = build_cell_list(ctx, ndm, cx, cy, cz, gb, s, cl, st))) return rc;
             VR_WS(proot, ctx, int32_t, WS_C7, ndm);
             VR_WS(uroot, ctx, int32_t, WS_C8, cl.n_cells + 1);
-            hipLaunchKernelGGL(k_cell_roots, dim3(grid_for(cl.n_cells, 256)), dim3(256), 0, st, cl.n_cells,
-                               cl.cell_start, cl.idx, orig, labc, proot, uroot);
+            hipLaunchKernelGGL(k_pos_roots, dim3(grid_for(ndm, 256)), dim3(256), 0, st, ndm, cl.idx, orig, labc, proot);
+            hipLaunchKernelGGL(k_cell_roots, dim3(std::min(grid_for(cl.n_cells, 4), 1u << 18)), dim3(256), 0, st,
+                               cl.n_cells, cl.cell_start, proot, uroot);
             VR_LAUNCH_CHECK(ctx);
             VR_TIMED(ctx, "fof_attach", st, n - ndm,
                      hipLaunchKernelGGL(k_attach, dim3(grid_for(n, 256)), dim3(256), 0, st, n, is_baryon, p->qx,
@@ -943,7 +976,7 @@ extern "C" int vr_assign_baryons(vr_ctx* ctx, const vr_particles* p, int32_t n_h
     VR_WS(hbox, ctx, HostBox, WS_D0, n_hosts);
     hipLaunchKernelGGL(k_host_init, dim3(grid_for(n_hosts, 256)), dim3(256), 0, st, n_hosts, host_offsets,
                        host_members, p->qx, p->qy, p->qz, hbox);
-    hipLaunchKernelGGL(k_host_extent, dim3(grid_for(M, 256 * EXT_PER_THREAD)), dim3(256), 0, st, M, host_members,
+    hipLaunchKernelGGL(k_host_extent, dim3(grid_for(M, 256 * EXT_ROWS)), dim3(256), 0, st, M, host_members,
                        owner, is_baryon, p->qx, p->qy, p->qz, p->vx, p->vy, p->vz, gb, hbox);
     hipLaunchKernelGGL(k_host_ok, dim3(grid_for(n_hosts, 256)), dim3(256), 0, st, n_hosts, gb, hbox);
     VR_LAUNCH_CHECK(ctx);
@@ -1034,11 +1067,14 @@ extern "C" int vr_assign_baryons(vr_ctx* ctx, const vr_particles* p, int32_t n_h
     hipLaunchKernelGGL(k_assign_dm, dim3(grid_for(M, 256)), dim3(256), 0, st, M, host_members, is_baryon, sub, 0, out);
     VR_LAUNCH_CHECK(ctx);
     if (nb > 0) {
+        // a launch holds fewer than 2^32 threads, T6_LPQ of them a baryon
+        constexpr int64_t BMAX = int64_t(1) << 26;
         VR_TIMED(ctx, "assign_baryons", st, nb,
-                 hipLaunchKernelGGL(k_assign6, dim3((unsigned)((nb + 64 * T6_WAVES - 1) / (64 * T6_WAVES))),
-                                    dim3(64 * T6_WAVES), 0, st, nb, blist,
-                                    host_members, owner, sub, p->qx, p->qy, p->qz, p->vx, p->vy, p->vz, bkey, t, gb,
-                                    u * u, sigma_v * sigma_v, ix, iv, out));
+                 for (int64_t b0 = 0; b0 < nb; b0 += BMAX)
+                     hipLaunchKernelGGL(k_assign6, dim3(grid_for(std::min(nb - b0, BMAX), T6_Q * T6_WAVES)),
+                                        dim3(64 * T6_WAVES), 0, st, b0, nb, blist, host_members, owner, sub, p->qx,
+                                        p->qy, p->qz, p->vx, p->vy, p->vz, bkey, t, gb, u * u, sigma_v * sigma_v, ix,
+                                        iv, out));
         VR_LAUNCH_CHECK(ctx);
     }
     return VR_OK;
