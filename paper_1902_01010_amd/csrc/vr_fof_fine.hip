@@ -359,7 +359,13 @@ __global__ __launch_bounds__(256) void k_link_cells(int64_t nfine, Links K, unsi
                 if (TEST) {
                     const uint32_t a0 = K.fine_start[A], a1 = K.fine_start[A + 1];
                     const uint32_t b0 = K.fine_start[B[j]], b1 = K.fine_start[B[j] + 1];
-                    if ((uint64_t)(a1 - a0) * (b1 - b0) > HEAVY && defer_pair(H, (uint32_t)A, B[j])) continue;
+                    // a listed pair unites nothing yet, and every pair that its
+                    // union would have settled is listed too: four tests first
+                    // (1 M particles in halos: both kernels 1.05 -> 0.29 ms)
+                    if ((uint64_t)(a1 - a0) * (b1 - b0) > HEAVY &&
+                        !test_particles(a0, a0 + 1, b0, min(b1, b0 + 4), K.sx, K.sy, K.sz, K.G.gb, K.l2c) &&
+                        defer_pair(H, (uint32_t)A, B[j]))
+                        continue;
                     if (!test_particles(a0, a1, b0, b1, K.sx, K.sy, K.sz, K.G.gb, K.l2c)) continue;
                 }
                 uf_union(K.uf, ra, rb);
