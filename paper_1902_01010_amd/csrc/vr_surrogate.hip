@@ -425,15 +425,25 @@ __device__ __forceinline__ void load_inputs(const uint16_t* __restrict__ feat, i
     bad = false;
     if (!valid) return;
     const uint16_t* fr = feat + row * NF;
-    for (int j = 0; j < 4; ++j) {
-        const uint16_t a = fr[4 * half + j];
-        in[j] = (short)a;
-        bad |= (a & 0x7FFFu) > 0x7F80u;
+    uint16_t a[4], b[4] = {0, 0, 0, 0};
+    if ((((uintptr_t)feat) & 7) == 0) {  // rows are 24 bytes
+        const uint2 q = *reinterpret_cast<const uint2*>(fr + 4 * half);
+        a[0] = (uint16_t)q.x, a[1] = (uint16_t)(q.x >> 16), a[2] = (uint16_t)q.y, a[3] = (uint16_t)(q.y >> 16);
         if (half == 0) {
-            const uint16_t b = fr[8 + j];
-            in[4 + j] = (short)b;
-            bad |= (b & 0x7FFFu) > 0x7F80u;
+            const uint2 r = *reinterpret_cast<const uint2*>(fr + 8);
+            b[0] = (uint16_t)r.x, b[1] = (uint16_t)(r.x >> 16), b[2] = (uint16_t)r.y, b[3] = (uint16_t)(r.y >> 16);
         }
+    } else {
+        for (int j = 0; j < 4; ++j) {
+            a[j] = fr[4 * half + j];
+            if (half == 0) b[j] = fr[8 + j];
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        in[j] = (short)a[j];
+        in[4 + j] = (short)b[j];
+        bad |= (a[j] & 0x7FFFu) > 0x7F80u || (b[j] & 0x7FFFu) > 0x7F80u;
     }
 }
 
@@ -532,75 +542,148 @@ __global__ __launch_bounds__(256) void k_mlp_forward(const float* __restrict__ w
 }
 
 // ---- training -----------------------------------------------------------------
-constexpr int GW = 4;                 // wavefronts per workgroup
-constexpr int GROWS = 32 * GW;        // batch rows per workgroup
-constexpr int NSLOT = NPARAM + 1;     // gradient + squared-error sum
+// Partial sums leave a workgroup in the order in which its lanes hold them:
+// W3 and W2 [t][u][j][lane] (accumulator entry j of output tile t, input tile
+// u), W1 [t][j][lane half][input], the four vectors of 64 by lane, then b4 and
+// the squared error.
+constexpr int NSLOT = NPARAM + 1;
+constexpr int SW3 = 0, SW2 = SW3 + H * H, SW1 = SW2 + H * H, SB3 = SW1 + NF * H, SB2 = SB3 + H, SB1 = SB2 + H,
+              S4 = SB1 + H, SB4 = S4 + H, SLOSS = SB4 + 1;
+static_assert(SLOSS + 1 == NSLOT, "slot layout");
 
-// Store the lane's 32 accumulator entries (one per hidden unit, of its row)
-// as BF16 into a [64 units][32 rows] tile in LDS.
-__device__ __forceinline__ void stash(const f16v a[2], uint16_t* tile, int lane) {
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int j = 0; j < 16; ++j) tile[(32 * t + acc_row(j, lane)) * 32 + (lane & 31)] = bf16_bits(a[t][j]);
+// The unit whose sum lane `lane` holds after rows_sum.
+__device__ __forceinline__ int sum_unit(int lane) { return 32 * ((lane >> 4) & 1) + acc_row(lane & 15, lane); }
+
+// Parameter of a slot (NPARAM: the squared error).
+__device__ __forceinline__ int slot_param(int s) {
+    if (s < SW1) {
+        const int r = s & (H * H - 1), lane = r & 63;
+        const int in = 32 * ((r >> 10) & 1) + (lane & 31), out = 32 * (r >> 11) + acc_row((r >> 6) & 15, lane);
+        return (s < SW2 ? OW3 : OW2) + in * H + out;
+    }
+    if (s < SB3) {
+        const int r = s - SW1, q = r / NF;
+        return OW1 + (r % NF) * H + 32 * (q >> 5) + acc_row((q >> 1) & 15, 32 * (q & 1));
+    }
+    if (s >= SB4) return s == SB4 ? OB4 : NPARAM;
+    const int r = s - SB3, v = r >> 6;
+    return (v == 0 ? OB3 : v == 1 ? OB2 : v == 2 ? OB1 : OW4) + sum_unit(r & 63);
 }
 
-// dW^T[out][in] += sum over the tile's 32 rows of delta[out][row] act[in][row]
-// (MFMA with the rows as the K dimension, slot s of lane half h in k-block
-// kb = row 16 kb + 8 h + s), added into the LDS gradient at W[in][out];
-// inputs in >= nin are skipped.
-__device__ __forceinline__ void weight_grad(const uint16_t* dl, const uint16_t* ac, int nin, float* gw, int lane) {
+// x of another lane of the row of 16.
+template <int CTRL>
+__device__ __forceinline__ float dpp(float x) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, false));
+}
+
+// Sums over the 32 rows (lanes of a half) of the lane's 32 accumulator
+// entries: lane l ends up with entry l % 32 of its half.  Each step halves the
+// entries a lane carries: it keeps one of two, adds the partner's and hands
+// over the other.
+__device__ __forceinline__ float rows_sum(const f16v a[2], int lane) {
+    float v[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+        // odd rows of 16 lanes of the first against even rows of the second
+        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a[0][j]), __float_as_uint(a[1][j]), false, false);
+        v[j] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    }
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const float keep = lane & 8 ? v[j + 8] : v[j], give = lane & 8 ? v[j] : v[j + 8];
+        v[j] = keep + dpp<0x128>(give);  // row_ror:8
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const float keep = lane & 4 ? v[j + 4] : v[j], give = lane & 4 ? v[j] : v[j + 4];
+        // lane ^ 4: a rotation by 4 or by 12
+        const float up = dpp<0x124>(give), down = dpp<0x12C>(give);
+        v[j] = keep + (lane & 4 ? up : down);
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const float keep = lane & 2 ? v[j + 2] : v[j], give = lane & 2 ? v[j] : v[j + 2];
+        v[j] = keep + dpp<0x4E>(give);  // quad_perm 2,3,0,1
+    }
+    const float keep = lane & 1 ? v[1] : v[0], give = lane & 1 ? v[0] : v[1];
+    return keep + dpp<0xB1>(give);  // quad_perm 1,0,3,2
+}
+
+// Sum of x over the 32 lanes of a half.
+__device__ __forceinline__ float half_sum(float x) {
+#pragma unroll
+    for (int o = 16; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
+    return x;
+}
+
+// The operands of a layer (BF16 values of its 64 units of the lane's row) as a
+// [64 units][32 rows] tile in LDS, TS entries a unit: 32 units' 16-byte reads
+// spread over the banks.
+constexpr int TS = 40;
+__device__ __forceinline__ void stash(const bf8 x[4], uint16_t* tile, int lane) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            tile[(32 * (q >> 1) + acc_row(8 * (q & 1) + k, lane)) * TS + (lane & 31)] = (uint16_t)x[q][k];
+}
+
+// g += dW^T[out][in] of the tile's 32 rows: sum of delta[out][row]
+// act[in][row] by MFMA with the rows as the K dimension, slot s of lane half h
+// in k-block kb = row 16 kb + 8 h + s; NU tiles of 32 inputs.
+template <int NU>
+__device__ __forceinline__ void weight_grad(const uint16_t* dl, const uint16_t* ac, f16v (&g)[2][NU], int lane) {
     const int half = lane >> 5, l32 = lane & 31;
-    const int ntin = (nin + 31) / 32;
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
-        for (int u = 0; u < ntin; ++u) {
-            f16v acc;
+    for (int kb = 0; kb < 2; ++kb) {
+        bf8 a[2], b[NU];
 #pragma unroll
-            for (int j = 0; j < 16; ++j) acc[j] = 0.f;
+        for (int t = 0; t < 2; ++t) a[t] = *reinterpret_cast<const bf8*>(dl + (32 * t + l32) * TS + 16 * kb + 8 * half);
 #pragma unroll
-            for (int kb = 0; kb < 2; ++kb) {
-                const bf8 a = *reinterpret_cast<const bf8*>(dl + (32 * t + l32) * 32 + 16 * kb + 8 * half);
-                const bf8 b = *reinterpret_cast<const bf8*>(ac + (32 * u + l32) * 32 + 16 * kb + 8 * half);
-                acc = mfma(a, b, acc);
-            }
-            const int in = 32 * u + l32;
-            if (in < nin)
+        for (int u = 0; u < NU; ++u) b[u] = *reinterpret_cast<const bf8*>(ac + (32 * u + l32) * TS + 16 * kb + 8 * half);
 #pragma unroll
-                for (int j = 0; j < 16; ++j) atomicAdd(&gw[in * H + 32 * t + acc_row(j, lane)], acc[j]);
-        }
-}
-
-__device__ __forceinline__ void bias_grad(const f16v d[2], float* gb, int lane, bool valid) {
-    if (!valid) return;
+        for (int t = 0; t < 2; ++t)
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int j = 0; j < 16; ++j) atomicAdd(&gb[32 * t + acc_row(j, lane)], d[t][j]);
+            for (int u = 0; u < NU; ++u) g[t][u] = mfma(a[t], b[u], g[t][u]);
+    }
 }
 
 // Gradient of the mean squared error over a batch of m rows (rows[] picks
-// them from feat/target, or rows 0..m-1): each workgroup takes 128-row tiles
-// and writes its partial sums (and its squared-error sum) to part[blockIdx].
-__global__ __launch_bounds__(256) void k_mlp_grad(const float* __restrict__ w, const bf8* __restrict__ pk, int64_t m,
-                                                  const uint16_t* __restrict__ feat, const int32_t* __restrict__ rows,
-                                                  const float* __restrict__ target, float* __restrict__ part) {
-    __shared__ float gacc[NSLOT];
-    __shared__ uint16_t dl_all[GW][H * 32];
-    __shared__ uint16_t ac_all[GW][H * 32];
-    for (int k = threadIdx.x; k < NSLOT; k += blockDim.x) gacc[k] = 0.f;
-    __syncthreads();
+// them from feat/target, or rows 0..m-1): wavefronts take tiles of 32 rows,
+// keep all sums in registers (weights by MFMA, vectors by rows_sum) and leave
+// one slot vector per workgroup in part, the wavefronts of a workgroup added
+// in order.  Bound by the chain of one tile: eleven layers of operand loads,
+// conversions and LDS transposes for 32 rows a wavefront; 8,192 rows are one
+// tile on every CU.  (Adding each tile into the workgroup's LDS by FP32
+// atomics, 32 lanes on an address or a bank, 128 rows a workgroup: 115 -> 15
+// us; 65,536 rows 440 -> 40 us.)
+template <int GW>
+__global__ __launch_bounds__(64 * GW, 1) void k_mlp_grad(const float* __restrict__ w,
+                                                         const bf8* __restrict__ packed, int64_t m, const uint16_t* __restrict__ feat,
+                                                         const int32_t* __restrict__ rows,
+                                                         const float* __restrict__ target, float* __restrict__ part) {
+    // two tiles a wavefront; the workgroup's sums take their place at the end
+    __shared__ __align__(16) uint16_t lds[GW * 2 * H * TS];
+    static_assert(GW == 1 || sizeof(lds) >= NSLOT * sizeof(float), "room for the sums");
+    float* sum = reinterpret_cast<float*>(lds);
     const int lane = __lane_id(), wv = threadIdx.x >> 6;
-    uint16_t* dl = dl_all[wv];
-    uint16_t* ac = ac_all[wv];
+    uint16_t* dl = lds + wv * 2 * H * TS;
+    uint16_t* ac = dl + H * TS;
     const float inv_m = 1.f / (float)m;
-    // workgroups stride over 128-row tiles, so the partial sums stay one
-    // slot vector per workgroup whatever the batch size
-    for (int64_t tile = blockIdx.x; tile * GROWS < m; tile += gridDim.x) {
-        const int64_t b = tile * GROWS + 32 * wv + (lane & 31);
+    f16v g3[2][2] = {}, g2[2][2] = {}, g1[2][1] = {};
+    float gb3 = 0.f, gb2 = 0.f, gb1 = 0.f, g4 = 0.f, gb4 = 0.f, loss = 0.f;
+    const int64_t ntiles = (m + 31) / 32;
+    int64_t tile = (int64_t)blockIdx.x * GW + wv;
+    // (GW = 1: a tile a workgroup)
+    while (tile < ntiles) {
+        // the operands come from the L2 for every tile: kept in registers over
+        // the loop they would spill
+        const bf8* pk = packed;
+        if (GW > 1) asm volatile("" : "+s"(pk));
+        const int64_t b = tile * 32 + (lane & 31);
         const bool valid = b < m;
         const int64_t row = valid ? (rows ? (int64_t)rows[b] : b) : 0;
-
+        const float want = valid ? target[row] : 0.f;
         bf8 x0;
         bool bad;
         load_inputs(feat, row, valid, lane, x0, bad);
@@ -616,90 +699,147 @@ __global__ __launch_bounds__(256) void k_mlp_grad(const float* __restrict__ w, c
 #pragma unroll
             for (int j = 0; j < 16; ++j) h3[t][j] = relu(h3[t][j]);
         const float y = out_layer(w, h3, lane);
-        const float r = valid ? y - target[row] : 0.f;
+        const float r = valid ? y - want : 0.f;
         const float gout = 2.f * r * inv_m;              // d loss / d output of this row
-        if (valid && lane < 32) {
-            atomicAdd(&gacc[NPARAM], r * r);
-            atomicAdd(&gacc[OB4], gout);
-        }
+        loss += half_sum(r * r);
+        gb4 += half_sum(gout);
         // layer 4 and the error at the pre-activations of layer 3
-        f16v d3[2];
+        f16v d[2], e4[2];
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
             for (int j = 0; j < 16; ++j) {
-                const int u = 32 * t + acc_row(j, lane);
-                if (valid) atomicAdd(&gacc[OW4 + u], gout * h3[t][j]);
-                d3[t][j] = h3[t][j] > 0.f ? gout * w[OW4 + u] : 0.f;
+                e4[t][j] = valid ? gout * h3[t][j] : 0.f;
+                d[t][j] = valid && h3[t][j] > 0.f ? gout * w[OW4 + 32 * t + acc_row(j, lane)] : 0.f;
             }
-        bias_grad(d3, gacc + OB3, lane, valid);
+        g4 += rows_sum(e4, lane);
+        gb3 += rows_sum(d, lane);
         // W3: delta3 x h2
-        stash(d3, dl, lane);
-        stash(h2, ac, lane);
-        __builtin_amdgcn_wave_barrier();
-        weight_grad(dl, ac, H, gacc + OW3, lane);
-        // delta2 = (W3 delta3) * [h2 > 0]
         bf8 xd[4];
-        to_operands(d3, xd);
-        f16v d2[2];
-        layer<4>(pk + PK_BWD3, nullptr, xd, lane, d2);
+        to_operands(d, xd);
+        __builtin_amdgcn_wave_barrier();
+        stash(xd, dl, lane);
+        stash(x2, ac, lane);
+        __builtin_amdgcn_wave_barrier();
+        weight_grad(dl, ac, g3, lane);
+        // delta2 = (W3 delta3) * [h2 > 0]
+        layer<4>(pk + PK_BWD3, nullptr, xd, lane, d);
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
-            for (int j = 0; j < 16; ++j) d2[t][j] = h2[t][j] > 0.f ? d2[t][j] : 0.f;
-        bias_grad(d2, gacc + OB2, lane, valid);
+            for (int j = 0; j < 16; ++j) d[t][j] = valid && h2[t][j] > 0.f ? d[t][j] : 0.f;
+        gb2 += rows_sum(d, lane);
+        to_operands(d, xd);
         __builtin_amdgcn_wave_barrier();
-        stash(d2, dl, lane);
-        stash(h1, ac, lane);
+        stash(xd, dl, lane);
+        stash(x1, ac, lane);
         __builtin_amdgcn_wave_barrier();
-        weight_grad(dl, ac, H, gacc + OW2, lane);
+        weight_grad(dl, ac, g2, lane);
         // delta1 = (W2 delta2) * [h1 > 0]
-        f16v d1[2];
-        to_operands(d2, xd);
-        layer<4>(pk + PK_BWD2, nullptr, xd, lane, d1);
+        layer<4>(pk + PK_BWD2, nullptr, xd, lane, d);
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
-            for (int j = 0; j < 16; ++j) d1[t][j] = h1[t][j] > 0.f ? d1[t][j] : 0.f;
-        bias_grad(d1, gacc + OB1, lane, valid);
+            for (int j = 0; j < 16; ++j) d[t][j] = valid && h1[t][j] > 0.f ? d[t][j] : 0.f;
+        gb1 += rows_sum(d, lane);
+        to_operands(d, xd);
         __builtin_amdgcn_wave_barrier();
-        stash(d1, dl, lane);
-        // the inputs as a [16][32] tile (rows of absent batch entries are zero)
+        stash(xd, dl, lane);
+        // the inputs as rows of the other tile (absent batch entries are
+        // zero); its rows 16..31 are former ones, but only inputs < 12 are
+        // kept (MFMA output columns do not mix)
+#pragma unroll
         for (int j = 0; j < 4; ++j) {
-            ac[(4 * (lane >> 5) + j) * 32 + (lane & 31)] = (uint16_t)x0[j];
-            ac[(8 + 4 * (lane >> 5) + j) * 32 + (lane & 31)] = (uint16_t)x0[4 + j];
+            ac[(4 * (lane >> 5) + j) * TS + (lane & 31)] = (uint16_t)x0[j];
+            ac[(8 + 4 * (lane >> 5) + j) * TS + (lane & 31)] = (uint16_t)x0[4 + j];
         }
         __builtin_amdgcn_wave_barrier();
-        // inputs 16..31 of the B tile read the next rows of ac, but only inputs
-        // < 12 are kept (MFMA output columns do not mix)
-        weight_grad(dl, ac, NF, gacc + OW1, lane);
-        __builtin_amdgcn_wave_barrier();
+        weight_grad(dl, ac, g1, lane);
+        if (GW == 1) break;
+        tile += (int64_t)gridDim.x * GW;
     }
-    __syncthreads();
     float* dst = part + (int64_t)blockIdx.x * NSLOT;
-    for (int k = threadIdx.x; k < NSLOT; k += blockDim.x) dst[k] = gacc[k];
+    auto each = [&](auto&& put) {
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int j = 0; j < 16; ++j) {
+                    put(SW3 + ((2 * t + u) * 16 + j) * 64 + lane, g3[t][u][j]);
+                    put(SW2 + ((2 * t + u) * 16 + j) * 64 + lane, g2[t][u][j]);
+                }
+            if ((lane & 31) < NF)
+#pragma unroll
+                for (int j = 0; j < 16; ++j)
+                    put(SW1 + ((16 * t + j) * 2 + (lane >> 5)) * NF + (lane & 31), g1[t][0][j]);
+        }
+        put(SB3 + lane, gb3);
+        put(SB2 + lane, gb2);
+        put(SB1 + lane, gb1);
+        put(S4 + lane, g4);
+        if (lane == 0) {
+            put(SB4, gb4);
+            put(SLOSS, loss);
+        }
+    };
+    if constexpr (GW == 1) {
+        each([&](int s, float x) { dst[s] = x; });
+    } else {
+        __syncthreads();
+        for (int v = 0; v < GW; ++v) {
+            if (wv == v) {
+                if (v == 0) each([&](int s, float x) { sum[s] = x; });
+                else each([&](int s, float x) { sum[s] += x; });
+            }
+            __syncthreads();
+        }
+        for (int k = threadIdx.x; k < NSLOT; k += 64 * GW) dst[k] = sum[k];
+    }
 }
 
-// Sum of the workgroup partials, in workgroup order (deterministic).
-__device__ __forceinline__ float part_sum(const float* __restrict__ part, int nwg, int k) {
+// Sums of the workgroups' partials for 64 slots a block: wavefront v takes
+// partials v, v + 16, ..., then the wavefronts' sums are added in order.  (One
+// thread a slot, one partial after the other: 29 us for 64, now 5 us for 256.)
+constexpr int RED_W = 16;
+__device__ __forceinline__ float part_sum(const float* __restrict__ part, int nwg, int slot, float (*sm)[64]) {
+    const int lane = __lane_id(), v = threadIdx.x >> 6;
     float s = 0.f;
-    for (int g = 0; g < nwg; ++g) s += part[(int64_t)g * NSLOT + k];
+    if (slot < NSLOT)
+#pragma unroll 8
+        for (int g = v; g < nwg; g += RED_W) s += part[(int64_t)g * NSLOT + slot];
+    sm[v][lane] = s;
+    __syncthreads();
+    s = 0.f;
+    if (v == 0)
+#pragma unroll
+        for (int k = 0; k < RED_W; ++k) s += sm[k][lane];
     return s;
 }
 
-__global__ void k_mlp_reduce(const float* __restrict__ part, int nwg, int64_t m, float* __restrict__ grad,
-                             float* __restrict__ loss) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < NPARAM && grad) grad[k] = part_sum(part, nwg, k);
-    if (k == NPARAM && loss) *loss = part_sum(part, nwg, NPARAM) / (float)m;
+__global__ __launch_bounds__(64 * RED_W) void k_mlp_reduce(const float* __restrict__ part, int nwg, int64_t m,
+                                                           float* __restrict__ grad, float* __restrict__ loss) {
+    __shared__ float sm[RED_W][64];
+    const int s = blockIdx.x * 64 + (int)__lane_id();
+    const float g = part_sum(part, nwg, s, sm);
+    if (threadIdx.x >= 64 || s >= NSLOT) return;
+    const int k = slot_param(s);
+    if (k < NPARAM && grad) grad[k] = g;
+    if (k == NPARAM && loss) *loss = g / (float)m;
 }
 
-__global__ void k_mlp_adam(const float* __restrict__ part, int nwg, int64_t m, float* __restrict__ w,
-                           float* __restrict__ st, vr_adam_params ap, int step, float* __restrict__ loss) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k == NPARAM && loss) *loss = part_sum(part, nwg, NPARAM) / (float)m;
-    if (k >= NPARAM) return;
-    const float g = part_sum(part, nwg, k);
+__global__ __launch_bounds__(64 * RED_W) void k_mlp_adam(const float* __restrict__ part, int nwg, int64_t m,
+                                                         float* __restrict__ w, float* __restrict__ st,
+                                                         vr_adam_params ap, int step, float* __restrict__ loss) {
+    __shared__ float sm[RED_W][64];
+    const int s = blockIdx.x * 64 + (int)__lane_id();
+    const float g = part_sum(part, nwg, s, sm);
+    if (threadIdx.x >= 64 || s >= NSLOT) return;
+    const int k = slot_param(s);
+    if (k == NPARAM) {
+        if (loss) *loss = g / (float)m;
+        return;
+    }
     float* m1 = st;
     float* m2 = st + NPARAM;
     const float a = ap.beta1 * m1[k] + (1.f - ap.beta1) * g;
@@ -747,10 +887,15 @@ int run_grad(vr_ctx* ctx, const float* w, int64_t m, const uint16_t* feat, const
     bf8* pk = nullptr;
     int rc = pack_weights(ctx, w, &pk, st);
     if (rc) return rc;
-    const int nwg = (int)std::min<int64_t>((m + GROWS - 1) / GROWS, (int64_t)ctx->num_cus * 2);
+    // one tile of 32 rows a wavefront and workgroup as long as the CUs hold
+    // two each; then four wavefronts a workgroup, which stride over the tiles
+    const int64_t ntiles = (m + 31) / 32;
+    const bool few = ntiles <= 2 * ctx->num_cus;
+    const int nwg = (int)(few ? ntiles : std::min<int64_t>((ntiles + 3) / 4, ctx->num_cus));
     VR_WS(part, ctx, float, WS_B8, (size_t)nwg * NSLOT);
     VR_TIMED(ctx, "mlp_grad", st, m,
-             hipLaunchKernelGGL(k_mlp_grad, dim3(nwg), dim3(64 * GW), 0, st, w, pk, m, feat, rows, target, part));
+             if (few) hipLaunchKernelGGL(k_mlp_grad<1>, dim3(nwg), dim3(64), 0, st, w, pk, m, feat, rows, target, part);
+             else hipLaunchKernelGGL(k_mlp_grad<4>, dim3(nwg), dim3(256), 0, st, w, pk, m, feat, rows, target, part));
     VR_LAUNCH_CHECK(ctx);
     *part_out = part;
     *nwg_out = nwg;
@@ -896,7 +1041,7 @@ int vr_mlp_grad(vr_ctx* ctx, const float* weights, int64_t m, const uint16_t* fe
     float* part = nullptr;
     int nwg = 0;
     if ((rc = run_grad(ctx, weights, m, feat, rows, target, &part, &nwg, st))) return rc;
-    hipLaunchKernelGGL(k_mlp_reduce, dim3(grid_for(NSLOT, 256)), dim3(256), 0, st, part, nwg, m, grad, loss);
+    hipLaunchKernelGGL(k_mlp_reduce, dim3(grid_for(NSLOT, 64)), dim3(64 * RED_W), 0, st, part, nwg, m, grad, loss);
     VR_LAUNCH_CHECK(ctx);
     return VR_OK;
 }
@@ -917,7 +1062,7 @@ int vr_mlp_train_step(vr_ctx* ctx, float* weights, float* adam_state, int64_t m,
     float* part = nullptr;
     int nwg = 0;
     if ((rc = run_grad(ctx, weights, m, feat, rows, target, &part, &nwg, st))) return rc;
-    hipLaunchKernelGGL(k_mlp_adam, dim3(grid_for(NSLOT, 256)), dim3(256), 0, st, part, nwg, m, weights, adam_state,
+    hipLaunchKernelGGL(k_mlp_adam, dim3(grid_for(NSLOT, 64)), dim3(64 * RED_W), 0, st, part, nwg, m, weights, adam_state,
                        *ap, step, loss);
     VR_LAUNCH_CHECK(ctx);
     return VR_OK;
