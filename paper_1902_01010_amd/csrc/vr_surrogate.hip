@@ -87,46 +87,83 @@ __global__ void k_rs_starts(int64_t m, const uint32_t* __restrict__ flag, const 
     if (i == 0) start[ncells] = (uint32_t)m;
 }
 
-__global__ void k_rs_clear(unsigned long long* __restrict__ hk, uint32_t size) {
+// A slot of the table of occupied cells: one 16-byte load a lookup brings the
+// cell and its members with the key.  Three arrays, three sectors a lookup:
+// 2 M particles' fine cells 365 us, now 290, coarse ones 57, now 35.  Bound by
+// the lookups' random lines, 27 a window; eight cells along x on one line
+// brought fewer of them but longer probes (564 and 116 us).
+struct alignas(16) Cell {
+    unsigned long long key;
+    uint32_t cell, count;
+};
+
+__global__ void k_rs_clear(Cell* __restrict__ table, uint32_t size) {
     const uint32_t h = blockIdx.x * blockDim.x + threadIdx.x;
-    if (h < size) hk[h] = EMPTY64;
+    if (h < size) table[h] = Cell{EMPTY64, 0u, 0u};
 }
 
 __global__ void k_rs_insert(uint32_t ncells, const uint64_t* __restrict__ keys, const uint32_t* __restrict__ start,
-                            uint32_t hmask, unsigned long long* __restrict__ hk, uint32_t* __restrict__ hv) {
+                            uint32_t hmask, Cell* __restrict__ table) {
     const uint32_t c = blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= ncells) return;
-    const unsigned long long k = keys[start[c]];
+    const uint32_t s = start[c], n = start[c + 1] - s;
+    const unsigned long long k = keys[s];
     uint32_t h = hash64(k, hmask);
     for (;;) {
-        const unsigned long long prev = atomicCAS(&hk[h], (unsigned long long)EMPTY64, k);
+        const unsigned long long prev = atomicCAS(&table[h].key, (unsigned long long)EMPTY64, k);
         if (prev == EMPTY64 || prev == k) {
-            hv[h] = c;
+            table[h].cell = c;
+            table[h].count = n;
             return;
         }
         h = (h + 1) & hmask;
     }
 }
 
-__device__ __forceinline__ int find64(const unsigned long long* __restrict__ hk, const uint32_t* __restrict__ hv,
-                                      uint32_t hmask, uint64_t k) {
-    uint32_t h = hash64(k, hmask);
-    for (;;) {
-        const unsigned long long kk = hk[h];
-        if (kk == k) return (int)hv[h];
-        if (kk == EMPTY64) return -1;
-        h = (h + 1) & hmask;
-    }
+__device__ __forceinline__ Cell load_slot(const Cell* __restrict__ table, uint32_t h) {
+    const ulonglong2 v = *reinterpret_cast<const ulonglong2*>(table + h);
+    return Cell{v.x, (uint32_t)v.y, (uint32_t)(v.y >> 32)};
 }
 
-// velocity sums of the members of each fine cell, FP64, in sorted order
+// The slot of key k, from its first probe e at h on (key EMPTY64: not there).
+__device__ __forceinline__ Cell find_from(const Cell* __restrict__ table, uint32_t hmask, uint64_t k, uint32_t h, Cell e) {
+    while (e.key != k && e.key != EMPTY64) {
+        h = (h + 1) & hmask;
+        e = load_slot(table, h);
+    }
+    return e;
+}
+
+// velocity sums of the members of each fine cell, FP64, in sorted order;
+// eight members' gathers in flight (one after the other, the fullest cells
+// took 172 us: 70 us)
 __global__ void k_rs_vsum(uint32_t ncells, const uint32_t* __restrict__ start, const uint32_t* __restrict__ rows,
                           const int32_t* __restrict__ mem, const float* __restrict__ vx, const float* __restrict__ vy,
                           const float* __restrict__ vz, double* __restrict__ vsum) {
     const uint32_t c = blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= ncells) return;
     double s0 = 0, s1 = 0, s2 = 0;
-    for (uint32_t k = start[c]; k < start[c + 1]; ++k) {
+    const uint32_t e = start[c + 1];
+    uint32_t k = start[c];
+    for (; k + 8 <= e; k += 8) {
+        int g[8];
+        float a[8], b[8], d[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) g[j] = mem[rows[k + j]];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            a[j] = vx[g[j]];
+            b[j] = vy[g[j]];
+            d[j] = vz[g[j]];
+        }
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            s0 += (double)a[j];
+            s1 += (double)b[j];
+            s2 += (double)d[j];
+        }
+    }
+    for (; k < e; ++k) {
         const int g = mem[rows[k]];
         s0 += (double)vx[g];
         s1 += (double)vy[g];
@@ -138,8 +175,7 @@ __global__ void k_rs_vsum(uint32_t ncells, const uint32_t* __restrict__ start, c
 }
 
 struct Level {
-    const unsigned long long* hk;
-    const uint32_t* hv;
+    const Cell* table;
     uint32_t hmask;
     const uint32_t* start;
     int cbits, b;
@@ -197,18 +233,17 @@ __device__ void jacobi3(double A[3][3], double lam[3], double V[3][3]) {
     }
 }
 
-// Members in the 27 cells around (cx, cy, cz).  Each z-layer's nine
-// lookups go out together: the nine first-probe keys in one round trip,
-// then the hits' values and member ranges; a probe continues one by one
-// only past a collision.
-__device__ __forceinline__ uint32_t window_count(const Level& L, uint32_t cx, uint32_t cy, uint32_t cz) {
+// Members in the 27 cells around (cx, cy, cz), and the slots of the cell and
+// its six face neighbours (-x, +x, -y, +y, -z, +z).  Each z-layer's nine first
+// probes go out together; a probe continues one by one only past a collision.
+__device__ __forceinline__ uint32_t window_count(const Level& L, uint32_t cx, uint32_t cy, uint32_t cz, Cell face[7]) {
     const uint32_t mask = (1u << L.b) - 1u;
     uint32_t n = 0;
 #pragma unroll
     for (int dz = -1; dz <= 1; ++dz) {
         uint64_t k[9];
         uint32_t h[9];
-        unsigned long long kk[9];
+        Cell e[9];
 #pragma unroll
         for (int j = 0; j < 9; ++j) {
             const int dy = j / 3 - 1, dx = j % 3 - 1;
@@ -216,17 +251,21 @@ __device__ __forceinline__ uint32_t window_count(const Level& L, uint32_t cx, ui
             h[j] = hash64(k[j], L.hmask);
         }
 #pragma unroll
-        for (int j = 0; j < 9; ++j) kk[j] = L.hk[h[j]];
-        int c[9];
+        for (int j = 0; j < 9; ++j) e[j] = load_slot(L.table, h[j]);
 #pragma unroll
         for (int j = 0; j < 9; ++j) {
-            if (kk[j] == k[j]) c[j] = (int)L.hv[h[j]];
-            else if (kk[j] == EMPTY64) c[j] = -1;
-            else c[j] = find64(L.hk, L.hv, L.hmask, k[j]);  // past a collision
+            e[j] = find_from(L.table, L.hmask, k[j], h[j], e[j]);
+            if (e[j].key == k[j]) n += e[j].count;
         }
-#pragma unroll
-        for (int j = 0; j < 9; ++j)
-            if (c[j] >= 0) n += L.start[c[j] + 1] - L.start[c[j]];
+        if (dz == 0) {
+            face[0] = e[4];
+            face[1] = e[3];
+            face[2] = e[5];
+            face[3] = e[1];
+            face[4] = e[7];
+        } else {
+            face[dz < 0 ? 5 : 6] = e[4];
+        }
     }
     return n;
 }
@@ -243,8 +282,9 @@ __global__ __launch_bounds__(256) void k_rs_coarsewin(uint32_t ncells, const uin
     if (c >= ncells) return;
     const uint64_t key = keys[coarse.start[c]];
     const uint32_t mask = (1u << coarse.b) - 1u;
+    Cell face[7];
     cwin[c] = window_count(coarse, (uint32_t)(key & mask), (uint32_t)((key >> coarse.b) & mask),
-                           (uint32_t)(key >> (2 * coarse.b)));
+                           (uint32_t)(key >> (2 * coarse.b)), face);
 }
 
 // What a row's features take from its fine cell alone, once per occupied
@@ -252,7 +292,8 @@ __global__ __launch_bounds__(256) void k_rs_coarsewin(uint32_t ncells, const uin
 // n_se neighbours at the density of the 27-cell window (the coarse window
 // where the fine one holds fewer than n_se), and the mean velocity of the
 // cell and its six face neighbours.  cf[4 c .. 4 c + 3] = (f0, vloc).
-__global__ __launch_bounds__(256) void k_rs_cellfeat(uint32_t ncells, const uint64_t* __restrict__ keys,
+// (four wavefronts a SIMD: 343 -> 291 us with the registers that takes)
+__global__ __launch_bounds__(256, 4) void k_rs_cellfeat(uint32_t ncells, const uint64_t* __restrict__ keys,
                                                      Level fine, Level coarse, const uint32_t* __restrict__ cwin,
                                                      const double* __restrict__ vsum, int n_se, double cell_len,
                                                      double* __restrict__ cf) {
@@ -262,7 +303,8 @@ __global__ __launch_bounds__(256) void k_rs_cellfeat(uint32_t ncells, const uint
     const uint32_t mask = (1u << fine.b) - 1u;
     const uint32_t cx = (uint32_t)(key & mask), cy = (uint32_t)((key >> fine.b) & mask),
                    cz = (uint32_t)(key >> (2 * fine.b));
-    const uint32_t nf = window_count(fine, cx, cy, cz);
+    Cell face[7];
+    const uint32_t nf = window_count(fine, cx, cy, cz, face);
     double nhat;
     if ((int)nf >= n_se) {
         nhat = (double)nf / (27.0 * cell_len * cell_len * cell_len);
@@ -270,41 +312,23 @@ __global__ __launch_bounds__(256) void k_rs_cellfeat(uint32_t ncells, const uint
         // the coarse grid's cells are 4 fine cells a side; the one holding
         // this fine cell is occupied, and its window count is precomputed
         const uint32_t cmask = (1u << coarse.b) - 1u;
-        const int c1 = find64(coarse.hk, coarse.hv, coarse.hmask,
-                              cell_key((cx >> 2) & cmask, (cy >> 2) & cmask, (cz >> 2) & cmask, coarse.b));
-        const uint32_t nc = c1 >= 0 ? cwin[c1] : 0u;
+        const uint64_t ck = cell_key((cx >> 2) & cmask, (cy >> 2) & cmask, (cz >> 2) & cmask, coarse.b);
+        const uint32_t h = hash64(ck, coarse.hmask);
+        const Cell e = find_from(coarse.table, coarse.hmask, ck, h, load_slot(coarse.table, h));
+        const uint32_t nc = e.key == ck ? cwin[e.cell] : 0u;
         const double L4 = 4.0 * cell_len;
         nhat = (double)nc / (27.0 * L4 * L4 * L4);
     }
     cf[4 * (size_t)c] = log(cbrt(3.0 * (double)n_se / (4.0 * M_PI * nhat)));
-    const int fo[7][3] = {{0, 0, 0}, {-1, 0, 0}, {1, 0, 0}, {0, -1, 0}, {0, 1, 0}, {0, 0, -1}, {0, 0, 1}};
-    // the seven lookups go out together, as in window_count
-    uint64_t fk[7];
-    uint32_t fh[7];
-    unsigned long long fkk[7];
-    int fc[7];
-#pragma unroll
-    for (int k = 0; k < 7; ++k) {
-        fk[k] = cell_key((cx + fo[k][0]) & mask, (cy + fo[k][1]) & mask, (cz + fo[k][2]) & mask, fine.b);
-        fh[k] = hash64(fk[k], fine.hmask);
-    }
-#pragma unroll
-    for (int k = 0; k < 7; ++k) fkk[k] = fine.hk[fh[k]];
-#pragma unroll
-    for (int k = 0; k < 7; ++k) {
-        if (fkk[k] == fk[k]) fc[k] = (int)fine.hv[fh[k]];
-        else if (fkk[k] == EMPTY64) fc[k] = -1;
-        else fc[k] = find64(fine.hk, fine.hv, fine.hmask, fk[k]);
-    }
     double s0 = 0, s1 = 0, s2 = 0, cnt = 0;
 #pragma unroll
     for (int k = 0; k < 7; ++k) {
-        const int cc = fc[k];
-        if (cc < 0) continue;
-        cnt += (double)(fine.start[cc + 1] - fine.start[cc]);
-        s0 += vsum[3 * (size_t)cc];
-        s1 += vsum[3 * (size_t)cc + 1];
-        s2 += vsum[3 * (size_t)cc + 2];
+        if (face[k].key == EMPTY64) continue;
+        const size_t cc = face[k].cell;
+        cnt += (double)face[k].count;
+        s0 += vsum[3 * cc];
+        s1 += vsum[3 * cc + 1];
+        s2 += vsum[3 * cc + 2];
     }
     cf[4 * (size_t)c + 1] = s0 / cnt;
     cf[4 * (size_t)c + 2] = s1 / cnt;
@@ -970,14 +994,13 @@ int vr_rs_features(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const in
         VR_LAUNCH_CHECK(ctx);
         uint32_t hsize = 64;
         while (hsize < 2u * ncells) hsize <<= 1;
-        VR_WS(hk, ctx, unsigned long long, WS_B1 + 3 * L, hsize);
-        VR_WS(hv, ctx, uint32_t, WS_B2 + 3 * L, hsize);
-        hipLaunchKernelGGL(k_rs_clear, dim3(grid_for(hsize, 256)), dim3(256), 0, st, hk, hsize);
+        VR_WS(table, ctx, Cell, WS_B1 + 3 * L, hsize);
+        hipLaunchKernelGGL(k_rs_clear, dim3(grid_for(hsize, 256)), dim3(256), 0, st, table, hsize);
         VR_LAUNCH_CHECK(ctx);
         hipLaunchKernelGGL(k_rs_insert, dim3(grid_for(ncells, 256)), dim3(256), 0, st, ncells, keys, start, hsize - 1,
-                           hk, hv);
+                           table);
         VR_LAUNCH_CHECK(ctx);
-        lv[L] = Level{hk, hv, hsize - 1, start, cb[L], b};
+        lv[L] = Level{table, hsize - 1, start, cb[L], b};
         ncell[L] = ncells;
         if (L == 1) keys1 = keys;
         if (L == 0) {
