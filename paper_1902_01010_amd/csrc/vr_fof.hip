@@ -178,6 +178,16 @@ __global__ void k_label_keys(int64_t n, const int32_t* __restrict__ label, const
     val[k] = (uint32_t)i;
 }
 
+// One pair a particle; unlabelled ones sort behind all labels.
+__global__ void k_all_keys(int64_t n, const int32_t* __restrict__ label, uint32_t* __restrict__ key,
+                           uint32_t* __restrict__ val) {
+    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const int l = label[i];
+    key[i] = l >= 0 && l < n ? (uint32_t)l : (uint32_t)n;
+    val[i] = (uint32_t)i;
+}
+
 __global__ void k_run_flags(int64_t n, const uint32_t* __restrict__ key, uint32_t* __restrict__ flag) {
     int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (p < n) flag[p] = (p == 0 || key[p] != key[p - 1]) ? 1u : 0u;
@@ -192,12 +202,18 @@ __global__ void k_run_starts(int64_t n, const uint32_t* __restrict__ key, const 
     if (p == n - 1) run_start[start ? scan[p] + 1 : scan[p]] = (uint32_t)n;
 }
 
-__global__ void k_run_keep(int64_t nrun, const uint32_t* __restrict__ run_start, int32_t n_min,
-                           uint32_t* __restrict__ keep) {
+// keep[s] for s < bound: run s < *nrun is a group (not the unlabelled ones,
+// whose key is n, and large enough)
+__global__ void k_run_keep(int64_t bound, const uint32_t* __restrict__ nrun, int64_t n, const uint32_t* __restrict__ key,
+                           const uint32_t* __restrict__ run_start, int32_t n_min, uint32_t* __restrict__ keep) {
     int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= nrun) return;
-    const uint32_t a = run_start[s], b = run_start[s + 1];
-    keep[s] = b - a >= (uint32_t)n_min ? 1u : 0u;
+    if (s >= bound) return;
+    bool k = false;
+    if (s < *nrun) {
+        const uint32_t a = run_start[s], b = run_start[s + 1];
+        k = b - a >= (uint32_t)n_min && key[a] < (uint32_t)n;
+    }
+    keep[s] = k ? 1u : 0u;
 }
 
 __global__ void k_run_compact(int64_t nrun, int64_t n, const uint32_t* __restrict__ keep,
@@ -386,47 +402,56 @@ extern "C" int vr_groups(vr_ctx* ctx, int64_t n, const int32_t* label, int32_t n
     VR_WS(kpos, ctx, uint32_t, WS_B7, n);
     VR_WS(run_group, ctx, int32_t, WS_B8, n);
     VR_WS(tot, ctx, uint32_t, WS_FLAG, 4);
-    // the labelled particles, compacted in index order: the byte flags live
-    // in keep and their positions in runid until the runs need them
-    uint8_t* flag = reinterpret_cast<uint8_t*>(keep);
-    hipLaunchKernelGGL(k_label_flags, dim3(grid_for(n, 256)), dim3(256), 0, st, n, label, flag, group_of);
-    VR_LAUNCH_CHECK(ctx);
-    int rc = scan_u8(ctx, flag, runid, n, st);
-    if (rc) return rc;
-    hipLaunchKernelGGL(k_label_total, dim3(1), dim3(64), 0, st, n, flag, runid, tot);
-    VR_LAUNCH_CHECK(ctx);
-    // labels are below n; the compacted pairs go where the sort ends in place
-    const int kbits = bits_for((uint64_t)(n - 1));
-    uint32_t *kin = key, *vin = val;
-    if ((rc = sort_input_u32(ctx, key, val, n, kbits, &kin, &vin))) return rc;
-    hipLaunchKernelGGL(k_label_keys, dim3(grid_for(n, 256)), dim3(256), 0, st, n, label, flag, runid, kin, vin);
-    VR_LAUNCH_CHECK(ctx);
-    uint32_t m32 = 0;
-    rc = read_back(ctx, tot, &m32, sizeof m32, st);
-    if (rc) return rc;
-    const int64_t m = m32;  // labelled particles
-    uint32_t nrun = 0;
+    int rc = VR_OK;
+    int64_t m = n;  // sorted pairs
+    uint32_t nrun = 0, ng = 0;
+    // A small set sorts its unlabelled particles with the others and learns
+    // the counts of runs and groups in one wait at the end (three waits of 20
+    // us and three launches more cost two sorts of 14 k labels 210 us each).
+    const bool few = n <= 131072;
+    if (few) {
+        const int kbits = bits_for((uint64_t)n);
+        uint32_t *kin = key, *vin = val;
+        if ((rc = sort_input_u32(ctx, key, val, n, kbits, &kin, &vin))) return rc;
+        hipLaunchKernelGGL(k_all_keys, dim3(grid_for(n, 256)), dim3(256), 0, st, n, label, kin, vin);
+        VR_LAUNCH_CHECK(ctx);
+        if ((rc = sort_pairs_u32_from(ctx, kin, vin, key, val, n, kbits, st))) return rc;
+    } else {
+        // the labelled particles, compacted in index order: the byte flags
+        // live in keep and their positions in runid until the runs need them
+        uint8_t* flag = reinterpret_cast<uint8_t*>(keep);
+        hipLaunchKernelGGL(k_label_flags, dim3(grid_for(n, 256)), dim3(256), 0, st, n, label, flag, group_of);
+        VR_LAUNCH_CHECK(ctx);
+        if ((rc = scan_u8(ctx, flag, runid, n, st))) return rc;
+        hipLaunchKernelGGL(k_label_total, dim3(1), dim3(64), 0, st, n, flag, runid, tot);
+        VR_LAUNCH_CHECK(ctx);
+        // labels are below n; the compacted pairs go where the sort ends in place
+        const int kbits = bits_for((uint64_t)(n - 1));
+        uint32_t *kin = key, *vin = val;
+        if ((rc = sort_input_u32(ctx, key, val, n, kbits, &kin, &vin))) return rc;
+        hipLaunchKernelGGL(k_label_keys, dim3(grid_for(n, 256)), dim3(256), 0, st, n, label, flag, runid, kin, vin);
+        VR_LAUNCH_CHECK(ctx);
+        uint32_t m32 = 0;
+        if ((rc = read_back(ctx, tot, &m32, sizeof m32, st))) return rc;
+        m = m32;
+        if (m > 0 && (rc = sort_pairs_u32_from(ctx, kin, vin, key, val, m, kbits, st))) return rc;
+    }
     if (m > 0) {
-        rc = sort_pairs_u32_from(ctx, kin, vin, key, val, m, kbits, st);
-        if (rc) return rc;
         hipLaunchKernelGGL(k_run_flags, dim3(grid_for(m, 256)), dim3(256), 0, st, m, key, runid);
         VR_LAUNCH_CHECK(ctx);
-        rc = scan_u32(ctx, runid, runid, m, tot, st);
-        if (rc) return rc;
+        if ((rc = scan_u32(ctx, runid, runid, m, tot, st))) return rc;
         hipLaunchKernelGGL(k_run_starts, dim3(grid_for(m, 256)), dim3(256), 0, st, m, key, runid, run_start);
         VR_LAUNCH_CHECK(ctx);
-        rc = read_back(ctx, tot, &nrun, sizeof nrun, st);
-        if (rc) return rc;
-    }
-    hipLaunchKernelGGL(k_run_keep, dim3(grid_for(nrun, 256)), dim3(256), 0, st, (int64_t)nrun, run_start, n_min,
-                       keep);
-    VR_LAUNCH_CHECK(ctx);
-    uint32_t ng = 0;
-    if (nrun > 0) {
-        rc = scan_u32(ctx, keep, kpos, nrun, tot, st);
-        if (rc) return rc;
-        rc = read_back(ctx, tot, &ng, sizeof ng, st);
-        if (rc) return rc;
+        nrun = (uint32_t)m;  // bound
+        if (!few && (rc = read_back(ctx, tot, &nrun, sizeof nrun, st))) return rc;
+        hipLaunchKernelGGL(k_run_keep, dim3(grid_for(nrun, 256)), dim3(256), 0, st, (int64_t)nrun, tot, n, key, run_start,
+                           n_min, keep);
+        VR_LAUNCH_CHECK(ctx);
+        if ((rc = scan_u32(ctx, keep, kpos, nrun, tot + 1, st))) return rc;
+        uint32_t c[2];
+        if ((rc = read_back(ctx, tot, c, sizeof c, st))) return rc;
+        nrun = c[0];
+        ng = c[1];
     }
     *n_groups = (int32_t)ng;
     VR_WS(gkey, ctx, uint32_t, WS_B9, ng + 1);

@@ -101,7 +101,7 @@ __global__ void k_ellv_final(int n_hosts, const int* __restrict__ chunk_off, con
 }
 
 __global__ void k_participants(int64_t n, const int32_t* __restrict__ host_of, const float* __restrict__ R,
-                               float thr, int32_t n_hosts, uint32_t* __restrict__ flag, int* __restrict__ bad) {
+                               float thr, int32_t n_hosts, uint32_t* __restrict__ flag) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const int h = host_of[i];
@@ -818,8 +818,8 @@ extern "C" int vr_host_ellv(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts,
         coff[h + 1] = (int)chunks.size();
     }
     const int nch = (int)chunks.size();
-    VR_WS(chunks_d, ctx, int4, WS_D4, nch);
-    VR_WS(coff_d, ctx, int, WS_D5, n_hosts + 1);
+    VR_WS(chunks_d, ctx, int4, WS_D4, (int64_t)nch + (n_hosts + 4) / 4);  // chunks, then the hosts' first ones
+    int* coff_d = reinterpret_cast<int*>(chunks_d + nch);
     VR_WS(part, ctx, double, WS_D6, (int64_t)nch * ELLV_PART);
     {
         // both tables through the pinned upload buffer: no wait here
@@ -828,8 +828,7 @@ extern "C" int vr_host_ellv(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts,
         if (!up) return VR_ERR_HIP;
         std::memcpy(up, chunks.data(), bc);
         std::memcpy(up + bc, coff.data(), bo);
-        VR_HIP(ctx, hipMemcpyAsync(chunks_d, up, bc, hipMemcpyHostToDevice, st));
-        VR_HIP(ctx, hipMemcpyAsync(coff_d, up + bc, bo, hipMemcpyHostToDevice, st));
+        VR_HIP(ctx, hipMemcpyAsync(chunks_d, up, bc + bo, hipMemcpyHostToDevice, st));
         if (int rc1 = upload_end(ctx, st)) return rc1;
     }
     hipLaunchKernelGGL(k_ellv_sums, dim3(nch), dim3(256), 0, st, chunks_d, host_members, host_offsets, p->vx, p->vy,
@@ -867,31 +866,28 @@ int link_outliers(vr_ctx* ctx, const vr_particles* p, const int32_t* host_of, co
         return set_err(ctx, VR_ERR_INVALID_ARG, "NULL array");
     VR_HIP(ctx, hipSetDevice(ctx->device));
     hipStream_t st = (hipStream_t)stream;
+    const double ell2 = u * u;
+    VR_WS(flag, ctx, uint32_t, WS_C0, n);
+    VR_WS(pos, ctx, uint32_t, WS_C1, n);
+    VR_WS(tot, ctx, uint32_t, WS_C9, 4);
+    hipLaunchKernelGGL(k_participants, dim3(grid_for(n, 256)), dim3(256), 0, st, n, host_of, R, R_threshold, n_hosts,
+                       flag);
+    VR_LAUNCH_CHECK(ctx);
+    rc = scan_u32(ctx, flag, pos, n, tot, st);
+    if (rc) return rc;
+    // the participants' count and the linking lengths in one wait
+    uint32_t* hostpin = reinterpret_cast<uint32_t*>(ctx->pinned);
+    VR_HIP(ctx, hipMemcpyAsync(hostpin, tot, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
     if (!sub && n_hosts > 0) {
         std::vector<double> ev(n_hosts);
         if ((rc = copy_to_host(ctx, ev.data(), ellv_host, n_hosts * sizeof(double), st))) return rc;
         for (int h = 0; h < n_hosts; ++h)
             if (!(ev[h] > 0) || !std::isfinite(ev[h]))
                 return set_err(ctx, VR_ERR_INVALID_ARG, "ellv_host[%d] = %g is not a positive number", h, ev[h]);
+    } else {
+        VR_HIP(ctx, hipStreamSynchronize(st));
     }
-    const double ell2 = u * u;
-    VR_WS(flag, ctx, uint32_t, WS_C0, n);
-    VR_WS(pos, ctx, uint32_t, WS_C1, n);
-    VR_WS(bad, ctx, int, WS_FLAG2, 4);
-    VR_WS(tot, ctx, uint32_t, WS_C9, 4);
-    rc = fill_i32(ctx, bad, 0, 1, st);
-    if (rc) return rc;
-    hipLaunchKernelGGL(k_participants, dim3(grid_for(n, 256)), dim3(256), 0, st, n, host_of, R, R_threshold, n_hosts,
-                       flag, bad);
-    VR_LAUNCH_CHECK(ctx);
-    rc = scan_u32(ctx, flag, pos, n, tot, st);
-    if (rc) return rc;
-    int32_t* hostpin = reinterpret_cast<int32_t*>(ctx->pinned);
-    VR_HIP(ctx, hipMemcpyAsync(hostpin, tot, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
-    VR_HIP(ctx, hipMemcpyAsync(hostpin + 1, bad, sizeof(int), hipMemcpyDeviceToHost, st));
-    VR_HIP(ctx, hipStreamSynchronize(st));
-    const int64_t np = (uint32_t)hostpin[0];
-    if (hostpin[1]) return set_err(ctx, VR_ERR_INVALID_ARG, "host_of holds a host id >= n_hosts");
+    const int64_t np = hostpin[0];
     rc = fill_i32(ctx, label6, -1, n, st);
     if (rc) return rc;
     if (np == 0) return VR_OK;
@@ -1025,8 +1021,7 @@ extern "C" int vr_sub_grow(vr_ctx* ctx, const vr_particles* p, const int32_t* ho
     VR_WS(tot, ctx, uint32_t, WS_C9, 4);
     VR_WS(size, ctx, int, WS_B0, n);
     if ((rc = fill_i32(ctx, bad, 0, 2, st)) || (rc = fill_i32(ctx, size, 0, n, st))) return rc;
-    hipLaunchKernelGGL(k_participants, dim3(grid_for(n, 256)), dim3(256), 0, st, n, host_of, L, Lth2, n_hosts, flag,
-                       bad);
+    hipLaunchKernelGGL(k_participants, dim3(grid_for(n, 256)), dim3(256), 0, st, n, host_of, L, Lth2, n_hosts, flag);
     hipLaunchKernelGGL(k_label_sizes, dim3(grid_for(n, 256)), dim3(256), 0, st, n, label1, size);
     hipLaunchKernelGGL(k_check_tagged, dim3(grid_for(n, 256)), dim3(256), 0, st, n, label1, size, n_min, flag, bad);
     VR_LAUNCH_CHECK(ctx);

@@ -191,11 +191,11 @@ __global__ __launch_bounds__(64) void k_pair_tables(FineGrid G, int64_t l2c, uin
 // Per coarse cell: the mask of its fine cells and its occupied neighbours.
 // Two cells in three of a cosmological box have none, and cost the later
 // passes one coalesced word.
-__global__ void k_coarse_rec(int64_t ncoarse, const uint32_t* __restrict__ cfs, const uint2* __restrict__ frec,
+__global__ void k_coarse_rec(const uint32_t* __restrict__ ncoarse, const uint32_t* __restrict__ cfs, const uint2* __restrict__ frec,
                              const uint64_t* __restrict__ key, const uint32_t* __restrict__ fine_start, FineGrid G,
                              const uint64_t* __restrict__ occ, uint4* __restrict__ crec, uint32_t* __restrict__ nbits) {
     const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= ncoarse) return;
+    if (c >= *ncoarse) return;
     const uint32_t f0 = cfs[c], f1 = cfs[c + 1];
     const uint64_t ck = key[fine_start[f0]] >> (3 * G.lr);
     const int ncm = G.nc - 1;
@@ -262,9 +262,9 @@ __device__ __forceinline__ uint32_t neighbour(const Links& K, const NeighbourRow
 // found in ascending cell order (itself if none): parents are smaller than
 // their children, so there are no cycles, and nothing waits for another
 // thread.
-__global__ __launch_bounds__(256) void k_hook(int64_t nfine, Links K) {
+__global__ __launch_bounds__(256) void k_hook(const uint32_t* __restrict__ nfine, Links K) {
     const int64_t F = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (F >= nfine) return;
+    if (F >= *nfine) return;
     const uint2 fr = K.frec[F];
     const uint32_t c = fr.x, a = fr.y;
     const uint4 own = K.crec[c];
@@ -298,9 +298,9 @@ __global__ __launch_bounds__(256) void k_hook(int64_t nfine, Links K) {
     K.uf[F] = par;
 }
 
-__global__ void k_flatten(int64_t nfine, int* uf) {
+__global__ void k_flatten(const uint32_t* __restrict__ nfine, int* uf) {
     const int64_t F = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (F >= nfine) return;
+    if (F >= *nfine) return;
     int p = uf[F];
     if (p == (int)F) return;
     for (int g = uf[p]; g != p; g = uf[p]) p = g;
@@ -308,9 +308,9 @@ __global__ void k_flatten(int64_t nfine, int* uf) {
 }
 
 // The root that all fine cells of a coarse cell share, or -1.
-__global__ void k_coarse_root(int64_t ncoarse, const int* __restrict__ uf, uint4* __restrict__ crec) {
+__global__ void k_coarse_root(const uint32_t* __restrict__ ncoarse, const int* __restrict__ uf, uint4* __restrict__ crec) {
     const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= ncoarse) return;
+    if (c >= *ncoarse) return;
     const uint4 r = crec[c];
     const uint32_t n = (uint32_t)__popcll(mask_of(r));
     const int root = uf[r.z];
@@ -324,9 +324,9 @@ __global__ void k_coarse_root(int64_t ncoarse, const int* __restrict__ uf, uint4
 // ones that are not certain, by testing their particles.  The roots are
 // flattened when the pass starts; a partner whose parent is A's root is done.
 template <bool TEST>
-__global__ __launch_bounds__(256) void k_link_cells(int64_t nfine, Links K, unsigned xchunk, HeavyList H) {
+__global__ __launch_bounds__(256) void k_link_cells(const uint32_t* __restrict__ nfine, Links K, unsigned xchunk, HeavyList H) {
     const int64_t A = (int64_t)xcd_swizzle(blockIdx.x, gridDim.x, xchunk) * blockDim.x + threadIdx.x;
-    if (A >= nfine) return;
+    if (A >= *nfine) return;
     const uint2 fr = K.frec[A];
     const uint32_t c = fr.x, a = fr.y;
     const uint32_t fwd = K.nbits[c] >> (OWN + 1);
@@ -410,28 +410,29 @@ __global__ void k_occ_count(int64_t words, const uint64_t* __restrict__ occ, uin
 }
 
 // fine-cell records: coarse cell, fine cell inside it
-__global__ void k_frec(int64_t nfine, const uint32_t* __restrict__ fine_start, const uint64_t* __restrict__ key,
+__global__ void k_frec(const uint32_t* __restrict__ nfine, const uint32_t* __restrict__ fine_start, const uint64_t* __restrict__ key,
                        const uint32_t* __restrict__ cid, int lr3, uint2* __restrict__ frec) {
     const int64_t F = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (F >= nfine) return;
+    if (F >= *nfine) return;
     frec[F] = make_uint2(cid[F], (uint32_t)key[fine_start[F]] & ((1u << lr3) - 1u));
 }
 
-// coarse-cell starts among the fine cells: flag[F] = 1 where F opens a coarse cell
-__global__ void k_coarse_flags(int64_t nfine, const uint32_t* __restrict__ fine_start,
+// coarse-cell starts among the fine cells: flag[F] = 1 where F < bound opens a
+// coarse cell
+__global__ void k_coarse_flags(int64_t bound, const uint32_t* __restrict__ nfine, const uint32_t* __restrict__ fine_start,
                                const uint64_t* __restrict__ key, int lr3, uint32_t* __restrict__ flag) {
     const int64_t F = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (F >= nfine) return;
-    flag[F] = (F == 0 || (key[fine_start[F]] >> lr3) != (key[fine_start[F - 1]] >> lr3)) ? 1u : 0u;
+    if (F >= bound) return;
+    flag[F] = F < *nfine && (F == 0 || (key[fine_start[F]] >> lr3) != (key[fine_start[F - 1]] >> lr3)) ? 1u : 0u;
 }
 
 // after an exclusive scan of the flags in place: cid[F] = coarse index of F,
 // cfs[c] = first fine cell of coarse cell c, cfs[ncoarse] = nfine
-__global__ void k_coarse_starts(int64_t nfine, const uint32_t* __restrict__ fine_start,
+__global__ void k_coarse_starts(const uint32_t* __restrict__ nfine, const uint32_t* __restrict__ fine_start,
                                 const uint64_t* __restrict__ key, int lr3, uint32_t* __restrict__ cid,
                                 uint32_t* __restrict__ cfs, unsigned long long* __restrict__ occ) {
     const int64_t F = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (F >= nfine) return;
+    if (F >= *nfine) return;
     const uint64_t ck = key[fine_start[F]] >> lr3;
     const bool start = F == 0 || ck != (key[fine_start[F - 1]] >> lr3);
     const uint32_t c = start ? cid[F] : cid[F] - 1;
@@ -440,7 +441,7 @@ __global__ void k_coarse_starts(int64_t nfine, const uint32_t* __restrict__ fine
         cfs[c] = (uint32_t)F;
         atomicOr(&occ[ck >> 6], 1ull << (ck & 63));
     }
-    if (F == nfine - 1) cfs[c + 1] = (uint32_t)nfine;
+    if (F == *nfine - 1) cfs[c + 1] = *nfine;
 }
 
 __device__ __forceinline__ int uf_root(const int* uf, int a) {
@@ -502,16 +503,16 @@ __global__ __launch_bounds__(64) void k_link_heavy(HeavyList H, Links K) {
 // index order (the sort is stable), so its first member's is its smallest:
 // every root first stores its own (no atomics for the many singletons), then
 // the other fine cells lower it.
-__global__ void k_root_idx_f(int64_t nfine, const int* __restrict__ uf, const uint32_t* __restrict__ fine_start,
+__global__ void k_root_idx_f(const uint32_t* __restrict__ nfine, const int* __restrict__ uf, const uint32_t* __restrict__ fine_start,
                              const uint32_t* __restrict__ idx, int* __restrict__ mn) {
     const int64_t F = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (F < nfine && uf[F] == (int)F) mn[F] = (int)idx[fine_start[F]];
+    if (F < *nfine && uf[F] == (int)F) mn[F] = (int)idx[fine_start[F]];
 }
 
-__global__ void k_min_orig_f(int64_t nfine, const int* __restrict__ uf, const uint32_t* __restrict__ fine_start,
+__global__ void k_min_orig_f(const uint32_t* __restrict__ nfine, const int* __restrict__ uf, const uint32_t* __restrict__ fine_start,
                              const uint32_t* __restrict__ idx, int* __restrict__ mn) {
     const int64_t F = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const bool valid = F < nfine && uf[F] != (int)F;
+    const bool valid = F < *nfine && uf[F] != (int)F;
     wave_atomic_min(mn, valid ? uf[F] : 0, valid ? (int)idx[fine_start[F]] : 0x7FFFFFFF, valid);
 }
 
@@ -527,6 +528,8 @@ bool fof3d_fine_applicable(int gb, int s) {
     const int b = gb - s;
     return b >= 2 && b <= 12;  // 4 .. 4096 coarse cells a side
 }
+
+constexpr int64_t FEW_PARTICLES = 131072;
 
 int fof3d_fine(vr_ctx* ctx, const vr_particles* p, double ell2, int s, int32_t* label, hipStream_t st) {
     const int64_t n = p->n;
@@ -566,8 +569,13 @@ int fof3d_fine(vr_ctx* ctx, const vr_particles* p, double ell2, int s, int32_t* 
     if ((rc = scan_u32(ctx, scan, scan, n, tot, st))) return rc;
     hipLaunchKernelGGL(k_fine_starts, dim3(gn), dim3(256), 0, st, n, key, scan, fine_start, fid);
     VR_LAUNCH_CHECK(ctx);
-    uint32_t nfine = 0;
-    if ((rc = read_back(ctx, tot, &nfine, sizeof nfine, st))) return rc;
+    // The kernels read the counts of cells from the device (tot); the host
+    // waits for them only where they save more than the wait: a small set
+    // without a workspace cap takes its particles for the bound of both (14 k
+    // particles: two waits of 20 us less).
+    const bool bound = n <= FEW_PARTICLES && ctx->max_ws == 0;
+    uint32_t nfine = (uint32_t)n;
+    if (!bound && (rc = read_back(ctx, tot, &nfine, sizeof nfine, st))) return rc;
     // coarse index per fine cell, first fine cell per coarse cell, the
     // occupancy bit of every coarse cell with prefix counts per 64 cells
     // (nc^3 / 8 + nc^3 / 16 bytes), and the records of both levels
@@ -583,13 +591,12 @@ int fof3d_fine(vr_ctx* ctx, const vr_particles* p, double ell2, int s, int32_t* 
     VR_WS(tables, ctx, uint64_t, WS_A8, 2 * 64 * NOFF);
     if ((rc = fill_u32(ctx, reinterpret_cast<uint32_t*>(occ), 0u, 2 * owords, st))) return rc;
     const unsigned gf = grid_for(nfine, 256);
-    hipLaunchKernelGGL(k_coarse_flags, dim3(gf), dim3(256), 0, st, (int64_t)nfine, fine_start, key, 3 * G.lr, cid);
+    hipLaunchKernelGGL(k_coarse_flags, dim3(gf), dim3(256), 0, st, (int64_t)nfine, tot, fine_start, key, 3 * G.lr, cid);
     VR_LAUNCH_CHECK(ctx);
-    if ((rc = scan_u32(ctx, cid, cid, nfine, tot, st))) return rc;
-    uint32_t ncoarse = 0;
-    if ((rc = read_back(ctx, tot, &ncoarse, sizeof ncoarse, st))) return rc;
-    hipLaunchKernelGGL(k_coarse_starts, dim3(gf), dim3(256), 0, st, (int64_t)nfine, fine_start, key, 3 * G.lr, cid,
-                       cfs, occ);
+    if ((rc = scan_u32(ctx, cid, cid, nfine, tot + 1, st))) return rc;
+    uint32_t ncoarse = nfine;
+    if (!bound && (rc = read_back(ctx, tot + 1, &ncoarse, sizeof ncoarse, st))) return rc;
+    hipLaunchKernelGGL(k_coarse_starts, dim3(gf), dim3(256), 0, st, tot, fine_start, key, 3 * G.lr, cid, cfs, occ);
     VR_LAUNCH_CHECK(ctx);
     hipLaunchKernelGGL(k_occ_count, dim3(grid_for(owords, 256)), dim3(256), 0, st, owords - 1,
                        reinterpret_cast<const uint64_t*>(occ), pre);
@@ -602,9 +609,9 @@ int fof3d_fine(vr_ctx* ctx, const vr_particles* p, double ell2, int s, int32_t* 
     const unsigned gc = grid_for(ncoarse, 256);
     hipLaunchKernelGGL(k_pair_tables, dim3(NOFF), dim3(64), 0, st, G, l2c, tables, tables + 64 * NOFF);
     VR_LAUNCH_CHECK(ctx);
-    hipLaunchKernelGGL(k_frec, dim3(gf), dim3(256), 0, st, (int64_t)nfine, fine_start, key, cid, 3 * G.lr, frec);
+    hipLaunchKernelGGL(k_frec, dim3(gf), dim3(256), 0, st, tot, fine_start, key, cid, 3 * G.lr, frec);
     VR_LAUNCH_CHECK(ctx);
-    hipLaunchKernelGGL(k_coarse_rec, dim3(gc), dim3(256), 0, st, (int64_t)ncoarse, cfs, frec, key, fine_start, G, occ_c,
+    hipLaunchKernelGGL(k_coarse_rec, dim3(gc), dim3(256), 0, st, tot + 1, cfs, frec, key, fine_start, G, occ_c,
                        crec, nbits);
     VR_LAUNCH_CHECK(ctx);
     VR_WS(cnt, ctx, int, WS_FLAG2, 4);
@@ -615,23 +622,23 @@ int fof3d_fine(vr_ctx* ctx, const vr_particles* p, double ell2, int s, int32_t* 
     const Links K{G, l2c, frec, crec, nbits, key, fine_start, occ_c, pre, tables, tables + 64 * NOFF, sx, sy, sz, uf};
     const unsigned xc = (unsigned)ctx->xcd_chunk;
     VR_TIMED(ctx, "fof_link3d", st, 0,
-             hipLaunchKernelGGL(k_hook, dim3(gf), dim3(256), 0, st, (int64_t)nfine, K);
-             hipLaunchKernelGGL(k_flatten, dim3(gf), dim3(256), 0, st, (int64_t)nfine, uf);
-             hipLaunchKernelGGL(k_coarse_root, dim3(gc), dim3(256), 0, st, (int64_t)ncoarse, uf, crec));
+             hipLaunchKernelGGL(k_hook, dim3(gf), dim3(256), 0, st, tot, K);
+             hipLaunchKernelGGL(k_flatten, dim3(gf), dim3(256), 0, st, tot, uf);
+             hipLaunchKernelGGL(k_coarse_root, dim3(gc), dim3(256), 0, st, tot + 1, uf, crec));
     VR_LAUNCH_CHECK(ctx);
     VR_TIMED(ctx, "fof_link3d", st, 0,
-             hipLaunchKernelGGL(k_link_cells<false>, dim3(gf), dim3(256), 0, st, (int64_t)nfine, K, xc, H);
-             hipLaunchKernelGGL(k_flatten, dim3(gf), dim3(256), 0, st, (int64_t)nfine, uf);
-             hipLaunchKernelGGL(k_coarse_root, dim3(gc), dim3(256), 0, st, (int64_t)ncoarse, uf, crec));
+             hipLaunchKernelGGL(k_link_cells<false>, dim3(gf), dim3(256), 0, st, tot, K, xc, H);
+             hipLaunchKernelGGL(k_flatten, dim3(gf), dim3(256), 0, st, tot, uf);
+             hipLaunchKernelGGL(k_coarse_root, dim3(gc), dim3(256), 0, st, tot + 1, uf, crec));
     VR_LAUNCH_CHECK(ctx);
     VR_TIMED(ctx, "fof_link3d", st, n,
-             hipLaunchKernelGGL(k_link_cells<true>, dim3(gf), dim3(256), 0, st, (int64_t)nfine, K, xc, H);
+             hipLaunchKernelGGL(k_link_cells<true>, dim3(gf), dim3(256), 0, st, tot, K, xc, H);
              hipLaunchKernelGGL(k_link_heavy, dim3((unsigned)(8 * ctx->num_cus)), dim3(64), 0, st, H, K);
-             hipLaunchKernelGGL(k_flatten, dim3(gf), dim3(256), 0, st, (int64_t)nfine, uf));
+             hipLaunchKernelGGL(k_flatten, dim3(gf), dim3(256), 0, st, tot, uf));
     VR_LAUNCH_CHECK(ctx);
-    hipLaunchKernelGGL(k_root_idx_f, dim3(gf), dim3(256), 0, st, (int64_t)nfine, uf, fine_start, idx, mn);
+    hipLaunchKernelGGL(k_root_idx_f, dim3(gf), dim3(256), 0, st, tot, uf, fine_start, idx, mn);
     VR_LAUNCH_CHECK(ctx);
-    hipLaunchKernelGGL(k_min_orig_f, dim3(gf), dim3(256), 0, st, (int64_t)nfine, uf, fine_start, idx, mn);
+    hipLaunchKernelGGL(k_min_orig_f, dim3(gf), dim3(256), 0, st, tot, uf, fine_start, idx, mn);
     VR_LAUNCH_CHECK(ctx);
     hipLaunchKernelGGL(k_label_f, dim3(gn), dim3(256), 0, st, n, uf, fid, idx, mn, label);
     VR_LAUNCH_CHECK(ctx);

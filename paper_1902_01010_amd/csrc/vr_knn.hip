@@ -963,8 +963,7 @@ extern "C" int vr_local_vdensity(vr_ctx* ctx, const vr_particles* p, int32_t n_h
         T.lbox = cv.add<float4>(2 * n_leaves);
         T.bbox = cv.add<float4>(2 * nb);
         T.leaf_bucket = cv.add<int>(n_leaves);
-        T.buckets = cv.add<int4>(nb);
-        T.host_bucket = cv.add<int>(n_hosts + 1);
+        T.buckets = cv.add<int4>(nb + (n_hosts + 4) / 4);  // and the hosts' first buckets, one upload
     };
     layout();
     const size_t total = cv.bytes;
@@ -978,8 +977,8 @@ extern "C" int vr_local_vdensity(vr_ctx* ctx, const vr_particles* p, int32_t n_h
         if (!up) return VR_ERR_HIP;
         std::memcpy(up, buckets.data(), b0);
         std::memcpy(up + b0, hb.data(), b1);
-        VR_HIP(ctx, hipMemcpyAsync(T.buckets, up, b0, hipMemcpyHostToDevice, st));
-        VR_HIP(ctx, hipMemcpyAsync(T.host_bucket, up + b0, b1, hipMemcpyHostToDevice, st));
+        VR_HIP(ctx, hipMemcpyAsync(T.buckets, up, b0 + b1, hipMemcpyHostToDevice, st));
+        T.host_bucket = reinterpret_cast<int*>(T.buckets + nb);
         if ((rc = upload_end(ctx, st))) return rc;
     }
     VR_WS(V, ctx, float4, WS_C0, n_slots);

@@ -57,3 +57,28 @@ def test_member_lists(vr, ref, n, cap):
     exp = ref.cell_moments(ref.Particles(q, v, None, 1.0, 1.0, BITS), off, mem)
     got = c.cell_moments(P, dev_tensor(off), dev_tensor(mem))
     assert (got["cell_of"].cpu().numpy() == exp["cell_of"]).all()
+
+
+@pytest.mark.parametrize("n", [1, 5, 4096, 131072, 131073])
+@pytest.mark.parametrize("share", [0.0, 0.4, 1.0])
+def test_groups_with_unlabelled(ctx, ref, n, share):
+    """A share of unlabelled particles, which small sets sort with the rest."""
+    rng = np.random.default_rng(n)
+    lab = rng.integers(0, max(1, n // 30), n)
+    lab[rng.random(n) < share] = -1
+    _, first, inv = np.unique(lab, return_index=True, return_inverse=True)
+    lab = np.where(lab < 0, -1, first[inv]).astype(np.int32)  # labels are smallest members
+    ng, of, off, mem = ctx.groups(dev_tensor(lab), 20)
+    eng, eof, eoff, emem = ref.groups(lab, 20)
+    assert ng == eng and (of.cpu().numpy() == eof).all() and (off.cpu().numpy() == eoff).all()
+    assert (mem.cpu().numpy()[:emem.size] == emem).all()
+
+
+@pytest.mark.parametrize("n", [5000, 131072])
+def test_labels_under_a_cap(vr, ref, n):
+    """With a workspace cap the cells' counts are waited for as in large sets."""
+    c = vr.Context(0, 1 << 30)
+    q, v = _clumps(n, n)
+    P = vr.Particles(dev_tensor(q.view(np.int32)), None, None, 1.0, 1.0, BITS)
+    exp = ref.fof3d(ref.Particles(q, None, None, 1.0, 1.0, BITS), 30.0 / (1 << BITS))
+    assert (c.fof3d(P, 30.0 / (1 << BITS)).cpu().numpy() == exp).all()
