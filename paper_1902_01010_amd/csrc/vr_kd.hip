@@ -114,15 +114,29 @@ __global__ void k_elems(int64_t M, int n_hosts, const int32_t* __restrict__ off,
         if (threadIdx.x == blockDim.x - 1) ends[1] = hm;
         __syncthreads();
         const bool one = ends[0] == ends[1];
-        for (int k = 0; k < 6; ++k) {
-            int v = k < 3 ? um[k] : -um[k - 3];
-            if (one) {
+        const int lane = threadIdx.x & 63;
+        if (one) {
+            for (int k = 0; k < 6; ++k) {
+                int v = k < 3 ? um[k] : -um[k - 3];
                 for (int o = 32; o > 0; o >>= 1) v = min(v, __shfl_xor(v, o, 64));
-                if ((threadIdx.x & 63) == 0) wmin[threadIdx.x >> 6][k] = v;
-            } else if (hm >= 0) {
-                int* at = hbox + 6 * (int64_t)hm + k;
-                if (v < *at) atomicMin(at, v);
+                if (lane == 0) wmin[threadIdx.x >> 6][k] = v;
             }
+        } else {
+            // hosts are runs of lanes: a minimum over each, then its last lane
+            int v[6] = {um[0], um[1], um[2], -um[0], -um[1], -um[2]};
+            for (int o = 1; o < 64; o <<= 1) {
+                const bool take = __shfl_up(hm, o, 64) == hm && lane >= o;
+                for (int k = 0; k < 6; ++k) {
+                    const int x = __shfl_up(v[k], o, 64);
+                    if (take) v[k] = min(v[k], x);
+                }
+            }
+            const int next = __shfl_down(hm, 1, 64);
+            if (hm >= 0 && (lane == 63 || next != hm))
+                for (int k = 0; k < 6; ++k) {
+                    int* at = hbox + 6 * (int64_t)hm + k;
+                    if (v[k] < *at) atomicMin(at, v[k]);
+                }
         }
         __syncthreads();
         if (one && threadIdx.x < 6) {
@@ -330,21 +344,29 @@ __global__ __launch_bounds__(256) void k_entropy(const int* __restrict__ nact, c
     }
 }
 
-// Reserves n slots of a global counter for each lane; one atomic per
-// wavefront.  Every lane of the wavefront must call it.
-__device__ __forceinline__ int wave_reserve(int* counter, int n) {
+// Reserves n[k] slots of each of three global counters for every lane; one
+// atomic per wavefront and counter, all three in flight.  Every lane of the
+// wavefront must call it.
+__device__ __forceinline__ void wave_reserve3(int* const (&counter)[3], const int (&n)[3], int (&first)[3]) {
     const int lane = __lane_id();
-    int x = n;
+    int x[3], base[3];
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int t = __shfl_up(x, o, 64);
-        if (lane >= o) x += t;
+    for (int k = 0; k < 3; ++k) {
+        x[k] = n[k];
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int t = __shfl_up(x[k], o, 64);
+            if (lane >= o) x[k] += t;
+        }
+        base[k] = 0;
     }
-    const int total = __shfl(x, 63, 64);
-    int base = 0;
-    if (lane == 63 && total > 0) base = atomicAdd(counter, total);
-    base = __shfl(base, 63, 64);
-    return base + x - n;
+    if (lane == 63) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+            if (x[k] > 0) base[k] = atomicAdd(counter[k], x[k]);
+    }
+#pragma unroll
+    for (int k = 0; k < 3; ++k) first[k] = __shfl(base[k], 63, 64) + x[k] - n[k];
 }
 
 // Split decision of every active node and creation of its children (their
@@ -365,17 +387,25 @@ __global__ __launch_bounds__(256) void k_split(const int* nact, const int* __res
     if (valid) {
         nd = nodes[id];
         if (mode >= KD_WIDEST) {
-            for (int d = 0; d < 3; ++d)
-                if ((mode == KD_BUCKETS || nd.bmax[d] > nd.bmin[d]) &&
-                    (best < 0 || nd.bmax[d] - nd.bmin[d] > nd.bmax[best] - nd.bmin[best]))
+            int widest = 0;
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                const int ext = nd.bmax[d] - nd.bmin[d];
+                if ((mode == KD_BUCKETS || ext > 0) && (best < 0 || ext > widest)) {
                     best = d;
+                    widest = ext;
+                }
+            }
         } else {
             const double S[3] = {Sdim[3 * (int64_t)i], Sdim[3 * (int64_t)i + 1], Sdim[3 * (int64_t)i + 2]};
+            double Sb = 0.0;
+#pragma unroll
             for (int d = 0; d < 3; ++d) {
                 if (nd.bmax[d] == nd.bmin[d]) continue;
-                if (best < 0) { best = d; continue; }
-                const bool better = mode == KD_MIN_ENTROPY ? (S[d] < S[best] - 1e-12) : (S[d] > S[best] + 1e-12);
-                if (better) best = d;
+                if (best < 0 || (mode == KD_MIN_ENTROPY ? S[d] < Sb - 1e-12 : S[d] > Sb + 1e-12)) {
+                    best = d;
+                    Sb = S[d];
+                }
             }
         }
     }
@@ -385,22 +415,28 @@ __global__ __launch_bounds__(256) void k_split(const int* nact, const int* __res
     const int n = split ? nd.end - nd.start : 0, nl = n / 2;
     const int nc = split ? ncell[nd.host] : 0;
     const bool lact = split && nl > nc, ract = split && n - nl > nc;
-    const int c0 = wave_reserve(&counters[CN_NODES], split ? 2 : 0);
-    const int na0 = wave_reserve(nnext, (int)lact + (int)ract);
-    const int nl0 = wave_reserve(&counters[CN_LEAVES], (int)stays + (split ? (int)!lact + (int)!ract : 0));
+    // the split value is fetched while the slots are reserved
+    const int* lb = best == 0 ? l0 : (best == 1 ? l1 : l2);
+    const int* ub = best == 0 ? u0 : (best == 1 ? u1 : u2);
+    const int t = split ? ub[lb[nd.start + nl]] : 0;
+    int slot[3];
+    wave_reserve3({&counters[CN_NODES], nnext, &counters[CN_LEAVES]},
+                  {split ? 2 : 0, (int)lact + (int)ract, (int)stays + (split ? (int)!lact + (int)!ract : 0)}, slot);
+    const int c0 = slot[0], na0 = slot[1], nl0 = slot[2];
     if (stays) {
         nodes[id].slot = -1;
         leaves[nl0] = id;
     }
     if (!split) return;
-    const int* lb = best == 0 ? l0 : (best == 1 ? l1 : l2);
-    const int* ub = best == 0 ? u0 : (best == 1 ? u1 : u2);
-    const int t = ub[lb[nd.start + nl]];
     KdNode L = nd, R = nd;
     L.end = nd.start + nl;
     R.start = nd.start + nl;
-    L.hi[best] = t - 1;
-    R.lo[best] = t;
+#pragma unroll
+    for (int d = 0; d < 3; ++d)
+        if (d == best) {
+            L.hi[d] = t - 1;
+            R.lo[d] = t;
+        }
     int ka = na0, kl = nl0;
     L.slot = lact ? ka++ : -1;
     R.slot = ract ? ka : -1;
