@@ -53,12 +53,13 @@ struct Removed {
 
 // Member-parallel set-up: member k of group g (found by bisection of the
 // offsets) gets its grid offsets from the group's first member, its
-// velocity and mass; its particle's bound flag and potential are reset.
+// velocity and mass; its sum, its particle's bound flag and potential are
+// reset.
 __global__ void k_ub_init(int ng, int64_t M, const int32_t* __restrict__ off, const int32_t* __restrict__ mem,
                           const uint32_t* __restrict__ qx, const uint32_t* __restrict__ qy,
                           const uint32_t* __restrict__ qz, const float* __restrict__ vx, const float* __restrict__ vy,
                           const float* __restrict__ vz, const float* __restrict__ mass, int gb, Members W,
-                          uint8_t* __restrict__ bound, double* __restrict__ phi) {
+                          double* __restrict__ acc, uint8_t* __restrict__ bound, double* __restrict__ phi) {
     const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= M) return;
     int lo = 0, hi = ng - 1;  // last group with off[g] <= k
@@ -72,6 +73,7 @@ __global__ void k_ub_init(int ng, int64_t M, const int32_t* __restrict__ off, co
     W.p[k] = make_float4((float)min_image((int)qx[i] - rx, gb), (float)min_image((int)qy[i] - ry, gb),
                          (float)min_image((int)qz[i] - rz, gb), mass ? mass[i] : 1.f);
     W.v[k] = make_float4(vx[i], vy[i], vz[i], __int_as_float(i));
+    acc[k] = 0.0;
     bound[i] = 0;
     phi[i] = NAN;
 }
@@ -477,6 +479,7 @@ __global__ __launch_bounds__(BS) void k_ub_group(const int* __restrict__ active,
     // members a thread, read before any is rewritten; the members before the
     // first removed one stay where they are.
     constexpr int CI = 4;
+    const int since0 = Rm.since[g];
     static_assert(CI * NW <= 64, "one wavefront scans the chunk's kept counts");
     uint32_t kept = 0, gone = 0;
     for (int c0 = 0; c0 < n; c0 += CI * BS) {
@@ -531,6 +534,13 @@ __global__ __launch_bounds__(BS) void k_ub_group(const int* __restrict__ active,
         gone += (uint32_t)min(CI * BS, n - c0) - tot;
         __syncthreads();
     }
+    // the next pass subtracts the removed terms while those removed since
+    // the last full recompute stay within a quarter of the survivors; else the
+    // sums start from zero
+    const int since = since0 + (int)gone;
+    const bool incr = 4 * (int64_t)since <= (int64_t)kept;
+    if (!incr && kept != (uint32_t)n)
+        for (int k = tid; k < (int)kept; k += blockDim.x) acc[base + k] = 0.0;
     if (kept == (uint32_t)n) {
         for (int k = tid; k < n; k += blockDim.x) bound[__float_as_int(W.v[base + k].w)] = 1;
         if (tid == 0) state[g] = ST_BOUND;
@@ -540,10 +550,6 @@ __global__ __launch_bounds__(BS) void k_ub_group(const int* __restrict__ active,
     if (tid == 0) {
         cnt[g] = (int)kept;
         iters[g] += 1;
-        // the next pass subtracts the removed terms while those removed since
-        // the last full recompute stay within a quarter of the survivors
-        const int since = Rm.since[g] + (int)gone;
-        const bool incr = 4 * (int64_t)since <= (int64_t)kept;
         Rm.nrm[g] = (int)gone;
         Rm.since[g] = incr ? since : 0;
         Rm.mode[g] = incr ? 1 : 0;
@@ -624,16 +630,6 @@ __global__ __launch_bounds__(PLAN_T) void k_ub_plan(int ng, const int* __restric
         plan->head = 0;
         plan->pairs += tp;
     }
-}
-
-__global__ void k_ub_zero_p(const UbPlan* __restrict__ plan, const int* __restrict__ act,
-                            const int32_t* __restrict__ off, const int* __restrict__ cnt, const int* __restrict__ mode,
-                            double* __restrict__ acc) {
-    if ((int)blockIdx.x >= plan->n_active) return;
-    const int g = act[blockIdx.x];
-    if (mode[g]) return;  // sums kept: the pass subtracts
-    const int s = off[g], e = s + cnt[g];
-    for (int k = s + threadIdx.x; k < e; k += blockDim.x) acc[k] = 0.0;
 }
 
 // Persistent potential kernel: wavefront w takes item w first, then pops
@@ -861,9 +857,9 @@ void ub_graph_release(vr_ctx* ctx) {
     ctx->ub_key.clear();
 }
 
-// One pass = plan (active list and work items) -> zero the accumulators of
-// the active groups -> persistent potential over the item queue -> one
-// workgroup per active group for frame, energies and compaction.  Passes are
+// One pass = plan (active list and work items) -> persistent potential over
+// the item queue -> one workgroup per active group for frame, energies,
+// compaction and, where the next pass recomputes, zeros for its sums.  Passes are
 // captured PASSES_PER_GRAPH at a time in a graph that is replayed until no
 // group is active; the host reads two counters per replay.
 int unbind_persistent(vr_ctx* ctx, const vr_particles* p, int32_t ng, const int32_t* offsets,
@@ -907,7 +903,6 @@ int unbind_persistent(vr_ctx* ctx, const vr_particles* p, int32_t ng, const int3
         for (int k = 0; k < PASSES_PER_GRAPH; ++k) {
             hipLaunchKernelGGL(k_ub_plan, dim3(1), dim3(PLAN_T), 0, cs, ng, cnt, state, iters, up->max_iter, jchunk,
                                Rm.nrm, Rm.mode, act, item_off, plan);
-            hipLaunchKernelGGL(k_ub_zero_p, dim3(ng), dim3(256), 0, cs, plan, act, offsets, cnt, Rm.mode, acc);
             if (uniform)
                 hipLaunchKernelGGL(k_ub_potential_p<true>, dim3(pgrid), dim3(UBP), lds, cs, plan, act, item_off,
                                    offsets, cnt, W.p, Rm.p, Rm.nrm, Rm.mode, eps2f, acc, jchunk);
@@ -1031,7 +1026,7 @@ extern "C" int vr_unbind(vr_ctx* ctx, const vr_particles* p, int32_t n_groups, c
                        ctx->unbind_wide, Rm, cnt, state, iters, nbig);
     VR_LAUNCH_CHECK(ctx);
     hipLaunchKernelGGL(k_ub_init, dim3(grid_for(M, 256)), dim3(256), 0, st, n_groups, (int64_t)M, offsets, members,
-                       p->qx, p->qy, p->qz, p->vx, p->vy, p->vz, p->mass, p->grid_bits, W, bound, phi);
+                       p->qx, p->qy, p->qz, p->vx, p->vy, p->vz, p->mass, p->grid_bits, W, acc, bound, phi);
     VR_LAUNCH_CHECK(ctx);
     const double unit = p->box / ldexp(1.0, p->grid_bits);
     const double epsg = up->eps / unit;
