@@ -323,9 +323,11 @@ __global__ void k_coarse_root(const uint32_t* __restrict__ ncoarse, const int* _
 // and the forward neighbours: the certain ones (TEST false), or the possible
 // ones that are not certain, by testing their particles.  The roots are
 // flattened when the pass starts; a partner whose parent is A's root is done.
-template <bool TEST>
+// LPC = 16: a lane per neighbour.
+template <bool TEST, int LPC>
 __global__ __launch_bounds__(256) void k_link_cells(const uint32_t* __restrict__ nfine, Links K, unsigned xchunk, HeavyList H) {
-    const int64_t A = (int64_t)xcd_swizzle(blockIdx.x, gridDim.x, xchunk) * blockDim.x + threadIdx.x;
+    const int64_t t = (int64_t)xcd_swizzle(blockIdx.x, gridDim.x, xchunk) * blockDim.x + threadIdx.x;
+    const int64_t A = t / LPC;
     if (A >= *nfine) return;
     const uint2 fr = K.frec[A];
     const uint32_t c = fr.x, a = fr.y;
@@ -376,12 +378,30 @@ __global__ __launch_bounds__(256) void k_link_cells(const uint32_t* __restrict__
         const uint64_t mc = K.cert[a * NOFF + o];
         return TEST ? K.poss[a * NOFF + o] & ~mc : mc;
     };
+    if constexpr (LPC == 16) {
+        // a lane a neighbour, the first one for the own cell
+        const int part = (int)(t % LPC), o = OWN + part;
+        if (part > 0) {
+            if (part > 13 || !((fwd >> (part - 1)) & 1u)) return;
+            const uint64_t ck = K.key[K.fine_start[own.z]] >> (3 * K.G.lr);
+            const int r = o / 3, d = o % 3;
+            uint32_t c2 = c + 1;  // the own row's last neighbour follows the own cell
+            NeighbourRow n;
+            if (r > 4 || ((int)(ck & (K.G.nc - 1)) == K.G.nc - 1)) {
+                n = neighbour_row(K, ck, r);
+                c2 = neighbour(K, n, r == 4 ? 4u : (fwd >> (3 * r - OWN - 1)) & 7u, d);
+            }
+            const uint4 cr = K.crec[c2];
+            if ((int)cr.w != r0) partners(cr, mask_of(cr) & candidates(o));
+            return;
+        }
+    }
     if ((int)own.w != r0) {
         const uint64_t later = a == 63 ? 0ull : ~0ull << (a + 1);
         const uint64_t m = mask_of(own) & later;
         if (m) partners(own, m & candidates(OWN));
     }
-    if (!fwd) return;
+    if (LPC > 1 || !fwd) return;
     const uint64_t ck = K.key[K.fine_start[own.z]] >> (3 * K.G.lr);
     // rows 4 (behind the own cell) to 8
     for (int r = 4; r < 9; ++r) {
@@ -529,6 +549,12 @@ bool fof3d_fine_applicable(int gb, int s) {
     return b >= 2 && b <= 12;  // 4 .. 4096 coarse cells a side
 }
 
+// Up to this many particles the link passes take a lane per fine cell and
+// neighbour: their time is the longest chain of one cell's partners (14 k
+// particles 98 -> 44 us in the testing pass, 44 k 114 -> 84), beyond it the
+// pairs that threads test before others have joined them (66 k 96 -> 101,
+// 118 k 93 -> 146, 256^3 2.07 -> 4.35 ms).
+constexpr int64_t LANE_PER_NEIGHBOUR = 32768;
 constexpr int64_t FEW_PARTICLES = 131072;
 
 int fof3d_fine(vr_ctx* ctx, const vr_particles* p, double ell2, int s, int32_t* label, hipStream_t st) {
@@ -621,18 +647,21 @@ int fof3d_fine(vr_ctx* ctx, const vr_particles* p, double ell2, int s, int32_t* 
     const HeavyList H{reinterpret_cast<uint2*>(cid), cnt, (uint32_t)(n / 2)};
     const Links K{G, l2c, frec, crec, nbits, key, fine_start, occ_c, pre, tables, tables + 64 * NOFF, sx, sy, sz, uf};
     const unsigned xc = (unsigned)ctx->xcd_chunk;
+    const bool lanes = n <= LANE_PER_NEIGHBOUR;
     VR_TIMED(ctx, "fof_link3d", st, 0,
              hipLaunchKernelGGL(k_hook, dim3(gf), dim3(256), 0, st, tot, K);
              hipLaunchKernelGGL(k_flatten, dim3(gf), dim3(256), 0, st, tot, uf);
              hipLaunchKernelGGL(k_coarse_root, dim3(gc), dim3(256), 0, st, tot + 1, uf, crec));
     VR_LAUNCH_CHECK(ctx);
     VR_TIMED(ctx, "fof_link3d", st, 0,
-             hipLaunchKernelGGL(k_link_cells<false>, dim3(gf), dim3(256), 0, st, tot, K, xc, H);
+             if (lanes) hipLaunchKernelGGL((k_link_cells<false, 16>), dim3(16 * gf), dim3(256), 0, st, tot, K, xc, H);
+             else hipLaunchKernelGGL((k_link_cells<false, 1>), dim3(gf), dim3(256), 0, st, tot, K, xc, H);
              hipLaunchKernelGGL(k_flatten, dim3(gf), dim3(256), 0, st, tot, uf);
              hipLaunchKernelGGL(k_coarse_root, dim3(gc), dim3(256), 0, st, tot + 1, uf, crec));
     VR_LAUNCH_CHECK(ctx);
     VR_TIMED(ctx, "fof_link3d", st, n,
-             hipLaunchKernelGGL(k_link_cells<true>, dim3(gf), dim3(256), 0, st, tot, K, xc, H);
+             if (lanes) hipLaunchKernelGGL((k_link_cells<true, 16>), dim3(16 * gf), dim3(256), 0, st, tot, K, xc, H);
+             else hipLaunchKernelGGL((k_link_cells<true, 1>), dim3(gf), dim3(256), 0, st, tot, K, xc, H);
              hipLaunchKernelGGL(k_link_heavy, dim3((unsigned)(8 * ctx->num_cus)), dim3(64), 0, st, H, K);
              hipLaunchKernelGGL(k_flatten, dim3(gf), dim3(256), 0, st, tot, uf));
     VR_LAUNCH_CHECK(ctx);

@@ -59,3 +59,17 @@ def test_many_particles_at_the_reach(ctx, vr, ref, gap, joined):
     q = np.concatenate([a, b + np.array([[99 + gap], [0], [0]])], axis=1).astype(np.int64) + x0
     lab = _labels(ctx, vr, ref, q.astype(np.uint32), 21, 1500.0)
     assert (lab[0] == lab[3000]) == joined
+
+
+@pytest.mark.parametrize("bits,ell_u,scale", [(21, 1500.0, 3000.0), (12, 0.9, 6.0), (12, 2.9, 12.0), (10, 200.0, 60.0),
+                                              (10, 255.9, 200.0), (12, 900.0, 700.0)])
+@pytest.mark.parametrize("n", [32768, 32769])
+def test_lane_per_cell_and_per_neighbour(ctx, vr, ref, bits, ell_u, scale, n):
+    """The same shapes on both sides of the size from which on a lane takes all
+    of a cell's neighbours."""
+    rng = np.random.default_rng(n + int(ell_u))
+    size = 1 << bits
+    a, b = n // 2, n // 3
+    pos = np.concatenate([rng.normal(0, scale, (3, a)), rng.normal(0, 5 * scale, (3, b)),
+                          rng.uniform(0, size, (3, n - a - b))], axis=1)
+    _labels(ctx, vr, ref, np.mod(np.rint(pos), size).astype(np.uint32), bits, ell_u)
