@@ -317,9 +317,10 @@ int build_cell_list(vr_ctx* ctx, int64_t n, const uint32_t* qx, const uint32_t* 
     if (!ncell_dev) return VR_ERR_OUT_OF_MEMORY;
     rc = scan_u32(ctx, flag, flag, n, ncell_dev, st);
     if (rc) return rc;
-    uint32_t ncell = 0;
-    rc = read_back(ctx, ncell_dev, &ncell, sizeof ncell, st);
-    if (rc) return rc;
+    // a small set without a workspace cap is sized for a cell per point
+    // instead of waiting 20 us for their number
+    uint32_t ncell = (uint32_t)n;
+    if ((n > 131072 || ctx->max_ws != 0) && (rc = read_back(ctx, ncell_dev, &ncell, sizeof ncell, st))) return rc;
     uint32_t hsize = 1024;
     while (hsize < 2u * ncell) hsize <<= 1;
     VR_WS(hkeys, ctx, ckey_t, WS_A7, hsize);
@@ -329,7 +330,7 @@ int build_cell_list(vr_ctx* ctx, int64_t n, const uint32_t* qx, const uint32_t* 
     hipLaunchKernelGGL(k_cell_starts, dim3(grid_for(n, 256)), dim3(256), 0, st, n, key, flag, cstart, hkeys, hvals,
                        hsize - 1);
     VR_LAUNCH_CHECK(ctx);
-    cl = CellList{key, idx, sx, sy, sz, cstart, hkeys, hvals, hsize - 1, (int64_t)ncell};
+    cl = CellList{key, idx, sx, sy, sz, cstart, hkeys, hvals, hsize - 1, (int64_t)ncell, ncell_dev};
     return VR_OK;
 }
 

@@ -288,19 +288,21 @@ __global__ __launch_bounds__(256) void k_link6d(int64_t np, const ckey_t* __rest
 // gives every cell its first tile.
 constexpr uint32_t HEAVY_CELL = 64;
 
-__global__ void k_tile_count(int64_t ncell, const uint32_t* __restrict__ cell_start, uint32_t* __restrict__ cnt) {
+// ncell: their number or a bound of it, *cells: their number.
+__global__ void k_tile_count(int64_t ncell, const uint32_t* __restrict__ cells, const uint32_t* __restrict__ cell_start,
+                             uint32_t* __restrict__ cnt) {
     const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= ncell) return;
-    const uint32_t m = cell_start[c + 1] - cell_start[c];
+    const uint32_t m = c < *cells ? cell_start[c + 1] - cell_start[c] : 0u;
     const uint32_t nt = (m + 63) >> 6;
     cnt[c] = m >= HEAVY_CELL ? nt : 0;
     cnt[ncell + c] = m >= HEAVY_CELL ? 0 : nt;
 }
 
-__global__ void k_tile_write(int64_t ncell, const uint32_t* __restrict__ cell_start, const uint32_t* __restrict__ toff,
-                             int2* __restrict__ tiles) {
+__global__ void k_tile_write(int64_t ncell, const uint32_t* __restrict__ cells, const uint32_t* __restrict__ cell_start,
+                             const uint32_t* __restrict__ toff, int2* __restrict__ tiles) {
     const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= ncell) return;
+    if (c >= *cells) return;
     const uint32_t s = cell_start[c], e = cell_start[c + 1];
     uint32_t t = e - s >= HEAVY_CELL ? toff[c] : toff[ncell + c];
     for (uint32_t q = s; q < e; q += 64) tiles[t++] = make_int2((int)c, (int)q);
@@ -942,10 +944,11 @@ int link_outliers(vr_ctx* ctx, const vr_particles* p, const int32_t* host_of, co
         VR_WS(tcnt, ctx, uint32_t, WS_D8, 2 * ncell + 1);
         VR_WS(ttot, ctx, uint32_t, WS_D9, 4);
         VR_WS(tiles, ctx, int2, WS_B7, tmax);
-        hipLaunchKernelGGL(k_tile_count, dim3(grid_for(ncell, 256)), dim3(256), 0, st, ncell, cl.cell_start, tcnt);
+        hipLaunchKernelGGL(k_tile_count, dim3(grid_for(ncell, 256)), dim3(256), 0, st, ncell, cl.n_cells_dev, cl.cell_start, tcnt);
         VR_LAUNCH_CHECK(ctx);
         if ((rc = scan_u32(ctx, tcnt, tcnt, 2 * ncell, ttot, st))) return rc;
-        hipLaunchKernelGGL(k_tile_write, dim3(grid_for(ncell, 256)), dim3(256), 0, st, ncell, cl.cell_start, tcnt, tiles);
+        hipLaunchKernelGGL(k_tile_write, dim3(grid_for(ncell, 256)), dim3(256), 0, st, ncell, cl.n_cells_dev, cl.cell_start, tcnt,
+                           tiles);
         VR_LAUNCH_CHECK(ctx);
 #define VR_LINK6T(PAPER)                                                                                           \
         VR_TIMED(ctx, sub ? "fof_link_sub" : "fof_link6d", st, np,                                               \

@@ -99,7 +99,8 @@ struct CellList {
     ckey_t* hkeys;
     uint32_t* hvals;
     uint32_t hmask;
-    int64_t n_cells;
+    int64_t n_cells;          // their number, or a bound of it
+    const uint32_t* n_cells_dev;
 };
 
 // 3D FOF on the two-level grid (coarse cells of side 2^s, fine cells whose

@@ -107,10 +107,10 @@ __global__ void k_pos_roots(int64_t ndm, const uint32_t* __restrict__ idx, const
 // per cell, since a thread alone with the members of a densest cell (5,000, a
 // chain of three lookups each) took 1.35 ms for 1 M particles; both kernels
 // now 110 us.
-__global__ __launch_bounds__(256) void k_cell_roots(int64_t ncell, const uint32_t* __restrict__ cstart,
+__global__ __launch_bounds__(256) void k_cell_roots(const uint32_t* __restrict__ cells, const uint32_t* __restrict__ cstart,
                                                     const int32_t* __restrict__ proot, int32_t* __restrict__ uroot) {
     const int lane = (int)lane_id();
-    for (int64_t c = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); c < ncell; c += (int64_t)gridDim.x * 4) {
+    for (int64_t c = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); c < *cells; c += (int64_t)gridDim.x * 4) {
         const uint32_t s = cstart[c], e = cstart[c + 1];
         const int u = proot[s];
         bool same = true;
@@ -892,7 +892,7 @@ extern "C" int vr_fof3d_dm(vr_ctx* ctx, const vr_particles* p, double ellx, cons
             VR_WS(uroot, ctx, int32_t, WS_C8, cl.n_cells + 1);
             hipLaunchKernelGGL(k_pos_roots, dim3(grid_for(ndm, 256)), dim3(256), 0, st, ndm, cl.idx, orig, labc, proot);
             hipLaunchKernelGGL(k_cell_roots, dim3(std::min(grid_for(cl.n_cells, 4), 1u << 18)), dim3(256), 0, st,
-                               cl.n_cells, cl.cell_start, proot, uroot);
+                               cl.n_cells_dev, cl.cell_start, proot, uroot);
             VR_LAUNCH_CHECK(ctx);
             VR_TIMED(ctx, "fof_attach", st, n - ndm,
                      hipLaunchKernelGGL(k_attach, dim3(grid_for(n, 256)), dim3(256), 0, st, n, is_baryon, p->qx,
