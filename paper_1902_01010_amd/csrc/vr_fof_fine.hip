@@ -530,8 +530,8 @@ __global__ void k_root_idx_f(const uint32_t* __restrict__ nfine, const int* __re
 }
 
 __global__ void k_min_orig_f(const uint32_t* __restrict__ nfine, const int* __restrict__ uf, const uint32_t* __restrict__ fine_start,
-                             const uint32_t* __restrict__ idx, int* __restrict__ mn) {
-    const int64_t F = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+                             const uint32_t* __restrict__ idx, int* __restrict__ mn, int stride) {
+    const int64_t F = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * stride;
     const bool valid = F < *nfine && uf[F] != (int)F;
     wave_atomic_min(mn, valid ? uf[F] : 0, valid ? (int)idx[fine_start[F]] : 0x7FFFFFFF, valid);
 }
@@ -667,7 +667,10 @@ int fof3d_fine(vr_ctx* ctx, const vr_particles* p, double ell2, int s, int32_t* 
     VR_LAUNCH_CHECK(ctx);
     hipLaunchKernelGGL(k_root_idx_f, dim3(gf), dim3(256), 0, st, tot, uf, fine_start, idx, mn);
     VR_LAUNCH_CHECK(ctx);
-    hipLaunchKernelGGL(k_min_orig_f, dim3(gf), dim3(256), 0, st, tot, uf, fine_start, idx, mn);
+    if (nfine > 65536)
+        hipLaunchKernelGGL(k_min_orig_f, dim3(grid_for(nfine, 64 * 256)), dim3(256), 0, st, tot, uf, fine_start, idx, mn,
+                           64);
+    hipLaunchKernelGGL(k_min_orig_f, dim3(gf), dim3(256), 0, st, tot, uf, fine_start, idx, mn, 1);
     VR_LAUNCH_CHECK(ctx);
     hipLaunchKernelGGL(k_label_f, dim3(gn), dim3(256), 0, st, n, uf, fid, idx, mn, label);
     VR_LAUNCH_CHECK(ctx);
