@@ -89,9 +89,10 @@ __global__ void k_rs_starts(int64_t m, const uint32_t* __restrict__ flag, const 
 
 // A slot of the table of occupied cells: one 16-byte load a lookup brings the
 // cell and its members with the key.  Three arrays, three sectors a lookup:
-// 2 M particles' fine cells 365 us, now 290, coarse ones 57, now 35.  Bound by
-// the lookups' random lines, 27 a window; eight cells along x on one line
-// brought fewer of them but longer probes (564 and 116 us).
+// 2 M particles' fine cells 365 us, now 290.  Bound by the lookups' random
+// lines, 27 a window; eight cells along x on one line brought fewer of them but
+// longer probes (564 us).  Of a coarse cell, `cell` becomes the members of its
+// 27-cell window.
 struct alignas(16) Cell {
     unsigned long long key;
     uint32_t cell, count;
@@ -114,6 +115,30 @@ __global__ void k_rs_insert(uint32_t ncells, const uint64_t* __restrict__ keys, 
         if (prev == EMPTY64 || prev == k) {
             table[h].cell = c;
             table[h].count = n;
+            return;
+        }
+        h = (h + 1) & hmask;
+    }
+}
+
+// The coarse cells (4 fine cells a side) and their members from the fine ones:
+// a second sort of the members, its cells and the wait for their number cost
+// 250 us for 2 M particles.
+__global__ void k_rs_coarse(uint32_t ncells, const uint64_t* __restrict__ keys, const uint32_t* __restrict__ start,
+                            int b, uint32_t hmask, Cell* __restrict__ table) {
+    const uint32_t c = blockIdx.x * blockDim.x + threadIdx.x;
+    if (c >= ncells) return;
+    const uint32_t s = start[c], n = start[c + 1] - s;
+    const uint64_t key = keys[s];
+    const uint32_t mask = (1u << b) - 1u;
+    const unsigned long long k = cell_key((uint32_t)(key & mask) >> 2, (uint32_t)((key >> b) & mask) >> 2,
+                                          (uint32_t)(key >> (2 * b)) >> 2, b - 2);
+    uint32_t h = hash64(k, hmask);
+    for (;;) {
+        unsigned long long prev = table[h].key;
+        if (prev == EMPTY64) prev = atomicCAS(&table[h].key, (unsigned long long)EMPTY64, k);
+        if (prev == EMPTY64 || prev == k) {
+            atomicAdd(&table[h].count, n);
             return;
         }
         h = (h + 1) & hmask;
@@ -177,8 +202,7 @@ __global__ void k_rs_vsum(uint32_t ncells, const uint32_t* __restrict__ start, c
 struct Level {
     const Cell* table;
     uint32_t hmask;
-    const uint32_t* start;
-    int cbits, b;
+    int b;
 };
 
 // Eigen-decomposition of a symmetric 3x3 matrix by cyclic Jacobi rotations
@@ -275,16 +299,17 @@ struct FeatNorm {
 };
 
 // Members in the 27-cell window of every occupied coarse cell (the fallback
-// density of the fine cells inside it), once per coarse cell.
-__global__ __launch_bounds__(256) void k_rs_coarsewin(uint32_t ncells, const uint64_t* __restrict__ keys,
-                                                      Level coarse, uint32_t* __restrict__ cwin) {
-    const uint32_t c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= ncells) return;
-    const uint64_t key = keys[coarse.start[c]];
+// density of the fine cells inside it), once per coarse cell: a lane a slot
+// of the table.
+__global__ __launch_bounds__(256) void k_rs_coarsewin(Level coarse, Cell* __restrict__ table) {
+    const uint32_t h = blockIdx.x * blockDim.x + threadIdx.x;
+    if (h > coarse.hmask) return;
+    const uint64_t key = table[h].key;
+    if (key == EMPTY64) return;
     const uint32_t mask = (1u << coarse.b) - 1u;
     Cell face[7];
-    cwin[c] = window_count(coarse, (uint32_t)(key & mask), (uint32_t)((key >> coarse.b) & mask),
-                           (uint32_t)(key >> (2 * coarse.b)), face);
+    table[h].cell = window_count(coarse, (uint32_t)(key & mask), (uint32_t)((key >> coarse.b) & mask),
+                                 (uint32_t)(key >> (2 * coarse.b)), face);
 }
 
 // What a row's features take from its fine cell alone, once per occupied
@@ -294,12 +319,12 @@ __global__ __launch_bounds__(256) void k_rs_coarsewin(uint32_t ncells, const uin
 // cell and its six face neighbours.  cf[4 c .. 4 c + 3] = (f0, vloc).
 // (four wavefronts a SIMD: 343 -> 291 us with the registers that takes)
 __global__ __launch_bounds__(256, 4) void k_rs_cellfeat(uint32_t ncells, const uint64_t* __restrict__ keys,
-                                                     Level fine, Level coarse, const uint32_t* __restrict__ cwin,
+                                                     const uint32_t* __restrict__ start, Level fine, Level coarse,
                                                      const double* __restrict__ vsum, int n_se, double cell_len,
                                                      double* __restrict__ cf) {
     const uint32_t c = blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= ncells) return;
-    const uint64_t key = keys[fine.start[c]];
+    const uint64_t key = keys[start[c]];
     const uint32_t mask = (1u << fine.b) - 1u;
     const uint32_t cx = (uint32_t)(key & mask), cy = (uint32_t)((key >> fine.b) & mask),
                    cz = (uint32_t)(key >> (2 * fine.b));
@@ -315,7 +340,7 @@ __global__ __launch_bounds__(256, 4) void k_rs_cellfeat(uint32_t ncells, const u
         const uint64_t ck = cell_key((cx >> 2) & cmask, (cy >> 2) & cmask, (cz >> 2) & cmask, coarse.b);
         const uint32_t h = hash64(ck, coarse.hmask);
         const Cell e = find_from(coarse.table, coarse.hmask, ck, h, load_slot(coarse.table, h));
-        const uint32_t nc = e.key == ck ? cwin[e.cell] : 0u;
+        const uint32_t nc = e.key == ck ? e.cell : 0u;
         const double L4 = 4.0 * cell_len;
         nhat = (double)nc / (27.0 * L4 * L4 * L4);
     }
@@ -960,75 +985,58 @@ int vr_rs_features(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const in
         nrm.shift[k] = shift ? shift[k] : 0.f;
         nrm.scale[k] = scale ? scale[k] : 1.f;
     }
-    Level lv[2];
-    const int cb[2] = {cell_bits, cell_bits + 2};
-    double* vsum = nullptr;
-    const uint32_t* order = nullptr;
-    const uint32_t* head0 = nullptr;
-    const uint32_t* cid0 = nullptr;
-    const uint64_t* keys0 = nullptr;
-    const uint64_t* keys1 = nullptr;
-    uint32_t ncell[2] = {0, 0};
-    for (int L = 0; L < 2; ++L) {
-        const int b = p->grid_bits - cb[L];
-        VR_WS(keys, ctx, uint64_t, WS_A0 + 4 * L, m);
-        VR_WS(rws, ctx, uint32_t, WS_A1 + 4 * L, m);
-        VR_WS(flag, ctx, uint32_t, WS_A2 + 4 * L, m);
-        VR_WS(cid, ctx, uint32_t, WS_A3 + 4 * L, m);
-        uint64_t* kin;
-        uint32_t* rin;
-        if ((rc = sort_input_u64(ctx, keys, rws, m, 3 * b, &kin, &rin))) return rc;
-        hipLaunchKernelGGL(k_rs_keys, dim3(grid_for(m, 256)), dim3(256), 0, st, m, host_members, p->qx, p->qy, p->qz,
-                           cb[L], b, kin, rin);
-        VR_LAUNCH_CHECK(ctx);
-        if ((rc = sort_pairs_u64_from(ctx, kin, rin, keys, rws, m, 3 * b, st))) return rc;
-        hipLaunchKernelGGL(k_rs_heads, dim3(grid_for(m, 256)), dim3(256), 0, st, m, keys, flag);
-        VR_LAUNCH_CHECK(ctx);
-        uint32_t* tot = reinterpret_cast<uint32_t*>(ctx->pinned);
-        VR_WS(totd, ctx, uint32_t, WS_FLAG, 4);
-        if ((rc = scan_u32(ctx, flag, cid, m, totd, st))) return rc;
-        if ((rc = read_back(ctx, totd, tot, sizeof(uint32_t), st))) return rc;
-        const uint32_t ncells = *tot;
-        VR_WS(start, ctx, uint32_t, WS_B0 + 3 * L, (size_t)ncells + 1);
-        hipLaunchKernelGGL(k_rs_starts, dim3(grid_for(m, 256)), dim3(256), 0, st, m, flag, cid, start, ncells);
-        VR_LAUNCH_CHECK(ctx);
-        uint32_t hsize = 64;
-        while (hsize < 2u * ncells) hsize <<= 1;
-        VR_WS(table, ctx, Cell, WS_B1 + 3 * L, hsize);
-        hipLaunchKernelGGL(k_rs_clear, dim3(grid_for(hsize, 256)), dim3(256), 0, st, table, hsize);
-        VR_LAUNCH_CHECK(ctx);
-        hipLaunchKernelGGL(k_rs_insert, dim3(grid_for(ncells, 256)), dim3(256), 0, st, ncells, keys, start, hsize - 1,
-                           table);
-        VR_LAUNCH_CHECK(ctx);
-        lv[L] = Level{table, hsize - 1, start, cb[L], b};
-        ncell[L] = ncells;
-        if (L == 1) keys1 = keys;
-        if (L == 0) {
-            head0 = flag;
-            cid0 = cid;
-            keys0 = keys;
-            VR_WS(vs, ctx, double, WS_B6, 3 * (size_t)ncells);
-            hipLaunchKernelGGL(k_rs_vsum, dim3(grid_for(ncells, 256)), dim3(256), 0, st, ncells, start, rws,
-                               host_members, p->vx, p->vy, p->vz, vs);
-            VR_LAUNCH_CHECK(ctx);
-            vsum = vs;
-            order = rws;
-        }
-    }
+    const int b = p->grid_bits - cell_bits;
+    VR_WS(keys, ctx, uint64_t, WS_A0, m);
+    VR_WS(order, ctx, uint32_t, WS_A1, m);
+    VR_WS(head, ctx, uint32_t, WS_A2, m);
+    VR_WS(cid, ctx, uint32_t, WS_A3, m);
+    uint64_t* kin;
+    uint32_t* rin;
+    if ((rc = sort_input_u64(ctx, keys, order, m, 3 * b, &kin, &rin))) return rc;
+    hipLaunchKernelGGL(k_rs_keys, dim3(grid_for(m, 256)), dim3(256), 0, st, m, host_members, p->qx, p->qy, p->qz,
+                       cell_bits, b, kin, rin);
+    VR_LAUNCH_CHECK(ctx);
+    if ((rc = sort_pairs_u64_from(ctx, kin, rin, keys, order, m, 3 * b, st))) return rc;
+    hipLaunchKernelGGL(k_rs_heads, dim3(grid_for(m, 256)), dim3(256), 0, st, m, keys, head);
+    VR_LAUNCH_CHECK(ctx);
+    VR_WS(totd, ctx, uint32_t, WS_FLAG, 4);
+    if ((rc = scan_u32(ctx, head, cid, m, totd, st))) return rc;
+    uint32_t ncells = 0;
+    if ((rc = read_back(ctx, totd, &ncells, sizeof ncells, st))) return rc;
+    VR_WS(start, ctx, uint32_t, WS_B0, (size_t)ncells + 1);
+    hipLaunchKernelGGL(k_rs_starts, dim3(grid_for(m, 256)), dim3(256), 0, st, m, head, cid, start, ncells);
+    VR_LAUNCH_CHECK(ctx);
+    // at most three slots in four taken (the coarse cells are no more than
+    // the fine ones)
+    uint32_t hsize = 64;
+    while (3ull * hsize < 4ull * ncells) hsize <<= 1;
+    VR_WS(ftab, ctx, Cell, WS_B1, hsize);
+    VR_WS(ctab, ctx, Cell, WS_B4, hsize);
+    for (Cell* t : {ftab, ctab})
+        hipLaunchKernelGGL(k_rs_clear, dim3(grid_for(hsize, 256)), dim3(256), 0, st, t, hsize);
+    VR_LAUNCH_CHECK(ctx);
+    hipLaunchKernelGGL(k_rs_insert, dim3(grid_for(ncells, 256)), dim3(256), 0, st, ncells, keys, start, hsize - 1, ftab);
+    VR_LAUNCH_CHECK(ctx);
+    hipLaunchKernelGGL(k_rs_coarse, dim3(grid_for(ncells, 256)), dim3(256), 0, st, ncells, keys, start, b, hsize - 1,
+                       ctab);
+    VR_LAUNCH_CHECK(ctx);
+    VR_WS(vsum, ctx, double, WS_B6, 3 * (size_t)ncells);
+    hipLaunchKernelGGL(k_rs_vsum, dim3(grid_for(ncells, 256)), dim3(256), 0, st, ncells, start, order, host_members,
+                       p->vx, p->vy, p->vz, vsum);
+    VR_LAUNCH_CHECK(ctx);
     const double cell_len = ldexp(p->box, cell_bits - p->grid_bits);
-    VR_WS(cf, ctx, double, WS_C0, 4 * (size_t)ncell[0]);
-    VR_WS(cwin, ctx, uint32_t, WS_C1, (size_t)ncell[1]);
+    VR_WS(cf, ctx, double, WS_C0, 4 * (size_t)ncells);
+    const Level fine{ftab, hsize - 1, b}, coarse{ctab, hsize - 1, b - 2};
     VR_TIMED(ctx, "rs_features", st, 0,
-             hipLaunchKernelGGL(k_rs_coarsewin, dim3(grid_for(ncell[1], 256)), dim3(256), 0, st, ncell[1], keys1, lv[1],
-                                cwin));
+             hipLaunchKernelGGL(k_rs_coarsewin, dim3(grid_for(hsize, 256)), dim3(256), 0, st, coarse, ctab));
     VR_LAUNCH_CHECK(ctx);
     VR_TIMED(ctx, "rs_features", st, 0,
-             hipLaunchKernelGGL(k_rs_cellfeat, dim3(grid_for(ncell[0], 256)), dim3(256), 0, st, ncell[0], keys0, lv[0],
-                                lv[1], cwin, vsum, n_se, cell_len, cf));
+             hipLaunchKernelGGL(k_rs_cellfeat, dim3(grid_for(ncells, 256)), dim3(256), 0, st, ncells, keys, start, fine,
+                                coarse, vsum, n_se, cell_len, cf));
     VR_LAUNCH_CHECK(ctx);
     VR_TIMED(ctx, "rs_features", st, m,
              hipLaunchKernelGGL(k_rs_features, dim3(grid_for(m, 256)), dim3(256), 0, st, m, host_members, p->vx, p->vy,
-                                p->vz, vbar, sigma, rho_cell, p->n, head0, cid0, cf, nrm, order, feat));
+                                p->vz, vbar, sigma, rho_cell, p->n, head, cid, cf, nrm, order, feat));
     VR_LAUNCH_CHECK(ctx);
     return VR_OK;
 }
