@@ -677,6 +677,8 @@ __global__ __launch_bounds__(64, 4) void k_knn(const uint32_t* __restrict__ qpos
         if (!__ballot(less)) break;
         if (less) h2 = nx;
     }
+    // fewer than n_v finite distances: no bandwidth
+    if (count_v(h2) < n_v) h2 = (double)NAN;
     double sw = 0.0;
     const double kW = 15.0 / (8.0 * M_PI);
 #pragma unroll

@@ -106,3 +106,23 @@ def test_host_wider_than_half_the_box(ctx, vr, ref, n_se, n_v):
     x[:, 0] = 0.5
     case[0].x[:, :6000] = x
     _check(ctx, vr, ref, case, n_se, n_v)
+
+
+@pytest.mark.parametrize("n_se,n_v", [(32, 8), (32, 32), (48, 16), (256, 32)])
+def test_infinite_velocities(ctx, vr, ref, n_se, n_v):
+    """R of the members of finite velocity where enough of the neighbours have
+    one, and no number where too few do."""
+    rng = np.random.default_rng(8)
+    w, off, mem, vbar, sigma = _hosts(rng, [600, 600])
+    few = rng.permutation(600)
+    w.v[0, few[:60]] = np.inf
+    w.v[1, 600 + few[4:]] = -np.inf
+    P, Pr = both(ctx, vr, ref, w)
+    exp = ref.local_vdensity(Pr, off, mem, vbar, sigma, n_se, n_v)["R"]
+    got = ctx.local_vdensity(P, dev_tensor(off), dev_tensor(mem), dev_tensor(vbar), dev_tensor(sigma), n_se, n_v)
+    fin = np.isfinite(w.v).all(axis=0)
+    got = got.cpu().numpy()
+    assert np.isnan(got[600:][fin[600:]]).all() and np.isnan(exp[600:][fin[600:]]).all()
+    some = fin & (np.arange(1200) < 600)
+    assert np.isfinite(exp[some]).any()
+    R_agrees(got, exp, where=some)
