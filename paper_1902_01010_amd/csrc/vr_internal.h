@@ -65,7 +65,6 @@ struct vr_ctx {
     // content hash, sizes and storage
     unsigned long long kd_pre_hash = 0;
     int64_t kd_pre_m = -1;
-    int kd_pre_bits = 0;
     void* kd_pre_ptr = nullptr;
     // graph of the persistent unbinding passes, reused while its arguments match
     void* cap_stream = nullptr;
@@ -204,10 +203,12 @@ int sort_pairs_u32_from(vr_ctx* ctx, uint32_t* kin, uint32_t* vin, uint32_t* key
                         int bits, hipStream_t s);
 // `batch` sorts of n <= SORT_BATCH_MAX pairs each whose arrays follow each
 // other, in the launches of one (larger ones fill the device alone).  Input
-// as placed by sort_input_u64 for batch * n pairs.
+// as placed by sort_input_* for batch * n pairs.
 constexpr int64_t SORT_BATCH_MAX = 524288;
-int sort_batch_u64(vr_ctx* ctx, uint64_t* kin, uint32_t* vin, uint64_t* keys, uint32_t* vals, int64_t n, int batch,
-                   int bits, hipStream_t s);
+int sort_batch(vr_ctx* ctx, uint64_t* kin, uint32_t* vin, uint64_t* keys, uint32_t* vals, int64_t n, int batch,
+               int bits, hipStream_t s);
+int sort_batch(vr_ctx* ctx, uint32_t* kin, uint32_t* vin, uint32_t* keys, uint32_t* vals, int64_t n, int batch,
+               int bits, hipStream_t s);
 // Fill helpers (kernels, never memset nodes, so they are safe to capture).
 int fill_i32(vr_ctx* ctx, int32_t* p, int32_t v, int64_t n, hipStream_t s);
 int fill_u32(vr_ctx* ctx, uint32_t* p, uint32_t v, int64_t n, hipStream_t s);

@@ -152,36 +152,47 @@ __global__ void k_elems(int64_t M, int n_hosts, const int32_t* __restrict__ off,
         atomicAdd(&hash[((uint64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) % HASH_SLOTS], hv);
 }
 
-// Raises *flag when a host spans half the box or more on some axis.  There
-// the periodic distance of two members can be below their coordinates'
-// difference, but is at least what the host's extent leaves of the box.
-__global__ void k_any_wide(int n_hosts, int half, const int* __restrict__ hbox, float* __restrict__ lim2,
-                           unsigned long long* __restrict__ flag) {
+// The hosts' extents: the largest of them in words[1], and words[0] raised when
+// a host spans half the box or more on some axis.  There the periodic distance
+// of two members can be below their coordinates' difference, but is at least
+// what the host's extent leaves of the box (lim2).
+__global__ void k_host_box(int n_hosts, int half, const int* __restrict__ hbox, float* __restrict__ lim2,
+                           unsigned long long* __restrict__ words) {
     const int h = blockIdx.x * blockDim.x + threadIdx.x;
-    if (h >= n_hosts) return;
-    const int* b = hbox + 6 * (int64_t)h;
-    float l = INFINITY;
-    for (int d = 0; d < 3; ++d) {
-        const int ext = -b[3 + d] - b[d];
-        if (ext < half) continue;
-        const float left = (float)(2 * half - ext);  // an integer below 2^21
-        l = fminf(l, left * left * 0.999999f);
-        *flag = 1;
+    int most = 0;
+    if (h < n_hosts) {
+        const int* b = hbox + 6 * (int64_t)h;
+        float l = INFINITY;
+        for (int d = 0; d < 3; ++d) {
+            const int ext = -b[3 + d] - b[d];
+            most = max(most, ext);
+            if (ext < half) continue;
+            const float left = (float)(2 * half - ext);  // an integer below 2^21
+            l = fminf(l, left * left * 0.999999f);
+            words[0] = 1;
+        }
+        lim2[h] = l;
     }
-    lim2[h] = l;
+    for (int o = 32; o > 0; o >>= 1) most = max(most, __shfl_xor(most, o, 64));
+    if (__lane_id() == 0) atomicMax(&words[1], (unsigned long long)most);
 }
 
-// blockIdx.y: the dimension of u0..u2 (a batch of sorts, one after the other).
-__global__ void k_presort_keys(int64_t M, const int* __restrict__ u0, const int* __restrict__ u1,
-                               const int* __restrict__ u2, const int* __restrict__ host, uint64_t* __restrict__ key,
-                               uint32_t* __restrict__ val) {
+// Sort keys (host, coordinate); blockIdx.y: the dimension d0 + y of u (a batch
+// of sorts, one after the other).  cb bits hold a coordinate relative to its
+// host's smallest (hbox), or, without hbox, shifted into 22 bits (unwrapped
+// ones lie in [-2^20, 3 * 2^20)).
+template <class K>
+__global__ void k_presort_keys(int64_t M, int d0, const int* __restrict__ u0, const int* __restrict__ u1,
+                               const int* __restrict__ u2, const int* __restrict__ host, const int* __restrict__ hbox,
+                               int cb, K* __restrict__ key, uint32_t* __restrict__ val) {
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= M) return;
-    const int* u = blockIdx.y == 0 ? u0 : (blockIdx.y == 1 ? u1 : u2);
+    const int d = d0 + (int)blockIdx.y;
+    const int* u = d == 0 ? u0 : (d == 1 ? u1 : u2);
     key += blockIdx.y * M;
     val += blockIdx.y * M;
-    // unwrapped coordinates lie in [-2^20, 3 * 2^20): 22 bits after the shift
-    key[e] = ((uint64_t)host[e] << 22) | (uint64_t)(uint32_t)(u[e] + (1 << 20));
+    const int h = host[e], base = hbox ? hbox[6 * (int64_t)h + d] : -(1 << 20);
+    key[e] = (K)h << cb | (K)(uint32_t)(u[e] - base);
     val[e] = (uint32_t)e;
 }
 
@@ -679,8 +690,8 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
     const int64_t M = off[n_hosts];
     const int use_mass = p->mass ? 1 : 0;
     const int counts = use_mass ? 0 : 1;
-    int hb = 1;
-    while ((1 << hb) <= n_hosts) ++hb;
+    int hb = 0;  // bits of a host
+    while ((1 << hb) < n_hosts) ++hb;
     // Sorts that do not fill the device run the three dimensions together
     // (a third of the launches); with a workspace cap one after the other,
     // in a third of the room.
@@ -693,7 +704,13 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
     int *C0[3], *C0alt[3];
     const int64_t MC = mode < KD_WIDEST ? M : 1;     // coordinates in list-0 order
     const int64_t MF = mode != KD_BUCKETS ? M : 1;   // members by position
-    const int64_t HB = mode == KD_BUCKETS ? 6 * (int64_t)n_hosts : 1;
+    // Bucket trees know their hosts' extents: keys relative to a host's box
+    // save a sort pass or two of four to five and mostly fit 32 bits (48/16
+    // neighbours of 200 k members, the whole search: 541 -> 518 us).
+    // For the other trees the extents cost k_elems what the passes gain
+    // (1.6 M members, cells and search: 3958 -> 4014 us).
+    const bool extents = mode == KD_BUCKETS;
+    const int64_t HB = extents ? 6 * (int64_t)n_hosts : 1;
     float *Ms, *lim2;
     uint8_t* lf8;
     uint32_t* tail;
@@ -725,8 +742,9 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
         F.mass = cv.add<float>(use_mass ? MF : 1);
         hbox = cv.add<int>(HB);
         lim2 = cv.add<float>(mode == KD_BUCKETS ? n_hosts : 1);
-        // one upload: content hash and wide-host flag, counters, cell sizes
-        hsh = cv.add<unsigned long long>(HASH_SLOTS + 1 + (CN_COUNT + n_hosts + 1) / 2);
+        // one upload: content hash, wide-host flag and largest extent, counters,
+        // cell sizes
+        hsh = cv.add<unsigned long long>(HASH_SLOTS + 2 + (CN_COUNT + n_hosts + 1) / 2);
     };
     layout();
     const size_t total = cv.bytes;
@@ -735,27 +753,27 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
     if (!cv.base) return VR_ERR_OUT_OF_MEMORY;
     layout();
     if (!use_mass) F.mass = nullptr;
-    counters = reinterpret_cast<int*>(hsh + HASH_SLOTS + 1);
+    counters = reinterpret_cast<int*>(hsh + HASH_SLOTS + 2);
     ncell_d = counters + CN_COUNT;
     {
-        const size_t nb = (HASH_SLOTS + 1) * sizeof(*hsh) + (CN_COUNT + (size_t)n_hosts) * sizeof(int);
+        const size_t nb = (HASH_SLOTS + 2) * sizeof(*hsh) + (CN_COUNT + (size_t)n_hosts) * sizeof(int);
         char* up = static_cast<char*>(upload_begin(ctx, nb));
         if (!up) return VR_ERR_HIP;
-        std::memset(up, 0, (HASH_SLOTS + 1) * sizeof(*hsh) + CN_COUNT * sizeof(int));
-        int* cn = reinterpret_cast<int*>(up + (HASH_SLOTS + 1) * sizeof(*hsh));
+        std::memset(up, 0, (HASH_SLOTS + 2) * sizeof(*hsh) + CN_COUNT * sizeof(int));
+        int* cn = reinterpret_cast<int*>(up + (HASH_SLOTS + 2) * sizeof(*hsh));
         cn[CN_NODES] = n_hosts;
         std::memcpy(cn + CN_COUNT, ncell.data(), (size_t)n_hosts * sizeof(int));
         VR_HIP(ctx, hipMemcpyAsync(hsh, up, nb, hipMemcpyHostToDevice, st));
         int rc = upload_end(ctx, st);
         if (rc) return rc;
-        if (mode == KD_BUCKETS && (rc = fill_i32(ctx, hbox, INT_MAX, HB, st))) return rc;
+        if (extents && (rc = fill_i32(ctx, hbox, INT_MAX, HB, st))) return rc;
     }
     hipLaunchKernelGGL(k_elems, dim3(grid_for(M, 256)), dim3(256), 0, st, M, n_hosts, host_offsets, host_members,
                        p->qx, p->qy, p->qz, p->mass, p->grid_bits, U[0], U[1], U[2], G, Ms, H, hsh,
-                       mode == KD_BUCKETS ? hbox : nullptr);
+                       extents ? hbox : nullptr);
     VR_LAUNCH_CHECK(ctx);
-    if (mode == KD_BUCKETS) {
-        hipLaunchKernelGGL(k_any_wide, dim3(grid_for(n_hosts, 256)), dim3(256), 0, st, n_hosts, 1 << (p->grid_bits - 1),
+    if (extents) {
+        hipLaunchKernelGGL(k_host_box, dim3(grid_for(n_hosts, 256)), dim3(256), 0, st, n_hosts, 1 << (p->grid_bits - 1),
                            hbox, lim2, hsh + HASH_SLOTS);
         VR_LAUNCH_CHECK(ctx);
     }
@@ -766,23 +784,25 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
     int* Lnext[3] = {L[0], L[1], L[2]};
     // The three lists sorted by (host, u_d, element) depend only on the
     // elements' members, unwrapped coordinates and hosts.  The context keeps
-    // the last build's lists and reuses them when this build's content hash,
-    // size and key width match (the entropy cells and the neighbour tree of
+    // the last build's lists and reuses them when this build's content hash and
+    // size match (the entropy cells and the neighbour tree of
     // one search are built over the same members); without room for them
     // under the workspace cap it simply sorts.
     {
-        unsigned long long parts[HASH_SLOTS + 1];
+        unsigned long long parts[HASH_SLOTS + 2];
         int rc = read_back(ctx, hsh, parts, sizeof parts, st);
         if (rc) return rc;
         tree.wide = parts[HASH_SLOTS] != 0;
         unsigned long long h64 = 0;
         for (int k = 0; k < HASH_SLOTS; ++k) h64 += parts[k];
-        const int bits = 22 + hb;
+        int cb = 22;  // bits of a coordinate
+        if (extents)
+            for (cb = 1; (1ull << cb) <= parts[HASH_SLOTS + 1];) ++cb;
+        const int bits = cb + hb;
         const std::string err_before = ctx->err;
         int* pre = static_cast<int*>(ws(ctx, WS_KD_PRE, 3 * (size_t)M * sizeof(int)));
         if (!pre) ctx->err = err_before;  // no room for the kept lists: not an error
-        const bool hit = pre && ctx->kd_pre_ptr == pre && ctx->kd_pre_m == M && ctx->kd_pre_bits == bits &&
-                         ctx->kd_pre_hash == h64;
+        const bool hit = pre && ctx->kd_pre_ptr == pre && ctx->kd_pre_m == M && ctx->kd_pre_hash == h64;
         if (hit) {
             for (int d = 0; d < 3; ++d) Lin[d] = pre + d * M;
         } else {
@@ -790,22 +810,30 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
             if (pre)
                 for (int d = 0; d < 3; ++d) Lin[d] = pre + d * M;
             const int step = batch && pre ? 3 : 1;  // dimensions a sort
-            for (int d = 0; d < 3; d += step) {
-                uint32_t* ld = reinterpret_cast<uint32_t*>(Lin[d]);
-                uint64_t* kin;
-                uint32_t* vin;
-                if ((rc = sort_input_u64(ctx, pkey, ld, step * M, bits, &kin, &vin))) return rc;
-                hipLaunchKernelGGL(k_presort_keys, dim3(grid_for(M, 256), step), dim3(256), 0, st, M, U[d],
-                                   step == 3 ? U[1] : nullptr, step == 3 ? U[2] : nullptr, H, kin, vin);
-                VR_LAUNCH_CHECK(ctx);
-                if ((rc = step == 3 ? sort_batch_u64(ctx, kin, vin, pkey, ld, M, 3, bits, st)
-                                    : sort_pairs_u64_from(ctx, kin, vin, pkey, ld, M, bits, st)))
-                    return rc;
-            }
+            auto presort = [&](auto* keys) {
+                using K = std::remove_pointer_t<decltype(keys)>;
+                for (int d = 0; d < 3; d += step) {
+                    uint32_t* ld = reinterpret_cast<uint32_t*>(Lin[d]);
+                    K* kin;
+                    uint32_t* vin;
+                    int e;
+                    if constexpr (sizeof(K) == 4) e = sort_input_u32(ctx, keys, ld, step * M, bits, &kin, &vin);
+                    else e = sort_input_u64(ctx, keys, ld, step * M, bits, &kin, &vin);
+                    if (e) return e;
+                    hipLaunchKernelGGL(k_presort_keys<K>, dim3(grid_for(M, 256), step), dim3(256), 0, st, M, d, U[0], U[1],
+                                       U[2], H, extents ? hbox : nullptr, cb, kin, vin);
+                    VR_LAUNCH_CHECK(ctx);
+                    if (step == 3) e = sort_batch(ctx, kin, vin, keys, ld, M, 3, bits, st);
+                    else if constexpr (sizeof(K) == 4) e = sort_pairs_u32_from(ctx, kin, vin, keys, ld, M, bits, st);
+                    else e = sort_pairs_u64_from(ctx, kin, vin, keys, ld, M, bits, st);
+                    if (e) return e;
+                }
+                return (int)VR_OK;
+            };
+            if ((rc = bits <= 32 ? presort(reinterpret_cast<uint32_t*>(pkey)) : presort(pkey))) return rc;
             if (pre) {
                 ctx->kd_pre_ptr = pre;
                 ctx->kd_pre_m = M;
-                ctx->kd_pre_bits = bits;
                 ctx->kd_pre_hash = h64;
             }
         }

@@ -574,10 +574,16 @@ int sort_pairs_u64_from(vr_ctx* ctx, uint64_t* kin, uint32_t* vin, uint64_t* key
     return sort_pairs_impl<uint64_t>(ctx, kin, vin, keys, vals, n, bits, s, first_bit);
 }
 
-int sort_batch_u64(vr_ctx* ctx, uint64_t* kin, uint32_t* vin, uint64_t* keys, uint32_t* vals, int64_t n, int batch,
-                   int bits, hipStream_t s) {
+int sort_batch(vr_ctx* ctx, uint64_t* kin, uint32_t* vin, uint64_t* keys, uint32_t* vals, int64_t n, int batch,
+               int bits, hipStream_t s) {
     if (n > SORT_BATCH_MAX) return set_err(ctx, VR_ERR_UNSUPPORTED, "batched sort of %lld pairs each", (long long)n);
     return sort_pairs_impl<uint64_t>(ctx, kin, vin, keys, vals, n, bits, s, 0, batch);
+}
+
+int sort_batch(vr_ctx* ctx, uint32_t* kin, uint32_t* vin, uint32_t* keys, uint32_t* vals, int64_t n, int batch,
+               int bits, hipStream_t s) {
+    if (n > SORT_BATCH_MAX) return set_err(ctx, VR_ERR_UNSUPPORTED, "batched sort of %lld pairs each", (long long)n);
+    return sort_pairs_impl<uint32_t>(ctx, kin, vin, keys, vals, n, bits, s, 0, batch);
 }
 
 int sort_input_u32(vr_ctx* ctx, uint32_t* keys, uint32_t* vals, int64_t n, int bits, uint32_t** kin,

@@ -126,3 +126,12 @@ def test_infinite_velocities(ctx, vr, ref, n_se, n_v):
     some = fin & (np.arange(1200) < 600)
     assert np.isfinite(exp[some]).any()
     R_agrees(got, exp, where=some)
+
+
+@pytest.mark.parametrize("n_hosts,extent", [(1, 0.0), (1, 0.01), (300, 1e-4), (1024, 0.02), (2100, 0.08)])
+def test_presort_key_widths(ctx, vr, ref, n_hosts, extent):
+    """Keys relative to a host's box, of 1 to 32 bits and of more; hosts of
+    coincident members and across the box's edge."""
+    rng = np.random.default_rng(n_hosts)
+    sizes = (64 + rng.integers(0, 40, n_hosts)).tolist() if n_hosts > 1 else [3000]
+    _check(ctx, vr, ref, _hosts(rng, sizes, extent=extent), 32, 8)
