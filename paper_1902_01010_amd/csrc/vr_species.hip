@@ -541,19 +541,22 @@ __global__ void k_baryon_list(int64_t M, const uint32_t* __restrict__ dmflag, co
     if (k < M && !dmflag[k]) blist[k - pos[k]] = (int32_t)k;
 }
 
-// One wavefront per T6_Q consecutive baryons of the tree-ordered list,
-// T6_LPQ lanes each.  The lanes of one host walk its tree together: a node is
+// One wavefront per 64 / LPQ consecutive baryons of the tree-ordered list,
+// LPQ lanes each.  The lanes of one host walk its tree together: a node is
 // opened when its box may hold a closer member for any of them, and a
 // baryon's lanes share its best.  Leaves are staged in LDS; a lane scores its
 // part of the members, exactly only when a float distance, with a margin for
 // the rounding of the scaled coordinates, does not already rule one out.
 // Bound by the longest walks: 64 baryons a wavefront open all their nodes one
 // after the other, 236 k baryons among 600 k members 3.03 ms (one lane a
-// baryon), 1.61 (two), 1.05 (four), 1.17 (eight), 1.79 (sixteen).
+// baryon), 1.61 (two), 1.05 (four), 1.17 (eight), 1.79 (sixteen).  Where there
+// are wavefronts enough for the chip the walks overlap, and fewer lanes walk
+// less in all: four against two lanes 2.95 and 3.23 ms at 0.57 M baryons, 5.97
+// and 5.66 at 1.1 M, 10.01 and 8.98 at 2.2 M, 29.9 and 27.0 at 4.5 M.
 constexpr int T6_WAVES = 4;
-constexpr int T6_LPQ = 4;
-constexpr int T6_Q = 64 / T6_LPQ;
+constexpr int64_t T6_MANY = 786432;  // baryons from which two lanes do for one
 
+template <int LPQ>
 __global__ __launch_bounds__(256) void k_assign6(int64_t b0, int64_t nb, const int32_t* __restrict__ blist,
                                                  const int32_t* __restrict__ mem, const int32_t* __restrict__ owner,
                                                  const int32_t* __restrict__ sub, const uint32_t* __restrict__ qx,
@@ -568,9 +571,10 @@ __global__ __launch_bounds__(256) void k_assign6(int64_t b0, int64_t nb, const i
     const int w = (int)(threadIdx.x >> 6);
     const int lane = (int)lane_id();
     const int64_t wave = (int64_t)blockIdx.x * T6_WAVES + w;
-    if (b0 + wave * T6_Q >= nb) return;
-    const int64_t bi = b0 + wave * T6_Q + lane / T6_LPQ;
-    const int part = lane % T6_LPQ;  // members part, part + T6_LPQ, ... of a leaf
+    constexpr int Q = 64 / LPQ;
+    if (b0 + wave * Q >= nb) return;
+    const int64_t bi = b0 + wave * Q + lane / LPQ;
+    const int part = lane % LPQ;  // members part, part + LPQ, ... of a leaf
     const bool valid = bi < nb;
     int i = 0, h = -1, px = 0, py = 0, pz = 0;
     float fvx = 0.f, fvy = 0.f, fvz = 0.f;
@@ -617,7 +621,7 @@ __global__ __launch_bounds__(256) void k_assign6(int64_t b0, int64_t nb, const i
     // the best of the lanes that share a baryon
     auto agree = [&]() __attribute__((always_inline)) {
 #pragma unroll
-        for (int o = 1; o < T6_LPQ; o <<= 1) {
+        for (int o = 1; o < LPQ; o <<= 1) {
             const double d = __shfl_xor(bst.d, o, 64);
             const int j = __shfl_xor(bst.j, o, 64);
             consider(bst, d, j);
@@ -637,7 +641,7 @@ __global__ __launch_bounds__(256) void k_assign6(int64_t b0, int64_t nb, const i
                 const int p1 = min(p0 + T6_FAN, d1);
                 stage(p0, p1, hb);
                 if (mine)
-                    for (int q = part; q < p1 - p0; q += T6_LPQ) exact(q);
+                    for (int q = part; q < p1 - p0; q += LPQ) exact(q);
                 __builtin_amdgcn_wave_barrier();
             }
             agree();
@@ -656,7 +660,7 @@ __global__ __launch_bounds__(256) void k_assign6(int64_t b0, int64_t nb, const i
                 else hi = mid;
             }
             const int q0 = max(d0, min(lo - 4, d1 - 8)), q1 = min(d1, q0 + 8);
-            for (int q = q0 + part; q < q1; q += T6_LPQ) {
+            for (int q = q0 + part; q < q1; q += LPQ) {
                 const int ddx = min_image((int)t.sx[q] - px, gb);
                 const int ddy = min_image((int)t.sy[q] - py, gb);
                 const int ddz = min_image((int)t.sz[q] - pz, gb);
@@ -720,7 +724,7 @@ __global__ __launch_bounds__(256) void k_assign6(int64_t b0, int64_t nb, const i
             if (lev == 1) {
                 stage(c0, c1, hb);
                 if (need) {
-                    for (int q = part; q < c1 - c0; q += T6_LPQ) {
+                    for (int q = part; q < c1 - c0; q += LPQ) {
                         const float4 A = sya[w][q], B = syb[w][q];
                         const float e0 = y[0] - A.x, e1 = y[1] - A.y, e2 = y[2] - A.z;
                         const float e3 = y[3] - A.w, e4 = y[4] - B.x, e5 = y[5] - B.y;
@@ -1080,11 +1084,13 @@ extern "C" int vr_assign_baryons(vr_ctx* ctx, const vr_particles* p, int32_t n_h
     hipLaunchKernelGGL(k_assign_dm, dim3(grid_for(M, 256)), dim3(256), 0, st, M, host_members, is_baryon, sub, 0, out);
     VR_LAUNCH_CHECK(ctx);
     if (nb > 0) {
-        // a launch holds fewer than 2^32 threads, T6_LPQ of them a baryon
+        // a launch holds fewer than 2^32 threads, up to four of them a baryon
         constexpr int64_t BMAX = int64_t(1) << 26;
+        const int lpq = nb >= T6_MANY ? 2 : 4;
         VR_TIMED(ctx, "assign_baryons", st, nb,
                  for (int64_t b0 = 0; b0 < nb; b0 += BMAX)
-                     hipLaunchKernelGGL(k_assign6, dim3(grid_for(std::min(nb - b0, BMAX), T6_Q * T6_WAVES)),
+                     hipLaunchKernelGGL(lpq == 2 ? k_assign6<2> : k_assign6<4>,
+                                        dim3(grid_for(std::min(nb - b0, BMAX), 64 / lpq * T6_WAVES)),
                                         dim3(64 * T6_WAVES), 0, st, b0, nb, blist, host_members, owner, sub, p->qx,
                                         p->qy, p->qz, p->vx, p->vy, p->vz, bkey, t, gb, u * u, sigma_v * sigma_v, ix,
                                         iv, out));

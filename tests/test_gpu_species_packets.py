@@ -65,3 +65,17 @@ def test_assign_and_link(ctx, vr, ref, dm, bar):
     assert (got[mem] == exp[mem]).all()
     exp = ref.fof3d_dm(Pr, ell, isb)
     assert (ctx.fof3d_dm(P, ell, dev_tensor(isb)).cpu().numpy() == exp).all()
+
+
+@pytest.mark.parametrize("more", [31, 32])
+def test_assign_many(ctx, vr, ref, more):
+    """Up to 786,431 baryons take four lanes each, more of them two."""
+    q, v, isb, off, mem = _hosts([200] * 199 + [5], [3932] * 199 + [3932 + more], 12.0, more)
+    n = q.shape[1]
+    assert isb.sum() == 786400 + more
+    sub = np.random.default_rng(n).integers(-1, 5, n).astype(np.int32)
+    P, Pr = vr.Particles(dev_tensor(q.view(np.int32)), dev_tensor(v), None, 1.0, 1.0, BITS), ref.Particles(q, v, None, 1.0, 1.0, BITS)
+    ell = 10.0 / (1 << BITS)
+    exp = ref.assign_baryons(Pr, off, mem, isb, sub, ell, 4.0)
+    got, _ = ctx.assign_baryons(P, dev_tensor(off), dev_tensor(mem), dev_tensor(isb), dev_tensor(sub), ell, 4.0)
+    assert (got.cpu().numpy()[mem] == exp[mem]).all()
