@@ -82,8 +82,7 @@ int vr_set_timing(vr_ctx* ctx, int enabled);
  * FP64 potentials only through the order of their partial sums):
  * "knn_leaf"      the neighbour-search tree's leaves of 32 members are built
  *                 in workgroups of at most 16 * knn_leaf members, 2048 at most
- *                 (16..256, 64); members per leaf of the search that takes
- *                 over where a host reaches round the box
+ *                 (16..256, 64)
  * "unbind_tile"   j-tile of the host-planned potential kernel staged in LDS
  *                 (64..4096, 256; the persistent kernel's tiles are fixed)
  * "unbind_jchunk" j-range of one potential work item (256..65536, 4096)
@@ -183,8 +182,8 @@ int vr_cell_moments(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts,
 
 /* Local velocity density ratio R = ln(f_l / f_bg) (Sec. 2.2, Eq. fvbg and
  * the ratio that follows the interpolation equation).  For particle k of a
- * host: S_k = the n_se members nearest in space (self included, ties by
- * index); V_k = the n_v members of S_k nearest in velocity; h = velocity
+ * host: S_k = the n_se members nearest in space (minimum image; self
+ * included, ties by index); V_k = the n_v members of S_k nearest in velocity; h = velocity
  * distance to the n_v-th; f_l = sum_V m_j W(|dv_j|/h) / (h^3 sum_S m_j) with
  * the 3D Epanechnikov kernel W(u) = 15/(8 pi) (1 - u^2); f_bg = Gaussian at
  * vbar(x_k), sigma(x_k) (vbar [n][3], sigma [n][6], particle-major as

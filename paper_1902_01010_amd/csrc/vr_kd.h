@@ -18,11 +18,10 @@ struct KdNode {
 struct Elems {
     int* u[3];      // coordinates unwrapped relative to the host's first member
     int* gidx;      // particle index
-    int* eid;       // element id
     float* mass;    // null for uniform mass
 };
 
-enum KdMode { KD_MIN_ENTROPY = 0, KD_MAX_ENTROPY = 1, KD_WIDEST = 2, KD_BUCKETS = 3 };
+enum KdMode { KD_MIN_ENTROPY = 0, KD_MAX_ENTROPY = 1, KD_BUCKETS = 2 };
 
 struct KdTree {
     KdNode* nodes = nullptr;
@@ -32,16 +31,15 @@ struct KdTree {
     int* leaf_min = nullptr;   // node id -> smallest particle index of the leaf
     Elems F{};                 // members by position (leaf segments are contiguous)
     int* elem_u[3] = {nullptr, nullptr, nullptr};  // coordinates by element id
-    int* elem_host = nullptr;  // host by element id (= by position: hosts keep their ranges)
     int use_mass = 0;
-    // KD_BUCKETS only: whether some host spans half the box or more; per
-    // host, the smallest squared distance a pair of its members can have
-    // through the box (rounded down; infinity for hosts below half the box);
+    // KD_BUCKETS only: null unless some host spans half the box or more; then
+    // six values a host, along each axis the upper end of its members' image
+    // one box below and the lower end of that one box above (far off on axes
+    // of less than half the box, whose differences are periodic distances);
     // element ids by position in the (coordinate, element) order of each
     // dimension inside every leaf; particle by element id; scratch of one int
     // per member, free for the caller
-    bool wide = false;
-    float* lim2 = nullptr;
+    float* images = nullptr;
     int* list[3] = {nullptr, nullptr, nullptr};
     int* elem_g = nullptr;
     int* scratch = nullptr;
@@ -51,10 +49,9 @@ struct KdTree {
 // at the member of rank floor(n/2) in (coordinate, particle index) order of
 // the dimension chosen by `mode`; the left child takes the members before it.
 // The root of host h has node id h.  A node whose members coincide stays a
-// leaf.  KD_BUCKETS splits the widest dimension as KD_WIDEST does, but halves
-// every node above ncell, so its leaves follow from the host sizes alone; it
-// returns the lists (list, elem_u, elem_g, elem_host, scratch) instead of
-// nodes, leaves and F.
+// leaf.  KD_BUCKETS splits the widest dimension and halves every node above
+// ncell, so its leaves follow from the host sizes alone; it returns the lists
+// (list, elem_u, elem_g, scratch) instead of nodes, leaves and F.
 int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t* host_offsets,
              const int32_t* host_members, const std::vector<int32_t>& off, const std::vector<int>& ncell,
              int mode, int nbins, KdTree& tree, hipStream_t st);

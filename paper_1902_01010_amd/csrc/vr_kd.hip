@@ -154,24 +154,23 @@ __global__ void k_elems(int64_t M, int n_hosts, const int32_t* __restrict__ off,
 
 // The hosts' extents: the largest of them in words[1], and words[0] raised when
 // a host spans half the box or more on some axis.  There the periodic distance
-// of two members can be below their coordinates' difference, but is at least
-// what the host's extent leaves of the box (lim2).
-__global__ void k_host_box(int n_hosts, int half, const int* __restrict__ hbox, float* __restrict__ lim2,
+// of two members can be below their coordinates' difference, where one of them
+// comes near the other's image a box away (images: the near ends of all
+// members' images, whole numbers below 2^23).
+__global__ void k_host_box(int n_hosts, int half, const int* __restrict__ hbox, float* __restrict__ images,
                            unsigned long long* __restrict__ words) {
     const int h = blockIdx.x * blockDim.x + threadIdx.x;
     int most = 0;
     if (h < n_hosts) {
         const int* b = hbox + 6 * (int64_t)h;
-        float l = INFINITY;
         for (int d = 0; d < 3; ++d) {
-            const int ext = -b[3 + d] - b[d];
-            most = max(most, ext);
-            if (ext < half) continue;
-            const float left = (float)(2 * half - ext);  // an integer below 2^21
-            l = fminf(l, left * left * 0.999999f);
-            words[0] = 1;
+            const int lo = b[d], hi = -b[3 + d];
+            most = max(most, hi - lo);
+            const bool wide = hi - lo >= half;
+            images[6 * (int64_t)h + d] = wide ? (float)(hi - 2 * half) : -1e30f;
+            images[6 * (int64_t)h + 3 + d] = wide ? (float)(lo + 2 * half) : 1e30f;
+            if (wide) words[0] = 1;
         }
-        lim2[h] = l;
     }
     for (int o = 32; o > 0; o >>= 1) most = max(most, __shfl_xor(most, o, 64));
     if (__lane_id() == 0) atomicMax(&words[1], (unsigned long long)most);
@@ -397,12 +396,12 @@ __global__ __launch_bounds__(256) void k_split(const int* nact, const int* __res
     int best = -1;
     if (valid) {
         nd = nodes[id];
-        if (mode >= KD_WIDEST) {
+        if (mode == KD_BUCKETS) {
             int widest = 0;
 #pragma unroll
             for (int d = 0; d < 3; ++d) {
                 const int ext = nd.bmax[d] - nd.bmin[d];
-                if ((mode == KD_BUCKETS || ext > 0) && (best < 0 || ext > widest)) {
+                if (best < 0 || ext > widest) {
                     best = d;
                     widest = ext;
                 }
@@ -629,9 +628,8 @@ __global__ __launch_bounds__(KB) void k_part3(int64_t M, int* __restrict__ seg_n
 }
 
 // Members by position in list-0 order, and the smallest index of each leaf.
-// c0..c2: the coordinates already in list-0 order, or null (then gathered).
+// c0..c2: the coordinates in list-0 order.
 __global__ void k_final(int64_t M, const int* __restrict__ l0, const int* __restrict__ seg_node,
-                        const int* __restrict__ u0, const int* __restrict__ u1, const int* __restrict__ u2,
                         const int* __restrict__ c0, const int* __restrict__ c1, const int* __restrict__ c2,
                         const int* __restrict__ g, const float* __restrict__ m, Elems F, int* __restrict__ leaf_min) {
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -639,11 +637,10 @@ __global__ void k_final(int64_t M, const int* __restrict__ l0, const int* __rest
     const int e = valid ? l0[p] : 0;
     const int gi = valid ? g[e] : 0x7FFFFFFF;
     if (valid) {
-        F.u[0][p] = c0 ? c0[p] : u0[e];
-        F.u[1][p] = c0 ? c1[p] : u1[e];
-        F.u[2][p] = c0 ? c2[p] : u2[e];
+        F.u[0][p] = c0[p];
+        F.u[1][p] = c1[p];
+        F.u[2][p] = c2[p];
         F.gidx[p] = gi;
-        F.eid[p] = e;
         if (m) F.mass[p] = m[e];
     }
     // smallest particle index per leaf: leaves are runs of positions, so a
@@ -702,8 +699,7 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
     Carve cv;
     int *U[3], *G, *H, *L[3], *Lalt[3], *seg, *leaf_min, *act0, *act1, *leaves, *ncell_d, *counters, *hbox;
     int *C0[3], *C0alt[3];
-    const int64_t MC = mode < KD_WIDEST ? M : 1;     // coordinates in list-0 order
-    const int64_t MF = mode != KD_BUCKETS ? M : 1;   // members by position
+    const int64_t MF = mode != KD_BUCKETS ? M : 1;  // coordinates in list-0 order, members by position
     // Bucket trees know their hosts' extents: keys relative to a host's box
     // save a sort pass or two of four to five and mostly fit 32 bits (48/16
     // neighbours of 200 k members, the whole search: 541 -> 518 us).
@@ -711,7 +707,7 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
     // (1.6 M members, cells and search: 3958 -> 4014 us).
     const bool extents = mode == KD_BUCKETS;
     const int64_t HB = extents ? 6 * (int64_t)n_hosts : 1;
-    float *Ms, *lim2;
+    float *Ms, *images;
     uint8_t* lf8;
     uint32_t* tail;
     uint64_t* pkey;
@@ -725,8 +721,8 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
         Ms = cv.add<float>(use_mass ? M : 1);
         for (int d = 0; d < 3; ++d) L[d] = cv.add<int>(M);
         for (int d = 0; d < 3; ++d) Lalt[d] = cv.add<int>(M);
-        for (int d = 0; d < 3; ++d) C0[d] = cv.add<int>(MC);
-        for (int d = 0; d < 3; ++d) C0alt[d] = cv.add<int>(MC);
+        for (int d = 0; d < 3; ++d) C0[d] = cv.add<int>(MF);
+        for (int d = 0; d < 3; ++d) C0alt[d] = cv.add<int>(MF);
         seg = cv.add<int>(M);
         lf8 = cv.add<uint8_t>(3 * M);
         tail = cv.add<uint32_t>(3 * tiles);
@@ -738,10 +734,9 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
         leaf_min = cv.add<int>(node_cap);
         for (int d = 0; d < 3; ++d) F.u[d] = cv.add<int>(MF);
         F.gidx = cv.add<int>(MF);
-        F.eid = cv.add<int>(MF);
         F.mass = cv.add<float>(use_mass ? MF : 1);
         hbox = cv.add<int>(HB);
-        lim2 = cv.add<float>(mode == KD_BUCKETS ? n_hosts : 1);
+        images = cv.add<float>(HB);
         // one upload: content hash, wide-host flag and largest extent, counters,
         // cell sizes
         hsh = cv.add<unsigned long long>(HASH_SLOTS + 2 + (CN_COUNT + n_hosts + 1) / 2);
@@ -774,7 +769,7 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
     VR_LAUNCH_CHECK(ctx);
     if (extents) {
         hipLaunchKernelGGL(k_host_box, dim3(grid_for(n_hosts, 256)), dim3(256), 0, st, n_hosts, 1 << (p->grid_bits - 1),
-                           hbox, lim2, hsh + HASH_SLOTS);
+                           hbox, images, hsh + HASH_SLOTS);
         VR_LAUNCH_CHECK(ctx);
     }
     // The lists a level reads: first the sorted ones, where they are kept (read
@@ -792,7 +787,7 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
         unsigned long long parts[HASH_SLOTS + 2];
         int rc = read_back(ctx, hsh, parts, sizeof parts, st);
         if (rc) return rc;
-        tree.wide = parts[HASH_SLOTS] != 0;
+        tree.images = parts[HASH_SLOTS] != 0 ? images : nullptr;
         unsigned long long h64 = 0;
         for (int k = 0; k < HASH_SLOTS; ++k) h64 += parts[k];
         int cb = 22;  // bits of a coordinate
@@ -888,7 +883,7 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
     uint32_t* hc = nullptr;
     double *hm = nullptr, *Sdim = nullptr;
     int64_t hwords = 0;  // 32-bit words a node
-    if (mode < KD_WIDEST && !plan_na.empty()) {
+    if (mode != KD_BUCKETS && !plan_na.empty()) {
         const int64_t na = *std::max_element(plan_na.begin(), plan_na.end());
         hwords = 3 * nbins * (counts ? 1 : 2);
         hc = static_cast<uint32_t*>(ws(ctx, WS_KD_HIST, na * hwords * sizeof(uint32_t)));
@@ -896,7 +891,7 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
         if (!hc || !Sdim) return VR_ERR_OUT_OF_MEMORY;
         hm = reinterpret_cast<double*>(hc);
     }
-    const bool have_c0 = mode < KD_WIDEST;
+    const bool have_c0 = mode != KD_BUCKETS;
     hipLaunchKernelGGL(k_start, dim3(gM), dim3(256), 0, st, M, n_hosts, host_offsets, ncell_d, H, Lin[0], Lin[1], Lin[2],
                        U[0], U[1], U[2], nodes, act0, counters, leaves, leaf_min, seg, have_c0 ? C0[0] : nullptr, C0[1],
                        C0[2], hc, plan_na.empty() ? 0 : plan_na[0] * hwords);
@@ -910,7 +905,7 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
             e0 = timer_event(ctx);
             (void)hipEventRecord(e0, st);
         }
-        if (mode < KD_WIDEST) {
+        if (mode != KD_BUCKETS) {
             if (counts)
                 hipLaunchKernelGGL(k_hist<true>, dim3(grid_for(M, hch)), dim3(KB), 0, st, M, seg, nodes, Lin[0], C0[0],
                                    C0[1], C0[2], Ms, nbins, hch, hc, hm);
@@ -957,20 +952,18 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
         std::swap(cur, nxt);
     }
     for (int d = 0; d < 3; ++d) tree.elem_u[d] = U[d];
-    tree.elem_host = H;
     tree.use_mass = use_mass;
     if (mode == KD_BUCKETS) {
         for (int d = 0; d < 3; ++d) tree.list[d] = Lin[d];
         tree.elem_g = G;
-        tree.lim2 = lim2;
         tree.scratch = Lout[0];
         return VR_OK;
     }
     int nleaf = 0;
     int rc = read_back(ctx, counters + CN_LEAVES, &nleaf, sizeof nleaf, st);
     if (rc) return rc;
-    hipLaunchKernelGGL(k_final, dim3(gM), dim3(256), 0, st, M, Lin[0], seg, U[0], U[1], U[2], have_c0 ? C0[0] : nullptr,
-                       have_c0 ? C0[1] : nullptr, have_c0 ? C0[2] : nullptr, G, use_mass ? Ms : nullptr, F, leaf_min);
+    hipLaunchKernelGGL(k_final, dim3(gM), dim3(256), 0, st, M, Lin[0], seg, C0[0], C0[1], C0[2], G,
+                       use_mass ? Ms : nullptr, F, leaf_min);
     VR_LAUNCH_CHECK(ctx);
     tree.nodes = nodes;
     tree.leaves = leaves;

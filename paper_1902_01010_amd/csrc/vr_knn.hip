@@ -19,19 +19,121 @@
 // rounding, or a lane whose list was too short) the largest exact keys leave
 // it: a key packs the exact integer squared distance above the member's rank
 // in its host's ascending index order, so ties break by particle index
-// exactly as the definition says.  Only the set matters from there on: the
+// exactly as the definition says.  Distances are plain differences of the
+// unwrapped coordinates; in a host of half the box's width or more they are
+// the periodic ones as long as a query's set ends before the members' images
+// a box away.  Only the set matters from there on: the
 // bandwidth is the n_v-th smallest velocity distance of the set, a member at
 // that distance has weight zero, and the sums of the Epanechnikov estimate
 // and the Gaussian background follow in FP64.  Queries whose lists overflow
-// (many coincident members) go to k_knn_wave, a wavefront per query with
-// exact keys throughout.
-#include "vr_knn.h"
+// (many coincident members) or whose sets reach an image go to k_knn_wave, a
+// wavefront per query with exact keys of periodic distances throughout.
+#include "vr_kd.h"
 
+#include <cmath>
 #include <cstring>
 #include <type_traits>
 
 namespace vr {
 namespace {
+
+constexpr int POS_BITS = 22;
+constexpr uint64_t POS_MASK = (uint64_t(1) << POS_BITS) - 1;
+
+// ln f_bg (Eq. fvbg): the log density of the trivariate Gaussian of mean
+// vbar(x) and covariance sigma(x), particle g, at velocity vq.  The
+// quadratic form is u^T adj(S) u / det S with u = vq - vbar; S is positive
+// definite iff its leading principal minors S_xx, S_xx S_yy - S_xy^2 and
+// det S are positive (Sylvester's criterion), else NaN.
+__device__ __forceinline__ double log_fbg(const float* __restrict__ sigma, const float* __restrict__ vbar,
+                                          int g, double vqx, double vqy, double vqz) {
+    const float* s = sigma + (int64_t)g * 6;  // particle-major
+    const double sxx = s[0], syy = s[1], szz = s[2];
+    const Sym3Adj A = sym3_adjugate(sxx, syy, szz, s[3], s[4], s[5]);
+    if (!(sxx > 0) || !(A.zz > 0) || !(A.det > 0)) return NAN;
+    const float* vb = vbar + (int64_t)g * 3;
+    const double ux = vqx - (double)vb[0];
+    const double uy = vqy - (double)vb[1];
+    const double uz = vqz - (double)vb[2];
+    const double diag = A.xx * ux * ux + A.yy * uy * uy + A.zz * uz * uz;
+    const double offd = A.xy * ux * uy + A.xz * ux * uz + A.yz * uy * uz;
+    // 3 ln(2 pi) / 2
+    constexpr double HALF3_LN_2PI = 2.7568155996140178;
+    return -0.5 * ((diag + 2.0 * offd) / A.det + log(A.det)) - HALF3_LN_2PI;
+}
+
+__device__ __forceinline__ bool vless(double a, int pa, double b, int pb) { return a < b || (a == b && pa < pb); }
+
+constexpr int BIG_CAP = 256;              // largest n_se
+constexpr int BIG_EXTRA = 192;            // keys appended past n_se before the buffer is cut back
+constexpr int BIG_BUF = BIG_CAP + BIG_EXTRA + 64;  // room for one more leaf chunk
+constexpr int BIG_J = BIG_BUF / 64;       // buffer slots per lane
+
+// The key of rank r (0-based) among the valid keys of the wavefront, by a
+// radix select over byte digits: per digit, a histogram of the keys that
+// share the digits chosen so far, and a wave-wide prefix over its 256
+// buckets to find the one holding rank r.  Keys are distinct.  hist: 256
+// words of LDS.
+__device__ __forceinline__ uint64_t wave_select(const uint64_t (&k)[BIG_J], const bool (&v)[BIG_J], int r,
+                                                uint32_t* hist) {
+    uint64_t lo = ~0ull, hi = 0;
+#pragma unroll
+    for (int j = 0; j < BIG_J; ++j)
+        if (v[j]) {
+            lo = min(lo, k[j]);
+            hi = max(hi, k[j]);
+        }
+    for (int o = 32; o > 0; o >>= 1) {
+        lo = min(lo, (uint64_t)__shfl_xor((unsigned long long)lo, o, 64));
+        hi = max(hi, (uint64_t)__shfl_xor((unsigned long long)hi, o, 64));
+    }
+    if (lo == hi) return lo;
+    const int lane = (int)lane_id();
+    // digits above the highest differing byte are those of every key
+    int shift = ((63 - __clzll(lo ^ hi)) >> 3) << 3;
+    uint64_t above = shift + 8 >= 64 ? 0 : ~0ull << (shift + 8);
+    uint64_t prefix = lo & above;
+    for (;;) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) hist[4 * lane + t] = 0;
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int j = 0; j < BIG_J; ++j)
+            if (v[j] && (k[j] & above) == prefix) atomicAdd(&hist[(k[j] >> shift) & 255], 1u);
+        __builtin_amdgcn_wave_barrier();
+        uint32_t c[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) c[t] = hist[4 * lane + t];
+        const uint32_t sum = c[0] + c[1] + c[2] + c[3];
+        uint32_t incl = sum;
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t y = __shfl_up(incl, o, 64);
+            if (lane >= o) incl += y;
+        }
+        const uint32_t excl = incl - sum;
+        // the lane whose buckets span rank r names the digit
+        int digit = -1;
+        uint32_t below = excl;
+        if ((uint32_t)r >= excl && (uint32_t)r < incl) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                if (digit < 0 && (uint32_t)r < below + c[t]) digit = 4 * lane + t;
+                else if (digit < 0) below += c[t];
+            }
+        }
+        const uint64_t owner = __ballot(digit >= 0);
+        const int src = __builtin_ctzll(owner);
+        digit = __shfl(digit, src, 64);
+        below = __shfl(below, src, 64);
+        r -= (int)below;
+        prefix |= (uint64_t)digit << shift;
+        __builtin_amdgcn_wave_barrier();
+        if (shift == 0) break;
+        above = ~0ull << shift;
+        shift -= 8;
+    }
+    return prefix;
+}
 
 constexpr int LEAF = 32;           // slots of a leaf
 constexpr int BUCKET_MAX = 2048;   // members of a bucket (64 leaves)
@@ -47,8 +149,8 @@ struct Slots {
     int4* buckets;      // [n_buckets] first list position, members, first leaf, host
     int* leaf_bucket;   // [n_leaves]
     int* host_bucket;   // [n_hosts + 1]
-    const float* lim2;  // [n_hosts] squared distances from here on may differ through the box
-    int* beyond;        // raised when a query's set reaches that far
+    const float* images;  // [n_hosts][6] ends of the members' images a box away, or null (no host of half the box)
+    float box;            // the box's side where there are images, else far off
 };
 
 __global__ void k_subset_slot(int64_t ns, int64_t n, const int32_t* __restrict__ subset, const int* __restrict__ slot_of,
@@ -344,11 +446,9 @@ __device__ __forceinline__ float box_gap2(float4 a0, float4 a1, float4 b0, float
     return fmaf(gx, gx, fmaf(gy, gy, gz * gz));
 }
 
-// (members more than half a box apart, in a host of that width, may exceed the
-// key's 42 bits; they are nobody's neighbours, or the call is done otherwise)
+// (no axis adds more than half a box, 2^20: the sum takes at most 42 bits)
 __device__ __forceinline__ uint64_t exact_key(int dx, int dy, int dz, int rank) {
-    const uint64_t d2 = min((uint64_t)((int64_t)dx * dx + (int64_t)dy * dy + (int64_t)dz * dz),
-                            (uint64_t(1) << (64 - POS_BITS)) - 1);
+    const uint64_t d2 = (uint64_t)((int64_t)dx * dx + (int64_t)dy * dy + (int64_t)dz * dz);
     return (d2 << POS_BITS) | (uint64_t)(uint32_t)rank;
 }
 
@@ -550,7 +650,13 @@ __global__ __launch_bounds__(64, 4) void k_knn(const uint32_t* __restrict__ qpos
             }
         }
         const float X = mine ? hi * SLACK : -1.f;
-        if (__ballot(X >= T.lim2[hh]) && lane == 0) *T.beyond = 1;
+        if (T.images) {
+            // how far the query's ball may reach before the nearest image
+            const float* im = T.images + 6 * (int64_t)hh;
+            const float gap = fminf(fminf(fminf(qx - im[0], im[3] - qx), fminf(qy - im[1], im[4] - qy)),
+                                    fminf(qz - im[2], im[5] - qz));
+            if (X >= gap * gap * 0.999999f) over = over || mine;
+        }
         // the members within X: the sign of d2 - X marks them (SLACK covers its
         // rounding), 32 marks a word, then each lane lists its marks
         int nl = 0;
@@ -698,7 +804,11 @@ __global__ __launch_bounds__(64, 4) void k_knn(const uint32_t* __restrict__ qpos
 }
 
 // ---- one wavefront per query, exact keys throughout -------------------------
-// For the queries the kernel above could not finish.  Candidates of a visited
+// For the queries the kernel above could not finish.  Distances are periodic:
+// an axis adds the smaller of the difference and what it leaves of the box,
+// for a box of members the smaller of the gap to it and those to its images
+// (a host's members lie within one box, so nothing else can be nearer).
+// Candidates of a visited
 // leaf are keyed by the lanes, and those below the current bound are appended
 // to an LDS buffer.  When the buffer holds n_se + 192 keys or more, a radix
 // select over the wave finds the n_se-th smallest key; the keys up to it are
@@ -719,7 +829,6 @@ __global__ __launch_bounds__(64) void k_knn_wave(const int* __restrict__ flagged
         const int h = T.buckets[T.leaf_bucket[slot / LEAF]].w;
         const int base = host_off[h];
         const float qx = T.x[slot], qy = T.y[slot], qz = T.z[slot];
-        const float4 q4 = make_float4(qx, qy, qz, 0.f);
         int nb = 0;            // keys in buf (uniform)
         uint64_t W = ~0ull;    // keys below W are taken (uniform)
         auto compact = [&]() __attribute__((always_inline)) {
@@ -750,9 +859,18 @@ __global__ __launch_bounds__(64) void k_knn_wave(const int* __restrict__ flagged
             nb = n_se;
             W = top;
         };
+        auto axis_gap = [&](float lo, float hi, float q) __attribute__((always_inline)) {
+            return fmaxf(fminf(fmaxf(lo - q, q - hi), fminf(lo + T.box - q, q - hi + T.box)), 0.f);
+        };
+        auto apart = [&](float a, float q) __attribute__((always_inline)) {
+            const float d = fabsf(a - q);
+            return (int)fminf(d, T.box - d);
+        };
         // whether the lane's box may hold a member of the set
         auto near = [&](const float4* box) __attribute__((always_inline)) {
-            const float g2 = box_gap2(box[0], box[1], q4, q4);
+            const float4 lo = box[0], hi = box[1];
+            const float gx = axis_gap(lo.x, hi.x, qx), gy = axis_gap(lo.y, hi.y, qy), gz = axis_gap(lo.z, hi.z, qz);
+            const float g2 = fmaf(gx, gx, fmaf(gy, gy, gz * gz));
             return nb < n_se || g2 <= (float)(W >> POS_BITS) * SLACK + 1.f;
         };
         // leaves first + i for the bits i of todo, two at a time (a half of
@@ -790,7 +908,7 @@ __global__ __launch_bounds__(64) void k_knn_wave(const int* __restrict__ flagged
                 bool take = false;
                 uint64_t key = 0;
                 if (c.gid >= 0) {
-                    key = exact_key((int)(c.x - qx), (int)(c.y - qy), (int)(c.z - qz), c.eid - base);
+                    key = exact_key(apart(c.x, qx), apart(c.y, qy), apart(c.z, qz), c.eid - base);
                     take = key < W;
                 }
                 const uint64_t m = __ballot(take);
@@ -819,8 +937,6 @@ __global__ __launch_bounds__(64) void k_knn_wave(const int* __restrict__ flagged
                 bucket(b0 + __builtin_ctzll(todo));
         }
         if (nb > n_se) compact();
-        for (int a = lane; a < n_se; a += 64)
-            if ((float)(buf[a] >> POS_BITS) * SLACK >= T.lim2[h]) *T.beyond = 1;
         // the n_se spatial neighbours: velocity distances and the mass of the set
         const float4 vq = V[slot];
         const double vqx = (double)vq.x, vqy = (double)vq.y, vqz = (double)vq.z;
@@ -910,8 +1026,10 @@ int launch_knn(vr_ctx* ctx, const uint32_t* qpos, int64_t nq, int64_t n_queries,
                                     R, (unsigned)ctx->xcd_chunk, flagged, n_flagged,
                                     ctx->timing ? ctx->knn_cand : nullptr));
     VR_LAUNCH_CHECK(ctx);
-    // almost always without work: a few wavefronts that stride over the flagged queries
-    const unsigned nw = (unsigned)std::min<int64_t>(n_queries, 4 * ctx->num_cus);
+    // almost always without work: a few wavefronts that stride over the flagged
+    // queries; as many as the CUs hold where a host's faces flag them by the
+    // thousand
+    const unsigned nw = (unsigned)std::min<int64_t>(n_queries, (T.images ? 20 : 4) * ctx->num_cus);
     hipLaunchKernelGGL(k_knn_wave, dim3(std::max(nw, 1u)), dim3(64), 0, st, flagged, n_flagged, T, V, FB, host_off, n_se,
                        n_v, use_mass, p->mass_value, R);
     VR_LAUNCH_CHECK(ctx);
@@ -949,7 +1067,7 @@ extern "C" int vr_local_vdensity(vr_ctx* ctx, const vr_particles* p, int32_t n_h
     VR_WS(dup, ctx, int, WS_FLAG, 4);
     rc = fill_i32(ctx, slot_of, -1, p->n, st);
     if (rc) return rc;
-    rc = fill_i32(ctx, dup, 0, 3, st);
+    rc = fill_i32(ctx, dup, 0, 2, st);
     if (rc) return rc;
     hipLaunchKernelGGL(k_rank_of, dim3(grid_for(M, 256)), dim3(256), 0, st, M, p->n, host_members, slot_of, dup);
     VR_LAUNCH_CHECK(ctx);
@@ -1045,9 +1163,9 @@ extern "C" int vr_local_vdensity(vr_ctx* ctx, const vr_particles* p, int32_t n_h
         qpos = qp;
         nq = n_queries = n_subset;
     }
-    int* nfl = dup + 1;  // zero, as dup[2], since the fill above
-    T.lim2 = tree.lim2;
-    T.beyond = dup + 2;
+    int* nfl = dup + 1;  // zero since the fill above
+    T.images = tree.images;
+    T.box = tree.images ? (float)(1 << p->grid_bits) : 1e30f;
     if (n_se <= 32)
         rc = launch_knn<4, 8, 12>(ctx, qpos, nq, n_queries, T, V, FB, host_offsets, p, n_se, n_v, R, flagged, nfl, st);
     else if (n_se <= 64)
@@ -1056,17 +1174,5 @@ extern "C" int vr_local_vdensity(vr_ctx* ctx, const vr_particles* p, int32_t n_h
         rc = launch_knn<16, 8, 14>(ctx, qpos, nq, n_queries, T, V, FB, host_offsets, p, n_se, n_v, R, flagged, nfl, st);
     else  // up to the paper's defaults (n_se 256, n_v 32)
         rc = launch_knn<16, 16, 24>(ctx, qpos, nq, n_queries, T, V, FB, host_offsets, p, n_se, n_v, R, flagged, nfl, st);
-    if (rc || !tree.wide) return rc;
-    // The search takes coordinate differences as they are.  In a host of half
-    // the box's width or more that is the periodic distance too unless a set
-    // reaches as far as the host's extent leaves of the box; then the whole
-    // call is done by the other search.
-    int beyond = 0;
-    if ((rc = read_back(ctx, T.beyond, &beyond, sizeof beyond, st))) return rc;
-    if (!beyond) return VR_OK;
-    if ((rc = fill_i32(ctx, slot_of, -1, p->n, st))) return rc;
-    hipLaunchKernelGGL(k_rank_of, dim3(grid_for(M, 256)), dim3(256), 0, st, M, p->n, host_members, slot_of, dup);
-    VR_LAUNCH_CHECK(ctx);
-    return local_vdensity_wide(ctx, p, n_hosts, host_offsets, host_members, off, slot_of, vbar, sigma, n_se, n_v, subset,
-                               n_subset, R, st);
+    return rc;
 }
