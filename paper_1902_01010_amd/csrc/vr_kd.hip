@@ -106,44 +106,42 @@ __global__ void k_elems(int64_t M, int n_hosts, const int32_t* __restrict__ off,
     }
     if (hbox) {
         // the host's extent: minima of u and of -u.  A block inside one host
-        // (its members are consecutive) reduces first; values only decrease,
-        // so a plain read that is already no larger makes the atomic
-        // unnecessary
-        __shared__ int ends[2], wmin[4][6];
-        if (threadIdx.x == 0) ends[0] = hm;
-        if (threadIdx.x == blockDim.x - 1) ends[1] = hm;
-        __syncthreads();
-        const bool one = ends[0] == ends[1];
-        const int lane = threadIdx.x & 63;
-        if (one) {
+        // (its members are consecutive) reduces; one with several collects them
+        // in LDS, and only the hosts that reach beyond it need atomics (every
+        // run of lanes by itself, 100,000 hosts of 33 members: 262 us, now
+        // 96).  Values only decrease, so a plain read that is already
+        // no larger makes the atomic unnecessary.
+        __shared__ int hb[256][6];
+        const int h0 = hrange[0], nh = hrange[1] - h0 + 1;
+        const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+        if (nh == 1) {
+#pragma unroll
             for (int k = 0; k < 6; ++k) {
-                int v = k < 3 ? um[k] : -um[k - 3];
+                int v = e < M ? (k < 3 ? um[k] : -um[k - 3]) : INT_MAX;
                 for (int o = 32; o > 0; o >>= 1) v = min(v, __shfl_xor(v, o, 64));
-                if (lane == 0) wmin[threadIdx.x >> 6][k] = v;
+                if (lane == 0) hb[w][k] = v;
+            }
+            __syncthreads();
+            if (threadIdx.x < 6) {
+                const int k = threadIdx.x;
+                const int v = min(min(hb[0][k], hb[1][k]), min(hb[2][k], hb[3][k]));
+                int* at = hbox + 6 * (int64_t)h0 + k;
+                if (v < *at) atomicMin(at, v);
             }
         } else {
-            // hosts are runs of lanes: a minimum over each, then its last lane
-            int v[6] = {um[0], um[1], um[2], -um[0], -um[1], -um[2]};
-            for (int o = 1; o < 64; o <<= 1) {
-                const bool take = __shfl_up(hm, o, 64) == hm && lane >= o;
-                for (int k = 0; k < 6; ++k) {
-                    const int x = __shfl_up(v[k], o, 64);
-                    if (take) v[k] = min(v[k], x);
-                }
+            for (int k = threadIdx.x; k < 6 * nh; k += blockDim.x) (&hb[0][0])[k] = INT_MAX;
+            __syncthreads();
+            if (hm >= 0)
+#pragma unroll
+                for (int k = 0; k < 6; ++k) atomicMin(&hb[hm - h0][k], k < 3 ? um[k] : -um[k - 3]);
+            __syncthreads();
+            const int64_t b0 = (int64_t)blockIdx.x * blockDim.x;
+            for (int k = threadIdx.x; k < 6 * nh; k += blockDim.x) {
+                const int h = h0 + k / 6, v = (&hb[0][0])[k];
+                int* at = hbox + 6 * (int64_t)h0 + k;
+                if (off[h] >= b0 && off[h + 1] <= b0 + blockDim.x) *at = v;
+                else if (v < *at) atomicMin(at, v);
             }
-            const int next = __shfl_down(hm, 1, 64);
-            if (hm >= 0 && (lane == 63 || next != hm))
-                for (int k = 0; k < 6; ++k) {
-                    int* at = hbox + 6 * (int64_t)hm + k;
-                    if (v[k] < *at) atomicMin(at, v[k]);
-                }
-        }
-        __syncthreads();
-        if (one && threadIdx.x < 6) {
-            const int k = threadIdx.x;
-            const int v = min(min(wmin[0][k], wmin[1][k]), min(wmin[2][k], wmin[3][k]));
-            int* at = hbox + 6 * (int64_t)hm + k;
-            if (v < *at) atomicMin(at, v);
         }
     }
     // every lane of the wavefront reaches the sum
@@ -159,16 +157,15 @@ __global__ void k_elems(int64_t M, int n_hosts, const int32_t* __restrict__ off,
 // members' images, whole numbers below 2^23).
 __global__ void k_host_box(int n_hosts, int half, const int* __restrict__ hbox, float* __restrict__ images,
                            unsigned long long* __restrict__ words) {
-    const int h = blockIdx.x * blockDim.x + threadIdx.x;
     int most = 0;
-    if (h < n_hosts) {
-        const int* b = hbox + 6 * (int64_t)h;
+    for (int64_t h = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; h < n_hosts; h += (int64_t)gridDim.x * blockDim.x) {
+        const int* b = hbox + 6 * h;
         for (int d = 0; d < 3; ++d) {
             const int lo = b[d], hi = -b[3 + d];
             most = max(most, hi - lo);
             const bool wide = hi - lo >= half;
-            images[6 * (int64_t)h + d] = wide ? (float)(hi - 2 * half) : -1e30f;
-            images[6 * (int64_t)h + 3 + d] = wide ? (float)(lo + 2 * half) : 1e30f;
+            images[6 * h + d] = wide ? (float)(hi - 2 * half) : -1e30f;
+            images[6 * h + 3 + d] = wide ? (float)(lo + 2 * half) : 1e30f;
             if (wide) words[0] = 1;
         }
     }
@@ -682,7 +679,7 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
     for (int h = 0; h < n_hosts; ++h) {
         const int64_t NH = (int64_t)off[h + 1] - off[h];
         const int64_t minleaf = std::max<int64_t>(1, (ncell[h] + 1) / 2);
-        node_cap += 2 * ((NH + minleaf - 1) / minleaf) + 1;
+        node_cap += NH <= ncell[h] ? 1 : 2 * ((NH + minleaf - 1) / minleaf) + 1;
     }
     const int64_t M = off[n_hosts];
     const int use_mass = p->mass ? 1 : 0;
@@ -768,7 +765,8 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
                        extents ? hbox : nullptr);
     VR_LAUNCH_CHECK(ctx);
     if (extents) {
-        hipLaunchKernelGGL(k_host_box, dim3(grid_for(n_hosts, 256)), dim3(256), 0, st, n_hosts, 1 << (p->grid_bits - 1),
+        // (few workgroups: their atomics meet on one word, a million hosts' 160 us)
+        hipLaunchKernelGGL(k_host_box, dim3(std::min(grid_for(n_hosts, 256), 256u)), dim3(256), 0, st, n_hosts, 1 << (p->grid_bits - 1),
                            hbox, images, hsh + HASH_SLOTS);
         VR_LAUNCH_CHECK(ctx);
     }
@@ -845,13 +843,12 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
     std::vector<int64_t> plan_na, plan_members;
     {
         struct Sz { int64_t s0, c0, c1; };  // c0 nodes of size s0, c1 of size s0 + 1
-        std::vector<Sz> sz(n_hosts);
-        for (int h = 0; h < n_hosts; ++h) sz[h] = Sz{(int64_t)off[h + 1] - off[h], 1, 0};
+        std::vector<std::pair<Sz, int>> sz;  // of the hosts that split, with their cells' size
+        for (int h = 0; h < n_hosts; ++h)
+            if (off[h + 1] - off[h] > ncell[h]) sz.push_back({Sz{(int64_t)off[h + 1] - off[h], 1, 0}, ncell[h]});
         for (;;) {
             int64_t na = 0, mem = 0;
-            for (int h = 0; h < n_hosts; ++h) {
-                Sz& z = sz[h];
-                const int64_t nc = ncell[h];
+            for (auto& [z, nc] : sz) {
                 int64_t a0 = z.s0 > nc ? z.c0 : 0, a1 = z.s0 + 1 > nc ? z.c1 : 0;
                 na += a0 + a1;
                 mem += a0 * z.s0 + a1 * (z.s0 + 1);
@@ -892,7 +889,9 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
         hm = reinterpret_cast<double*>(hc);
     }
     const bool have_c0 = mode != KD_BUCKETS;
-    hipLaunchKernelGGL(k_start, dim3(gM), dim3(256), 0, st, M, n_hosts, host_offsets, ncell_d, H, Lin[0], Lin[1], Lin[2],
+    // (buckets that are whole hosts need no nodes)
+    if (have_c0 || !plan_na.empty())
+        hipLaunchKernelGGL(k_start, dim3(gM), dim3(256), 0, st, M, n_hosts, host_offsets, ncell_d, H, Lin[0], Lin[1], Lin[2],
                        U[0], U[1], U[2], nodes, act0, counters, leaves, leaf_min, seg, have_c0 ? C0[0] : nullptr, C0[1],
                        C0[2], hc, plan_na.empty() ? 0 : plan_na[0] * hwords);
     VR_LAUNCH_CHECK(ctx);

@@ -137,6 +137,7 @@ __device__ __forceinline__ uint64_t wave_select(const uint64_t (&k)[BIG_J], cons
 
 constexpr int LEAF = 32;           // slots of a leaf
 constexpr int BUCKET_MAX = 2048;   // members of a bucket (64 leaves)
+constexpr int BUCKET_SMALL = 512;  // and of those that a wavefront finishes, 16 leaves of them at a time
 constexpr float PAD = 1e30f;       // coordinate of an empty slot
 constexpr float SLACK = 1.000002f; // above the rounding of an FP32 squared distance (3 * 2^-24)
 
@@ -203,53 +204,124 @@ __device__ __forceinline__ int leaf_slot(int i, int lpq_log2) {
     return (i & (lpq - 1)) * (LEAF >> lpq_log2) + (i >> lpq_log2);
 }
 
-// One workgroup finishes one bucket's tree in LDS.  The members' three
-// sorted lists (local ids, local id = position in list 0) are split by
-// stable partitions, segment by segment: at a multiple of 32 members nearest
+// One workgroup finishes its buckets' trees in LDS (run: the first of them
+// and their number).  Each bucket begins at a leaf of the workgroup's
+// positions.  The members' three sorted lists (local ids, local id = position
+// in list 0) are split by stable partitions, segment by segment: at a multiple of 32 members nearest
 // the middle while a segment holds more than a leaf, then in halves down to
 // four.  Members, boxes and slots are written in the resulting order.
 // Bound by LDS round trips and barriers (three workgroups of 53 KB a CU); on
 // the 6.2 M members of a 256^3 box it takes 0.68 ms in place of three to four
 // device-wide levels of about 0.25 ms, and leaves of 32 instead of 192 (2,354
-// candidate distances a query before, about 600 now).
-__global__ __launch_bounds__(256) void k_buckets(const int* __restrict__ l0, const int* __restrict__ l1,
-                                                 const int* __restrict__ l2, const int* __restrict__ u0,
-                                                 const int* __restrict__ u1, const int* __restrict__ u2,
-                                                 const int* __restrict__ g, int* loc, int lpq_log2, Slots T,
-                                                 int* __restrict__ slot_of) {
-    constexpr int NT = 256, PT = BUCKET_MAX / NT;  // 8 consecutive positions a thread
-    __shared__ int cu[3][BUCKET_MAX];
-    __shared__ __align__(16) uint16_t ls[3][BUCKET_MAX];
-    __shared__ uint16_t pre[3][BUCKET_MAX];
-    __shared__ uint8_t side[BUCKET_MAX], sdim[BUCKET_MAX];
+// candidate distances a query before, 688 now).
+// NT = 64 takes the buckets of up to 512 members, as many as 16 leaves hold.
+// (A workgroup of 256 for each of 100,000 hosts of 33 members: 2.92 ms, a
+// wavefront for each 0.86, eight of them a wavefront 0.20.)
+template <int NT>
+__global__ __launch_bounds__(NT) void k_buckets(const int2* __restrict__ runs, const int* __restrict__ l0,
+                                                const int* __restrict__ l1, const int* __restrict__ l2,
+                                                const int* __restrict__ u0, const int* __restrict__ u1,
+                                                const int* __restrict__ u2, const int* __restrict__ g, int* loc,
+                                                int lpq_log2, Slots T, int* __restrict__ slot_of) {
+    constexpr int PT = 8, MAX = NT * PT;  // consecutive positions a thread, members
+    static_assert(MAX == BUCKET_MAX || MAX == BUCKET_SMALL, "bucket sizes");
+    __shared__ int cu[3][MAX];
+    __shared__ __align__(16) uint16_t ls[3][MAX];
+    __shared__ __align__(16) uint16_t pre[3][MAX];
+    __shared__ uint8_t side[MAX], sdim[MAX];
     __shared__ unsigned long long wsum[NT / 64];
-    __shared__ int wbox[NT / 64][6];
+    // the leaves' buckets, by their numbers in the run
+    __shared__ uint8_t lbk[MAX / LEAF];
+    __shared__ int4 bks[NT == 64 ? MAX / LEAF : 1];
+    int (*lb)[MAX / LEAF] = reinterpret_cast<int (*)[MAX / LEAF]>(&pre[0][0]);  // and, in the end, boxes
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-    const int4 bk = T.buckets[blockIdx.x];
-    const int start = bk.x, n = bk.y, leaf0 = bk.z;
-    const int nleaf = (n + LEAF - 1) / LEAF;
-    for (int p = t; p < n; p += NT) {
-        const int e = l0[start + p];
-        cu[0][p] = u0[e];
-        cu[1][p] = u1[e];
-        cu[2][p] = u2[e];
-        ls[0][p] = (uint16_t)p;
-        loc[e] = p;
+    // (without runs: a workgroup a bucket)
+    const int2 run = runs ? runs[blockIdx.x] : make_int2((int)blockIdx.x, 1);
+    const int4 head = T.buckets[run.x];
+    const int leaf0 = head.z;
+    int all = (head.y + LEAF - 1) / LEAF;  // leaves of the run
+    if (NT == 64) {
+        const int4 last = T.buckets[run.x + run.y - 1];
+        all = last.z - leaf0 + (last.y + LEAF - 1) / LEAF;
+        if (t < run.y) {
+            const int4 bk = T.buckets[run.x + t];
+            bks[t] = bk;
+            for (int l = bk.z - leaf0; l < bk.z - leaf0 + (bk.y + LEAF - 1) / LEAF; ++l) lbk[l] = (uint8_t)t;
+        }
+        __syncthreads();
+    }
+    auto bucket_of = [&](int l) __attribute__((always_inline)) { return NT == 64 ? bks[lbk[l]] : head; };
+    // the place of position p in its host's lists, -1: none
+    auto place = [&](int p) __attribute__((always_inline)) {
+        if (p >= all * LEAF) return -1;
+        const int4 bk = bucket_of(p / LEAF);
+        const int k = p - (bk.z - leaf0) * LEAF;
+        return k < bk.y ? bk.x + k : -1;
+    };
+    // (a thread's loads of each kind together: 0.30 -> 0.20 ms of those hosts)
+    {
+        int e[PT], c[3][PT];
+#pragma unroll
+        for (int j = 0; j < PT; ++j) {
+            const int at = place(t + j * NT);
+            e[j] = at >= 0 ? l0[at] : -1;
+        }
+#pragma unroll
+        for (int j = 0; j < PT; ++j) {
+            c[0][j] = u0[max(e[j], 0)];
+            c[1][j] = u1[max(e[j], 0)];
+            c[2][j] = u2[max(e[j], 0)];
+        }
+#pragma unroll
+        for (int j = 0; j < PT; ++j) {
+            const int p = t + j * NT;
+            if (e[j] < 0) continue;
+#pragma unroll
+            for (int d = 0; d < 3; ++d) cu[d][p] = c[d][j];
+            ls[0][p] = (uint16_t)p;
+            loc[e[j]] = p;
+        }
     }
     __syncthreads();
-    for (int p = t; p < n; p += NT) {
-        ls[1][p] = (uint16_t)loc[l1[start + p]];
-        ls[2][p] = (uint16_t)loc[l2[start + p]];
+    {
+        int e[2][PT];
+#pragma unroll
+        for (int j = 0; j < PT; ++j) {
+            const int at = place(t + j * NT);
+            e[0][j] = at >= 0 ? l1[at] : -1;
+            e[1][j] = at >= 0 ? l2[at] : -1;
+        }
+#pragma unroll
+        for (int d = 0; d < 2; ++d)
+#pragma unroll
+            for (int j = 0; j < PT; ++j)
+                if (e[d][j] >= 0) e[d][j] = loc[e[d][j]];
+#pragma unroll
+        for (int j = 0; j < PT; ++j)
+            if (e[0][j] >= 0) {
+                ls[1][t + j * NT] = (uint16_t)e[0][j];
+                ls[2][t + j * NT] = (uint16_t)e[1][j];
+            }
     }
+    // a thread's positions lie in one leaf
     const int p0 = t * PT;
+    const bool have = p0 < all * LEAF;
+    const int4 bk = bucket_of(have ? p0 / LEAF : 0);
+    const int b = run.x + (NT == 64 && have ? lbk[p0 / LEAF] : 0);
+    const int first = (bk.z - leaf0) * LEAF, n = have ? first + bk.y : 0;  // the bucket's positions
     uint32_t se[PT];  // segment of the position: start << 16 | end
 #pragma unroll
-    for (int j = 0; j < PT; ++j) se[j] = (uint32_t)n;
+    for (int j = 0; j < PT; ++j) se[j] = (uint32_t)first << 16 | (uint32_t)n;
     auto middle = [](int s, int e) __attribute__((always_inline)) {
         const int m = e - s;
         return m > LEAF ? s + LEAF * (((m + LEAF - 1) / LEAF) >> 1) : s + (m >> 1);
     };
-    const int levels = (nleaf > 1 ? 32 - __clz(nleaf - 1) : 0) + 3;
+    int most = have ? (bk.y + LEAF - 1) / LEAF : 1;  // leaves of the largest bucket
+    if (NT == 64)
+        for (int o = 32; o > 0; o >>= 1) most = max(most, __shfl_xor(most, o, 64));
+    else
+        most = all;
+    const int levels = (most > 1 ? 32 - __clz(most - 1) : 0) + 3;
     __syncthreads();
     for (int lev = 0; lev < levels; ++lev) {
         // the widest dimension of every segment, from the ends of its lists
@@ -327,30 +399,31 @@ __global__ __launch_bounds__(256) void k_buckets(const int* __restrict__ l0, con
     }
     // members into slots, and the boxes of leaves and bucket
     int mn[3] = {INT32_MAX, INT32_MAX, INT32_MAX}, mx[3] = {INT32_MIN, INT32_MIN, INT32_MIN};
+    if (have) {
+        int a[PT], e[PT], gi[PT];
 #pragma unroll
-    for (int j = 0; j < PT; ++j) {
-        const int p = p0 + j;
-        if (p >= nleaf * LEAF) break;
-        const int slot = (leaf0 + (p / LEAF)) * LEAF + leaf_slot(p & (LEAF - 1), lpq_log2);
-        if (p < n) {
-            const int a = ls[0][p];
-            const int e = l0[start + a], gi = g[e];
-            const int q[3] = {cu[0][a], cu[1][a], cu[2][a]};
+        for (int j = 0; j < PT; ++j) {
+            a[j] = p0 + j < n ? ls[0][p0 + j] : first;
+            e[j] = l0[bk.x + a[j] - first];
+        }
+#pragma unroll
+        for (int j = 0; j < PT; ++j) gi[j] = g[e[j]];
+#pragma unroll
+        for (int j = 0; j < PT; ++j) {
+            const int p = p0 + j, slot = (leaf0 + (p / LEAF)) * LEAF + leaf_slot(p & (LEAF - 1), lpq_log2);
+            const bool in = p < n;
+            const int q[3] = {cu[0][a[j]], cu[1][a[j]], cu[2][a[j]]};
 #pragma unroll
             for (int d = 0; d < 3; ++d) {
-                mn[d] = min(mn[d], q[d]);
-                mx[d] = max(mx[d], q[d]);
+                mn[d] = in ? min(mn[d], q[d]) : mn[d];
+                mx[d] = in ? max(mx[d], q[d]) : mx[d];
             }
-            T.x[slot] = (float)q[0];
-            T.y[slot] = (float)q[1];
-            T.z[slot] = (float)q[2];
-            T.gid[slot] = gi;
-            T.eid[slot] = e;
-            slot_of[gi] = slot;
-        } else {
-            T.x[slot] = T.y[slot] = T.z[slot] = PAD;
-            T.gid[slot] = -1;
-            T.eid[slot] = 0;
+            T.x[slot] = in ? (float)q[0] : PAD;
+            T.y[slot] = in ? (float)q[1] : PAD;
+            T.z[slot] = in ? (float)q[2] : PAD;
+            T.gid[slot] = in ? gi[j] : -1;
+            T.eid[slot] = in ? e[j] : 0;
+            if (in) slot_of[gi[j]] = slot;
         }
     }
     // a leaf is the 32 positions of four threads
@@ -362,34 +435,42 @@ __global__ __launch_bounds__(256) void k_buckets(const int* __restrict__ l0, con
             mx[d] = max(mx[d], __shfl_xor(mx[d], o, 64));
         }
     }
-    if ((t & 3) == 0 && p0 < n) {
-        const int leaf = leaf0 + p0 / LEAF;
+    if ((t & 3) == 0 && have) {
+        const int l = p0 / LEAF, leaf = leaf0 + l;
         T.lbox[2 * leaf] = make_float4((float)mn[0], (float)mn[1], (float)mn[2], 0.f);
         T.lbox[2 * leaf + 1] = make_float4((float)mx[0], (float)mx[1], (float)mx[2], 0.f);
-        T.leaf_bucket[leaf] = blockIdx.x;
-    }
+        T.leaf_bucket[leaf] = b;
 #pragma unroll
-    for (int d = 0; d < 3; ++d) {
-#pragma unroll
-        for (int o = 4; o < 64; o <<= 1) {
-            mn[d] = min(mn[d], __shfl_xor(mn[d], o, 64));
-            mx[d] = max(mx[d], __shfl_xor(mx[d], o, 64));
-        }
-        if (lane == 0) {
-            wbox[wv][d] = mn[d];
-            wbox[wv][3 + d] = mx[d];
+        for (int d = 0; d < 3; ++d) {
+            lb[d][l] = mn[d];
+            lb[3 + d][l] = -mx[d];
         }
     }
     __syncthreads();
-    if (t == 0) {
-        for (int w = 1; w < NT / 64; ++w)
-            for (int d = 0; d < 3; ++d) {
-                wbox[0][d] = min(wbox[0][d], wbox[w][d]);
-                wbox[0][3 + d] = max(wbox[0][3 + d], wbox[w][3 + d]);
-            }
-        T.bbox[2 * blockIdx.x] = make_float4((float)wbox[0][0], (float)wbox[0][1], (float)wbox[0][2], 0.f);
-        T.bbox[2 * blockIdx.x + 1] = make_float4((float)wbox[0][3], (float)wbox[0][4], (float)wbox[0][5], 0.f);
+    // the buckets' boxes: a lane per bucket of a run, or all of one bucket
+    int m[6];
+    if (NT == 64) {
+        if (t >= run.y) return;
+        const int4 own = T.buckets[run.x + t];
+        const int l0 = own.z - leaf0, l1 = l0 + (own.y + LEAF - 1) / LEAF;
+#pragma unroll
+        for (int d = 0; d < 6; ++d) {
+            m[d] = INT32_MAX;
+            for (int l = l0; l < l1; ++l) m[d] = min(m[d], lb[d][l]);
+        }
+    } else {
+        if (wv > 0) return;
+#pragma unroll
+        for (int d = 0; d < 6; ++d) {
+            m[d] = lane < all ? lb[d][lane] : INT32_MAX;
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) m[d] = min(m[d], __shfl_xor(m[d], o, 64));
+        }
+        if (lane > 0) return;
     }
+    float4* box = T.bbox + 2 * (run.x + (NT == 64 ? t : 0));
+    box[0] = make_float4((float)m[0], (float)m[1], (float)m[2], 0.f);
+    box[1] = make_float4((float)-m[3], (float)-m[4], (float)-m[5], 0.f);
 }
 
 // ---- reductions over a query's lanes and the wavefront ---------------------
@@ -488,6 +569,7 @@ __global__ __launch_bounds__(64, 4) void k_knn(const uint32_t* __restrict__ qpos
     if (active) slot = qpos ? (int)qpos[qi] : (int)(qi & ~(int64_t)(LEAF - 1)) + leaf_slot((int)qi & (LEAF - 1), LOG2);
     const int gid = T.gid[slot];
     active = active && gid >= 0;
+    if (!__ballot(active)) return;  // the empty half of a small host's leaf
     const int own = slot / LEAF;
     const int obk = T.leaf_bucket[own];
     const int h = active ? T.buckets[obk].w : -1;
@@ -1082,27 +1164,35 @@ extern "C" int vr_local_vdensity(vr_ctx* ctx, const vr_particles* p, int32_t n_h
     rc = kd_build(ctx, p, n_hosts, host_offsets, host_members, off, nc, KD_BUCKETS, 2, tree, st);
     if (rc) return rc;
     // The buckets follow from the sizes: every node above `cap` is halved.
-    std::vector<int4> buckets;
-    std::vector<int> hb(n_hosts + 1, 0);
-    int64_t n_leaves = 0;
-    for (int h = 0; h < n_hosts; ++h) {
-        std::vector<std::pair<int, int>> todo{{off[h], off[h + 1] - off[h]}};
-        while (!todo.empty()) {
-            const auto [s, n] = todo.back();
-            todo.pop_back();
-            if (n > cap) {
-                todo.push_back({s + n / 2, n - n / 2});
-                todo.push_back({s, n / 2});
-                continue;
+    auto each_bucket = [&](int s, int n, auto&& put) {
+        if (n <= cap) return put(s, n);
+        // (a host of 2^22 members is halved 14 times)
+        std::pair<int, int> todo[32] = {{s, n}};
+        for (int left = 1; left > 0;) {
+            const auto [at, m] = todo[--left];
+            if (m > cap) {
+                todo[left++] = {at + m / 2, m - m / 2};
+                todo[left++] = {at, m / 2};
+            } else {
+                put(at, m);
             }
-            buckets.push_back(make_int4(s, n, (int)n_leaves, h));
-            n_leaves += (n + LEAF - 1) / LEAF;
         }
-        hb[h + 1] = (int)buckets.size();
-    }
-    const int64_t nb = (int64_t)buckets.size(), n_slots = n_leaves * LEAF;
+    };
+    int64_t nb = 0, n_leaves = 0, fit = 0;
+    for (int h = 0; h < n_hosts; ++h)
+        each_bucket(off[h], off[h + 1] - off[h], [&](int, int n) {
+            ++nb;
+            n_leaves += (n + LEAF - 1) / LEAF;
+            fit += n <= BUCKET_SMALL;
+        });
+    // The small ones get their own launch where the chip could not hold them
+    // all beside the others anyway: the launches follow each other, 59 and 45 us
+    // where a workgroup each took 59 in all (300 buckets).
+    const bool split = fit > 3 * ctx->num_cus;
+    const int64_t n_slots = n_leaves * LEAF;
     if (n_slots > INT32_MAX) return set_err(ctx, VR_ERR_UNSUPPORTED, "too many host members for one call");
     Slots T{};
+    const int2* runs = nullptr;
     Carve cv;
     auto layout = [&]() {
         T.x = cv.add<float>(n_slots);
@@ -1113,7 +1203,8 @@ extern "C" int vr_local_vdensity(vr_ctx* ctx, const vr_particles* p, int32_t n_h
         T.lbox = cv.add<float4>(2 * n_leaves);
         T.bbox = cv.add<float4>(2 * nb);
         T.leaf_bucket = cv.add<int>(n_leaves);
-        T.buckets = cv.add<int4>(nb + (n_hosts + 4) / 4);  // and the hosts' first buckets, one upload
+        // one upload: buckets, the hosts' first ones, the workgroups' runs of them
+        T.buckets = cv.add<int4>(nb + (2 * nb + n_hosts + 5) / 4);
     };
     layout();
     const size_t total = cv.bytes;
@@ -1121,22 +1212,59 @@ extern "C" int vr_local_vdensity(vr_ctx* ctx, const vr_particles* p, int32_t n_h
     cv.base = static_cast<char*>(ws(ctx, WS_C3, total));
     if (!cv.base) return VR_ERR_OUT_OF_MEMORY;
     layout();
+    // runs of one large bucket, then those of small ones
+    const int64_t n_large = nb - (split ? fit : 0);
+    int64_t n_runs = n_large;
     {
-        const size_t b0 = nb * sizeof(int4), b1 = hb.size() * sizeof(int);
-        char* up = static_cast<char*>(upload_begin(ctx, b0 + b1));
+        const size_t room = nb * (sizeof(int4) + sizeof(int2)) + ((size_t)n_hosts + 2) * sizeof(int);
+        int4* up = static_cast<int4*>(upload_begin(ctx, room));
         if (!up) return VR_ERR_HIP;
-        std::memcpy(up, buckets.data(), b0);
-        std::memcpy(up + b0, hb.data(), b1);
-        VR_HIP(ctx, hipMemcpyAsync(T.buckets, up, b0 + b1, hipMemcpyHostToDevice, st));
-        T.host_bucket = reinterpret_cast<int*>(T.buckets + nb);
+        int* uh = reinterpret_cast<int*>(up + nb);
+        int2* ur = reinterpret_cast<int2*>(uh + ((n_hosts + 2) & ~1));
+        int2 run = make_int2(0, 0);  // the run of small buckets being filled, and its leaves
+        int k = 0, leaf = 0, filled = 0;
+        int64_t at = 0;
+        auto close = [&]() {
+            if (run.y > 0) ur[n_runs++] = run;
+            run.y = filled = 0;
+        };
+        for (int h = 0; h < n_hosts; ++h) {
+            uh[h] = k;
+            each_bucket(off[h], off[h + 1] - off[h], [&](int s, int n) {
+                const int nl = (n + LEAF - 1) / LEAF;
+                up[k] = make_int4(s, n, leaf, h);
+                if (split && n <= BUCKET_SMALL) {
+                    if (filled + nl > BUCKET_SMALL / LEAF) close();
+                    if (run.y++ == 0) run.x = k;
+                    filled += nl;
+                } else if (split) {
+                    close();
+                    ur[at++] = make_int2(k, 1);
+                }
+                ++k;
+                leaf += nl;
+            });
+        }
+        uh[n_hosts] = k;
+        close();
+        runs = reinterpret_cast<int2*>(reinterpret_cast<char*>(T.buckets) + ((char*)ur - (char*)up));
+        const size_t used = (char*)(ur + (split ? n_runs : 0)) - (char*)up;
+        VR_HIP(ctx, hipMemcpyAsync(T.buckets, up, used, hipMemcpyHostToDevice, st));
         if ((rc = upload_end(ctx, st))) return rc;
     }
+    T.host_bucket = reinterpret_cast<int*>(T.buckets + nb);
     VR_WS(V, ctx, float4, WS_C0, n_slots);
     VR_WS(FB, ctx, double, WS_C1, n_slots);
     VR_WS(flagged, ctx, int, WS_C4, subset ? n_subset : M);
     const int lpq_log2 = n_se > 64 ? 4 : 2;
-    hipLaunchKernelGGL(k_buckets, dim3((unsigned)nb), dim3(256), 0, st, tree.list[0], tree.list[1], tree.list[2],
-                       tree.elem_u[0], tree.elem_u[1], tree.elem_u[2], tree.elem_g, tree.scratch, lpq_log2, T, slot_of);
+    if (n_large > 0)
+        hipLaunchKernelGGL(k_buckets<256>, dim3((unsigned)n_large), dim3(256), 0, st, split ? runs : nullptr, tree.list[0], tree.list[1],
+                           tree.list[2], tree.elem_u[0], tree.elem_u[1], tree.elem_u[2], tree.elem_g, tree.scratch,
+                           lpq_log2, T, slot_of);
+    if (n_runs > n_large)
+        hipLaunchKernelGGL(k_buckets<64>, dim3((unsigned)(n_runs - n_large)), dim3(64), 0, st, runs + n_large, tree.list[0],
+                           tree.list[1], tree.list[2], tree.elem_u[0], tree.elem_u[1], tree.elem_u[2], tree.elem_g,
+                           tree.scratch, lpq_log2, T, slot_of);
     VR_LAUNCH_CHECK(ctx);
     hipLaunchKernelGGL(k_member_records, dim3(grid_for(p->n, 256)), dim3(256), 0, st, p->n, slot_of, p->vx, p->vy,
                        p->vz, p->mass, vbar, sigma, V, FB);

@@ -135,3 +135,19 @@ def test_presort_key_widths(ctx, vr, ref, n_hosts, extent):
     rng = np.random.default_rng(n_hosts)
     sizes = (64 + rng.integers(0, 40, n_hosts)).tolist() if n_hosts > 1 else [3000]
     _check(ctx, vr, ref, _hosts(rng, sizes, extent=extent), 32, 8)
+
+
+@pytest.mark.parametrize("n_se,n_v,lo,hi", [(2, 2, 2, 5), (32, 8, 32, 70), (48, 16, 48, 130), (256, 32, 256, 300)])
+@pytest.mark.parametrize("leaf", [16, 256])
+def test_many_small_hosts(ctx, vr, ref, leaf, n_se, n_v, lo, hi):
+    """More small buckets than the chip holds at once: a wavefront takes as many
+    of them as 16 leaves hold, with larger ones and full ones in between."""
+    rng = np.random.default_rng(n_se + leaf)
+    sizes = rng.integers(lo, hi + 1, 900)
+    sizes[[0, 100, 101, 450, 899]] = [512, 513, 511, 2500, 481]
+    saved = ctx.get_tune("knn_leaf")
+    try:
+        ctx.tune("knn_leaf", leaf)
+        _check(ctx, vr, ref, _hosts(rng, sizes.tolist(), extent=1e-3, masses=n_se == 48), n_se, n_v)
+    finally:
+        ctx.tune("knn_leaf", saved)
