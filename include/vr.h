@@ -191,7 +191,10 @@ int vr_cell_moments(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts,
  * n_se > 64 (the paper's defaults, 256 and 32, are the largest case), every host has
  * >= n_se members.  subset (may be NULL = all host members) lists the particles to
  * process; R is written only for them (NaN if sigma is not positive
- * definite, +inf if h = 0).  VR_ERR_INVALID_ARG, with nothing written to R,
+ * definite, +inf if h = 0).  Hosts are searched in ranges whose members,
+ * padded to 32 a host, stay within 5/4 of all members (2^24 where no cap is
+ * set), so small hosts need no more workspace a member than large ones; a
+ * host holds at most 2^22 members.  VR_ERR_INVALID_ARG, with nothing written to R,
  * if host_members lists a particle twice or one outside [0, n). */
 int vr_local_vdensity(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts,
                       const int32_t* host_offsets, const int32_t* host_members,

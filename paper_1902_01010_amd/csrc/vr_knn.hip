@@ -165,6 +165,26 @@ __global__ void k_subset_slot(int64_t ns, int64_t n, const int32_t* __restrict__
     qval[s] = (uint32_t)s;
 }
 
+// cut[i] = the number of sorted ranks below cut[i]
+__global__ void k_cuts(int nc, int* __restrict__ cut, int64_t ns, const uint32_t* __restrict__ rank) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= nc) return;
+    int64_t lo = 0, hi = ns;
+    while (lo < hi) {
+        const int64_t mid = (lo + hi) >> 1;
+        if (rank[mid] < (uint32_t)cut[i]) lo = mid + 1;
+        else hi = mid;
+    }
+    cut[i] = (int)lo;
+}
+
+// the slots of members by rank, in place
+__global__ void k_rank_slot(int64_t ns, const int* __restrict__ mem, const int* __restrict__ slot_of,
+                            uint32_t* __restrict__ q) {
+    const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (s < ns) q[s] = (uint32_t)slot_of[mem[q[s]]];
+}
+
 // slot_of[g] = the position of particle g in host_members (-1 beforehand; the
 // bucket build replaces it by the slot); a member outside [0, n) or listed
 // twice raises *bad
@@ -1178,33 +1198,56 @@ extern "C" int vr_local_vdensity(vr_ctx* ctx, const vr_particles* p, int32_t n_h
             }
         }
     };
-    int64_t nb = 0, n_leaves = 0, fit = 0;
-    for (int h = 0; h < n_hosts; ++h)
-        each_bucket(off[h], off[h + 1] - off[h], [&](int, int n) {
-            ++nb;
-            n_leaves += (n + LEAF - 1) / LEAF;
-            fit += n <= BUCKET_SMALL;
-        });
-    // The small ones get their own launch where the chip could not hold them
-    // all beside the others anyway: the launches follow each other, 59 and 45 us
-    // where a workgroup each took 59 in all (300 buckets).
-    const bool split = fit > 3 * ctx->num_cus;
-    const int64_t n_slots = n_leaves * LEAF;
-    if (n_slots > INT32_MAX) return set_err(ctx, VR_ERR_UNSUPPORTED, "too many host members for one call");
+    // A host's leaves are its own, so small hosts pad theirs: two members take
+    // 32 slots.  The hosts are searched in ranges whose slots stay within 5/4
+    // of the members (or 2^24 where nothing caps the workspace), at least one
+    // host each: one range where the hosts have 128 members or more.
+    struct Range {
+        int h0, h1;
+        int64_t nb, leaves, fit;  // buckets, their leaves, buckets a wavefront finishes
+    };
+    std::vector<Range> ranges;
+    Range most{0, 0, 0, 0, 0};  // of each the largest
+    {
+        const int64_t room = std::max(M + M / 4, ctx->max_ws ? int64_t(0) : int64_t(1) << 24) / LEAF;
+        Range r{0, 0, 0, 0, 0};
+        auto close = [&](int h) {
+            r.h1 = h;
+            ranges.push_back(r);
+            most.h1 = std::max(most.h1, r.h1 - r.h0);
+            most.nb = std::max(most.nb, r.nb);
+            most.leaves = std::max(most.leaves, r.leaves);
+            r = Range{h, h, 0, 0, 0};
+        };
+        for (int h = 0; h < n_hosts; ++h) {
+            int64_t nb = 0, leaves = 0, fit = 0;
+            each_bucket(off[h], off[h + 1] - off[h], [&](int, int n) {
+                ++nb;
+                leaves += (n + LEAF - 1) / LEAF;
+                fit += n <= BUCKET_SMALL;
+            });
+            if (r.leaves > 0 && r.leaves + leaves > std::min<int64_t>(room, INT32_MAX / LEAF)) close(h);
+            r.nb += nb;
+            r.leaves += leaves;
+            r.fit += fit;
+        }
+        close(n_hosts);
+    }
+    const int nr = (int)ranges.size();
     Slots T{};
-    const int2* runs = nullptr;
     Carve cv;
     auto layout = [&]() {
+        const int64_t n_slots = most.leaves * LEAF;
         T.x = cv.add<float>(n_slots);
         T.y = cv.add<float>(n_slots);
         T.z = cv.add<float>(n_slots);
         T.gid = cv.add<int>(n_slots);
         T.eid = cv.add<int>(n_slots);
-        T.lbox = cv.add<float4>(2 * n_leaves);
-        T.bbox = cv.add<float4>(2 * nb);
-        T.leaf_bucket = cv.add<int>(n_leaves);
+        T.lbox = cv.add<float4>(2 * most.leaves);
+        T.bbox = cv.add<float4>(2 * most.nb);
+        T.leaf_bucket = cv.add<int>(most.leaves);
         // one upload: buckets, the hosts' first ones, the workgroups' runs of them
-        T.buckets = cv.add<int4>(nb + (2 * nb + n_hosts + 5) / 4);
+        T.buckets = cv.add<int4>(most.nb + (2 * most.nb + most.h1 + 5) / 4);
     };
     layout();
     const size_t total = cv.bytes;
@@ -1212,95 +1255,138 @@ extern "C" int vr_local_vdensity(vr_ctx* ctx, const vr_particles* p, int32_t n_h
     cv.base = static_cast<char*>(ws(ctx, WS_C3, total));
     if (!cv.base) return VR_ERR_OUT_OF_MEMORY;
     layout();
-    // runs of one large bucket, then those of small ones
-    const int64_t n_large = nb - (split ? fit : 0);
-    int64_t n_runs = n_large;
-    {
-        const size_t room = nb * (sizeof(int4) + sizeof(int2)) + ((size_t)n_hosts + 2) * sizeof(int);
-        int4* up = static_cast<int4*>(upload_begin(ctx, room));
-        if (!up) return VR_ERR_HIP;
-        int* uh = reinterpret_cast<int*>(up + nb);
-        int2* ur = reinterpret_cast<int2*>(uh + ((n_hosts + 2) & ~1));
-        int2 run = make_int2(0, 0);  // the run of small buckets being filled, and its leaves
-        int k = 0, leaf = 0, filled = 0;
-        int64_t at = 0;
-        auto close = [&]() {
-            if (run.y > 0) ur[n_runs++] = run;
-            run.y = filled = 0;
-        };
-        for (int h = 0; h < n_hosts; ++h) {
-            uh[h] = k;
-            each_bucket(off[h], off[h + 1] - off[h], [&](int s, int n) {
-                const int nl = (n + LEAF - 1) / LEAF;
-                up[k] = make_int4(s, n, leaf, h);
-                if (split && n <= BUCKET_SMALL) {
-                    if (filled + nl > BUCKET_SMALL / LEAF) close();
-                    if (run.y++ == 0) run.x = k;
-                    filled += nl;
-                } else if (split) {
-                    close();
-                    ur[at++] = make_int2(k, 1);
-                }
-                ++k;
-                leaf += nl;
-            });
-        }
-        uh[n_hosts] = k;
-        close();
-        runs = reinterpret_cast<int2*>(reinterpret_cast<char*>(T.buckets) + ((char*)ur - (char*)up));
-        const size_t used = (char*)(ur + (split ? n_runs : 0)) - (char*)up;
-        VR_HIP(ctx, hipMemcpyAsync(T.buckets, up, used, hipMemcpyHostToDevice, st));
-        if ((rc = upload_end(ctx, st))) return rc;
-    }
-    T.host_bucket = reinterpret_cast<int*>(T.buckets + nb);
-    VR_WS(V, ctx, float4, WS_C0, n_slots);
-    VR_WS(FB, ctx, double, WS_C1, n_slots);
+    VR_WS(V, ctx, float4, WS_C0, most.leaves * LEAF);
+    VR_WS(FB, ctx, double, WS_C1, most.leaves * LEAF);
     VR_WS(flagged, ctx, int, WS_C4, subset ? n_subset : M);
     const int lpq_log2 = n_se > 64 ? 4 : 2;
-    if (n_large > 0)
-        hipLaunchKernelGGL(k_buckets<256>, dim3((unsigned)n_large), dim3(256), 0, st, split ? runs : nullptr, tree.list[0], tree.list[1],
-                           tree.list[2], tree.elem_u[0], tree.elem_u[1], tree.elem_u[2], tree.elem_g, tree.scratch,
-                           lpq_log2, T, slot_of);
-    if (n_runs > n_large)
-        hipLaunchKernelGGL(k_buckets<64>, dim3((unsigned)(n_runs - n_large)), dim3(64), 0, st, runs + n_large, tree.list[0],
-                           tree.list[1], tree.list[2], tree.elem_u[0], tree.elem_u[1], tree.elem_u[2], tree.elem_g,
-                           tree.scratch, lpq_log2, T, slot_of);
-    VR_LAUNCH_CHECK(ctx);
-    hipLaunchKernelGGL(k_member_records, dim3(grid_for(p->n, 256)), dim3(256), 0, st, p->n, slot_of, p->vx, p->vy,
-                       p->vz, p->mass, vbar, sigma, V, FB);
-    VR_LAUNCH_CHECK(ctx);
-    const uint32_t* qpos = nullptr;
-    int64_t nq = n_slots, n_queries = M;
-    if (subset) {
-        VR_WS(qp, ctx, uint32_t, WS_C5, n_subset);
-        VR_WS(qv, ctx, uint32_t, WS_C6, n_subset);
+    uint32_t *qp = nullptr, *qv = nullptr;
+    std::vector<int> cut;  // the ranges' queries, by rank
+    auto subset_places = [&](int64_t places) -> int {
         VR_WS(bad, ctx, int, WS_FLAG2, 4);
-        rc = fill_i32(ctx, bad, 0, 1, st);
-        if (rc) return rc;
+        if ((rc = fill_i32(ctx, bad, 0, 1, st))) return rc;
         hipLaunchKernelGGL(k_subset_slot, dim3(grid_for(n_subset, 256)), dim3(256), 0, st, n_subset, p->n, subset,
                            slot_of, qp, qv, bad);
         VR_LAUNCH_CHECK(ctx);
         int badh = 0;
-        rc = read_back(ctx, bad, &badh, sizeof badh, st);
-        if (rc) return rc;
+        if ((rc = read_back(ctx, bad, &badh, sizeof badh, st))) return rc;
         if (badh) return set_err(ctx, VR_ERR_INVALID_ARG, "subset lists a particle that is in no host");
         int bits = 1;
-        while ((int64_t(1) << bits) < n_slots) ++bits;
-        rc = sort_pairs_u32(ctx, qp, qv, n_subset, bits, st);
-        if (rc) return rc;
-        qpos = qp;
-        nq = n_queries = n_subset;
+        while ((int64_t(1) << bits) < places) ++bits;
+        return sort_pairs_u32(ctx, qp, qv, n_subset, bits, st);
+    };
+    if (subset) {
+        VR_WS(qp_w, ctx, uint32_t, WS_C5, n_subset);
+        VR_WS(qv_w, ctx, uint32_t, WS_C6, n_subset);
+        qp = qp_w;
+        qv = qv_w;
+        if (nr > 1) {
+            if ((rc = subset_places(M))) return rc;  // slot_of still holds the ranks
+            cut.resize(nr + 1);
+            VR_WS(cut_d, ctx, int, WS_C7, nr + 1);
+            int* up = static_cast<int*>(upload_begin(ctx, (nr + 1) * sizeof(int)));
+            if (!up) return VR_ERR_HIP;
+            for (int i = 0; i <= nr; ++i) up[i] = i < nr ? off[ranges[i].h0] : (int)M;
+            VR_HIP(ctx, hipMemcpyAsync(cut_d, up, (nr + 1) * sizeof(int), hipMemcpyHostToDevice, st));
+            if ((rc = upload_end(ctx, st))) return rc;
+            hipLaunchKernelGGL(k_cuts, dim3(grid_for(nr + 1, 64)), dim3(64), 0, st, nr + 1, cut_d, n_subset, qp);
+            VR_LAUNCH_CHECK(ctx);
+            if ((rc = read_back(ctx, cut_d, cut.data(), (nr + 1) * sizeof(int), st))) return rc;
+        }
     }
     int* nfl = dup + 1;  // zero since the fill above
-    T.images = tree.images;
+    T.images = nullptr;
     T.box = tree.images ? (float)(1 << p->grid_bits) : 1e30f;
-    if (n_se <= 32)
-        rc = launch_knn<4, 8, 12>(ctx, qpos, nq, n_queries, T, V, FB, host_offsets, p, n_se, n_v, R, flagged, nfl, st);
-    else if (n_se <= 64)
-        rc = launch_knn<4, 16, 22>(ctx, qpos, nq, n_queries, T, V, FB, host_offsets, p, n_se, n_v, R, flagged, nfl, st);
-    else if (n_se <= 128)
-        rc = launch_knn<16, 8, 14>(ctx, qpos, nq, n_queries, T, V, FB, host_offsets, p, n_se, n_v, R, flagged, nfl, st);
-    else  // up to the paper's defaults (n_se 256, n_v 32)
-        rc = launch_knn<16, 16, 24>(ctx, qpos, nq, n_queries, T, V, FB, host_offsets, p, n_se, n_v, R, flagged, nfl, st);
-    return rc;
+    for (int ri = 0; ri < nr; ++ri) {
+        const Range& r = ranges[ri];
+        if (nr > 1 && subset && cut[ri] == cut[ri + 1]) continue;
+        if (nr > 1 && ((rc = fill_i32(ctx, slot_of, -1, p->n, st)) || (rc = fill_i32(ctx, nfl, 0, 1, st)))) return rc;
+        const int64_t nb = r.nb, n_slots = r.leaves * LEAF;
+        const int nh = r.h1 - r.h0;
+        // The small buckets get their own launch where the chip could not hold
+        // them all beside the others anyway: the launches follow each other, 59
+        // and 45 us where a workgroup each took 59 in all (300 buckets).
+        const bool split = r.fit > 3 * ctx->num_cus;
+        // runs of one large bucket, then those of small ones
+        const int64_t n_large = nb - (split ? r.fit : 0);
+        int64_t n_runs = n_large;
+        const int2* runs = nullptr;
+        {
+            const size_t room = nb * (sizeof(int4) + sizeof(int2)) + ((size_t)nh + 2) * sizeof(int);
+            int4* up = static_cast<int4*>(upload_begin(ctx, room));
+            if (!up) return VR_ERR_HIP;
+            int* uh = reinterpret_cast<int*>(up + nb);
+            int2* ur = reinterpret_cast<int2*>(uh + ((nh + 2) & ~1));
+            int2 run = make_int2(0, 0);  // the run of small buckets being filled
+            int k = 0, leaf = 0, filled = 0;
+            int64_t at = 0;
+            auto close = [&]() {
+                if (run.y > 0) ur[n_runs++] = run;
+                run.y = filled = 0;
+            };
+            for (int h = r.h0; h < r.h1; ++h) {
+                uh[h - r.h0] = k;
+                each_bucket(off[h], off[h + 1] - off[h], [&](int s, int n) {
+                    const int nl = (n + LEAF - 1) / LEAF;
+                    up[k] = make_int4(s, n, leaf, h - r.h0);
+                    if (split && n <= BUCKET_SMALL) {
+                        if (filled + nl > BUCKET_SMALL / LEAF) close();
+                        if (run.y++ == 0) run.x = k;
+                        filled += nl;
+                    } else if (split) {
+                        close();
+                        ur[at++] = make_int2(k, 1);
+                    }
+                    ++k;
+                    leaf += nl;
+                });
+            }
+            uh[nh] = k;
+            close();
+            T.host_bucket = reinterpret_cast<int*>(T.buckets + nb);
+            if (split) runs = reinterpret_cast<int2*>(T.host_bucket + ((nh + 2) & ~1));
+            const size_t used = (char*)(ur + (split ? n_runs : 0)) - (char*)up;
+            VR_HIP(ctx, hipMemcpyAsync(T.buckets, up, used, hipMemcpyHostToDevice, st));
+            if ((rc = upload_end(ctx, st))) return rc;
+        }
+        if (tree.images) T.images = tree.images + 6 * (int64_t)r.h0;
+        auto build = [&](auto kernel, int64_t n, const int2* run, int threads) {
+            if (n > 0)
+                hipLaunchKernelGGL(kernel, dim3((unsigned)n), dim3(threads), 0, st, run, tree.list[0], tree.list[1],
+                                   tree.list[2], tree.elem_u[0], tree.elem_u[1], tree.elem_u[2], tree.elem_g,
+                                   tree.scratch, lpq_log2, T, slot_of);
+        };
+        build(k_buckets<256>, n_large, runs, 256);
+        build(k_buckets<64>, n_runs - n_large, runs + n_large, 64);
+        VR_LAUNCH_CHECK(ctx);
+        hipLaunchKernelGGL(k_member_records, dim3(grid_for(p->n, 256)), dim3(256), 0, st, p->n, slot_of, p->vx, p->vy,
+                           p->vz, p->mass, vbar, sigma, V, FB);
+        VR_LAUNCH_CHECK(ctx);
+        const uint32_t* qpos = nullptr;
+        int64_t nq = n_slots, n_queries = off[r.h1] - off[r.h0];
+        if (subset && nr == 1) {
+            if ((rc = subset_places(n_slots))) return rc;
+            qpos = qp;
+            nq = n_queries = n_subset;
+        } else if (subset) {
+            uint32_t* q = qp + cut[ri];
+            nq = n_queries = cut[ri + 1] - cut[ri];
+            hipLaunchKernelGGL(k_rank_slot, dim3(grid_for(nq, 256)), dim3(256), 0, st, nq, host_members, slot_of, q);
+            VR_LAUNCH_CHECK(ctx);
+            int bits = 1;
+            while ((int64_t(1) << bits) < n_slots) ++bits;
+            if ((rc = sort_pairs_u32(ctx, q, qv, nq, bits, st))) return rc;
+            qpos = q;
+        }
+        const int32_t* ho = host_offsets + r.h0;
+        if (n_se <= 32)
+            rc = launch_knn<4, 8, 12>(ctx, qpos, nq, n_queries, T, V, FB, ho, p, n_se, n_v, R, flagged, nfl, st);
+        else if (n_se <= 64)
+            rc = launch_knn<4, 16, 22>(ctx, qpos, nq, n_queries, T, V, FB, ho, p, n_se, n_v, R, flagged, nfl, st);
+        else if (n_se <= 128)
+            rc = launch_knn<16, 8, 14>(ctx, qpos, nq, n_queries, T, V, FB, ho, p, n_se, n_v, R, flagged, nfl, st);
+        else  // up to the paper's defaults (n_se 256, n_v 32)
+            rc = launch_knn<16, 16, 24>(ctx, qpos, nq, n_queries, T, V, FB, ho, p, n_se, n_v, R, flagged, nfl, st);
+        if (rc) return rc;
+    }
+    return VR_OK;
 }

@@ -151,3 +151,32 @@ def test_many_small_hosts(ctx, vr, ref, leaf, n_se, n_v, lo, hi):
         _check(ctx, vr, ref, _hosts(rng, sizes.tolist(), extent=1e-3, masses=n_se == 48), n_se, n_v)
     finally:
         ctx.tune("knn_leaf", saved)
+
+
+@pytest.mark.parametrize("n_hosts,size,n_se,n_v,subset,room", [(20000, 2, 2, 2, False, 360), (20000, 2, 2, 2, True, 372),
+                                                               (3000, 33, 32, 8, False, 196), (3000, 33, 32, 8, True, 207),
+                                                               (3000, 65, 32, 8, False, 190)])
+def test_small_hosts_within_a_workspace_cap(vr, ref, n_hosts, size, n_se, n_v, subset, room):
+    """Hosts that pad their leaves most, in as many ranges as `room` bytes a
+    member allow (what the search needed before its leaves were padded)."""
+    rng = np.random.default_rng(size)
+    case = _hosts(rng, [size] * n_hosts, extent=1e-3)
+    n = case[0].n
+    capped = vr.Context(0, max_workspace_bytes=room * n)
+    _check(capped, vr, ref, case, n_se, n_v, subset=rng.permutation(n)[:n // 2].astype(np.int32) if subset else None)
+    assert capped.workspace_bytes() <= room * n
+
+
+def test_ranges_of_hosts_of_all_sizes(vr, ref):
+    """Large hosts between runs of small ones, whole and by a subset that leaves
+    whole ranges out."""
+    rng = np.random.default_rng(12)
+    sizes = np.concatenate([rng.integers(32, 40, 2500), [5000], rng.integers(32, 40, 2500), [700, 4096], [33] * 300])
+    case = _hosts(rng, sizes.tolist(), extent=2e-3, masses=True)
+    n = case[0].n
+    capped = vr.Context(0, max_workspace_bytes=215 * n)
+    _check(capped, vr, ref, case, 32, 8)
+    off = case[1]
+    for lo, hi in ((0, n), (2490, 2510), (off[2500], off[2501]), (off[5001], n)):
+        sub = rng.permutation(np.arange(lo, hi))[:1500].astype(np.int32)
+        _check(capped, vr, ref, case, 32, 8, subset=sub)
