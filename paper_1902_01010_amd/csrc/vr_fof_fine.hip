@@ -612,9 +612,10 @@ int fof3d_fine(vr_ctx* ctx, const vr_particles* p, double ell2, int s, int32_t* 
     VR_WS(occ, ctx, unsigned long long, WS_B4, owords);
     VR_WS(pre, ctx, uint32_t, WS_B5, owords + 1);
     VR_WS(frec, ctx, uint2, WS_B6, (int64_t)nfine);
-    VR_WS(uf, ctx, int, WS_B0, (int64_t)nfine);
-    VR_WS(mn, ctx, int, WS_B1, (int64_t)nfine);
-    VR_WS(tables, ctx, uint64_t, WS_A8, 2 * 64 * NOFF);
+    // (the union-find and what the passes read beside the records lie in the
+    // sort's other buffers: particles in cells of their own, the most there can
+    // be, then need no more room than one tree over the particles did)
+    VR_WS(uf, ctx, int, WS_SORT_VALS_B, (int64_t)nfine);
     if ((rc = fill_u32(ctx, reinterpret_cast<uint32_t*>(occ), 0u, 2 * owords, st))) return rc;
     const unsigned gf = grid_for(nfine, 256);
     hipLaunchKernelGGL(k_coarse_flags, dim3(gf), dim3(256), 0, st, (int64_t)nfine, tot, fine_start, key, 3 * G.lr, cid);
@@ -629,7 +630,21 @@ int fof3d_fine(vr_ctx* ctx, const vr_particles* p, double ell2, int s, int32_t* 
     VR_LAUNCH_CHECK(ctx);
     if ((rc = scan_u32(ctx, pre, pre, owords, nullptr, st))) return rc;
     VR_WS(crec, ctx, uint4, WS_B3, (int64_t)ncoarse);
-    VR_WS(nbits, ctx, uint32_t, WS_B7, (int64_t)ncoarse);
+    uint64_t* tables = nullptr;
+    uint32_t* nbits = nullptr;
+    int* mn = nullptr;
+    Carve cv;
+    auto layout = [&]() {
+        tables = cv.add<uint64_t>(2 * 64 * NOFF);
+        nbits = cv.add<uint32_t>(ncoarse);
+        mn = cv.add<int>(nfine);
+    };
+    layout();
+    const size_t rest = cv.bytes;
+    cv.bytes = 0;
+    cv.base = static_cast<char*>(ws(ctx, WS_SORT_KEYS_B, rest));
+    if (!cv.base) return VR_ERR_OUT_OF_MEMORY;
+    layout();
     const int64_t l2c = (int64_t)std::ceil(ell2);  // ell2 < 2^40: exact
     const uint64_t* occ_c = reinterpret_cast<const uint64_t*>(occ);
     const unsigned gc = grid_for(ncoarse, 256);

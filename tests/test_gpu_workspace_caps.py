@@ -1,0 +1,56 @@
+"""Calls under the smallest workspace cap that each has run with: the result of
+a context without a cap, within the room."""
+import numpy as np
+import pytest
+
+from paper_1902_01010_amd import synth
+from tests.gpu_common import dev_tensor
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def vr():
+    from paper_1902_01010_amd import vr as m
+    return m
+
+
+def _sparse(vr, ctx, n, seed=1, box=1.0, masses=False):
+    """Particles mostly in grid cells of their own, the most cells there can be."""
+    rng = np.random.default_rng(seed)
+    x = (rng.random((3, n)) * box * (1 - 1e-6)).astype(np.float32)
+    v = rng.normal(0, 100, (3, n)).astype(np.float32)
+    m = dev_tensor((0.5 + rng.random(n)).astype(np.float32)) if masses else None
+    return rng, vr.Particles(ctx.quantize(dev_tensor(x), box, 21), dev_tensor(v), m, 1.0, box, 21)
+
+
+def fof3d(vr, ctx, n):
+    _, P = _sparse(vr, ctx, n)
+    return [ctx.fof3d(P, 0.5 * n ** (-1 / 3))]
+
+
+def fof3d_dm(vr, ctx, n):
+    rng, P = _sparse(vr, ctx, n)
+    return [ctx.fof3d_dm(P, 0.5 * n ** (-1 / 3), dev_tensor((rng.random(n) < 0.4).astype(np.uint8)))]
+
+
+CALLS = {f.__name__: f for f in (fof3d, fof3d_dm)}
+
+# (call, particles, bytes)
+ROOM = [("fof3d", 20000, 2079011), ("fof3d", 200000, 19994736), ("fof3d_dm", 20000, 2569251),
+        ("fof3d_dm", 200000, 23420408)]
+
+
+@pytest.mark.parametrize("name,n,room", ROOM)
+def test_same_result_within_the_cap(vr, name, n, room):
+    call = CALLS[name]
+    free = call(vr, vr.Context(0), n)
+    capped = vr.Context(0, max_workspace_bytes=room)
+    got = call(vr, capped, n)
+    assert capped.workspace_bytes() <= room
+    for a, b in zip(free, got):
+        a, b = a.cpu().numpy(), b.cpu().numpy()
+        if a.dtype.kind == "f":
+            np.testing.assert_allclose(b, a, rtol=1e-5, atol=1e-6 * np.nanmax(np.abs(a)))
+        else:
+            assert (a == b).all()
