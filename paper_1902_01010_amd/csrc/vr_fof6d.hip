@@ -898,9 +898,12 @@ int link_outliers(vr_ctx* ctx, const vr_particles* p, const int32_t* host_of, co
     rc = fill_i32(ctx, label6, -1, n, st);
     if (rc) return rc;
     if (np == 0) return VR_OK;
-    VR_WS(cx, ctx, uint32_t, WS_C2, np);
-    VR_WS(cy, ctx, uint32_t, WS_C3, np);
-    VR_WS(cz, ctx, uint32_t, WS_C4, np);
+    // (buffers change hands, so that the 16-byte records take no more room than
+    // single values would: the participants' coordinates give theirs to the
+    // velocities once the cell list holds them in order, the flags and their
+    // positions to the sorted indices and the union-find)
+    VR_WS(vel, ctx, float4, WS_C2, np);
+    uint32_t *cx = reinterpret_cast<uint32_t*>(vel), *cy = cx + np, *cz = cy + np;
     VR_WS(orig, ctx, int32_t, WS_C5, np);
     hipLaunchKernelGGL(k_compact_part, dim3(grid_for(n, 256)), dim3(256), 0, st, n, flag, pos, p->qx, p->qy, p->qz, cx,
                        cy, cz, orig);
@@ -910,10 +913,9 @@ int link_outliers(vr_ctx* ctx, const vr_particles* p, const int32_t* host_of, co
     CellList cl;
     rc = build_cell_list(ctx, np, cx, cy, cz, gb, s, cl, st);
     if (rc) return rc;
-    VR_WS(sorig, ctx, int32_t, WS_C6, np);
+    int32_t* sorig = reinterpret_cast<int32_t*>(flag);
+    int* parent = reinterpret_cast<int*>(pos);
     VR_WS(rec, ctx, int4, WS_C7, np);
-    VR_WS(vel, ctx, float4, WS_C8, np);
-    VR_WS(parent, ctx, int, WS_D2, np);
     VR_WS(mn, ctx, int, WS_D3, np);
     hipLaunchKernelGGL(k_sorted_attrs, dim3(grid_for(np, 256)), dim3(256), 0, st, np, cl.idx, orig, cl.sx, cl.sy, cl.sz,
                        p->vx, p->vy, p->vz, host_of, sorig, nullptr, rec, vel);

@@ -15,13 +15,12 @@ def vr():
     return m
 
 
-def _sparse(vr, ctx, n, seed=1, box=1.0, masses=False):
+def _sparse(vr, ctx, n):
     """Particles mostly in grid cells of their own, the most cells there can be."""
-    rng = np.random.default_rng(seed)
-    x = (rng.random((3, n)) * box * (1 - 1e-6)).astype(np.float32)
+    rng = np.random.default_rng(1)
+    x = (rng.random((3, n)) * (1 - 1e-6)).astype(np.float32)
     v = rng.normal(0, 100, (3, n)).astype(np.float32)
-    m = dev_tensor((0.5 + rng.random(n)).astype(np.float32)) if masses else None
-    return rng, vr.Particles(ctx.quantize(dev_tensor(x), box, 21), dev_tensor(v), m, 1.0, box, 21)
+    return rng, vr.Particles(ctx.quantize(dev_tensor(x), 1.0, 21), dev_tensor(v), None, 1.0, 1.0, 21)
 
 
 def fof3d(vr, ctx, n):
@@ -34,11 +33,36 @@ def fof3d_dm(vr, ctx, n):
     return [ctx.fof3d_dm(P, 0.5 * n ** (-1 / 3), dev_tensor((rng.random(n) < 0.4).astype(np.uint8)))]
 
 
-CALLS = {f.__name__: f for f in (fof3d, fof3d_dm)}
+def _hosted(vr, ctx, n):
+    rng, P = _sparse(vr, ctx, n)
+    return rng, P, dev_tensor((np.arange(n) * 50 // n).astype(np.int32))
+
+
+def fof6d(vr, ctx, n):
+    rng, P, host = _hosted(vr, ctx, n)
+    return [ctx.fof6d(P, host, dev_tensor(np.full(50, 100.0)), 0.5 * n ** (-1 / 3), None)]
+
+
+def fof6d_outliers(vr, ctx, n):
+    rng, P, host = _hosted(vr, ctx, n)
+    R = dev_tensor(rng.normal(1.5, 1, n).astype(np.float32))
+    return [ctx.fof6d(P, host, dev_tensor(np.full(50, 100.0)), 0.5 * n ** (-1 / 3), R, 1.0)]
+
+
+def fof_sub(vr, ctx, n):
+    rng, P, host = _hosted(vr, ctx, n)
+    L = dev_tensor(rng.normal(1.5, 1, n).astype(np.float32))
+    vbar = dev_tensor(rng.normal(0, 10, (3, n)).astype(np.float32))
+    return [ctx.fof_sub(P, host, 50, vbar, 0.5 * n ** (-1 / 3), L, 1.0)]
+
+
+CALLS = {f.__name__: f for f in (fof3d, fof3d_dm, fof6d, fof6d_outliers, fof_sub)}
 
 # (call, particles, bytes)
 ROOM = [("fof3d", 20000, 2079011), ("fof3d", 200000, 19994736), ("fof3d_dm", 20000, 2569251),
-        ("fof3d_dm", 200000, 23420408)]
+        ("fof3d_dm", 200000, 23420408), ("fof6d", 20000, 3297780), ("fof6d", 200000, 34597218),
+        ("fof6d_outliers", 20000, 2556727), ("fof6d_outliers", 200000, 23265044), ("fof_sub", 20000, 3128095),
+        ("fof_sub", 200000, 28811670)]
 
 
 @pytest.mark.parametrize("name,n,room", ROOM)
