@@ -408,8 +408,10 @@ extern "C" int vr_groups(vr_ctx* ctx, int64_t n, const int32_t* label, int32_t n
     uint32_t nrun = 0, ng = 0;
     // A small set sorts its unlabelled particles with the others and learns
     // the counts of runs and groups in one wait at the end (three waits of 20
-    // us and three launches more cost two sorts of 14 k labels 210 us each).
-    const bool few = n <= 131072;
+    // us and three launches more cost two sorts of 14 k labels 210 us each);
+    // not under a workspace cap, since the sort's buffers are then sized for
+    // all particles.
+    const bool few = n <= 131072 && ctx->max_ws == 0;
     if (few) {
         const int kbits = bits_for((uint64_t)n);
         uint32_t *kin = key, *vin = val;

@@ -467,7 +467,8 @@ int sort_pairs_impl(vr_ctx* ctx, K* kin, uint32_t* vin, K* keys, uint32_t* vals,
         }
         return VR_OK;
     }
-    const bool one = n <= RS_ONE_MAX, small = n <= RS_SMALL_MAX;
+    // (a cap on the workspace leaves the counts the room of the larger tiles)
+    const bool one = n <= RS_ONE_MAX, small = n <= RS_SMALL_MAX && ctx->max_ws == 0;
     const int tile = RS_BLOCK * (small ? RS_ITEMS_SMALL : RS_ITEMS);
     const int num_tiles = (int)((n + tile - 1) / tile);
     const bool fused = num_tiles <= RS_FUSED_TILES;

@@ -56,13 +56,29 @@ def fof_sub(vr, ctx, n):
     return [ctx.fof_sub(P, host, 50, vbar, 0.5 * n ** (-1 / 3), L, 1.0)]
 
 
-CALLS = {f.__name__: f for f in (fof3d, fof3d_dm, fof6d, fof6d_outliers, fof_sub)}
+def groups(vr, ctx, n):
+    """Half of the particles carry a label."""
+    i = np.arange(n)
+    _, of, off, mem = ctx.groups(dev_tensor(np.where(i < n // 2, i // 40, -1).astype(np.int32)), 20)
+    return [of, off, mem[:int(off[-1])]]
+
+
+def assign_baryons(vr, ctx, n):
+    rng, P, host = _hosted(vr, ctx, n)
+    off = dev_tensor(np.searchsorted(host.cpu().numpy(), np.arange(51)).astype(np.int32))
+    star = dev_tensor((rng.random(n) < 0.4).astype(np.uint8))
+    out, _ = ctx.assign_baryons(P, off, dev_tensor(np.arange(n, dtype=np.int32)), star, host, n ** (-1 / 3), 100.0)
+    return [out]
+
+
+CALLS = {f.__name__: f for f in (fof3d, fof3d_dm, fof6d, fof6d_outliers, fof_sub, groups, assign_baryons)}
 
 # (call, particles, bytes)
 ROOM = [("fof3d", 20000, 2079011), ("fof3d", 200000, 19994736), ("fof3d_dm", 20000, 2569251),
         ("fof3d_dm", 200000, 23420408), ("fof6d", 20000, 3297780), ("fof6d", 200000, 34597218),
         ("fof6d_outliers", 20000, 2556727), ("fof6d_outliers", 200000, 23265044), ("fof_sub", 20000, 3128095),
-        ("fof_sub", 200000, 28811670)]
+        ("fof_sub", 200000, 28811670), ("groups", 100000, 4492281),
+        ("assign_baryons", 20000, 1619863), ("assign_baryons", 200000, 15100764)]
 
 
 @pytest.mark.parametrize("name,n,room", ROOM)
