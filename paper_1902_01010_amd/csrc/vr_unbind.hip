@@ -47,7 +47,7 @@ struct Members {
 // full recompute; mode = 1 when the next pass may subtract them instead of
 // recomputing.
 struct Removed {
-    float4* p;
+    float* p;  // x, y, z and, unless all masses are equal, mass
     int *nrm, *since, *mode;
 };
 
@@ -527,7 +527,14 @@ __global__ __launch_bounds__(BS) void k_ub_group(const int* __restrict__ active,
                     acc[dst] = a[u];
                 }
             } else {
-                Rm.p[base + (int)(gone + (uint32_t)ci - kbefore)] = P[u];
+                const int64_t k = base + (int)(gone + (uint32_t)ci - kbefore);
+                if (uniform) {
+                    Rm.p[3 * k] = P[u].x;
+                    Rm.p[3 * k + 1] = P[u].y;
+                    Rm.p[3 * k + 2] = P[u].z;
+                } else {
+                    reinterpret_cast<float4*>(Rm.p)[k] = P[u];
+                }
             }
         }
         kept += tot;
@@ -727,7 +734,7 @@ template <bool UNIFORM>
 __global__ __launch_bounds__(UBP, 2) void k_ub_potential_p(UbPlan* plan, const int* __restrict__ act,
                                                        const int* __restrict__ item_off, const int32_t* __restrict__ off,
                                                        const int* __restrict__ cnt, const float4* __restrict__ wp,
-                                                       const float4* __restrict__ rp, const int* __restrict__ nrm,
+                                                       const float* __restrict__ rp, const int* __restrict__ nrm,
                                                        const int* __restrict__ mode, float eps2,
                                                        double* __restrict__ acc, int jchunk) {
     extern __shared__ __align__(16) char ldsall[];
@@ -766,7 +773,11 @@ __global__ __launch_bounds__(UBP, 2) void k_ub_potential_p(UbPlan* plan, const i
             for (int jb = j0; jb < j1; jb += STAGE) {
                 const int jn = min(STAGE, j1 - jb);
                 __builtin_amdgcn_wave_barrier();
-                for (int t = lane; t < jn; t += 64) sj[t] = rp[base + jb + t];
+                for (int t = lane; t < jn; t += 64) {
+                    const int64_t k = base + jb + t;
+                    sj[t] = UNIFORM ? make_float4(rp[3 * k], rp[3 * k + 1], rp[3 * k + 2], 1.f)
+                                    : reinterpret_cast<const float4*>(rp)[k];
+                }
                 __builtin_amdgcn_wave_barrier();
                 // a removed member is never i itself; only coincident pairs need care
                 for (int t0 = 0; t0 < jn; t0 += 64) {
@@ -1014,7 +1025,7 @@ extern "C" int vr_unbind(vr_ctx* ctx, const vr_particles* p, int32_t n_groups, c
     VR_WS(state, ctx, int, WS_D1, n_groups);
     VR_WS(act, ctx, int, WS_D2, n_groups);
     Removed Rm;
-    VR_WS(rp, ctx, float4, WS_B0, M);
+    VR_WS(rp, ctx, float, WS_B0, (uniform ? 3 : 4) * M);
     VR_WS(nrm, ctx, int, WS_B4, n_groups); VR_WS(since, ctx, int, WS_B5, n_groups); VR_WS(mode, ctx, int, WS_B6, n_groups);
     Rm.p = rp; Rm.nrm = nrm; Rm.since = since; Rm.mode = mode;
     VR_WS(nbig, ctx, int, WS_D6, 1);

@@ -71,14 +71,22 @@ def assign_baryons(vr, ctx, n):
     return [out]
 
 
-CALLS = {f.__name__: f for f in (fof3d, fof3d_dm, fof6d, fof6d_outliers, fof_sub, groups, assign_baryons)}
+def unbind(vr, ctx, n):
+    """Equal masses, persistent passes."""
+    _, P = _sparse(vr, ctx, n)
+    off = dev_tensor(np.linspace(0, n, 101).astype(np.int32))
+    ub = ctx.unbind(P, off, dev_tensor(np.arange(n, dtype=np.int32)), 1e-3, 1e-3)
+    return [ub["bound"], ub["phi"], ub["iters"]]
+
+
+CALLS = {f.__name__: f for f in (fof3d, fof3d_dm, fof6d, fof6d_outliers, fof_sub, groups, assign_baryons, unbind)}
 
 # (call, particles, bytes)
 ROOM = [("fof3d", 20000, 2079011), ("fof3d", 200000, 19994736), ("fof3d_dm", 20000, 2569251),
         ("fof3d_dm", 200000, 23420408), ("fof6d", 20000, 3297780), ("fof6d", 200000, 34597218),
         ("fof6d_outliers", 20000, 2556727), ("fof6d_outliers", 200000, 23265044), ("fof_sub", 20000, 3128095),
-        ("fof_sub", 200000, 28811670), ("groups", 100000, 4492281),
-        ("assign_baryons", 20000, 1619863), ("assign_baryons", 200000, 15100764)]
+        ("fof_sub", 200000, 28811670), ("groups", 100000, 4492281), ("assign_baryons", 20000, 1619863),
+        ("assign_baryons", 200000, 15100764), ("unbind", 20000, 1353420), ("unbind", 200000, 12886565)]
 
 
 @pytest.mark.parametrize("name,n,room", ROOM)
