@@ -2,6 +2,7 @@
 a context without a cap, within the room."""
 import numpy as np
 import pytest
+import torch
 
 from paper_1902_01010_amd import synth
 from tests.gpu_common import dev_tensor
@@ -79,14 +80,23 @@ def unbind(vr, ctx, n):
     return [ub["bound"], ub["phi"], ub["iters"]]
 
 
-CALLS = {f.__name__: f for f in (fof3d, fof3d_dm, fof6d, fof6d_outliers, fof_sub, groups, assign_baryons, unbind)}
+def train(vr, ctx, n):
+    rng = np.random.default_rng(3)
+    feat = dev_tensor(rng.normal(size=(n, 12)).astype(np.float32)).bfloat16().view(torch.int16)
+    w = dev_tensor(synth.mlp_init(1))
+    return list(ctx.mlp_grad(w, feat, dev_tensor(rng.normal(size=n).astype(np.float32))))
+
+
+CALLS = {f.__name__: f for f in (
+    fof3d, fof3d_dm, fof6d, fof6d_outliers, fof_sub, groups, assign_baryons, unbind, train)}
 
 # (call, particles, bytes)
 ROOM = [("fof3d", 20000, 2079011), ("fof3d", 200000, 19994736), ("fof3d_dm", 20000, 2569251),
         ("fof3d_dm", 200000, 23420408), ("fof6d", 20000, 3297780), ("fof6d", 200000, 34597218),
         ("fof6d_outliers", 20000, 2556727), ("fof6d_outliers", 200000, 23265044), ("fof_sub", 20000, 3128095),
         ("fof_sub", 200000, 28811670), ("groups", 100000, 4492281), ("assign_baryons", 20000, 1619863),
-        ("assign_baryons", 200000, 15100764), ("unbind", 20000, 1353420), ("unbind", 200000, 12886565)]
+        ("assign_baryons", 200000, 15100764), ("unbind", 20000, 1353420), ("unbind", 200000, 12886565),
+        ("train", 2048, 637609), ("train", 8192, 2407613), ("train", 20000, 5837002)]
 
 
 @pytest.mark.parametrize("name,n,room", ROOM)
