@@ -36,6 +36,11 @@ constexpr int HCH = 2048;  // positions per histogram block
 // counts each, and HCH in the histograms.
 constexpr int64_t SMALL_M = 1 << 20;
 constexpr int BIG_TILE = 1024;
+// A level whose largest node spans more tiles than this scans their counts
+// first; below, every block of the partition adds up those it needs.
+// (One host, seven levels, all levels scanned and none: 2^22 members 1.62 and
+// 1.61 ms, 2^23 3.56 and 3.64, 2^25 14.7 and 15.9, 2^28 113 and 160.)
+constexpr int64_t SCAN_TILES = 4096;
 // Counters of a build: leaves, nodes, and from CN_ACTIVE on the active nodes
 // of every level.
 constexpr int MAX_LEVELS = 64;
@@ -521,7 +526,8 @@ __global__ __launch_bounds__(NT) void k_lflag3(int64_t M, const int* __restrict_
 // on, so the tails of those tiles add up to what is missing.  (Scanned flags
 // took three more launches and 24 bytes a member and level: 1.42 ms against
 // 1.18 ms for the 15 levels of a 256^3 box.)
-template <int IT>
+// (SCANNED: the tails' prefix sums, whose difference of two is that sum.)
+template <int IT, bool SCANNED>
 __global__ __launch_bounds__(KB) void k_part3(int64_t M, int* __restrict__ seg_node, KdNode* __restrict__ nodes,
                                               const int* __restrict__ l0, const int* __restrict__ l1,
                                               const int* __restrict__ l2, const int* __restrict__ u0,
@@ -543,9 +549,16 @@ __global__ __launch_bounds__(KB) void k_part3(int64_t M, int* __restrict__ seg_n
     uint32_t b[3] = {0, 0, 0};
     {
         const KdNode& nd = nodes[seg_node[p0]];
-        if (nd.dim >= 0 && nd.start < p0)
-            for (int64_t k = nd.start / (KB * IT) + tid; k < tile; k += KB)
-                for (int j = 0; j < 3; ++j) b[j] += tail[j * tiles + k];
+        if (nd.dim >= 0 && nd.start < p0) {
+            const int64_t k0 = nd.start / (KB * IT);
+            if (SCANNED) {
+                if (tid == 0)
+                    for (int j = 0; j < 3; ++j) b[j] = tail[j * tiles + tile] - tail[j * tiles + k0];
+            } else {
+                for (int64_t k = k0 + tid; k < tile; k += KB)
+                    for (int j = 0; j < 3; ++j) b[j] += tail[j * tiles + k];
+            }
+        }
     }
 #pragma unroll
     for (int j = 0; j < 3; ++j) {
@@ -840,18 +853,19 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
     // A node of coincident members that stays a leaf only lowers the true
     // counts, which the kernels read from the device; these bound the grids
     // and the number of levels, so no level waits for the host.
-    std::vector<int64_t> plan_na, plan_members;
+    std::vector<int64_t> plan_na, plan_members, plan_largest;
     {
         struct Sz { int64_t s0, c0, c1; };  // c0 nodes of size s0, c1 of size s0 + 1
         std::vector<std::pair<Sz, int>> sz;  // of the hosts that split, with their cells' size
         for (int h = 0; h < n_hosts; ++h)
             if (off[h + 1] - off[h] > ncell[h]) sz.push_back({Sz{(int64_t)off[h + 1] - off[h], 1, 0}, ncell[h]});
         for (;;) {
-            int64_t na = 0, mem = 0;
+            int64_t na = 0, mem = 0, largest = 0;
             for (auto& [z, nc] : sz) {
                 int64_t a0 = z.s0 > nc ? z.c0 : 0, a1 = z.s0 + 1 > nc ? z.c1 : 0;
                 na += a0 + a1;
                 mem += a0 * z.s0 + a1 * (z.s0 + 1);
+                if (a0 + a1 > 0) largest = std::max(largest, z.s0 + 1);
                 // children of the active ones: floor and ceil halves
                 int64_t lo = INT64_MAX, cnt[3] = {0, 0, 0};
                 const int64_t sizes[2] = {z.s0, z.s0 + 1}, counts[2] = {a0, a1};
@@ -873,6 +887,7 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
             if (na == 0) break;
             plan_na.push_back(na);
             plan_members.push_back(mem);
+            plan_largest.push_back(largest);
             if (plan_na.size() > MAX_LEVELS) return set_err(ctx, VR_ERR_NOT_CONVERGED, "KD build exceeded 64 levels");
         }
     }
@@ -931,8 +946,14 @@ int kd_build(vr_ctx* ctx, const vr_particles* p, int32_t n_hosts, const int32_t*
             hipLaunchKernelGGL(k_lflag3<TILE>, dim3((unsigned)tiles), dim3(TILE), 0, st, M, seg, nodes, Lin[0], Lin[1],
                                Lin[2], U[0], U[1], U[2], lf8, tail);
             VR_LAUNCH_CHECK(ctx);
-            hipLaunchKernelGGL(k_part3<TILE / KB>, dim3((unsigned)tiles), dim3(KB), 0, st, M, seg, nodes, Lin[0],
-                               Lin[1], Lin[2], U[0], U[1], U[2], lf8, tail, Lout[0], Lout[1], Lout[2], cl0, hc, hz);
+            const bool scanned = plan_largest[level] > SCAN_TILES * TILE;
+            if (scanned) {
+                const int e = scan_u32(ctx, tail, tail, 3 * tiles, nullptr, st);
+                if (e) return e;
+            }
+            hipLaunchKernelGGL((scanned ? k_part3<TILE / KB, true> : k_part3<TILE / KB, false>), dim3((unsigned)tiles),
+                               dim3(KB), 0, st, M, seg, nodes, Lin[0], Lin[1], Lin[2], U[0], U[1], U[2], lf8, tail, Lout[0],
+                               Lout[1], Lout[2], cl0, hc, hz);
             VR_LAUNCH_CHECK(ctx);
             return (int)VR_OK;
         };
