@@ -101,10 +101,11 @@ int vr_get_tune(const vr_ctx* ctx, const char* knob, int* value);
 
 /* Autotuner of those knobs.  Unless force is set and if cache_path (may be
  * NULL) names a readable cache written for this GPU architecture, its knobs
- * are applied and nothing is timed.  Otherwise the call times vr_unbind
- * (persistent) over unbind_tile x unbind_jchunk x unbind_bpc, then over
- * unbind_wide at the fastest of those, on a synthetic heavy-tailed group set
- * (sizes 32 .. 32768) and vr_local_vdensity over
+ * are applied and nothing is timed.  Otherwise the call times vr_unbind over
+ * unbind_jchunk x unbind_bpc (persistent) and unbind_jchunk x unbind_tile
+ * (host-planned), then (persistent) over unbind_wide at the setting with the
+ * smallest sum of both, on a synthetic heavy-tailed group set
+ * (sizes 32 .. 131072) and vr_local_vdensity over
  * knn_leaf x xcd_chunk on synthetic hosts (2000 cusped halos whose sizes
  * follow dN/dlnN ~ N^-0.9 on [256, 2^21], 6.6 M members), applies the
  * fastest settings and writes them, with every timing, to cache_path as

@@ -3,9 +3,11 @@
 // choice in a small JSON cache keyed by the GPU architecture.
 //
 // Knobs never change integer results (FP64 sums only through their order):
-//   unbind_tile, unbind_jchunk, unbind_bpc   persistent potential schedule
-//   unbind_wide                              size class of the group kernel
-//   knn_leaf, xcd_chunk                      neighbour-search tree and order
+//   unbind_tile                  tile of the host-planned potential kernel
+//   unbind_jchunk                j-range of a work item, of both schedules
+//   unbind_bpc                   workgroups per CU of the persistent schedule
+//   unbind_wide                  size class of the group kernel
+//   knn_leaf, xcd_chunk          neighbour-search tree and order
 #include "vr_internal.h"
 
 #include <algorithm>
@@ -178,10 +180,12 @@ extern "C" int vr_autotune(vr_ctx* ctx, const char* cache_path, int force) {
     DevBufs mem;
     std::ostringstream log;
 
-    // ---- unbinding: heavy-tailed group sizes 32 .. 32768 ------------------
+    // ---- unbinding: heavy-tailed group sizes 32 .. 131072 -----------------
+    // (with 32768 the largest, 0.6 ms of unbinding preferred j-ranges of 1024,
+    // 5% slower than 4096 for a heavy group of 7 ms)
     std::vector<int32_t> off{0};
-    for (int k = 15; k >= 5; --k) {
-        const int count = std::max(1, (1 << (15 - k)) / 2);
+    for (int k = 17; k >= 5; --k) {
+        const int count = std::max(1, (1 << (17 - k)) / 2);
         for (int c = 0; c < count; ++c) off.push_back(off.back() + (1 << k));
     }
     const int ng = (int)off.size() - 1;
@@ -210,7 +214,8 @@ extern "C" int vr_autotune(vr_ctx* ctx, const char* cache_path, int force) {
     up.frame_type = 1; up.max_iter = 100; up.persistent = 1; up.tile = 0;
     const int saved_timing = ctx->timing;
     ctx->timing = 0;
-    auto time_unbind = [&](float* ms) -> int {
+    auto time_unbind = [&](int persistent, float* ms) -> int {
+        up.persistent = persistent;
         float bestms = 1e30f;
         for (int rep = 0; rep < 3; ++rep) {
             VR_HIP(ctx, hipEventRecord(e0, st));
@@ -230,24 +235,36 @@ extern "C" int vr_autotune(vr_ctx* ctx, const char* cache_path, int force) {
     const int tiles[] = {64, 128, 256, 512, 1024};
     const int jchunks[] = {1024, 4096, 16384};
     const int bpcs[] = {0, 1, 2, 4};
-    for (int t : tiles)
-        for (int j : jchunks)
-            for (int b : bpcs) {
-                ctx->tuned_tile = t;
-                ctx->unbind_jchunk = j;
-                ctx->unbind_bpc = b;
-                float ms = 0;
-                int rc = time_unbind(&ms);
-                if (rc) { ctx->timing = saved_timing; return rc; }
-                log << "    {\"tile\": " << t << ", \"jchunk\": " << j << ", \"bpc\": " << b << ", \"ms\": " << ms
-                    << "},\n";
+    // the host-planned schedule reads the tile and the j-range, the persistent
+    // one the j-range and the workgroups: each over its own two, and the j-range
+    // by the sum
+    for (int j : jchunks) {
+        ctx->unbind_jchunk = j;
+        float persistent[4], planned[5];
+        int rc = VR_OK;
+        for (int b = 0; b < 4 && !rc; ++b) {
+            ctx->unbind_bpc = bpcs[b];
+            rc = time_unbind(1, &persistent[b]);
+        }
+        for (int t = 0; t < 5 && !rc; ++t) {
+            ctx->tuned_tile = tiles[t];
+            rc = time_unbind(0, &planned[t]);
+        }
+        if (rc) { ctx->timing = saved_timing; return rc; }
+        for (int t = 0; t < 5; ++t)
+            for (int b = 0; b < 4; ++b) {
+                const float ms = persistent[b] + planned[t];
+                log << "    {\"tile\": " << tiles[t] << ", \"jchunk\": " << j << ", \"bpc\": " << bpcs[b]
+                    << ", \"persistent_ms\": " << persistent[b] << ", \"planned_ms\": " << planned[t]
+                    << ", \"ms\": " << ms << "},\n";
                 if (ms < best_ub) {
                     best_ub = ms;
-                    best.unbind_tile = t;
+                    best.unbind_tile = tiles[t];
                     best.unbind_jchunk = j;
-                    best.unbind_bpc = b;
+                    best.unbind_bpc = bpcs[b];
                 }
             }
+    }
     apply(ctx, best);
     // then the size class at that schedule: the group kernel's 1024-thread
     // form for the leading groups from 1024 members up, ..., or for none
@@ -257,7 +274,7 @@ extern "C" int vr_autotune(vr_ctx* ctx, const char* cache_path, int force) {
     for (int wm : wides) {
         ctx->unbind_wide = wm;
         float ms = 0;
-        int rc = time_unbind(&ms);
+        int rc = time_unbind(1, &ms);
         if (rc) { ctx->timing = saved_timing; return rc; }
         wlog << "    {\"wide\": " << wm << ", \"ms\": " << ms << "},\n";
         if (ms < best_w) {
@@ -269,8 +286,7 @@ extern "C" int vr_autotune(vr_ctx* ctx, const char* cache_path, int force) {
 
     // ---- neighbour search: 2000 hosts, dN/dlnN ~ N^-0.9 on [256, 2^21] -----
     // Sizes at the mid-quantiles of that distribution (6.6 M members, largest
-    // 1.07 M): the searched hosts of a 256^3 box, whose largest hosts set the
-    // best leaf size.
+    // 1.07 M): the searched hosts of a 256^3 box.
     const int nh = 2000;
     std::vector<int32_t> hoff(nh + 1);
     hoff[0] = 0;
@@ -311,8 +327,13 @@ extern "C" int vr_autotune(vr_ctx* ctx, const char* cache_path, int force) {
     std::ostringstream klog;
     struct KnnRun { int leaf, xchunk; float ms; };
     std::vector<KnnRun> kruns;
-    const int leaves[] = {64, 96, 128, 192, 256};
-    const int xchunks[] = {0, 16, 64, 256};
+    // leaves of different bucket sizes (1024 and 2048, which every larger value
+    // gives too); runs of workgroups of 16 queries each, to 256: the FOF linking
+    // sweeps read the run too and leave XCDs idle with longer ones (at 1024 a 3 M
+    // field with its 6D pass takes 4.0 ms, not 3.5, and a 256^3 box 10% longer,
+    // where this search gains nothing)
+    const int leaves[] = {64, 128};
+    const int xchunks[] = {0, 4, 8, 16, 32, 48, 64, 96, 128, 256};
     for (int L : leaves)
         for (int X : xchunks) {
             ctx->knn_leaf = L;

@@ -48,3 +48,22 @@ def test_autotune_sweep_cache_and_parity(tmp_path, ref):
     for g in np.nonzero(clean)[0]:
         m = mem[off[g]:off[g + 1]]
         assert (gb[m] == exp["bound"][m]).all()
+
+
+def test_autotune_times_what_reads_each_knob(tmp_path):
+    """The tile is the host-planned schedule's alone and bucket sizes stop
+    growing at 2048 members: each knob is timed where it is read, and no
+    setting is timed twice under two names."""
+    from paper_1902_01010_amd import vr
+    path = tmp_path / "tune.json"
+    vr.Context(0).autotune(path, force=True)
+    data = json.loads(path.read_text())
+    rows = data["unbind_sweep"]
+    persistent, planned = {}, {}
+    for r in rows:
+        assert persistent.setdefault((r["jchunk"], r["bpc"]), r["persistent_ms"]) == r["persistent_ms"]
+        assert planned.setdefault((r["jchunk"], r["tile"]), r["planned_ms"]) == r["planned_ms"]
+        assert abs(r["ms"] - r["persistent_ms"] - r["planned_ms"]) <= 1e-5 * r["ms"]
+    assert len(persistent) == 12 and len(planned) == 15
+    settings = {(min(2048, 16 * r["leaf"]), r["xcd_chunk"]) for r in data["knn_sweep"]}
+    assert len(settings) == len(data["knn_sweep"]) == 20
