@@ -317,10 +317,8 @@ int build_cell_list(vr_ctx* ctx, int64_t n, const uint32_t* qx, const uint32_t* 
     if (!ncell_dev) return VR_ERR_OUT_OF_MEMORY;
     rc = scan_u32(ctx, flag, flag, n, ncell_dev, st);
     if (rc) return rc;
-    // a small set without a workspace cap is sized for a cell per point
-    // instead of waiting 20 us for their number
     uint32_t ncell = (uint32_t)n;
-    if ((n > 131072 || ctx->max_ws != 0) && (rc = read_back(ctx, ncell_dev, &ncell, sizeof ncell, st))) return rc;
+    if ((n > FEW_POINTS || ctx->max_ws != 0) && (rc = read_back(ctx, ncell_dev, &ncell, sizeof ncell, st))) return rc;
     uint32_t hsize = 1024;
     while (hsize < 2u * ncell) hsize <<= 1;
     VR_WS(hkeys, ctx, ckey_t, WS_A7, hsize);
@@ -407,11 +405,10 @@ extern "C" int vr_groups(vr_ctx* ctx, int64_t n, const int32_t* label, int32_t n
     int64_t m = n;  // sorted pairs
     uint32_t nrun = 0, ng = 0;
     // A small set sorts its unlabelled particles with the others and learns
-    // the counts of runs and groups in one wait at the end (three waits of 20
-    // us and three launches more cost two sorts of 14 k labels 210 us each);
-    // not under a workspace cap, since the sort's buffers are then sized for
-    // all particles.
-    const bool few = n <= 131072 && ctx->max_ws == 0;
+    // the counts of runs and groups in one wait at the end instead of three and
+    // three launches more; not under a workspace cap, since the sort's buffers
+    // are then sized for all particles.
+    const bool few = n <= FEW_POINTS && ctx->max_ws == 0;
     if (few) {
         const int kbits = bits_for((uint64_t)n);
         uint32_t *kin = key, *vin = val;

@@ -550,12 +550,13 @@ bool fof3d_fine_applicable(int gb, int s) {
 }
 
 // Up to this many particles the link passes take a lane per fine cell and
-// neighbour: their time is the longest chain of one cell's partners (14 k
-// particles 98 -> 44 us in the testing pass, 44 k 114 -> 84), beyond it the
-// pairs that threads test before others have joined them (66 k 96 -> 101,
-// 118 k 93 -> 146, 256^3 2.07 -> 4.35 ms).
+// neighbour: their time is the longest chain of one cell's partners, beyond it
+// the pairs that threads test before others have joined them.  The call without
+// and with it: a halo 247 -> 230 us at 14 k particles, 261 -> 233 at 28 k, from
+// -6 to 9% (three halos) at 35 k, 270 -> 286 at 48 k, 300 -> 330 at 117 k; a box,
+// whose pairs are spread wider, 251 -> 183 at 14 k, 328 -> 311 at 111 k, 355 -> 371
+// at 262 k, 904 -> 1330 at 2.1 M.
 constexpr int64_t LANE_PER_NEIGHBOUR = 32768;
-constexpr int64_t FEW_PARTICLES = 131072;
 
 int fof3d_fine(vr_ctx* ctx, const vr_particles* p, double ell2, int s, int32_t* label, hipStream_t st) {
     const int64_t n = p->n;
@@ -596,10 +597,8 @@ int fof3d_fine(vr_ctx* ctx, const vr_particles* p, double ell2, int s, int32_t* 
     hipLaunchKernelGGL(k_fine_starts, dim3(gn), dim3(256), 0, st, n, key, scan, fine_start, fid);
     VR_LAUNCH_CHECK(ctx);
     // The kernels read the counts of cells from the device (tot); the host
-    // waits for them only where they save more than the wait: a small set
-    // without a workspace cap takes its particles for the bound of both (14 k
-    // particles: two waits of 20 us less).
-    const bool bound = n <= FEW_PARTICLES && ctx->max_ws == 0;
+    // waits for them only where they save more than the wait.
+    const bool bound = n <= FEW_POINTS && ctx->max_ws == 0;
     uint32_t nfine = (uint32_t)n;
     if (!bound && (rc = read_back(ctx, tot, &nfine, sizeof nfine, st))) return rc;
     // coarse index per fine cell, first fine cell per coarse cell, the

@@ -108,6 +108,17 @@ struct CellList {
 bool fof3d_fine_applicable(int gb, int s);
 int fof3d_fine(vr_ctx* ctx, const vr_particles* p, double ell2, int s, int32_t* label, hipStream_t st);
 
+// Up to this many points the counts that a set's cells, runs and groups turn
+// out to have are not waited for where no workspace cap makes them count: the
+// buffers are sized for one a point, the kernels read the count on the device.
+// Measured with and without the waits on halos: 3D FOF 280 and 247 us at 14 k
+// particles, 353 and 300 at 117 k, 471 and 426 at 408 k, 565 and 597 at 583 k;
+// groups 143 and 98 us at 14 k, 177 and 134 at 408 k, 193 and 148 at 583 k; the
+// cell list in a 6D FOF 1197 and 1174 us at 117 k, 1775 and 1757 at 408 k, 2803
+// and 2818 at 583 k: beyond the line the passes over the bound cost what the
+// waits do.
+constexpr int64_t FEW_POINTS = int64_t(1) << 19;
+
 // Cell list of n points with cells of side 2^s grid units.  Uses workspace
 // slots A0..A8, FLAG and the sort slots.
 int build_cell_list(vr_ctx* ctx, int64_t n, const uint32_t* qx, const uint32_t* qy, const uint32_t* qz, int gb,

@@ -112,3 +112,12 @@ def test_same_result_within_the_cap(vr, name, n, room):
             np.testing.assert_allclose(b, a, rtol=1e-5, atol=1e-6 * np.nanmax(np.abs(a)))
         else:
             assert (a == b).all()
+
+
+@pytest.mark.parametrize("n", [131073, 1 << 19, (1 << 19) + 1])
+@pytest.mark.parametrize("name", ["fof3d", "fof3d_dm", "fof6d", "groups"])
+def test_same_result_with_counts_bounded_and_read(vr, name, n):
+    """The buffers sized for a cell, run and group a particle against those
+    sized for the counts read, which any cap asks for."""
+    for a, b in zip(CALLS[name](vr, vr.Context(0), n), CALLS[name](vr, vr.Context(0, max_workspace_bytes=1 << 30), n)):
+        assert torch.equal(a, b)
