@@ -9,7 +9,7 @@
 // element-parallel passes for all nodes of all hosts at once: entropy
 // histograms (cells tree), the split decision per node, a left/right flag
 // per member with counts per tile of positions, and a stable partition of
-// each list from the tiles' prefixes: four launches, two without histograms
+// each list from the tiles' prefixes: five launches, three without histograms
 // (eleven and eight before: 12 k members in ten levels 1.0 -> 0.5 ms).  No
 // node is ever handled by a single workgroup, so the few huge top-level
 // nodes cost no more per member than the many small ones.  The levels and

@@ -231,7 +231,7 @@ __device__ __forceinline__ int leaf_slot(int i, int lpq_log2) {
 // the middle while a segment holds more than a leaf, then in halves down to
 // four.  Members, boxes and slots are written in the resulting order.
 // Bound by LDS round trips and barriers (three workgroups of 53 KB a CU); on
-// the 6.2 M members of a 256^3 box it takes 0.68 ms in place of three to four
+// the 6.2 M members of a 256^3 box it takes 0.65 ms in place of three to four
 // device-wide levels of about 0.25 ms, and leaves of 32 instead of 192 (2,354
 // candidate distances a query before, 688 now).
 // NT = 64 takes the buckets of up to 512 members, as many as 16 leaves hold.
@@ -502,7 +502,7 @@ __device__ __forceinline__ int dpp(int v) {
 }
 constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_HALF_MIRROR = 0x141, DPP_MIRROR = 0x140;
 
-// Folds v over groups of N lanes (N = 4, 8 or 16); every lane gets the result.
+// Folds v over groups of N lanes (4 or 16); every lane gets the result.
 template <int N, class T, class OP>
 __device__ __forceinline__ T fold(T v, OP op) {
     auto mv = [&](auto c, T x) __attribute__((always_inline)) {
@@ -519,8 +519,10 @@ __device__ __forceinline__ T fold(T v, OP op) {
     };
     v = op(v, mv(std::integral_constant<int, DPP_XOR1>{}, v));
     v = op(v, mv(std::integral_constant<int, DPP_XOR2>{}, v));
-    if constexpr (N >= 8) v = op(v, mv(std::integral_constant<int, DPP_HALF_MIRROR>{}, v));
-    if constexpr (N >= 16) v = op(v, mv(std::integral_constant<int, DPP_MIRROR>{}, v));
+    if constexpr (N == 16) {
+        v = op(v, mv(std::integral_constant<int, DPP_HALF_MIRROR>{}, v));
+        v = op(v, mv(std::integral_constant<int, DPP_MIRROR>{}, v));
+    }
     return v;
 }
 struct OpMax { template <class T> __device__ __forceinline__ T operator()(T a, T b) const { return a > b ? a : b; } };
@@ -558,14 +560,14 @@ constexpr int VMAX = 256;  // leaves one wavefront may visit for one host
 // LPQ lanes a query; KL * LPQ >= n_se; L > KL distances kept a lane, so that
 // a lane's share of the n_se nearest seldom exceeds its list.
 //
-// Bound by VALU issue: 9.0 k instructions a wavefront of 16 queries at 32/8,
+// Bound by VALU issue: 8.2 k instructions a wavefront of 16 queries at 32/8,
 // half of them the walk (19 leaves of 32, 18 instructions a lane and member),
 // a sixth the second pass, against 62 k for 64 queries of the one-lane-a-query
 // form with 64-bit keys in LDS that it replaces.  256^3 box, 6.2 M queries,
-// 32/8: 11.5 -> 5.6 ms; 48/16, 159 k queries: 4.2 -> 0.24 ms; 256/32, 335 k
+// 32/8: 11.5 -> 6.0 ms; 48/16, 159 k queries: 4.2 -> 0.24 ms; 256/32, 335 k
 // queries (one wavefront a query before): 5.5 -> 1.6 ms.  L = 12 for KL = 8
 // (10: 12% slower by the exact removals, 14: 1%).  Four wavefronts a SIMD
-// (116 of 128 VGPRs): three were 12% slower, five 8% (spills).  Eight lanes a
+// (103 of 128 VGPRs): three were 12% slower, five 8% (spills).  Eight lanes a
 // query were 3% slower on the box: a leaf visit's fixed cost falls on half
 // the queries.
 template <int LPQ, int KL, int L>
@@ -578,7 +580,7 @@ __global__ __launch_bounds__(64, 4) void k_knn(const uint32_t* __restrict__ qpos
     constexpr int W = 64 / LPQ;        // queries of the wavefront
     constexpr int E = LEAF / LPQ;      // members of a leaf a lane takes
     constexpr int CAPL = L + 12;       // listed members a lane
-    constexpr int LOG2 = LPQ == 4 ? 2 : LPQ == 8 ? 3 : 4;
+    constexpr int LOG2 = LPQ == 4 ? 2 : 4;
     __shared__ int vis[VMAX];
     __shared__ uint16_t lst[CAPL][64];
     __shared__ int nbr[W][KL * LPQ];

@@ -317,7 +317,8 @@ __global__ __launch_bounds__(256) void k_rs_coarsewin(Level coarse, Cell* __rest
 // n_se neighbours at the density of the 27-cell window (the coarse window
 // where the fine one holds fewer than n_se), and the mean velocity of the
 // cell and its six face neighbours.  cf[4 c .. 4 c + 3] = (f0, vloc).
-// (four wavefronts a SIMD: 343 -> 291 us with the registers that takes)
+// (four wavefronts a SIMD: 343 -> 291 us on 2 M particles, though 63 of the
+// window's values then lie in 248 bytes of scratch a lane)
 __global__ __launch_bounds__(256, 4) void k_rs_cellfeat(uint32_t ncells, const uint64_t* __restrict__ keys,
                                                      const uint32_t* __restrict__ start, Level fine, Level coarse,
                                                      const double* __restrict__ vsum, int n_se, double cell_len,
